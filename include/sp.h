@@ -69,12 +69,13 @@ typedef struct {
     int32_t last_layer_all_tokens;
                       /* Only the first token of each sequence feeds the head (the pooled representation of
                          Section 3.1), so in the last layer every other row is dead work.  0 (default): bf16
-                         calls with >= 1024 tokens compute the last layer for the first-token rows only:
+                         calls with more than 256 tokens compute the last layer for the first-token rows only:
                          their queries are folded through the key projection, the other tokens' keys and
                          values are never formed, and the output projection, FFN and LayerNorms run on
-                         `batch` rows (same function; the rounding points of attention differ); bf16 calls
-                         of up to four sequences (and fewer than 1024 tokens) compute the last layer's attention for every
-                         token and everything after it for the first-token rows only.  1: every token goes
+                         `batch` rows (same function; the rounding points of attention differ; fewer than 1024
+                         tokens: only where the call's buffers hold the folded queries); smaller bf16 calls form
+                         the last layer's queries, keys and values of every token and compute everything after
+                         them for the first tokens only.  1: every token goes
                          through the whole last layer (what a stock BERT does; the fp32 path always does). */
     int32_t single_stream;
                       /* 0 (default): a call with >= 2048 tokens and k_active >= 2 runs the active students

@@ -113,7 +113,7 @@ WsLayout make_ws_layout(const sp_config& c, int total_tokens, int batch)
     W.cg = take(K * crows * F * ab);
     W.cqt = take(K * crows * (size_t)c.heads * H * ab);
     W.cxb = take(K * crows * (size_t)c.heads * H * ab);
-    W.part = take(K * (size_t)kSplitMax * kSplitRows * H * 4);
+    W.part = take(K * (size_t)kRowsU * H * 4);
     W.lpart = take(2 * (size_t)batch * c.classes * 4);
     if (c.dtype == SP_DTYPE_FP8 && rows >= (size_t)kFp8MinRows) {
         W.xq = take(K * rows * H);
@@ -199,21 +199,25 @@ struct Writer {
             memcpy(dst, src, n * 4);
         }
     }
-    // dst[o][i] = src[i][o]; src is [n_in][n_out]; dst row stride n_in
-    void transpose(char* dst, const float* src, size_t n_in, size_t n_out) const
+    // The matrix of rows o (o < n_o) and reduction index i (i < n_i) whose element (o, i) is src[i * si + o * so], as a
+    // projection operand.  fp32: [o][i].  bf16: blocks of 16 rows x 8 elements, [o / 16][i / 8][o % 16][i % 8], so that the
+    // sixteen rows by 32 elements (or 32 by 16) one matrix instruction takes are whole 256-byte runs, lane after lane.
+    void operand(char* dst, const float* src, size_t n_o, size_t n_i, size_t so, size_t si) const
     {
         const size_t T = 32;
-        for (size_t i0 = 0; i0 < n_in; i0 += T)
-            for (size_t o0 = 0; o0 < n_out; o0 += T) {
-                const size_t i1 = i0 + T < n_in ? i0 + T : n_in, o1 = o0 + T < n_out ? o0 + T : n_out;
+        for (size_t i0 = 0; i0 < n_i; i0 += T)
+            for (size_t o0 = 0; o0 < n_o; o0 += T) {
+                const size_t i1 = i0 + T < n_i ? i0 + T : n_i, o1 = o0 + T < n_o ? o0 + T : n_o;
                 for (size_t o = o0; o < o1; ++o)
                     for (size_t i = i0; i < i1; ++i) {
-                        const float v = src[i * n_out + o];
-                        if (bf16) ((uint16_t*)dst)[o * n_in + i] = f32_to_bf16_rne(v);
-                        else ((float*)dst)[o * n_in + i] = v;
+                        const float v = src[i * si + o * so];
+                        if (bf16) ((uint16_t*)dst)[((o >> 4) * (n_i >> 3) + (i >> 3)) * 128 + (o & 15) * 8 + (i & 7)] = f32_to_bf16_rne(v);
+                        else ((float*)dst)[o * n_i + i] = v;
                     }
             }
     }
+    // src is [n_in][n_out]: rows = outputs
+    void transpose(char* dst, const float* src, size_t n_in, size_t n_out) const { operand(dst, src, n_out, n_in, 1, n_out); }
 };
 
 static void fill_student(const sp_config& c, const ArenaLayout& L, const float* src, char* dst)
@@ -229,7 +233,7 @@ static void fill_student(const sp_config& c, const ArenaLayout& L, const float* 
     for (int l = 0; l < c.layers; ++l) {
         char* lb = dst + L.layer0 + (size_t)l * L.layer_stride;
         for (int part = 0; part < 3; ++part) {  // Wq bq Wk bk Wv bv -> rows [part*H, part*H+H) of the fused matrix
-            if (part == 1) w.copy(lb + L.wk_io, p, H * H);
+            if (part == 1) w.operand(lb + L.wk_io, p, H, H, H, 1);
             if (q8) quantize_transposed((uint8_t*)(lb + L.wqkv8) + (size_t)part * H * H, (float*)(lb + L.sqkv) + part * H, p, H, H);
             w.transpose(lb + L.wqkv + (size_t)part * H * H * wb, p, H, H); p += H * H;
             memcpy(lb + L.bqkv + (size_t)part * H * 4, p, H * 4); p += H;
@@ -285,7 +289,7 @@ static int run_students(const sp_model* M0, const WsLayout& W, const int32_t* id
     const sp_model* M = &shifted;
     const int H = c.hidden, F = c.ffn, rows = W.rows;
     // rows actually computed: the packed tokens rounded up to the token tile the GEMMs will use
-    const int mtile = T > 256 ? 256 : (T > 64 ? 128 : 64);
+    const int mtile = T > 256 ? 256 : 64;
     const int mrows = (T + mtile - 1) / mtile * mtile;
     const size_t ab = W.act_bytes;
     const size_t sH = (size_t)rows * H * ab, s3H = 3 * sH, sF = (size_t)rows * F * ab;
@@ -305,90 +309,125 @@ static int run_students(const sp_model* M0, const WsLayout& W, const int32_t* id
     char *xq = fp8 ? w + W.xq + m0 * qH : nullptr, *x1q = fp8 ? w + W.x1q + m0 * qH : nullptr;
     char *gq = fp8 ? w + W.gq + m0 * qF : nullptr, *attq = fp8 ? w + W.attq + m0 * qH : nullptr;
     SP_MARK(-1);
-    SP_TRY(launch_embed_ln(M, ids, cu, B, T, rows, mrows, k, x, att, s, xq, kActQuantScale, attq));
-    SP_MARK(SP_PHASE_EMBED);
     // Last layer on the first-token rows only (see sp_config.last_layer_all_tokens).  Not used by the partial
     // forwards of the tests unless they stop before the last layer.
-    const bool first_only = !c.last_layer_all_tokens && with_head && T >= kFirstOnlyMinTokens &&
-                            attention_first_fold_supported(c, max_seqlen);
+    // Calls of fewer than kFirstOnlyMinTokens tokens have no compact buffers: their first-token rows use the q|k|v and FFN
+    // buffers, which the folded layer leaves free, where those are large enough.
+    const bool first_only = !c.last_layer_all_tokens && with_head && attention_first_fold_supported(c, max_seqlen) &&
+                            (T >= kFirstOnlyMinTokens ||
+                             ((size_t)B * c.heads <= (size_t)3 * rows && (size_t)B * c.heads * H <= (size_t)rows * F));
     const int crows = W.crows;
-    const int ctile = B > 256 ? 256 : (B > 64 ? 128 : 64);
-    const int cmrows = (B + ctile - 1) / ctile * ctile;
-    const int nh = c.heads;
-    const size_t cH = (size_t)crows * H * ab, cF = (size_t)crows * F * ab, cHH = (size_t)crows * nh * H;   // cHH: elements
-    char *cx = w + W.cx + m0 * cH, *cq = w + W.cq + m0 * cH, *catt = w + W.catt + m0 * cH, *cu2 = w + W.cu_ + m0 * cH;
-    char *cx1 = w + W.cx1 + m0 * cH, *cg = w + W.cg + m0 * cF;
-    char *cqt = w + W.cqt + m0 * cHH * ab, *cxb = w + W.cxb + m0 * cHH * ab;
-    bool compact_final = false, small_head = false, first_tail = false;
-    size_t small_head_lo = 0;
-    int small_head_splits = 1;
-    // Calls of a few dozen tokens: split the reduction range of the two projections that are followed by a LayerNorm
-    // (largest slice count that leaves every slice at least two 64-wide k-tiles).
-    const size_t slice = (size_t)kSplitRows * H;
-    float* part = (float*)(w + W.part) + (size_t)m0 * kSplitMax * slice;
-    int split_o = 1, split_d = 1;
-    if (bf16_path(c) && mrows <= kSplitRows) {
-        for (int sp = kSplitMax; sp > 1; --sp) {
-            if (split_o == 1 && (H / 64) % sp == 0 && H / 64 / sp >= 2) split_o = sp;
-            if (split_d == 1 && (F / 64) % sp == 0 && F / 64 / sp >= 2) split_d = sp;
+    // fp32 rows of the few-row projections: four regions of 256 rows per student
+    const size_t u_ss = (size_t)kRowsU * H;
+    float* uo = (float*)(w + W.part) + (size_t)m0 * u_ss;   // after the attention-output projection
+    float *ud = uo + (size_t)256 * H, *pooled = uo + (size_t)512 * H;   // after the FFN; pooled first-token rows
+    // g = gelu(LN(uo; ln1) W1^T + b1) of n rows: fused while the rows of all students are few, else a LayerNorm launch and
+    // the tile kernel
+    auto ffn_up = [&](size_t lo, int n, void* x1r, size_t x1_ss, void* gr, size_t g_ss, bool packed) -> hipError_t {
+        if ((long)n * k * H <= kRowsLnMaxElems)
+            return launch_rows_ffn_up(M, lo, uo, u_ss, n, x1r, x1_ss, gr, g_ss, packed ? packed_layout(F) : rows_layout(F), k, s);
+        const hipError_t e = launch_rows_ln_out(M, lo + L.ln1g, lo + L.ln1b, uo, u_ss, x1r, x1_ss, n, k, s);
+        if (e != hipSuccess) return e;
+        return launch_gemm(M, x1r, H, lo + L.w1, lo + L.b1, gr, F, nullptr, 0, (n + 63) / 64 * 64, F, H, k, EPI_BIAS_GELU,
+                           x1_ss * ab, g_ss * ab, 0, s, nullptr, 0, 0, 0, packed);
+    };
+    // Last layer of n sequences (at most kRowsMaxSeqs) from sequence b0 on, from the attention output of their first tokens:
+    // A holds token rows (a_first) or one row per sequence; x1c and gc are scratch of one row per sequence.  ss: student
+    // strides, elements.
+    auto first_rows_tail = [&](size_t lo, int b0, int n, const bf16* A, size_t a_ss, bool a_first, bf16* x1c, size_t x1c_ss,
+                               bf16* gc, size_t gc_ss) -> int {
+        const size_t sT = (size_t)rows * H;
+        SP_TRY(launch_rows_residual(M, lo + L.wo, lo + L.bo, A, a_ss, rows_layout(H), H, a_first, (const bf16*)x, sT, true, uo,
+                                    u_ss, cu + b0, T, n, k, s));
+        SP_MARK(SP_PHASE_LAST_FIRST);
+        SP_TRY(ffn_up(lo, n, x1c, x1c_ss, gc, gc_ss, true));
+        SP_MARK(SP_PHASE_LAST_FIRST);
+        SP_TRY(launch_rows_residual(M, lo + L.w2, lo + L.b2, gc, gc_ss, packed_layout(F), F, false, x1c, x1c_ss, false, ud,
+                                    u_ss, cu + b0, T, n, k, s));
+        SP_MARK(SP_PHASE_LAST_FIRST);
+        SP_TRY(launch_rows_pooler(M, lo, ud, u_ss, n, pooled, u_ss, k, s));
+        SP_TRY(launch_head_classify(M, pooled, n, B, kRowsU, k, z + (size_t)b0 * c.classes,
+                                    logits ? logits + (size_t)b0 * c.classes : nullptr, s));
+        SP_MARK(SP_PHASE_HEAD);
+        return SP_OK;
+    };
+    if (bf16_path(c) && T <= kRowsMaxTokens) {
+        const size_t sT = (size_t)rows * H, sG = (size_t)rows * F;
+        // (the partial forwards of the tests read the FFN activations row by row)
+        const RowsLayout gl = with_head ? packed_layout(F) : rows_layout(F);
+        if (stop_layers == 0) {
+            SP_TRY(launch_embed_ln(M, ids, cu, B, T, rows, mrows, k, x, att, s));
+            SP_MARK(SP_PHASE_EMBED);
         }
-    }
-    // the same for the first-token rows of the last layer when they are few (a batch of up to 128 sequences)
-    int csplit_o = 1, csplit_d = 1;
-    if (first_only && cmrows <= kSplitRows) {
-        for (int sp = kSplitMax; sp > 1; --sp) {
-            if (csplit_o == 1 && (H / 64) % sp == 0 && H / 64 / sp >= 2) csplit_o = sp;
-            if (csplit_d == 1 && (F / 64) % sp == 0 && F / 64 / sp >= 2) csplit_d = sp;
+        for (int l = 0; l < stop_layers; ++l) {
+            const size_t lo = L.layer0 + (size_t)l * L.layer_stride, pl = lo - L.layer_stride;
+            if ((long)T * k * H <= kRowsLnMaxElems) {
+                SP_TRY(launch_rows_qkv(M, lo, l ? ud : nullptr, u_ss, l ? pl + L.ln2g : L.emb_g, l ? pl + L.ln2b : L.emb_b,
+                                       ids, cu, B, T, x, qkv, vt, rows, k, s));
+            } else {
+                // (the embedding kernel zeroes the padding rows of x, and nothing writes them afterwards)
+                if (l == 0) SP_TRY(launch_embed_ln(M, ids, cu, B, T, rows, mrows, k, x, att, s));
+                else SP_TRY(launch_rows_ln_out(M, pl + L.ln2g, pl + L.ln2b, ud, u_ss, x, sT, T, k, s));
+                SP_MARK(l == 0 ? SP_PHASE_EMBED : SP_PHASE_LAYERNORM);
+                SP_TRY(launch_gemm(M, x, H, lo + L.wqkv, lo + L.bqkv, qkv, 3 * H, nullptr, 0, mrows, 3 * H, H, k, EPI_QKV, sH,
+                                   s3H, 0, s, vt, 2 * H, rows, sH));
+            }
+            SP_MARK(SP_PHASE_QKV);
+            if (with_head && !c.last_layer_all_tokens && l == c.layers - 1) {
+                SP_TRY(launch_attention_first(M, qkv, vt, att, cu, B, T, max_seqlen, rows, k, s));
+                SP_MARK(SP_PHASE_LAST_FIRST);
+                return first_rows_tail(lo, 0, B, (const bf16*)att, sT, true, (bf16*)x1, sT, (bf16*)g, sG);
+            }
+            SP_TRY(launch_attention(M, qkv, vt, att, cu, B, T, max_seqlen, rows, k, s));
+            SP_MARK(SP_PHASE_ATTENTION);
+            SP_TRY(launch_rows_residual(M, lo + L.wo, lo + L.bo, (const bf16*)att, sT, rows_layout(H), H, false,
+                                        (const bf16*)x, sT, false, uo, u_ss, cu, T, T, k, s));
+            SP_MARK(SP_PHASE_OPROJ);
+            SP_TRY(ffn_up(lo, T, x1, sT, g, sG, with_head));
+            SP_MARK(SP_PHASE_FFN_UP);
+            SP_TRY(launch_rows_residual(M, lo + L.w2, lo + L.b2, (const bf16*)g, sG, gl, F, false, (const bf16*)x1, sT, false,
+                                        ud, u_ss, cu, T, T, k, s));
+            SP_MARK(SP_PHASE_FFN_DOWN);
+            if (l == stop_layers - 1) {
+                SP_TRY(launch_rows_ln_out(M, lo + L.ln2g, lo + L.ln2b, ud, u_ss, x, sT, T, k, s));
+                SP_MARK(SP_PHASE_LAYERNORM);
+            }
         }
+        if (with_head) {
+            SP_TRY(launch_head(M, x, cu, B, T, rows, k, z, zpart, logits, s));
+            SP_MARK(SP_PHASE_HEAD);
+        }
+        return SP_OK;
     }
+    SP_TRY(launch_embed_ln(M, ids, cu, B, T, rows, mrows, k, x, att, s, xq, kActQuantScale, attq));
+    SP_MARK(SP_PHASE_EMBED);
     for (int l = 0; l < stop_layers; ++l) {
         const size_t lo = L.layer0 + (size_t)l * L.layer_stride;
         if (first_only && l == c.layers - 1) {
-            SP_TRY(launch_gather_first(M, x, cu, B, T, rows, cx, catt, crows, cmrows, k, s));
-            SP_MARK(SP_PHASE_LAST_FIRST);
-            // queries of the first tokens, folded through the key projection: qt[b][h] = Wk[:, h] q[b][h]
-            SP_TRY(launch_gemm(M, cx, H, lo + L.wqkv, lo + L.bqkv, cq, H, nullptr, 0, cmrows, H, H, k, EPI_BIAS, cH, cH, 0,
-                               s));
-            SP_TRY(launch_head_gemm(M, cq, (size_t)crows * H, 64, H, lo + L.wk_io, 64, H, 0, 0, false, cqt, cHH, H, nh * H,
-                                    cmrows, H, 64, k, s));
-            SP_MARK(SP_PHASE_LAST_FIRST);
-            // p-weighted mean of the token rows per (sequence, head), then the value projection of those rows
-            SP_TRY(launch_attention_first_fold(M, x, cqt, cxb, cu, B, T, max_seqlen, rows, crows, cmrows, k, s));
-            SP_TRY(launch_head_gemm(M, cxb, cHH, H, nh * H, lo + L.wqkv + (size_t)2 * H * H * ab, (size_t)64 * H, H,
-                                    lo + L.bqkv + (size_t)2 * H * 4, 64, true, catt, (size_t)crows * H, 64, H, cmrows, 64, H,
-                                    k, s));
-            SP_MARK(SP_PHASE_LAST_FIRST);
-            if (csplit_o > 1) {
-                // few rows: a 64-row tile walking the whole reduction range is a long serial chain; split it over
-                // workgroups and add the slices together with bias, residual and LayerNorm
-                SP_TRY(launch_gemm_splitk(M, catt, H, lo + L.wo, part, cmrows, H, H, k, csplit_o, cH, slice, s));
+            const bool own = T >= kFirstOnlyMinTokens;
+            const size_t sT = (size_t)rows * H, sC = (size_t)crows * H, hH = (size_t)c.heads * H;
+            const size_t s1 = own ? sC : sT, sq = own ? sC * c.heads : 3 * sT, sx = own ? sC * c.heads : (size_t)rows * F;
+            const size_t sg = (size_t)(own ? crows : rows) * F;
+            bf16* q1 = own ? (bf16*)(w + W.cq) + m0 * sC : (bf16*)vt;
+            bf16* att1 = own ? (bf16*)(w + W.catt) + m0 * sC : (bf16*)att;
+            bf16* qt1 = own ? (bf16*)(w + W.cqt) + m0 * sq : (bf16*)qkv;
+            bf16* xb1 = own ? (bf16*)(w + W.cxb) + m0 * sx : (bf16*)g;
+            bf16* x11 = own ? (bf16*)(w + W.cx1) + m0 * sC : (bf16*)x1;
+            bf16* g1 = own ? (bf16*)(w + W.cg) + m0 * sg : (bf16*)g;
+            for (int b0 = 0; b0 < B; b0 += kRowsMaxSeqs) {
+                const int n = B - b0 < kRowsMaxSeqs ? B - b0 : kRowsMaxSeqs;
+                SP_TRY(launch_fold_query(M, lo, x, rows, cu + b0, T, n, q1 + (size_t)b0 * H, s1, qt1 + b0 * hH, sq, k, s));
                 SP_MARK(SP_PHASE_LAST_FIRST);
-                SP_TRY(launch_ln_reduce(M, part, csplit_o, slice, lo + L.bo, cx, cx1, crows, cmrows, k, lo + L.ln1g,
-                                        lo + L.ln1b, s));
-            } else {
-                SP_TRY(launch_gemm(M, catt, H, lo + L.wo, lo + L.bo, cu2, H, cx, H, cmrows, H, H, k, EPI_BIAS_RESIDUAL, cH,
-                                   cH, cH, s));
+                SP_TRY(launch_attention_first_fold(M, x, qt1 + b0 * hH, sq, xb1 + b0 * hH, sx, cu + b0, n, T, max_seqlen, rows,
+                                                   k, s));
                 SP_MARK(SP_PHASE_LAST_FIRST);
-                SP_TRY(launch_layernorm(M, cu2, cx1, crows, cmrows, k, lo + L.ln1g, lo + L.ln1b, s));
+                SP_TRY(launch_rows_head_values(M, lo, xb1 + b0 * hH, sx, att1 + (size_t)b0 * H, s1, n, k, s));
+                SP_MARK(SP_PHASE_LAST_FIRST);
+                const int rc = first_rows_tail(lo, b0, n, att1 + (size_t)b0 * H, s1, false, x11 + (size_t)b0 * H, s1,
+                                               g1 + (size_t)b0 * F, sg);
+                if (rc != SP_OK) return rc;
             }
-            SP_MARK(SP_PHASE_LAST_FIRST);
-            SP_TRY(launch_gemm(M, cx1, H, lo + L.w1, lo + L.b1, cg, F, nullptr, 0, cmrows, F, H, k, EPI_BIAS_GELU, cH, cF, 0,
-                               s));
-            SP_MARK(SP_PHASE_LAST_FIRST);
-            if (csplit_d > 1) {
-                SP_TRY(launch_gemm_splitk(M, cg, F, lo + L.w2, part, cmrows, H, F, k, csplit_d, cF, slice, s));
-                SP_MARK(SP_PHASE_LAST_FIRST);
-                SP_TRY(launch_ln_reduce(M, part, csplit_d, slice, lo + L.b2, cx1, cx, crows, cmrows, k, lo + L.ln2g,
-                                        lo + L.ln2b, s));
-            } else {
-                SP_TRY(launch_gemm(M, cg, F, lo + L.w2, lo + L.b2, cu2, H, cx1, H, cmrows, H, F, k, EPI_BIAS_RESIDUAL, cF,
-                                   cH, cH, s));
-                SP_MARK(SP_PHASE_LAST_FIRST);
-                SP_TRY(launch_layernorm(M, cu2, cx, crows, cmrows, k, lo + L.ln2g, lo + L.ln2b, s));
-            }
-            SP_MARK(SP_PHASE_LAST_FIRST);
-            compact_final = true;
-            continue;
+            return SP_OK;
         }
         if (fp8)
             SP_TRY(launch_gemm_fp8(M, xq, H, lo + L.wqkv8, lo + L.sqkv, lo + L.bqkv, kActQuantScale, qkv, 3 * H, nullptr, 0,
@@ -405,43 +444,14 @@ static int run_students(const sp_model* M0, const WsLayout& W, const int32_t* id
         SP_TRY(launch_attention(M, qkv, vt, fp8 && with_head ? nullptr : att, cu, B, T, max_seqlen, rows, k, s, attq,
                                 kActQuantScale));
         SP_MARK(SP_PHASE_ATTENTION);
-        if (with_head && !c.last_layer_all_tokens && l == c.layers - 1 && m0 == 0 && first_rows_tail_supported(c, B)) {
-            // last layer of a whole forward of a few sequences: from here on only their first-token rows are needed,
-            // and those go through per-feature dot products instead of 64-row tiles.  Calls of up to 128 tokens: the
-            // small-call head takes over from the raw down-projection (one slice); longer ones: pooler by dot
-            // products as well, then the classifier kernel (the pooled rows sit behind the scratch).
-            float* ut = part + (size_t)k * slice;           // behind the slice the head reads
-            if (split_o > 1 && split_d > 1) {
-                SP_TRY(launch_first_rows_tail(M, lo, att, x, x1, g, ut, part, slice, nullptr, cu, B, T, rows, k, s));
-                small_head = true;
-                small_head_lo = lo;
-                small_head_splits = 1;
-            } else {
-                SP_TRY(launch_first_rows_tail(M, lo, att, x, x1, g, ut, nullptr, 0, ut + first_rows_tail_scratch_floats(c, k),
-                                              cu, B, T, rows, k, s));
-                first_tail = true;
-            }
-            SP_MARK(SP_PHASE_LAST_FIRST);
-            continue;
-        }
-        if (split_o > 1) {
-            // few tokens: the reduction range is split over workgroups, and the slices are added together with the
-            // bias, the residual and the LayerNorm
-            SP_TRY(launch_gemm_splitk(M, att, H, lo + L.wo, part, mrows, H, H, k, split_o, sH, slice, s));
-            SP_MARK(SP_PHASE_OPROJ);
-            SP_TRY(launch_ln_reduce(M, part, split_o, slice, lo + L.bo, x, x1, rows, mrows, k, lo + L.ln1g, lo + L.ln1b, s));
-            SP_MARK(SP_PHASE_LAYERNORM);
-        } else {
-            if (fp8)
-                SP_TRY(launch_gemm_fp8(M, attq, H, lo + L.wo8, lo + L.so, lo + L.bo, kActQuantScale, u, H, x, H, mrows, H, H,
-                                       k, EPI_BIAS_RESIDUAL, qH, sH, sH, s, nullptr, 0, 0, 0, 1.f));
-            else
-                SP_TRY(launch_gemm(M, att, H, lo + L.wo, lo + L.bo, u, H, x, H, mrows, H, H, k, EPI_BIAS_RESIDUAL, sH, sH,
-                                   sH, s));
-            SP_MARK(SP_PHASE_OPROJ);
-            SP_TRY(launch_layernorm(M, u, x1, rows, mrows, k, lo + L.ln1g, lo + L.ln1b, s, x1q, kActQuantScale));
-            SP_MARK(SP_PHASE_LAYERNORM);
-        }
+        if (fp8)
+            SP_TRY(launch_gemm_fp8(M, attq, H, lo + L.wo8, lo + L.so, lo + L.bo, kActQuantScale, u, H, x, H, mrows, H, H, k,
+                                   EPI_BIAS_RESIDUAL, qH, sH, sH, s, nullptr, 0, 0, 0, 1.f));
+        else
+            SP_TRY(launch_gemm(M, att, H, lo + L.wo, lo + L.bo, u, H, x, H, mrows, H, H, k, EPI_BIAS_RESIDUAL, sH, sH, sH, s));
+        SP_MARK(SP_PHASE_OPROJ);
+        SP_TRY(launch_layernorm(M, u, x1, rows, mrows, k, lo + L.ln1g, lo + L.ln1b, s, x1q, kActQuantScale));
+        SP_MARK(SP_PHASE_LAYERNORM);
         if (fp8)
             SP_TRY(launch_gemm_fp8(M, x1q, H, lo + L.w18, lo + L.s1, lo + L.b1, kActQuantScale, gq, F, nullptr, 0, mrows, F,
                                    H, k, EPI_BIAS_GELU, qH, qF, 0, s, nullptr, 0, 0, 0, kActQuantScale));
@@ -449,46 +459,17 @@ static int run_students(const sp_model* M0, const WsLayout& W, const int32_t* id
             SP_TRY(launch_gemm(M, x1, H, lo + L.w1, lo + L.b1, g, F, nullptr, 0, mrows, F, H, k, EPI_BIAS_GELU, sH, sF, 0,
                                s));
         SP_MARK(SP_PHASE_FFN_UP);
-        if (split_d > 1) {
-            SP_TRY(launch_gemm_splitk(M, g, F, lo + L.w2, part, mrows, H, F, k, split_d, sF, slice, s));
-            SP_MARK(SP_PHASE_FFN_DOWN);
-            if (with_head && l == c.layers - 1 && m0 == 0) {
-                // last layer of a whole forward: only the first-token rows go on, and the head rebuilds them from the
-                // slices itself
-                small_head = true;
-                small_head_lo = lo;
-                small_head_splits = split_d;
-            } else {
-                SP_TRY(launch_ln_reduce(M, part, split_d, slice, lo + L.b2, x1, x, rows, mrows, k, lo + L.ln2g, lo + L.ln2b, s));
-                SP_MARK(SP_PHASE_LAYERNORM);
-            }
-        } else {
-            if (fp8)
-                SP_TRY(launch_gemm_fp8(M, gq, F, lo + L.w28, lo + L.s2, lo + L.b2, kActQuantScale, u, H, x1, H, mrows, H, F,
-                                       k, EPI_BIAS_RESIDUAL, qF, sH, sH, s, nullptr, 0, 0, 0, 1.f));
-            else
-                SP_TRY(launch_gemm(M, g, F, lo + L.w2, lo + L.b2, u, H, x1, H, mrows, H, F, k, EPI_BIAS_RESIDUAL, sF, sH,
-                                   sH, s));
-            SP_MARK(SP_PHASE_FFN_DOWN);
-            SP_TRY(launch_layernorm(M, u, x, rows, mrows, k, lo + L.ln2g, lo + L.ln2b, s, xq, kActQuantScale));
-            SP_MARK(SP_PHASE_LAYERNORM);
-        }
+        if (fp8)
+            SP_TRY(launch_gemm_fp8(M, gq, F, lo + L.w28, lo + L.s2, lo + L.b2, kActQuantScale, u, H, x1, H, mrows, H, F, k,
+                                   EPI_BIAS_RESIDUAL, qF, sH, sH, s, nullptr, 0, 0, 0, 1.f));
+        else
+            SP_TRY(launch_gemm(M, g, F, lo + L.w2, lo + L.b2, u, H, x1, H, mrows, H, F, k, EPI_BIAS_RESIDUAL, sF, sH, sH, s));
+        SP_MARK(SP_PHASE_FFN_DOWN);
+        SP_TRY(launch_layernorm(M, u, x, rows, mrows, k, lo + L.ln2g, lo + L.ln2b, s, xq, kActQuantScale));
+        SP_MARK(SP_PHASE_LAYERNORM);
     }
     if (with_head) {
-        if (compact_final) {
-            // pooler as one more student-grouped projection (tanh epilogue) on the first-token rows, then the classifier
-            // (into the pre-LayerNorm scratch rows, which are free by now: the queries and the attention output of the
-            // first tokens stay readable after the call)
-            SP_TRY(launch_gemm(M, cx, H, L.wp_t, L.bp, cu2, H, nullptr, 0, cmrows, H, H, k, EPI_BIAS_TANH, cH, cH, 0, s));
-            SP_TRY(launch_head_classify(M, cu2, B, crows, k, z, logits, s));
-        } else if (first_tail)
-            SP_TRY(launch_head_classify(M, part + (size_t)k * slice + first_rows_tail_scratch_floats(c, k), B,
-                                        first_rows_tail_pooled_rows(), k, z, logits, s, true));
-        else if (small_head)
-            SP_TRY(launch_head_small(M, part, small_head_splits, slice, small_head_lo + L.b2, x1, small_head_lo + L.ln2g,
-                                     small_head_lo + L.ln2b, cu, B, T, rows, k, z, zpart, logits, s));
-        else
-            SP_TRY(launch_head(M, x, cu, B, T, rows, k, z, zpart, logits, s));
+        SP_TRY(launch_head(M, x, cu, B, T, rows, k, z, zpart, logits, s));
         SP_MARK(SP_PHASE_HEAD);
     }
 #undef SP_MARK

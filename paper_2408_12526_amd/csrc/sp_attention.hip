@@ -509,135 +509,6 @@ __global__ __launch_bounds__(256, 2) void attention_bf16_kernel(const bf16* __re
 // of every token onto 2 H features, and reading those back, by one read of x.
 // -------------------------------------------------------------------------------------
 
-// Per-head small products: out[m][r][h][n] = sum_k A[m][r][h][k] W[m][h][n][k] (+ bias[m][h][n]), r < 32 * mtiles,
-// n < 32 * NT * nstrips, k < Kd.  One strip of 32 rows x (32 NT) outputs per wave (the strip shares the row operand and
-// writes runs of 64 NT contiguous bytes), fragments read straight from global memory (the work is a few GFLOP per
-// call).  Strides are in elements; the weights live in the arena at w_off (+ student stride).
-template <int NT>
-__global__ __launch_bounds__(256) void head_gemm_kernel(const bf16* __restrict__ A, size_t a_ss, size_t a_hs, int lda,
-                                                        const char* __restrict__ arena, size_t student_stride,
-                                                        size_t w_off, size_t w_hs, int ldw, size_t b_off, size_t b_hs,
-                                                        int has_bias, bf16* __restrict__ out, size_t o_ss, size_t o_hs,
-                                                        int ldo, int mtiles, int nstrips, int Kd, int heads, int total)
-{
-    // XCD-aware order: consecutive workgroup ids go to different XCDs; each XCD gets a contiguous run of (student,
-    // head, group of four strips), so a head's weight slice is fetched into one L2 instead of all eight.
-    const int chunk = (total + 7) >> 3;
-    const int lin = (int)(blockIdx.x & 7) * chunk + (int)(blockIdx.x >> 3);
-    if ((int)(blockIdx.x >> 3) >= chunk || lin >= total) return;
-    const int per_head = (mtiles * nstrips + 3) / 4;
-    const int m = lin / (per_head * heads), h = (lin / per_head) % heads;
-    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-    const int item = (lin % per_head) * 4 + wave;
-    if (item >= mtiles * nstrips) return;
-    const int ns = item % nstrips, mt = item / nstrips;
-    const int j31 = lane & 31, g = lane >> 5;
-    const bf16* a = A + (size_t)m * a_ss + (size_t)h * a_hs + (size_t)(mt * 32 + j31) * lda + 8 * g;
-    const bf16* w = (const bf16*)(arena + (size_t)m * student_stride + w_off) + (size_t)h * w_hs +
-                    (size_t)(ns * NT * 32 + j31) * ldw + 8 * g;
-    f32x16 acc[NT];
-#pragma unroll
-    for (int t = 0; t < NT; ++t)
-#pragma unroll
-        for (int e = 0; e < 16; ++e) acc[t][e] = 0.f;
-#pragma unroll 8
-    for (int k0 = 0; k0 < Kd; k0 += 16) {
-        const bf16x8 fa = *(const bf16x8*)(a + k0);
-#pragma unroll
-        for (int t = 0; t < NT; ++t) {
-            const bf16x8 fw = *(const bf16x8*)(w + (size_t)t * 32 * ldw + k0);
-            acc[t] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(fw, fa, acc[t], 0, 0, 0);   // rows: output features, columns: r
-        }
-    }
-    // lane: row r = j31 of the strip; output features 32 t + 8 (v / 4) + 4 g + v % 4.  The strip goes through a
-    // wave-private LDS tile so that it leaves as whole 16-byte-per-lane row segments (eight-byte pieces scattered
-    // over 32 rows per instruction are several times slower on the way to memory).
-    constexpr int SW = NT * 32;                             // strip width (features)
-    constexpr int PITCH = SW * 2 + 16;                      // bytes per staged row
-    __shared__ __attribute__((aligned(16))) char stage_all[4][32 * PITCH];
-    char* stg = stage_all[wave];
-    const float* bias = (const float*)(arena + (size_t)m * student_stride + b_off) + (size_t)h * b_hs + ns * SW;
-#pragma unroll
-    for (int t = 0; t < NT; ++t)
-#pragma unroll
-        for (int v4 = 0; v4 < 4; ++v4) {
-            const int f = 32 * t + 8 * v4 + 4 * g;
-            bf16x4 r;
-#pragma unroll
-            for (int e = 0; e < 4; ++e) r[e] = (bf16)(acc[t][4 * v4 + e] + (has_bias ? bias[f + e] : 0.f));
-            *(bf16x4*)(stg + j31 * PITCH + f * 2) = r;
-        }
-    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-    __builtin_amdgcn_wave_barrier();
-    constexpr int CPR = SW / 8, RPI = 64 / CPR;             // 16-byte chunks per row, rows per instruction
-    const int rr = lane / CPR, cc = lane % CPR;
-    bf16* o = out + (size_t)m * o_ss + (size_t)h * o_hs + (size_t)(mt * 32) * ldo + ns * SW + cc * 8;
-#pragma unroll
-    for (int r0 = 0; r0 < 32; r0 += RPI)
-        *(uint4*)(o + (size_t)(r0 + rr) * ldo) = *(const uint4*)(stg + (r0 + rr) * PITCH + cc * 16);
-}
-
-// The same products when the reduction is long and the outputs are few (the value projection of the weighted mean rows:
-// Kd = H, 64 outputs per head): one 32-row x 64-output item per workgroup, its four waves split the reduction range, and
-// the partial tiles are added through LDS (waves in a fixed order), so that a wave's chain of dependent loads is a quarter
-// as long and four times as many compute units take part.  Kd must be a multiple of 64.
-__global__ __launch_bounds__(256) void head_gemm_ksplit_kernel(const bf16* __restrict__ A, size_t a_ss, size_t a_hs,
-                                                               int lda, const char* __restrict__ arena,
-                                                               size_t student_stride, size_t w_off, size_t w_hs,
-                                                               int ldw, size_t b_off, size_t b_hs, int has_bias,
-                                                               bf16* __restrict__ out, size_t o_ss, size_t o_hs, int ldo,
-                                                               int mtiles, int nstrips, int Kd, int heads, int total)
-{
-    constexpr int NT = 2, SW = NT * 32, PP = 33;            // strip width; pitch of a feature's 32 rows (floats)
-    __shared__ float part[4 * SW * PP];
-    // XCD-aware order as in head_gemm_kernel: a head's weight slice is fetched into one L2
-    const int chunk = (total + 7) >> 3;
-    const int lin = (int)(blockIdx.x & 7) * chunk + (int)(blockIdx.x >> 3);
-    if ((int)(blockIdx.x >> 3) >= chunk || lin >= total) return;
-    const int per_head = mtiles * nstrips;
-    const int m = lin / (per_head * heads), h = (lin / per_head) % heads, item = lin % per_head;
-    const int ns = item % nstrips, mt = item / nstrips;
-    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-    const int j31 = lane & 31, g = lane >> 5;
-    const int kw = Kd / 4;                                  // this wave's share of the reduction range
-    const bf16* a = A + (size_t)m * a_ss + (size_t)h * a_hs + (size_t)(mt * 32 + j31) * lda + wave * kw + 8 * g;
-    const bf16* w = (const bf16*)(arena + (size_t)m * student_stride + w_off) + (size_t)h * w_hs +
-                    (size_t)(ns * SW + j31) * ldw + wave * kw + 8 * g;
-    f32x16 acc[NT];
-#pragma unroll
-    for (int t = 0; t < NT; ++t)
-#pragma unroll
-        for (int e = 0; e < 16; ++e) acc[t][e] = 0.f;
-#pragma unroll 12
-    for (int k0 = 0; k0 < kw; k0 += 16) {
-        const bf16x8 fa = *(const bf16x8*)(a + k0);
-#pragma unroll
-        for (int t = 0; t < NT; ++t) {
-            const bf16x8 fw = *(const bf16x8*)(w + (size_t)t * 32 * ldw + k0);
-            acc[t] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(fw, fa, acc[t], 0, 0, 0);   // rows: output features, columns: r
-        }
-    }
-    // lane: row r = j31 of the strip; output features 32 t + 8 (v / 4) + 4 g + v % 4
-#pragma unroll
-    for (int t = 0; t < NT; ++t)
-#pragma unroll
-        for (int v = 0; v < 16; ++v)
-            part[(wave * SW + 32 * t + 8 * (v / 4) + 4 * g + v % 4) * PP + j31] = acc[t][v];
-    __syncthreads();
-    // thread: row r = tid % 32, eight neighbouring features: one 16-byte piece of the output row
-    const int r = tid & 31, f0 = (tid >> 5) * 8;
-    const float* bias = (const float*)(arena + (size_t)m * student_stride + b_off) + (size_t)h * b_hs + ns * SW + f0;
-    bf16x8 o8;
-#pragma unroll
-    for (int i = 0; i < 8; ++i) {
-        float sum = has_bias ? bias[i] : 0.f;
-#pragma unroll
-        for (int wv = 0; wv < 4; ++wv) sum += part[(wv * SW + f0 + i) * PP + r];
-        o8[i] = (bf16)sum;
-    }
-    *(bf16x8*)(out + (size_t)m * o_ss + (size_t)h * o_hs + (size_t)(mt * 32 + r) * ldo + ns * SW + f0) = o8;
-}
-
 typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
 
 // Maximum / sum over the four lanes l % 16 + {0, 16, 32, 48} (every lane active).
@@ -677,7 +548,7 @@ __device__ inline float sum_across_rows(float v)
 // 66 KB of LDS at hidden width 768 and at most 128 registers, so two workgroups share a compute unit and one's
 // start-up and barrier waits are covered by the other.
 //   qt   [m][b][head][H]   folded queries (row stride HEADS * H)
-//   xbar [m][b][head][H]   output; rows b in [B, gridDim.x) are zeroed (they feed padded projections)
+//   xbar [m][b][head][H]   output
 constexpr int kFoldWaves = 8;
 template <int HEADS>
 struct FoldLds {
@@ -693,7 +564,8 @@ __global__ __launch_bounds__(512, HEADS == 16 ? 2 : 4) void attention_first_fold
                                                                       const bf16* __restrict__ qt,
                                                                       bf16* __restrict__ xbar,
                                                                       const int32_t* __restrict__ cu, int B, int Tn,
-                                                                      int rows, int crows, int max_seqlen)
+                                                                      int rows, size_t qt_ss, size_t xb_ss,
+                                                                      int max_seqlen)
 {
     using F = FoldLds<HEADS>;
     constexpr int H = F::H, FW = F::FW, SCP = F::SCP, NW = kFoldWaves;
@@ -705,11 +577,7 @@ __global__ __launch_bounds__(512, HEADS == 16 ? 2 : 4) void attention_first_fold
     const int m = blockIdx.y, b = blockIdx.x;
     const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     char* slab = (char*)fold_smem + wave * F::slab_bytes;   // this wave's features of the tile: [token][FW / 8 chunks]
-    bf16* xb = xbar + ((size_t)m * crows + b) * HEADS * H;
-    if (b >= B) {
-        for (int c = tid; c < HEADS * H / 8; c += 64 * NW) ((uint4*)xb)[c] = make_uint4(0, 0, 0, 0);
-        return;
-    }
+    bf16* xb = xbar + (size_t)m * xb_ss + (size_t)b * HEADS * H;
     int t0 = cu[b], t1 = cu[b + 1];
     t0 = t0 < 0 ? 0 : (t0 > Tn - 1 ? Tn - 1 : t0);
     int L = t1 - t0;
@@ -723,7 +591,7 @@ __global__ __launch_bounds__(512, HEADS == 16 ? 2 : 4) void attention_first_fold
     // folded-query operands: row = head, the wave's features in steps of 32 (lane: eight of them)
     bf16x8 fq[KS];
     {
-        const bf16* qr = qt + (((size_t)m * crows + b) * HEADS + (l16 < HEADS ? l16 : 0)) * H + wave * FW + 8 * kg;
+        const bf16* qr = qt + (size_t)m * qt_ss + ((size_t)b * HEADS + (l16 < HEADS ? l16 : 0)) * H + wave * FW + 8 * kg;
 #pragma unroll
         for (int st = 0; st < KS; ++st) {
             fq[st] = *(const bf16x8*)(qr + 32 * st);
@@ -959,53 +827,19 @@ hipError_t launch_attention(const sp_model* M, const void* qkv, const void* vt, 
     return hipGetLastError();
 }
 
-hipError_t launch_head_gemm(const sp_model* M, const void* A, size_t a_ss, size_t a_hs, int lda, size_t w_off,
-                            size_t w_hs, int ldw, size_t b_off, size_t b_hs, bool has_bias, void* out, size_t o_ss,
-                            size_t o_hs, int ldo, int mrows, int N, int Kd, int k, hipStream_t s)
-{
-    const sp_config& c = M->cfg;
-    if (!bf16_path(c) || mrows % 32 || N % 32 || Kd % 16 || lda % 8 || ldw % 8 || ldo % 8 || a_hs % 8 ||
-        w_hs % 8 || o_hs % 8)
-        return hipErrorInvalidValue;
-    const int mtiles = mrows / 32;
-    if (N % 128 != 0 && N % 64 == 0 && Kd >= 256 && Kd % 64 == 0) {
-        const int nstrips = N / 64;
-        const int total = k * c.heads * mtiles * nstrips;
-        dim3 grid((unsigned)((total + 7) / 8 * 8));
-        hipLaunchKernelGGL(head_gemm_ksplit_kernel, grid, dim3(256), 0, s, (const bf16*)A, a_ss, a_hs, lda, M->arena,
-                           M->L.student_stride, w_off, w_hs, ldw, b_off, b_hs, has_bias ? 1 : 0, (bf16*)out, o_ss, o_hs,
-                           ldo, mtiles, nstrips, Kd, c.heads, total);
-        return hipGetLastError();
-    }
-#define SP_HEAD_GEMM(NT)                                                                                            \
-    do {                                                                                                            \
-        const int nstrips = N / (32 * NT);                                                                          \
-        const int total = k * c.heads * ((mtiles * nstrips + 3) / 4);                                               \
-        dim3 grid((unsigned)((total + 7) / 8 * 8));                                                                 \
-        hipLaunchKernelGGL(head_gemm_kernel<NT>, grid, dim3(256), 0, s, (const bf16*)A, a_ss, a_hs, lda, M->arena,  \
-                           M->L.student_stride, w_off, w_hs, ldw, b_off, b_hs, has_bias ? 1 : 0, (bf16*)out, o_ss,  \
-                           o_hs, ldo, mtiles, nstrips, Kd, c.heads, total);                                         \
-    } while (0)
-    if (N % 128 == 0) SP_HEAD_GEMM(4);
-    else if (N % 64 == 0) SP_HEAD_GEMM(2);
-    else SP_HEAD_GEMM(1);
-#undef SP_HEAD_GEMM
-    return hipGetLastError();
-}
-
 bool attention_first_fold_supported(const sp_config& c, int max_seqlen)
 {
     (void)max_seqlen;                                       // any length: the softmax is a running one
     return bf16_path(c) && c.hidden / c.heads == kD && c.heads % 4 == 0 && c.heads <= 16;
 }
 
-hipError_t launch_attention_first_fold(const sp_model* M, const void* x, const void* qt, void* xbar, const int32_t* cu,
-                                       int B, int T, int max_seqlen, int rows, int crows, int cmrows, int k,
+hipError_t launch_attention_first_fold(const sp_model* M, const void* x, const void* qt, size_t qt_ss, void* xbar,
+                                       size_t xb_ss, const int32_t* cu, int B, int T, int max_seqlen, int rows, int k,
                                        hipStream_t s)
 {
     const sp_config& c = M->cfg;
-    if (!attention_first_fold_supported(c, max_seqlen) || cmrows < B || cmrows > crows) return hipErrorInvalidValue;
-    dim3 grid((unsigned)cmrows, (unsigned)k);
+    if (!attention_first_fold_supported(c, max_seqlen)) return hipErrorInvalidValue;
+    dim3 grid((unsigned)B, (unsigned)k);
 #define SP_FOLD(HEADS)                                                                                              \
     do {                                                                                                            \
         auto kern = attention_first_fold_kernel<HEADS>;                                                             \
@@ -1018,7 +852,7 @@ hipError_t launch_attention_first_fold(const sp_model* M, const void* x, const v
             raised = true;                                                                                          \
         }                                                                                                           \
         hipLaunchKernelGGL(kern, grid, dim3(64 * kFoldWaves), smem, s, (const bf16*)x, (const bf16*)qt, (bf16*)xbar,  \
-                           cu, B, T, rows, crows, max_seqlen);                                                      \
+                           cu, B, T, rows, qt_ss, xb_ss, max_seqlen);                                              \
     } while (0)
     switch (c.heads) {
         case 4: SP_FOLD(4); break;

@@ -198,75 +198,6 @@ __global__ __launch_bounds__(256) void layernorm_kernel(const char* arena, size_
     }
 }
 
-// Sum of the slices of a split reduction + bias + residual, then LayerNorm: one wave per row.
-template <typename T, int MAXC>
-__global__ __launch_bounds__(256) void ln_reduce_kernel(const char* arena, size_t student_stride, size_t g_off,
-                                                        size_t b_off, size_t bias_off, const float* __restrict__ part,
-                                                        int splits, size_t slice_elems, const T* __restrict__ res,
-                                                        T* __restrict__ out, int rows, int mrows, int H, float eps)
-{
-    const int m = blockIdx.y, lane = threadIdx.x & 63;
-    const int row = blockIdx.x * 4 + (threadIdx.x >> 6);
-    if (row >= mrows) return;
-    const int nch = H >> 3;
-    const char* sb = arena + (size_t)m * student_stride;
-    float gg[MAXC][8], bb[MAXC][8];
-    load_gamma_beta<MAXC>((const float*)(sb + g_off), (const float*)(sb + b_off), nch, lane, gg, bb);
-    const float* bias = (const float*)(sb + bias_off);
-    const T* rrow = res + ((size_t)m * rows + row) * H;
-    const float* prow = part + (size_t)m * splits * slice_elems + (size_t)row * H;
-    float v[MAXC][8];
-#pragma unroll
-    for (int i = 0; i < MAXC; ++i) {
-        const int c = lane + 64 * i;
-        if (c < nch) {
-            float r8[8], b8[8];
-            load8(rrow + c * 8, r8);
-            load8(bias + c * 8, b8);
-#pragma unroll
-            for (int e = 0; e < 8; ++e) v[i][e] = r8[e] + b8[e];
-            float p8[kSplitMax][8];                           // all slices requested at once, added in ascending order
-#pragma unroll
-            for (int sidx = 0; sidx < kSplitMax; ++sidx)
-                if (sidx < splits) load8(prow + (size_t)sidx * slice_elems + c * 8, p8[sidx]);
-#pragma unroll
-            for (int sidx = 0; sidx < kSplitMax; ++sidx)
-                if (sidx < splits) {
-#pragma unroll
-                    for (int e = 0; e < 8; ++e) v[i][e] += p8[sidx][e];
-                }
-        }
-    }
-    ln_row_store<T, MAXC>(v, nch, lane, H, gg, bb, eps, out + ((size_t)m * rows + row) * H);
-}
-
-// First-token rows: one wave per (student, sequence).
-template <typename T>
-__global__ __launch_bounds__(256) void gather_first_kernel(const T* __restrict__ x, const int32_t* __restrict__ cu, int B,
-                                                           int Tn, int rows, int H, T* __restrict__ xc,
-                                                           T* __restrict__ attc, int crows, int cmrows)
-{
-    const int m = blockIdx.y, lane = threadIdx.x & 63;
-    const int b = blockIdx.x * 4 + (threadIdx.x >> 6);
-    if (b >= cmrows) return;
-    const int nch = H >> 3;
-    T* dst = xc + ((size_t)m * crows + b) * H;
-    if (b >= B) {                                  // padding rows of the compact tile: finite contents
-        const float zero8[8] = {0, 0, 0, 0, 0, 0, 0, 0};
-        T* arow = attc + ((size_t)m * crows + b) * H;
-        for (int c = lane; c < nch; c += 64) { store8(dst + c * 8, zero8); store8(arow + c * 8, zero8); }
-        return;
-    }
-    int r = cu[b];
-    r = r < 0 ? 0 : (r >= Tn ? Tn - 1 : r);
-    const T* src = x + ((size_t)m * rows + r) * H;
-    for (int c = lane; c < nch; c += 64) {
-        float v[8];
-        load8(src + c * 8, v);
-        store8(dst + c * 8, v);
-    }
-}
-
 // ---- head -------------------------------------------------------------------------
 // Stage 1: one workgroup = (group of kSeqPerWg sequences, student, slice of 64 pooler outputs).
 // pooled[n] = tanh(bp[n] + sum_i cls[i] Wp[i][n]); the slice's share of the classifier,
@@ -450,102 +381,6 @@ __global__ __launch_bounds__(256) void head_sum_kernel(const char* arena, size_t
     }
 }
 
-// Stage 1 of the head for calls of a few dozen tokens (same grid and pooler as head_pool_kernel): the first-token
-// rows are rebuilt from the slices of the last split reduction: slices (ascending) + bias + residual, LayerNorm,
-// rounded to bf16: exactly what ln_reduce_kernel would have stored for these rows (the other rows of the last layer
-// reach no result, so that launch is saved).  Taking the sums of stage 2 in the workgroup that finishes last (a ticket
-// counter after a device-scope fence) was measured slower than the launch of head_sum_kernel it saves.
-__global__ __launch_bounds__(256) void head_small_kernel(const char* arena, size_t student_stride, size_t wp_off,
-                                                         size_t bp_off, size_t wc_off, size_t bc_off, size_t g_off,
-                                                         size_t b_off, size_t bias_off, const float* __restrict__ part,
-                                                         int splits, size_t slice_elems, const bf16* __restrict__ res,
-                                                         const int32_t* __restrict__ cu, int B, int Tn, int rows, int H,
-                                                         int C, float eps, float* __restrict__ zpart)
-{
-    extern __shared__ float smem[];
-    float* xs = smem;                      // [kSeqPerWg][H]
-    float* red = smem + kSeqPerWg * H;     // [4][kSeqPerWg][64]
-    const int b0 = blockIdx.x * kSeqPerWg, m = blockIdx.y, slice = blockIdx.z, nslice = gridDim.z;
-    const int tid = threadIdx.x, lane = tid & 63, wv = tid >> 6;
-    const int nseq = (B - b0) < kSeqPerWg ? (B - b0) : kSeqPerWg;
-    const char* sb = arena + (size_t)m * student_stride;
-    const float* bias = (const float*)(sb + bias_off);
-    const float* gam = (const float*)(sb + g_off);
-    const float* bet = (const float*)(sb + b_off);
-    PoolerWeights<bf16> pw;
-    pw.request((const bf16*)(sb + wp_off), H, slice, lane, wv);
-    // A thread owns elements tid + 256 j of a row (H <= 1024: j < 4).  Everything a row needs is requested before
-    // anything is used (a loop that loads and uses per element would pay one memory round trip per iteration).
-    constexpr int MAXJ = 4;                // hidden <= 1024 (checked by the launcher)
-    __shared__ float wsum[2][4];
-    float gj[MAXJ], bj[MAXJ], biasj[MAXJ];
-#pragma unroll
-    for (int j = 0; j < MAXJ; ++j) {
-        const int i = tid + 256 * j;
-        gj[j] = i < H ? gam[i] : 0.f;
-        bj[j] = i < H ? bet[i] : 0.f;
-        biasj[j] = i < H ? bias[i] : 0.f;
-    }
-    for (int s = 0; s < nseq; ++s) {
-        int r = cu[b0 + s];
-        r = r < 0 ? 0 : (r >= Tn ? Tn - 1 : r);
-        const bf16* rrow = res + ((size_t)m * rows + r) * H;
-        const float* prow = part + (size_t)m * splits * slice_elems + (size_t)r * H;
-        float v[MAXJ], p8[MAXJ][kSplitMax];
-#pragma unroll
-        for (int j = 0; j < MAXJ; ++j) {
-            const int i = tid + 256 * j;
-            v[j] = i < H ? (float)rrow[i] : 0.f;
-#pragma unroll
-            for (int sidx = 0; sidx < kSplitMax; ++sidx)
-                p8[j][sidx] = i < H && sidx < splits ? prow[(size_t)sidx * slice_elems + i] : 0.f;
-        }
-        float sum = 0.f;
-#pragma unroll
-        for (int j = 0; j < MAXJ; ++j) {
-            v[j] += biasj[j];
-#pragma unroll
-            for (int sidx = 0; sidx < kSplitMax; ++sidx)      // slices in ascending order
-                if (sidx < splits) v[j] += p8[j][sidx];
-            if (tid + 256 * j < H) sum += v[j];
-        }
-        sum = wave_sum(sum);
-        if (lane == 0) wsum[0][wv] = sum;
-        __syncthreads();
-        const float inv_h = __builtin_amdgcn_rcpf((float)H);
-        const float mean = (wsum[0][0] + wsum[0][1] + wsum[0][2] + wsum[0][3]) * inv_h;
-        float q = 0.f;
-#pragma unroll
-        for (int j = 0; j < MAXJ; ++j)
-            if (tid + 256 * j < H) { const float d = v[j] - mean; q += d * d; }
-        q = wave_sum(q);
-        if (lane == 0) wsum[1][wv] = q;
-        __syncthreads();
-        const float inv = __builtin_amdgcn_rsqf((wsum[1][0] + wsum[1][1] + wsum[1][2] + wsum[1][3]) * inv_h + eps);
-#pragma unroll
-        for (int j = 0; j < MAXJ; ++j) {
-            const int i = tid + 256 * j;
-            if (i < H) xs[s * H + i] = (float)(bf16)(gj[j] * ((v[j] - mean) * inv) + bj[j]);
-        }
-        __syncthreads();                       // wsum is rewritten for the next row; xs is read by everybody below
-    }
-    const int n = slice * 64 + lane;
-    pw.multiply(xs, red, H, nseq, lane, wv);
-    __syncthreads();
-    const float bpn = ((const float*)(sb + bp_off))[n];
-    const bf16* Wc = (const bf16*)(sb + wc_off);
-    for (int s = wv; s < nseq; s += 4) {
-        float p = bpn;
-#pragma unroll
-        for (int q = 0; q < 4; ++q) p += red[(q * kSeqPerWg + s) * 64 + lane];
-        p = tanhf(p);
-        for (int c = 0; c < C; ++c) {
-            const float t = wave_sum(p * (float)Wc[(size_t)n * C + c]);
-            if (lane == 0) zpart[(((size_t)m * nslice + slice) * B + (b0 + s)) * C + c] = t;
-        }
-    }
-}
-
 // logits[i] = sum over students of z[m][i], m ascending.
 __global__ void sum_students_kernel(const float* __restrict__ z, int n, int k, float* __restrict__ logits)
 {
@@ -558,29 +393,47 @@ __global__ void sum_students_kernel(const float* __restrict__ z, int n, int k, f
 }
 
 // Classifier on pooled rows and the cross-student sum: one workgroup per sequence, wave w takes students w, w + 4, ...
-// (T: type of the classifier matrix in the arena, P: type of the pooled rows)
-template <typename T, typename P = T>
+// One pass over the row for CB classes at a time and all its loads requested together: a student is one memory round trip
+// (a pass per class, a chain of dependent iterations each, took 11.6 us for one sequence and eight students).
+template <int CB>
 __global__ __launch_bounds__(256) void head_classify_kernel(const char* arena, size_t student_stride, size_t wc_off,
-                                                            size_t bc_off, const P* __restrict__ pooled, int B, int crows,
-                                                            int H, int C, int k, float* __restrict__ z,
+                                                            size_t bc_off, const float* __restrict__ pooled, int zrows,
+                                                            int prows, int H, int C, int k, float* __restrict__ z,
                                                             float* __restrict__ logits)
 {
     __shared__ float zs[64][16];                 // [student][class]
     const int b = blockIdx.x, lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
     for (int m = wave; m < k; m += 4) {
         const char* sb = arena + (size_t)m * student_stride;
-        const T* Wc = (const T*)(sb + wc_off);
-        const float* bc = (const float*)(sb + bc_off);
-        const P* p = pooled + ((size_t)m * crows + b) * H;
-        for (int c = 0; c < C; ++c) {
-            float acc = 0.f;
-            for (int n = lane; n < H; n += 64) acc += (float)p[n] * (float)Wc[(size_t)n * C + c];
-            acc = wave_sum(acc);
-            if (lane == 0) { const float v = acc + bc[c]; zs[m][c] = v; z[((size_t)m * B + b) * C + c] = v; }
+        const bf16* Wc = (const bf16*)(sb + wc_off);
+        const float* p = pooled + ((size_t)m * prows + b) * H;
+        for (int c0 = 0; c0 < C; c0 += CB) {
+            float pv[16];
+            bf16 wv[16][CB];
+#pragma unroll
+            for (int i = 0; i < 16; ++i) {       // hidden <= 1024, a multiple of 64; pieces beyond it count as zero
+                const int n = lane + (64 * i < H ? 64 * i : 0);
+                pv[i] = p[n];
+#pragma unroll
+                for (int c = 0; c < CB; ++c) wv[i][c] = Wc[(size_t)n * C + (c0 + c < C ? c0 + c : C - 1)];
+            }
+            float acc[CB];
+#pragma unroll
+            for (int c = 0; c < CB; ++c) {
+                acc[c] = 0.f;
+#pragma unroll
+                for (int i = 0; i < 16; ++i) acc[c] += 64 * i < H ? pv[i] * (float)wv[i][c] : 0.f;
+                acc[c] = wave_sum(acc[c]);
+                if (lane == 0 && c0 + c < C) {
+                    const float v = acc[c] + ((const float*)(sb + bc_off))[c0 + c];
+                    zs[m][c0 + c] = v;
+                    z[((size_t)m * zrows + b) * C + c0 + c] = v;
+                }
+            }
         }
     }
     __syncthreads();
-    if (threadIdx.x < C) {
+    if (logits && threadIdx.x < C) {
         float total = 0.f;
         for (int m = 0; m < k; ++m) total += zs[m][threadIdx.x];   // students in training order
         logits[(size_t)b * C + threadIdx.x] = total;
@@ -589,18 +442,16 @@ __global__ __launch_bounds__(256) void head_classify_kernel(const char* arena, s
 
 }  // namespace
 
-hipError_t launch_head_classify(const sp_model* M, const void* pooled, int B, int crows, int k, float* z, float* logits,
-                                hipStream_t s, bool pooled_f32)
+hipError_t launch_head_classify(const sp_model* M, const float* pooled, int n, int zrows, int prows, int k, float* z,
+                                float* logits, hipStream_t s)
 {
     const sp_config& c = M->cfg;
-    if (!bf16_path(c) || k > 64) return hipErrorInvalidValue;
-    if (pooled_f32) {
-        hipLaunchKernelGGL((head_classify_kernel<bf16, float>), dim3(B), dim3(256), 0, s, M->arena, M->L.student_stride, M->L.wc,
-                           M->L.bc, (const float*)pooled, B, crows, c.hidden, c.classes, k, z, logits);
-        return hipGetLastError();
-    }
-    hipLaunchKernelGGL(head_classify_kernel<bf16>, dim3(B), dim3(256), 0, s, M->arena, M->L.student_stride, M->L.wc,
-                       M->L.bc, (const bf16*)pooled, B, crows, c.hidden, c.classes, k, z, logits);
+    if (!bf16_path(c) || k > 64 || c.hidden > 1024 || c.hidden % 64) return hipErrorInvalidValue;
+#define SP_CLASSIFY(CB)                                                                                             \
+    hipLaunchKernelGGL(head_classify_kernel<CB>, dim3((unsigned)n), dim3(256), 0, s, M->arena, M->L.student_stride, M->L.wc, \
+                       M->L.bc, pooled, zrows, prows, c.hidden, c.classes, k, z, logits)
+    if (c.classes <= 2) SP_CLASSIFY(2); else SP_CLASSIFY(4);
+#undef SP_CLASSIFY
     return hipGetLastError();
 }
 
@@ -696,60 +547,6 @@ hipError_t launch_check_inputs(const int32_t* ids, const int32_t* cu, int B, int
 hipError_t launch_sum_students(const float* z, int n, int k, float* logits, hipStream_t s)
 {
     hipLaunchKernelGGL(sum_students_kernel, dim3((n + 255) / 256), dim3(256), 0, s, z, n, k, logits);
-    return hipGetLastError();
-}
-
-hipError_t launch_ln_reduce(const sp_model* M, const float* partials, int splits, size_t slice_elems, size_t bias_off,
-                            const void* residual, void* out, int rows, int mrows, int k, size_t g_off, size_t b_off,
-                            hipStream_t s)
-{
-    const sp_config& c = M->cfg;
-    if (!bf16_path(c) || splits < 1 || splits > kSplitMax) return hipErrorInvalidValue;
-    dim3 grid((mrows + 3) / 4, k);
-    const int maxc = (c.hidden / 8 + 63) / 64;
-    if (maxc > kMaxChunks) return hipErrorInvalidValue;
-#define SP_LNR(MAXC)                                                                                               \
-    hipLaunchKernelGGL((ln_reduce_kernel<bf16, MAXC>), grid, dim3(256), 0, s, M->arena, M->L.student_stride, g_off, \
-                       b_off, bias_off, partials, splits, slice_elems, (const bf16*)residual, (bf16*)out, rows, mrows, \
-                       c.hidden, c.ln_eps)
-    if (maxc <= 1) SP_LNR(1); else if (maxc == 2) SP_LNR(2); else SP_LNR(4);
-#undef SP_LNR
-    return hipGetLastError();
-}
-
-hipError_t launch_gather_first(const sp_model* M, const void* x, const int32_t* cu, int B, int T, int rows, void* xc,
-                               void* attc, int crows, int cmrows, int k, hipStream_t s)
-{
-    const sp_config& c = M->cfg;
-    dim3 grid((cmrows + 3) / 4, k);
-    if (bf16_path(c))
-        hipLaunchKernelGGL(gather_first_kernel<bf16>, grid, dim3(256), 0, s, (const bf16*)x, cu, B, T, rows, c.hidden,
-                           (bf16*)xc, (bf16*)attc, crows, cmrows);
-    else
-        hipLaunchKernelGGL(gather_first_kernel<float>, grid, dim3(256), 0, s, (const float*)x, cu, B, T, rows, c.hidden,
-                           (float*)xc, (float*)attc, crows, cmrows);
-    return hipGetLastError();
-}
-
-hipError_t launch_head_small(const sp_model* M, const float* partials, int splits, size_t slice_elems, size_t bias_off,
-                             const void* residual, size_t g_off, size_t b_off, const int32_t* cu, int B, int T, int rows,
-                             int k, float* z, float* zpart, float* logits, hipStream_t s)
-{
-    const sp_config& c = M->cfg;
-    const ArenaLayout& L = M->L;
-    if (!bf16_path(c) || splits < 1 || splits > kSplitMax || c.hidden > 1024 || k > kSumStudents)
-        return hipErrorInvalidValue;
-    const int nslice = c.hidden / 64;
-    dim3 grid((B + kSeqPerWg - 1) / kSeqPerWg, k, nslice);
-    const size_t smem = (size_t)(kSeqPerWg * c.hidden + 4 * kSeqPerWg * 64) * sizeof(float);
-    hipLaunchKernelGGL(head_small_kernel, grid, dim3(256), smem, s, M->arena, L.student_stride, L.wp, L.bp, L.wc, L.bc,
-                       g_off, b_off, bias_off, partials, splits, slice_elems, (const bf16*)residual, cu, B, T, rows,
-                       c.hidden, c.classes, c.ln_eps, zpart);
-    hipError_t e = hipGetLastError();
-    if (e != hipSuccess) return e;
-    const int n = B * c.classes;
-    hipLaunchKernelGGL(head_sum_kernel, dim3((n + 31) / 32), dim3(256), 0, s, M->arena, L.student_stride, L.bc, zpart, B,
-                       c.classes, k, nslice, z, logits);
     return hipGetLastError();
 }
 

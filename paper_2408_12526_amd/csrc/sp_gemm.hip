@@ -23,9 +23,10 @@ __device__ inline float gelu_erf(float u) { return 0.5f * u * (1.0f + erff(u * 0
 // Data movement
 //   * global -> LDS with direct-to-LDS loads (no register staging).  A wave-load moves 8 rows x 128 bytes
 //     (64 reduction elements) and lands as 1 KB of contiguous LDS.
-//   * LDS tile = [row][8 slots of 16 B]; slot s of row r holds k-chunk s ^ ((r >> 1) & 7).  The 16 lanes that
+//   * activation tile in LDS = [row][8 slots of 16 B]; slot s of row r holds k-chunk s ^ ((r >> 1) & 7).  The 16 lanes that
 //     a ds_read_b128 serves per cycle then hit 16 distinct 16-byte bank groups (no bank conflicts), and the
-//     global side still reads whole 128-byte rows.
+//     global side still reads whole 128-byte rows.  Weights are stored in operand blocks (16 features x 8 elements, see
+//     ArenaLayout) and keep that order in LDS: 256 contiguous bytes per sixteen lanes.
 //   * ring of two stages (128 x 128 tile) or three (64 x 64) over the reduction dimension.  The loads that refill
 //     a stage are spread over the MFMAs of two k-steps (a burst of loads stalls the issuing wave behind the
 //     address unit's queue), and the fragments of k-step s + 1 are read while step s multiplies.  One barrier per 64-wide k-tile, placed where
@@ -70,7 +71,7 @@ __global__ __launch_bounds__(256, 1) void gemm_bf16_kernel(const bf16* __restric
                                                            size_t o_ss, const bf16* __restrict__ res, int ldr,
                                                            size_t r_ss, int Kd, int mtiles, int ntiles, int total,
                                                            bf16* __restrict__ out2, int n_split, int ld2, size_t o2_ss,
-                                                           int ksplit, int ldw, int mb)
+                                                           int mb, RowsLayout ol)
 {
     using G = GemmTile<BM, BN>;
     constexpr int BK = G::BK, NS = G::NS, STEPS = G::STEPS, LSPREAD = G::LSPREAD;
@@ -87,10 +88,7 @@ __global__ __launch_bounds__(256, 1) void gemm_bf16_kernel(const bf16* __restric
     const int chunk = (total + 7) >> 3;
     const int lin = (int)(blockIdx.x & 7) * chunk + (int)(blockIdx.x >> 3);
     if (lin >= total) return;
-    // (student, slice of the reduction range, token tile, feature tile); ksplit > 1 only with EPI_PARTIAL, where a
-    // workgroup reduces over Kd elements starting at sp * Kd and the slices are added by a later kernel
-    const int tiles = ntiles * mtiles, tl = lin % tiles, sp = (lin / tiles) % ksplit;
-    const int m = lin / (tiles * ksplit);
+    const int tiles = ntiles * mtiles, tl = lin % tiles, m = lin / tiles;
     // inside a student: blocks of mb token tiles; inside a block the feature tile is the slow index, so the
     // workgroups resident at one time share mb activation tiles (which then stay in the L2) and stream the weights
     const int gi = tl / (mb * ntiles), rb = tl - gi * mb * ntiles;
@@ -99,20 +97,22 @@ __global__ __launch_bounds__(256, 1) void gemm_bf16_kernel(const bf16* __restric
     const int m0 = mt * BM, n0 = nt * BN;
     const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int wm = wave & 1, wn = wave >> 1;
-    const bf16* Ag = A + (size_t)m * a_ss + (size_t)m0 * lda + (size_t)sp * Kd;
-    const bf16* Wg = (const bf16*)(arena + (size_t)m * student_stride + w_off) + (size_t)n0 * ldw + (size_t)sp * Kd;
+    const bf16* Ag = A + (size_t)m * a_ss + (size_t)m0 * lda;
+    const bf16* Wg = (const bf16*)(arena + (size_t)m * student_stride + w_off) + (size_t)n0 * Kd;
 
     // loader: lane -> (row lane / 8 of the wave-load, LDS slot lane % 8); it fetches k-chunk slot ^ key(row)
     const int lrow = lane >> 3, lslot = lane & 7;
     const int lchunk = lslot ^ ((4 * wave + (lrow >> 1)) & 7);
     const bf16* a_src = Ag + (size_t)(wave * 8 + lrow) * lda + lchunk * 8;
-    const bf16* w_src = Wg + (size_t)(wave * 8 + lrow) * ldw + lchunk * 8;
+    // weights: blocks of 16 features x 8 elements, 256 bytes each; a k-tile of a block of 16 features is 2 KB in a row, two
+    // wave-loads, and lies in LDS as it does in memory
+    const bf16* w_src = Wg + (size_t)(wave >> 1) * 16 * Kd + (wave & 1) * 512 + lane * 8;
     auto issue1 = [&](int i, int k0, int stage) {           // i-th wave-load of a stage (activation rows first)
         if (i < LA)
             __builtin_amdgcn_global_load_lds((gbl_void*)(a_src + (size_t)i * 32 * lda + k0),
                                              (lds_void*)(smem + stage * STAGE + (wave + i * 4) * 64), 16, 0, 0);
         else
-            __builtin_amdgcn_global_load_lds((gbl_void*)(w_src + (size_t)(i - LA) * 32 * ldw + k0),
+            __builtin_amdgcn_global_load_lds((gbl_void*)(w_src + (size_t)(i - LA) * 32 * Kd + (size_t)k0 * 16),
                                              (lds_void*)(smem + stage * STAGE + BM * 8 + (wave + (i - LA) * 4) * 64),
                                              16, 0, 0);
     };
@@ -125,7 +125,6 @@ __global__ __launch_bounds__(256, 1) void gemm_bf16_kernel(const bf16* __restric
     const int j31 = lane & 31, g = lane >> 5;
     f32x4 b4[TN][4];
     auto request_bias = [&](float* seed_lds) {
-        if (EPI == EPI_PARTIAL) return;
         const float* bias_w = (const float*)(arena + (size_t)m * student_stride + b_off) + n0 + wn * G::WTN;
         __builtin_amdgcn_global_load_lds((gbl_void*)(bias_w + 4 * (lane % (G::WTN / 4))), (lds_void*)seed_lds, 16, 0, 0);
     };
@@ -134,7 +133,7 @@ __global__ __launch_bounds__(256, 1) void gemm_bf16_kernel(const bf16* __restric
         for (int i = 0; i < TN; ++i)
 #pragma unroll
             for (int v4 = 0; v4 < 4; ++v4)
-                b4[i][v4] = EPI == EPI_PARTIAL ? f32x4{0.f, 0.f, 0.f, 0.f} : *(const f32x4*)(seed_lds + 4 * g + i * 32 + 8 * v4);
+                b4[i][v4] = *(const f32x4*)(seed_lds + 4 * g + i * 32 + 8 * v4);
         __builtin_amdgcn_sched_barrier(0);
     };
 
@@ -182,9 +181,9 @@ __global__ __launch_bounds__(256, 1) void gemm_bf16_kernel(const bf16* __restric
                     (lds_void*)(base + (pr * 16 + q * RPI) * ROWB), 16, 0, 0);
     };
 
-    int woff[TN], xoff[TM], wkey[TN], xkey[TM];
+    int woff[TN], xoff[TM], xkey[TM];
 #pragma unroll
-    for (int i = 0; i < TN; ++i) { const int r = wn * G::WTN + i * 32 + j31; woff[i] = (G::RING5 ? 0 : BM * 8) + r * 8; wkey[i] = (r >> 1) & 7; }
+    for (int i = 0; i < TN; ++i) { const int r = wn * G::WTN + i * 32 + j31; woff[i] = (G::RING5 ? 0 : BM * 8) + (r >> 4) * 128 + (r & 15); }
 #pragma unroll
     for (int j = 0; j < TM; ++j) { const int r = wm * G::WTM + j * 32 + j31; xoff[j] = r * 8; xkey[j] = (r >> 1) & 7; }
     bf16x8 fw[2][TN], fx[2][TM];
@@ -198,7 +197,7 @@ __global__ __launch_bounds__(256, 1) void gemm_bf16_kernel(const bf16* __restric
                                              (lds_void*)(smem + slot * SLOT + (wave + i * 4) * 64), 16, 0, 0);
         };
         auto issue_w = [&](int i, int k0, int slot) {       // ... of a weight tile
-            __builtin_amdgcn_global_load_lds((gbl_void*)(w_src + (size_t)i * 32 * ldw + k0),
+            __builtin_amdgcn_global_load_lds((gbl_void*)(w_src + (size_t)i * 32 * Kd + (size_t)k0 * 16),
                                              (lds_void*)(smem + slot * SLOT + (wave + i * 4) * 64), 16, 0, 0);
         };
         // k-tile t: activations in slot 2 t mod 5, weights in slot (2 t + 1) mod 5.  Start: the wave's 128 bias values
@@ -227,7 +226,7 @@ __global__ __launch_bounds__(256, 1) void gemm_bf16_kernel(const bf16* __restric
         __builtin_amdgcn_s_waitcnt(0xc07f);                 // lgkmcnt(0): the bias is read before slot 4 is refilled
         __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
-        for (int i = 0; i < TN; ++i) fw[0][i] = __builtin_bit_cast(bf16x8, smem[SLOT + woff[i] + (g ^ wkey[i])]);
+        for (int i = 0; i < TN; ++i) fw[0][i] = __builtin_bit_cast(bf16x8, smem[SLOT + woff[i] + g * 16]);
 #pragma unroll
         for (int j = 0; j < TM; ++j) fx[0][j] = __builtin_bit_cast(bf16x8, smem[xoff[j] + (g ^ xkey[j])]);
 
@@ -270,7 +269,7 @@ __global__ __launch_bounds__(256, 1) void gemm_bf16_kernel(const bf16* __restric
 #pragma unroll
                         for (int f = q * NF / 4; f < (q + 1) * NF / 4; ++f) {
                             if (f < TN)
-                                fw[(s + 1) & 1][f] = __builtin_bit_cast(bf16x8, smem[wslot * SLOT + woff[f] + (kg ^ wkey[f])]);
+                                fw[(s + 1) & 1][f] = __builtin_bit_cast(bf16x8, smem[wslot * SLOT + woff[f] + kg * 16]);
                             else
                                 fx[(s + 1) & 1][f - TN] =
                                     __builtin_bit_cast(bf16x8, smem[xslot * SLOT + xoff[f - TN] + (kg ^ xkey[f - TN])]);
@@ -316,7 +315,7 @@ __global__ __launch_bounds__(256, 1) void gemm_bf16_kernel(const bf16* __restric
 #pragma unroll
                 for (int e = 0; e < 16; ++e) acc[i][j][e] = b4[i][e >> 2][e & 3];
 #pragma unroll
-        for (int i = 0; i < TN; ++i) fw[0][i] = __builtin_bit_cast(bf16x8, smem[woff[i] + (g ^ wkey[i])]);
+        for (int i = 0; i < TN; ++i) fw[0][i] = __builtin_bit_cast(bf16x8, smem[woff[i] + g * 16]);
 #pragma unroll
         for (int j = 0; j < TM; ++j) fx[0][j] = __builtin_bit_cast(bf16x8, smem[xoff[j] + (g ^ xkey[j])]);
 
@@ -355,7 +354,7 @@ __global__ __launch_bounds__(256, 1) void gemm_bf16_kernel(const bf16* __restric
 #pragma unroll
                         for (int f = q * NF / 4; f < (q + 1) * NF / 4; ++f) {
                             if (f < TN)
-                                fw[(s + 1) & 1][f] = __builtin_bit_cast(bf16x8, smem[fstage * STAGE + woff[f] + (kg ^ wkey[f])]);
+                                fw[(s + 1) & 1][f] = __builtin_bit_cast(bf16x8, smem[fstage * STAGE + woff[f] + kg * 16]);
                             else
                                 fx[(s + 1) & 1][f - TN] =
                                     __builtin_bit_cast(bf16x8, smem[fstage * STAGE + xoff[f - TN] + (kg ^ xkey[f - TN])]);
@@ -387,19 +386,6 @@ __global__ __launch_bounds__(256, 1) void gemm_bf16_kernel(const bf16* __restric
     // feature = 8 * (v / 4) + 4 * (l / 32) + v % 4 inside the 32x32 block.
     // The barrier in the last step of the last k-tile already separates every fragment read from what follows:
     // the ring is free.
-    if (EPI == EPI_PARTIAL) {
-        // fp32 partial sums of this slice of the reduction range: out[(m * ksplit + sp)][row][feature], no bias
-        float* po = (float*)out + ((size_t)m * ksplit + sp) * o_ss + (row0 + j31) * ldo + col0 + 4 * g;
-#pragma unroll
-        for (int jj = 0; jj < TM; ++jj)
-#pragma unroll
-            for (int i = 0; i < TN; ++i)
-#pragma unroll
-                for (int v4 = 0; v4 < 4; ++v4)
-                    *(f32x4*)(po + (size_t)jj * 32 * ldo + i * 32 + 8 * v4) =
-                        f32x4{acc[i][jj][4 * v4], acc[i][jj][4 * v4 + 1], acc[i][jj][4 * v4 + 2], acc[i][jj][4 * v4 + 3]};
-        return;
-    }
     if (EPI == EPI_BIAS_RESIDUAL) issue_residual(1);
     // EPI_QKV: feature tiles at or beyond n_split (the value projection) are staged feature-major and written
     // transposed, out2[feature - n_split][token]; the choice is uniform over the workgroup.
@@ -409,12 +395,15 @@ __global__ __launch_bounds__(256, 1) void gemm_bf16_kernel(const bf16* __restric
         const int h = r / HR, rh = r % HR;
         return half_ptr(h) + rh * ROWB + (swz(rh, c >> 3) << 4) + (c & 7) * 2;
     };
+    // (staged rows leave in groups of sixteen: bytes from group to group, row to row, chunk of eight columns to chunk)
     char* dst = (char*)(EPI == EPI_QKV && transposed ? out2 + (size_t)m * o2_ss + (size_t)(col0 - n_split) * ld2 + row0
-                                                     : out + (size_t)m * o_ss + row0 * ldo + col0);
-    const unsigned dpitch = 2u * (unsigned)(EPI == EPI_QKV && transposed ? ld2 : ldo);   // bytes
+                                                     : out + (size_t)m * o_ss + (row0 / 16) * ol.rb + (size_t)(col0 / 8) * ol.cs);
+    const size_t d16 = EPI == EPI_QKV && transposed ? (size_t)ld2 * 32 : ol.rb * 2;
+    const unsigned drow = 2u * (unsigned)(EPI == EPI_QKV && transposed ? ld2 : ol.rs);
+    const unsigned dchunk = 2u * (unsigned)(EPI == EPI_QKV && transposed ? 8 : ol.cs);
     unsigned doff[NQ];
 #pragma unroll
-    for (int q = 0; q < NQ; ++q) doff[q] = (unsigned)(q * RPI + rr) * dpitch + (unsigned)cc * 16u;
+    for (int q = 0; q < NQ; ++q) doff[q] = (unsigned)(q * RPI + rr) * drow + (unsigned)cc * dchunk;
     // accumulators of token blocks [j0, j1) -> staging (bias is already in them)
     auto stage_blocks = [&](int j0, int j1) {
 #pragma unroll
@@ -430,10 +419,6 @@ __global__ __launch_bounds__(256, 1) void gemm_bf16_kernel(const bf16* __restric
                     if (EPI == EPI_BIAS_GELU) {
 #pragma unroll
                         for (int e = 0; e < 4; ++e) r[e] = gelu_erf_fast(r[e]);
-                    }
-                    if (EPI == EPI_BIAS_TANH) {
-#pragma unroll
-                        for (int e = 0; e < 4; ++e) r[e] = tanhf(r[e]);
                     }
                     if (EPI == EPI_QKV && transposed) {
 #pragma unroll
@@ -456,12 +441,12 @@ __global__ __launch_bounds__(256, 1) void gemm_bf16_kernel(const bf16* __restric
     // if transposed)
     auto store_half = [&](int h) {
         const char* base = half_ptr(h);
-        char* db = dst + (size_t)h * HR * dpitch;
+        char* db = dst + (size_t)h * (HR / 16) * d16;
 #pragma unroll 2
         for (int pr = 0; pr < HR / 16; ++pr)
 #pragma unroll
             for (int q = 0; q < NQ; ++q)
-                *(uint4*)(db + (size_t)pr * 16 * dpitch + doff[q]) = *(const uint4*)(base + pr * 16 * ROWB + soff[q]);
+                *(uint4*)(db + (size_t)pr * d16 + doff[q]) = *(const uint4*)(base + pr * 16 * ROWB + soff[q]);
     };
     constexpr int NRL = HR / RPI;                           // residual loads, and row stores, per half
     if (TM >= 2 && !(EPI == EPI_QKV && transposed)) {
@@ -644,11 +629,9 @@ __global__ __launch_bounds__(256) void gemm_f32_ksplit_kernel(const float* __res
 template <int BM, int BN, int EPI>
 hipError_t launch_bf16_tile(const sp_model* M, const void* A, int lda, size_t w_off, size_t b_off, void* out, int ldo,
                             const void* residual, int ldr, int mrows, int N, int Kd, int k, size_t a_ss, size_t o_ss,
-                            size_t r_ss, hipStream_t s, void* out2, int n_split, int ld2, size_t o2_ss, int ksplit = 1,
-                            int ldw = 0)
+                            size_t r_ss, hipStream_t s, void* out2, int n_split, int ld2, size_t o2_ss, RowsLayout ol)
 {
     static_assert(BM == BN, "the transposed epilogue assumes a square wave tile");
-    if (ldw == 0) ldw = Kd;
     constexpr size_t smem = GemmTile<BM, BN>::smem_bytes;
     auto kern = gemm_bf16_kernel<BM, BN, EPI>;
     if (smem > 48 * 1024) {
@@ -659,18 +642,17 @@ hipError_t launch_bf16_tile(const sp_model* M, const void* A, int lda, size_t w_
             raised.store(true, std::memory_order_release);
         }
     }
-    const int mtiles = mrows / BM, ntiles = N / BN, total = k * ksplit * mtiles * ntiles;
+    const int mtiles = mrows / BM, ntiles = N / BN, total = k * mtiles * ntiles;
     const int grid = ((total + 7) / 8) * 8;
     // token-tile blocking of the tile order (see the kernel): with the large tile and many feature tiles, the 32
     // workgroups an XCD runs at a time then cover about 5 x 6 tiles and fetch 11 operand tiles instead of 15, and the
     // activation tiles are re-used from the L2 by the next feature tiles; measured 4-5 % faster for the
     // QKV and FFN up-projections, no gain or slower with three feature tiles
     const int mb = BM == 256 && ntiles >= 6 ? 5 : 1;
-    // (o_ss: bytes per student for the bf16 epilogues, fp32 elements per slice for EPI_PARTIAL)
     hipLaunchKernelGGL(kern, dim3(grid), dim3(256), smem, s, (const bf16*)A, lda, a_ss / 2, M->arena,
-                       M->L.student_stride, w_off, b_off, (bf16*)out, ldo, EPI == EPI_PARTIAL ? o_ss : o_ss / 2,
+                       M->L.student_stride, w_off, b_off, (bf16*)out, ldo, o_ss / 2,
                        (const bf16*)residual, ldr, r_ss / 2, Kd, mtiles, ntiles, total, (bf16*)out2, n_split, ld2,
-                       o2_ss / 2, ksplit, ldw, mb);
+                       o2_ss / 2, mb, ol);
     return hipGetLastError();
 }
 
@@ -680,9 +662,9 @@ constexpr long kLargeTileMinWorkgroups = 256;
 template <int EPI>
 hipError_t launch_bf16(const sp_model* M, const void* A, int lda, size_t w_off, size_t b_off, void* out, int ldo,
                        const void* residual, int ldr, int mrows, int N, int Kd, int k, size_t a_ss, size_t o_ss,
-                       size_t r_ss, hipStream_t s, void* out2, int n_split, int ld2, size_t o2_ss)
+                       size_t r_ss, hipStream_t s, void* out2, int n_split, int ld2, size_t o2_ss, RowsLayout ol)
 {
-#define SP_ARGS M, A, lda, w_off, b_off, out, ldo, residual, ldr, mrows, N, Kd, k, a_ss, o_ss, r_ss, s, out2, n_split, ld2, o2_ss
+#define SP_ARGS M, A, lda, w_off, b_off, out, ldo, residual, ldr, mrows, N, Kd, k, a_ss, o_ss, r_ss, s, out2, n_split, ld2, o2_ss, ol
     // a feature tile must lie entirely on one side of n_split
     // (a grid of fewer large tiles than compute units leaves part of the chip idle: smaller tiles then; measured on the
     // batch-32 workload, one student: 0.285 -> 0.236 ms per call)
@@ -743,33 +725,24 @@ hipError_t launch_gelu_probe(const float* x, float* y, long n, hipStream_t s)
     return hipGetLastError();
 }
 
-hipError_t launch_gemm_splitk(const sp_model* M, const void* A, int lda, size_t w_off, float* partials, int mrows, int N,
-                              int Kd, int k, int splits, size_t a_student_stride, size_t slice_elems, hipStream_t s)
-{
-    if (!bf16_path(M->cfg) || splits < 1 || mrows % 64 || N % 64 || Kd % (64 * splits) || Kd / splits < 128 ||
-        slice_elems < (size_t)mrows * N)
-        return hipErrorInvalidValue;
-    return launch_bf16_tile<64, 64, EPI_PARTIAL>(M, A, lda, w_off, 0, partials, N, nullptr, 0, mrows, N, Kd / splits, k,
-                                                 a_student_stride, slice_elems, 0, s, nullptr, 0, 0, 0, splits, Kd);
-}
-
 hipError_t launch_gemm(const sp_model* M, const void* A, int lda, size_t w_off, size_t b_off, void* out, int ldo,
                        const void* residual, int ldr, int mrows, int N, int Kd, int k, Epilogue epi,
                        size_t a_student_stride, size_t o_student_stride, size_t r_student_stride, hipStream_t s,
-                       void* out2, int n_split, int ld2, size_t o2_student_stride)
+                       void* out2, int n_split, int ld2, size_t o2_student_stride, bool packed_out)
 {
     // shapes the kernels assume; config_supported() guarantees them for every model that loads
     if (mrows % 64 || N % 64 || Kd % 128 || (epi == EPI_BIAS_RESIDUAL && !residual)) return hipErrorInvalidValue;
     if (epi == EPI_QKV && (!bf16_path(M->cfg) || !out2 || n_split % 64 || ld2 % 8)) return hipErrorInvalidValue;
 #define SP_ARGS M, A, lda, w_off, b_off, out, ldo, residual, ldr, mrows, N, Kd, k, a_student_stride, \
                 o_student_stride, r_student_stride, s
+    if (packed_out && (!bf16_path(M->cfg) || epi == EPI_QKV)) return hipErrorInvalidValue;
     if (bf16_path(M->cfg)) {
+        const RowsLayout ol = packed_out ? packed_layout(ldo) : rows_layout(ldo);
         switch (epi) {
-            case EPI_BIAS: return launch_bf16<EPI_BIAS>(SP_ARGS, nullptr, 0, 0, 0);
-            case EPI_BIAS_GELU: return launch_bf16<EPI_BIAS_GELU>(SP_ARGS, nullptr, 0, 0, 0);
-            case EPI_QKV: return launch_bf16<EPI_QKV>(SP_ARGS, out2, n_split, ld2, o2_student_stride);
-            case EPI_BIAS_TANH: return launch_bf16<EPI_BIAS_TANH>(SP_ARGS, nullptr, 0, 0, 0);
-            default: return launch_bf16<EPI_BIAS_RESIDUAL>(SP_ARGS, nullptr, 0, 0, 0);
+            case EPI_BIAS_GELU: return launch_bf16<EPI_BIAS_GELU>(SP_ARGS, nullptr, 0, 0, 0, ol);
+            case EPI_QKV: return launch_bf16<EPI_QKV>(SP_ARGS, out2, n_split, ld2, o2_student_stride, ol);
+            case EPI_BIAS_RESIDUAL: return launch_bf16<EPI_BIAS_RESIDUAL>(SP_ARGS, nullptr, 0, 0, 0, ol);
+            default: return hipErrorInvalidValue;
         }
     }
     if (epi == EPI_QKV || epi == EPI_BIAS_TANH) return hipErrorInvalidValue;   // bf16 path only

@@ -141,8 +141,13 @@ __device__ inline void barrier_lds()
 #endif  // __HIPCC__
 
 constexpr int kRowPad = 256;  // activation rows per student are padded to a multiple of this
-constexpr int kSplitMax = 8;  // slices of a split reduction (small calls only)
-constexpr int kSplitRows = 128;   // most token rows a call may compute and still take the split path
+constexpr int kRowsMaxTokens = 256;   // largest call whose all-token layers run on the few-row projections
+constexpr int kRowsMaxSeqs = 256;     // most sequences whose first-token rows do
+// Most elements (rows of all students x hidden width) that the fused LayerNorm + projection kernels take: every workgroup
+// repeats the statistics of its rows, and beyond this a LayerNorm launch and the tile kernel are faster (hidden 768: 256 rows
+// 35.4 us for a layer's embedding, q|k|v and FFN up against 38, 352 rows 40 against 38; hidden 256: 528 rows 17.5 against 26).
+constexpr long kRowsLnMaxElems = 262144;
+constexpr int kRowsU = 1024;          // fp32 rows per student of the few-row projections' scratch (four regions of 256)
 constexpr int kFirstOnlyMinTokens = 1024;   // smallest call whose last layer runs on the first-token rows only
 // fp8 projections: activations are quantised as e4m3(value * kActQuantScale) by the kernel that produces them
 // (LayerNorm outputs and GELU outputs are of order one: 448 / 16 = 28 before saturation, 2^-6 / 16 = 1e-3 before the
@@ -151,19 +156,19 @@ constexpr float kActQuantScale = 16.f;
 constexpr int kFp8MinRows = 2048;
 
 // Byte offsets of every tensor inside one student's slab of the weight arena.
-// The encoder matrices are stored transposed with respect to the host blob,
-// [out][in], so that the reduction index is contiguous for both GEMM operands;
-// the pooler and classifier matrices keep the blob's [in][out] order.
+// The encoder matrices are stored transposed with respect to the host blob, reduction index innermost: fp32 as
+// [out][in], bf16 in blocks of 16 outputs x 8 inputs, [out / 16][in / 8][16][8] (what a matrix instruction takes is then
+// contiguous); wp and the classifier matrix keep the blob's [in][out] order.
 struct ArenaLayout {
     size_t tok, pos, emb_g, emb_b;
     size_t layer0, layer_stride;
     // relative to the start of a layer
     size_t wqkv, bqkv, wo, bo, ln1g, ln1b, w1, b1, w2, b2, ln2g, ln2b;
-    size_t wk_io;                  // the key projection once more, [in][out] as in the host blob (folded first-token queries)
+    size_t wk_io;                  // the key projection once more with the roles exchanged: rows in, reduction index out (folded first-token queries)
     // SP_DTYPE_FP8 only (0 otherwise), relative to the start of a layer: the fused q|k|v, attention-output, FFN-up and
     // FFN-down matrices once more as e4m3 codes, [out][in] bytes, and their per-output-feature scales (fp32)
     size_t wqkv8, sqkv, wo8, so, w18, s1, w28, s2;
-    size_t wp, wp_t, bp, wc, bc;   // wp: [in][out] (column-parallel head kernel); wp_t: [out][in] (GEMM operand)
+    size_t wp, wp_t, bp, wc, bc;   // wp: [in][out] (column-parallel head kernel); wp_t: projection operand
     size_t student_stride;
 };
 
@@ -174,7 +179,7 @@ struct WsLayout {
     size_t x, qkv, vt, att, u, x1, g, z, zpart, end;
     size_t cx, cq, catt, cu_, cx1, cg;   // first-token rows only: [K][crows][H] (cg: [F]), last layer
     size_t cqt, cxb;                     // folded queries / weighted mean rows: [K][crows][heads][H]
-    size_t part;                         // fp32 partial sums of split reductions: [K][kSplitMax][kSplitRows][H]
+    size_t part;                         // fp32 rows between the few-row projections: [K][kRowsU][H]
     size_t lpart;                        // per-group logit sums when two groups of students run side by side: [2][B][C]
     size_t xq, x1q, attq, gq;            // SP_DTYPE_FP8 only: fp8 copies of x, x1 and att ([K][rows][H] bytes), fp8 g ([K][rows][F])
     int rows, crows;
@@ -196,6 +201,11 @@ struct sp_model {
 
 namespace sp {
 
+// Where element (row r, column c) of an activation buffer sits: (r / 16) rb + (r % 16) rs + (c / 8) cs + c % 8 (elements).
+struct RowsLayout { size_t rb; int rs, cs; };
+inline RowsLayout rows_layout(int width) { return {(size_t)16 * width, width, 8}; }           // row after row
+inline RowsLayout packed_layout(int width) { return {(size_t)16 * width, 8, 128}; }          // matrix-operand blocks of 16 rows x 8
+
 // ---- launchers (each returns the hipError_t of its launch) ------------------
 
 // X[m][row][:] = LN(tok[id[row]] + pos[row - cu[seq(row)]]) for row < T; zero rows up to `rows`.
@@ -212,7 +222,7 @@ hipError_t launch_layernorm(const sp_model* M, const void* u, void* out, int row
 
 // EPI_QKV (bf16 path only): bias; output columns >= n_split (the value projection) are written transposed,
 // out2[m][column - n_split][row], so that attention reads key-contiguous value tiles.
-enum Epilogue { EPI_BIAS = 0, EPI_BIAS_GELU = 1, EPI_BIAS_RESIDUAL = 2, EPI_QKV = 3, EPI_BIAS_TANH = 4, EPI_PARTIAL = 5 };
+enum Epilogue { EPI_BIAS = 0, EPI_BIAS_GELU = 1, EPI_BIAS_RESIDUAL = 2, EPI_QKV = 3, EPI_BIAS_TANH = 4 };
 
 // out[m][row][0..N) = epi(A[m][row][0..Kd) . W^T + bias), W stored [N][Kd] at w_off of each student.
 // lda / ldo / ldr are row strides in elements; residual may be null unless EPI_BIAS_RESIDUAL;
@@ -220,7 +230,8 @@ enum Epilogue { EPI_BIAS = 0, EPI_BIAS_GELU = 1, EPI_BIAS_RESIDUAL = 2, EPI_QKV 
 hipError_t launch_gemm(const sp_model* M, const void* A, int lda, size_t w_off, size_t b_off, void* out, int ldo,
                        const void* residual, int ldr, int mrows, int N, int Kd, int k, Epilogue epi,
                        size_t a_student_stride, size_t o_student_stride, size_t r_student_stride, hipStream_t s,
-                       void* out2 = nullptr, int n_split = 0, int ld2 = 0, size_t o2_student_stride = 0);
+                       void* out2 = nullptr, int n_split = 0, int ld2 = 0, size_t o2_student_stride = 0,
+                       bool packed_out = false);   // packed_out (bf16): out in packed_layout(ldo)
 
 // The same projection on fp8 operands (SP_DTYPE_FP8; 256 x 256 tile only: mrows and N multiples of 256, Kd of 128).
 // A8: e4m3 codes of activation * a_qscale, [m][row][lda] bytes; weights at w_off (e4m3, [N][Kd] bytes) with fp32
@@ -233,32 +244,38 @@ hipError_t launch_gemm_fp8(const sp_model* M, const void* A8, int lda, size_t w_
                            size_t o2_student_stride, float out_qscale);
 
 // y[i] = GELU as the bf16 FFN up-projection's epilogue evaluates it, in fp32 (i < n).  Test aid.
-// Last layer after its attention for the first-token rows of a call of a few sequences (see sp_gemv.hip): scratch is
-// fp32 memory of first_rows_tail_scratch_floats elements, g the FFN activation buffer (its first rows are used), x1 the
-// buffer whose first-token rows receive LN(u).  Exactly one of part and pooled is given: part, the split-reduction
-// buffer whose slice 0 receives the raw down-projection at the first tokens' rows (student stride part_ss elements;
-// launch_head_small with one slice finishes the call), or pooled, fp32 [k][first_rows_tail_pooled_rows][H], whose rows
-// b receive the pooled rows (launch_head_classify with pooled_f32 finishes the call).
-bool first_rows_tail_supported(const sp_config& c, int B);
-size_t first_rows_tail_scratch_floats(const sp_config& c, int k);
-int first_rows_tail_pooled_rows();
-hipError_t launch_first_rows_tail(const sp_model* M, size_t lo, const void* att, const void* x, void* x1, void* g,
-                                  float* scratch, float* part, size_t part_ss, float* pooled, const int32_t* cu, int B,
-                                  int T, int rows, int k, hipStream_t s);
 hipError_t launch_gelu_probe(const float* x, float* y, long n, hipStream_t s);
 hipError_t launch_gelu_q8_probe(const float* x, float* y, long n, hipStream_t s);
 
-// Split reduction for calls of a few dozen tokens, where one workgroup per 64x64 output tile walking the whole
-// reduction range is a long serial chain: partials[m][s][row][0..N) = A[m][row][s*Kd/splits ..) . W^T (fp32, no bias),
-// s < splits; slice_elems = elements between consecutive slices (>= mrows * N).  bf16 path only.
-hipError_t launch_gemm_splitk(const sp_model* M, const void* A, int lda, size_t w_off, float* partials, int mrows, int N,
-                              int Kd, int k, int splits, size_t a_student_stride, size_t slice_elems, hipStream_t s);
-
-// out[m][row][:] = LN(sum_s partials[m][s][row][:] + bias + residual[m][row][:]; g, b): the reduction of
-// launch_gemm_splitk fused with the bias, the residual add and the LayerNorm that follow the projection.
-hipError_t launch_ln_reduce(const sp_model* M, const float* partials, int splits, size_t slice_elems, size_t bias_off,
-                            const void* residual, void* out, int rows, int mrows, int k, size_t g_off, size_t b_off,
-                            hipStream_t s);
+// ---- projections of few rows (sp_rows.hip; bf16 path).  u: fp32 rows before a LayerNorm, [student][u_ss], row stride H.
+// Student strides (_ss) are in elements.
+// q|k|v of all T tokens (values transposed into vt) from the embedding rows (u null; g_off / b_off: the embedding
+// LayerNorm) or from LN(u); the normalised rows go to x as well.
+hipError_t launch_rows_qkv(const sp_model* M, size_t lo, const float* u, size_t u_ss, size_t g_off, size_t b_off,
+                           const int32_t* ids, const int32_t* cu, int B, int T, void* x, void* qkv, void* vt, int rows,
+                           int k, hipStream_t s);
+// g = gelu(LN(u; ln1) W1^T + b1), the normalised rows to x1 (row stride H)
+hipError_t launch_rows_ffn_up(const sp_model* M, size_t lo, const float* u, size_t u_ss, int nrows, void* x1, size_t x1_ss,
+                              void* g, size_t g_ss, RowsLayout gl, int k, hipStream_t s);
+// pooled = tanh(LN(u; ln2) Wp + bp), fp32
+hipError_t launch_rows_pooler(const sp_model* M, size_t lo, const float* u, size_t u_ss, int nrows, float* pooled,
+                              size_t p_ss, int k, hipStream_t s);
+// out[r] (fp32, H wide) = A[r or cu[r]] W^T + bias + res[r or cu[r]]; Kd columns of A
+hipError_t launch_rows_residual(const sp_model* M, size_t w_off, size_t b_off, const bf16* A, size_t a_ss, RowsLayout al,
+                                int Kd, bool a_first, const bf16* res, size_t r_ss, bool r_first, float* out, size_t o_ss,
+                                const int32_t* cu, int T, int nrows, int k, hipStream_t s);
+// att[b][h*64..] = Wv_h xbar[b][h] + bv_h
+hipError_t launch_rows_head_values(const sp_model* M, size_t lo, const void* xbar, size_t xb_ss, void* att, size_t att_ss,
+                                   int nrows, int k, hipStream_t s);
+// q[b] = x[cu[b]] Wq^T + bq; qt[b][h] = Wk_h q[b][h]
+hipError_t launch_fold_query(const sp_model* M, size_t lo, const void* x, int rows, const int32_t* cu, int T, int B,
+                             void* q, size_t q_ss, void* qt, size_t qt_ss, int k, hipStream_t s);
+// attention output of the first token of every sequence, at its token row
+hipError_t launch_attention_first(const sp_model* M, const void* qkv, const void* vt, void* att, const int32_t* cu, int B,
+                                  int T, int max_seqlen, int rows, int k, hipStream_t s);
+// out = LN(u), bf16 rows
+hipError_t launch_rows_ln_out(const sp_model* M, size_t g_off, size_t b_off, const float* u, size_t u_ss, void* out,
+                              size_t o_ss, int nrows, int k, hipStream_t s);
 
 // att[m][t][h*64..] = softmax(q k^T / 8) v inside each sequence; qkv rows are [q | k | v] of width 3H.
 // bf16 path: the values are read from vt[m][H][rows] (transposed) instead of the third slice of qkv.
@@ -267,29 +284,18 @@ hipError_t launch_attention(const sp_model* M, const void* qkv, const void* vt, 
                             int T, int max_seqlen, int rows, int k, hipStream_t s, void* attq = nullptr,
                             float qscale = 1.f);
 
-// First-token rows of every sequence: xc[m][b][:] = x[m][cu[b]][:] (b < B), zero rows up to cmrows; the same
-// rows of attc are zeroed.
-hipError_t launch_gather_first(const sp_model* M, const void* x, const int32_t* cu, int B, int T, int rows, void* xc,
-                               void* attc, int crows, int cmrows, int k, hipStream_t s);
-
-// Per-head small products on the matrix cores: out[m][r][h][n] = sum_k A[m][r][h][k] W[m][h][n][k] (+ bias[m][h][n])
-// for r < mrows, n < N, k < Kd, every head h and student m < k.  Strides (_ss per student, _hs per head, ld per
-// row) are in elements; w_off / b_off are byte offsets into the student slab (bias: fp32).
-hipError_t launch_head_gemm(const sp_model* M, const void* A, size_t a_ss, size_t a_hs, int lda, size_t w_off,
-                            size_t w_hs, int ldw, size_t b_off, size_t b_hs, bool has_bias, void* out, size_t o_ss,
-                            size_t o_hs, int ldo, int mrows, int N, int Kd, int k, hipStream_t s);
-
 // Attention of the first token of each sequence with folded queries: for sequence b and head h,
 // p = softmax_t(qt[m][b][h] . x[m][t] / 8) over the tokens t of the sequence and xbar[m][b][h][:] = sum_t p_t x[m][t][:].
-// qt and xbar are [m][crows][heads][H]; rows b in [B, cmrows) of xbar are zeroed.
+// qt and xbar are [m][.._ss elements], rows of [heads][H].
 bool attention_first_fold_supported(const sp_config& c, int max_seqlen);
-hipError_t launch_attention_first_fold(const sp_model* M, const void* x, const void* qt, void* xbar, const int32_t* cu,
-                                       int B, int T, int max_seqlen, int rows, int crows, int cmrows, int k,
+hipError_t launch_attention_first_fold(const sp_model* M, const void* x, const void* qt, size_t qt_ss, void* xbar,
+                                       size_t xb_ss, const int32_t* cu, int B, int T, int max_seqlen, int rows, int k,
                                        hipStream_t s);
 
-// Head on pooled rows: z[m][b][c] = pooled[m][b] . Wc + bc; logits[b][c] = sum_{m<k} z[m][b][c] (m ascending).
-hipError_t launch_head_classify(const sp_model* M, const void* pooled, int B, int crows, int k, float* z, float* logits,
-                                hipStream_t s, bool pooled_f32 = false);   // pooled rows bf16, or fp32 if pooled_f32
+// Head on fp32 pooled rows of n sequences: z[m][b][c] = pooled[m][b] . Wc + bc; logits[b][c] = sum_{m<k} z[m][b][c] (m
+// ascending; not written if null).  Student strides: prows pooled rows, zrows rows of z.
+hipError_t launch_head_classify(const sp_model* M, const float* pooled, int n, int zrows, int prows, int k, float* z,
+                                float* logits, hipStream_t s);
 
 // flags[0] |= SP_BAD_* bits for the inputs of a forward (flags[0] is cleared first, on the same stream).
 hipError_t launch_check_inputs(const int32_t* ids, const int32_t* cu, int B, int T, int max_seqlen, int vocab,
@@ -301,12 +307,5 @@ hipError_t launch_sum_students(const float* z, int n, int k, float* logits, hipS
 // z[m][b][c] = tanh(x[m][cu[b]] Wp + bp) Wc + bc (row b itself if cu is null) ; logits[b][c] = sum_{m<k} z[m][b][c] (m ascending).
 hipError_t launch_head(const sp_model* M, const void* x, const int32_t* cu, int B, int T, int rows, int k, float* z,
                        float* zpart, float* logits, hipStream_t s);
-
-// The same head for calls of a few dozen tokens: stage 1 rebuilds the first-token rows from the slices of the last split
-// reduction (+ bias + residual + LayerNorm: what launch_ln_reduce would have written), so that launch is not needed
-// for the last layer of a whole forward.  bf16 only.
-hipError_t launch_head_small(const sp_model* M, const float* partials, int splits, size_t slice_elems, size_t bias_off,
-                             const void* residual, size_t g_off, size_t b_off, const int32_t* cu, int B, int T, int rows,
-                             int k, float* z, float* zpart, float* logits, hipStream_t s);
 
 }  // namespace sp

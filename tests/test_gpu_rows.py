@@ -1,0 +1,53 @@
+"""The few-row projections (small calls and the first-token last layer) at the edges of their tiles.  Needs an MI355X."""
+import numpy as np
+import pytest
+import torch
+
+from oracle.sp_oracle import OracleConfig
+from paper_2408_12526_amd import synth
+
+pytestmark = pytest.mark.gpu
+
+
+def _run(oracle64, shape, lengths, ks, seed):
+    from paper_2408_12526_amd import sp
+    rng = np.random.default_rng(seed)
+    lengths = np.array(lengths, dtype=np.int32)
+    ids = synth.make_ids(rng, int(lengths.sum()), shape.vocab)
+    blob = synth.make_weights(rng, shape, std=0.04, ln_random=True)
+    cu = sp.sp_pack(lengths)
+    st = sp.Students(sp.config_from_shape(shape), blob)
+    ow = torch.from_numpy(blob).to(torch.bfloat16).to(torch.float32).numpy()
+    cfg = OracleConfig(shape.K, shape.layers, shape.hidden, shape.heads, shape.ffn, shape.vocab, shape.max_pos, shape.classes,
+                       shape.ln_eps)
+    pick = np.arange(len(lengths)) if len(lengths) <= 6 else np.unique(np.r_[0, len(lengths) - 1, rng.integers(0, len(lengths), 4)])
+    sub_ids = np.concatenate([ids[cu[b]:cu[b + 1]] for b in pick])
+    sub_cu = np.concatenate([[0], np.cumsum(lengths[pick])]).astype(np.int32)
+    for k in ks:
+        got = st.sp_forward(torch.from_numpy(ids).cuda(), torch.from_numpy(cu).cuda(), int(lengths.max()), k).double().cpu().numpy()
+        want = oracle64.forward(cfg, ow, sub_ids, sub_cu, k)
+        assert np.isfinite(got).all()
+        err = np.abs(got[pick] - want).max() / max(np.abs(want).max(), 1e-3)
+        assert err <= 3e-2, f"{shape}, lengths {lengths[:6]}, k_active {k}: {err:.3e}"
+    st.close()
+
+
+# widths with an instance of their own (256, 768, 1024) and between them; reduction depths of one and several passes
+@pytest.mark.parametrize("hidden,ffn", [(128, 128), (256, 1024), (384, 640), (768, 3072), (896, 2176), (1024, 4096)])
+@pytest.mark.parametrize("lengths", [(1,), (15,), (16,), (17,), (5, 28), (57, 58), (64, 1, 63), (9,) * 20, (250, 6)])
+def test_small_calls_on_every_width(oracle64, hidden, ffn, lengths):
+    """Row blocks of sixteen just missed, met and passed, both sides of the fused LayerNorm's limit, one and several steps
+    of the first-token attention."""
+    shape = synth.StudentShape(K=5, layers=2, hidden=hidden, heads=hidden // 64, ffn=ffn, vocab=60, max_pos=256, classes=3,
+                               dtype="bf16")
+    _run(oracle64, shape, lengths, (1, 5), 7 * hidden + sum(lengths))
+
+
+@pytest.mark.parametrize("nseq,length", [(33, 8), (64, 9), (255, 3), (256, 5), (257, 5), (300, 4), (600, 2)])
+@pytest.mark.parametrize("hidden", [256, 768])
+def test_first_token_rows_of_many_sequences(oracle64, hidden, nseq, length):
+    """The folded last layer at row blocks of every tile and beyond the 256 sequences one pass takes; below 1024 tokens its
+    rows share the buffers of the all-token layers."""
+    shape = synth.StudentShape(K=3, layers=2, hidden=hidden, heads=hidden // 64, ffn=4 * hidden, vocab=60, max_pos=16, classes=2,
+                               dtype="bf16")
+    _run(oracle64, shape, (length,) * nseq, (1, 3), hidden + nseq)
