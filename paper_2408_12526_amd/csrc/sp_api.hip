@@ -278,9 +278,10 @@ struct PhaseTimer {
 
 // The forward of students [m0, m0 + k) of the model (k >= 1), all of it enqueued on stream s.  Every buffer of the
 // workspace is sliced per student, so groups of students can run side by side on different streams.  With
-// with_head the group's z rows are written; logits (the group's own sum, in student order) only if non-null.
+// with_head the group's z rows are written; logits (the group's own sum, in student order) only if non-null.  sole: no
+// other group runs beside this one (m0 is 0), so the buffers of the students beyond it are free.
 static int run_students(const sp_model* M0, const WsLayout& W, const int32_t* ids, const int32_t* cu, int B, int T,
-                        int max_seqlen, int m0, int k, int stop_layers, bool with_head, char* w, float* logits,
+                        int max_seqlen, int m0, int k, bool sole, int stop_layers, bool with_head, char* w, float* logits,
                         hipStream_t s, PhaseTimer* pt)
 {
     const sp_config& c = M0->cfg;
@@ -288,9 +289,13 @@ static int run_students(const sp_model* M0, const WsLayout& W, const int32_t* id
     shifted.arena = M0->arena + (size_t)m0 * M0->L.student_stride;
     const sp_model* M = &shifted;
     const int H = c.hidden, F = c.ffn, rows = W.rows;
-    // rows actually computed: the packed tokens rounded up to the token tile the GEMMs will use
-    const int mtile = T > 256 ? 256 : 64;
-    const int mrows = (T + mtile - 1) / mtile * mtile;
+    // quantised students: the four projections of the all-token layers on fp8 operands (large calls only)
+    // (the fp8 kernel has one tile size, 256 x 256: widths that are not multiples of it stay on the bf16 path)
+    const bool fp8 = c.dtype == SP_DTYPE_FP8 && rows >= kFp8MinRows && W.xq && H % 256 == 0 && F % 256 == 0;
+    // rows actually computed
+    const int mtile = fp8 || !bf16_path(c) ? 256 : 64;
+    const int mrows = !bf16_path(c) && T <= 256 ? (T + (T > 64 ? 127 : 63)) / (T > 64 ? 128 : 64) * (T > 64 ? 128 : 64)
+                                                : (T + mtile - 1) / mtile * mtile;
     const size_t ab = W.act_bytes;
     const size_t sH = (size_t)rows * H * ab, s3H = 3 * sH, sF = (size_t)rows * F * ab;
     char *x = w + W.x + m0 * sH, *qkv = w + W.qkv + m0 * s3H, *vt = w + W.vt + m0 * sH, *att = w + W.att + m0 * sH;
@@ -301,10 +306,6 @@ static int run_students(const sp_model* M0, const WsLayout& W, const int32_t* id
 
 #define SP_TRY(expr) do { if ((expr) != hipSuccess) return SP_EHIP; } while (0)
 #define SP_MARK(ph) do { if (pt) pt->mark(ph, s); } while (0)
-    // quantised students: the three large projections of the all-token layers on fp8 operands (large calls only)
-    // (the fp8 kernel has one tile size, 256 x 256: widths that are not multiples of it stay on the bf16 path)
-    const bool fp8 = c.dtype == SP_DTYPE_FP8 && mrows % 256 == 0 && mrows >= kFp8MinRows && W.xq && H % 256 == 0 &&
-                     F % 256 == 0;
     const size_t qH = (size_t)rows * H, qF = (size_t)rows * F;       // bytes per student of the fp8 buffers
     char *xq = fp8 ? w + W.xq + m0 * qH : nullptr, *x1q = fp8 ? w + W.x1q + m0 * qH : nullptr;
     char *gq = fp8 ? w + W.gq + m0 * qF : nullptr, *attq = fp8 ? w + W.attq + m0 * qH : nullptr;
@@ -321,6 +322,36 @@ static int run_students(const sp_model* M0, const WsLayout& W, const int32_t* id
     const size_t u_ss = (size_t)kRowsU * H;
     float* uo = (float*)(w + W.part) + (size_t)m0 * u_ss;   // after the attention-output projection
     float *ud = uo + (size_t)256 * H, *pooled = uo + (size_t)512 * H;   // after the FFN; pooled first-token rows
+    // Projection onto the hidden width, residual and LayerNorm of the T token rows (bf16): out = LN(A W^T + b + res).  A launch
+    // of fewer than a tile per compute unit splits the reduction range over workgroups; the fp32 slices go into the buffers
+    // that are free at that point (q|k|v and values, and behind them the attention output and the pre-LayerNorm rows once
+    // the output projection is done), and the LayerNorm adds them.
+    auto project_ln = [&](const char* A, int Kd, size_t a_ss, size_t w_off, size_t b_off, const char* res, char* out, size_t g_off,
+                          size_t be_off, int phase) -> int {
+        int splits = 1;
+        const long tiles = (long)((mrows + 63) / 64) * (H / 256) * k;
+        if (sole && with_head && H % 256 == 0 && tiles < 256) {   // (partial forwards keep the buffers for the tests)
+            const int room = (A == att ? 2 : 3) * c.K / k;
+            for (int sp : {2, 3, 4, 6, 8})
+                if (sp <= room && (Kd / 64) % (2 * sp) == 0 && Kd / sp >= 256) {
+                    splits = sp;
+                    if (tiles * sp >= 224) break;
+                }
+        }
+        if (splits > 1) {
+            float* ps = (float*)(w + W.qkv);
+            const size_t p_ss = (size_t)rows * H, slice = p_ss * k;
+            SP_TRY(launch_gemm_split(M, A, Kd, w_off, ps, slice, mrows, H, Kd, k, splits, a_ss, p_ss, s));
+            SP_MARK(phase);
+            SP_TRY(launch_ln_slices(M, ps, slice, p_ss, splits, b_off, res, out, rows, T, k, g_off, be_off, s));
+        } else {
+            SP_TRY(launch_gemm(M, A, Kd, w_off, b_off, u, H, res, H, mrows, H, Kd, k, EPI_BIAS_RESIDUAL, a_ss, sH, sH, s));
+            SP_MARK(phase);
+            SP_TRY(launch_layernorm(M, u, out, rows, mrows, k, g_off, be_off, s));
+        }
+        SP_MARK(SP_PHASE_LAYERNORM);
+        return SP_OK;
+    };
     // g = gelu(LN(uo; ln1) W1^T + b1) of n rows: fused while the rows of all students are few, else a LayerNorm launch and
     // the tile kernel
     auto ffn_up = [&](size_t lo, int n, void* x1r, size_t x1_ss, void* gr, size_t g_ss, bool packed) -> hipError_t {
@@ -353,6 +384,10 @@ static int run_students(const sp_model* M0, const WsLayout& W, const int32_t* id
     };
     if (bf16_path(c) && T <= kRowsMaxTokens) {
         const size_t sT = (size_t)rows * H, sG = (size_t)rows * F;
+        // Many rows over all students: the tile kernel with a split reduction for the two projections onto the hidden width as
+        // well (hidden 768, 960 rows, us for both projections of a layer and their LayerNorms: 31.4 against 34.7; 352 rows 22.6
+        // against 23.1; hidden 1024, 768 rows: 43.4 against 50.9)
+        const bool tiles_from_here = H % 256 == 0 && (long)T * k * H > 2 * kRowsLnMaxElems;
         // (the partial forwards of the tests read the FFN activations row by row)
         const RowsLayout gl = with_head ? packed_layout(F) : rows_layout(F);
         if (stop_layers == 0) {
@@ -367,7 +402,7 @@ static int run_students(const sp_model* M0, const WsLayout& W, const int32_t* id
             } else {
                 // (the embedding kernel zeroes the padding rows of x, and nothing writes them afterwards)
                 if (l == 0) SP_TRY(launch_embed_ln(M, ids, cu, B, T, rows, mrows, k, x, att, s));
-                else SP_TRY(launch_rows_ln_out(M, pl + L.ln2g, pl + L.ln2b, ud, u_ss, x, sT, T, k, s));
+                else if (!tiles_from_here) SP_TRY(launch_rows_ln_out(M, pl + L.ln2g, pl + L.ln2b, ud, u_ss, x, sT, T, k, s));
                 SP_MARK(l == 0 ? SP_PHASE_EMBED : SP_PHASE_LAYERNORM);
                 SP_TRY(launch_gemm(M, x, H, lo + L.wqkv, lo + L.bqkv, qkv, 3 * H, nullptr, 0, mrows, 3 * H, H, k, EPI_QKV, sH,
                                    s3H, 0, s, vt, 2 * H, rows, sH));
@@ -380,6 +415,15 @@ static int run_students(const sp_model* M0, const WsLayout& W, const int32_t* id
             }
             SP_TRY(launch_attention(M, qkv, vt, att, cu, B, T, max_seqlen, rows, k, s));
             SP_MARK(SP_PHASE_ATTENTION);
+            if (tiles_from_here) {
+                int rc = project_ln(att, H, sH, lo + L.wo, lo + L.bo, x, x1, lo + L.ln1g, lo + L.ln1b, SP_PHASE_OPROJ);
+                if (rc != SP_OK) return rc;
+                SP_TRY(launch_gemm(M, x1, H, lo + L.w1, lo + L.b1, g, F, nullptr, 0, mrows, F, H, k, EPI_BIAS_GELU, sH, sF, 0, s));
+                SP_MARK(SP_PHASE_FFN_UP);
+                rc = project_ln(g, F, sF, lo + L.w2, lo + L.b2, x1, x, lo + L.ln2g, lo + L.ln2b, SP_PHASE_FFN_DOWN);
+                if (rc != SP_OK) return rc;
+                continue;
+            }
             SP_TRY(launch_rows_residual(M, lo + L.wo, lo + L.bo, (const bf16*)att, sT, rows_layout(H), H, false,
                                         (const bf16*)x, sT, false, uo, u_ss, cu, T, T, k, s));
             SP_MARK(SP_PHASE_OPROJ);
@@ -444,6 +488,15 @@ static int run_students(const sp_model* M0, const WsLayout& W, const int32_t* id
         SP_TRY(launch_attention(M, qkv, vt, fp8 && with_head ? nullptr : att, cu, B, T, max_seqlen, rows, k, s, attq,
                                 kActQuantScale));
         SP_MARK(SP_PHASE_ATTENTION);
+        if (bf16_path(c) && !fp8) {
+            int rc = project_ln(att, H, sH, lo + L.wo, lo + L.bo, x, x1, lo + L.ln1g, lo + L.ln1b, SP_PHASE_OPROJ);
+            if (rc != SP_OK) return rc;
+            SP_TRY(launch_gemm(M, x1, H, lo + L.w1, lo + L.b1, g, F, nullptr, 0, mrows, F, H, k, EPI_BIAS_GELU, sH, sF, 0, s));
+            SP_MARK(SP_PHASE_FFN_UP);
+            rc = project_ln(g, F, sF, lo + L.w2, lo + L.b2, x1, x, lo + L.ln2g, lo + L.ln2b, SP_PHASE_FFN_DOWN);
+            if (rc != SP_OK) return rc;
+            continue;
+        }
         if (fp8)
             SP_TRY(launch_gemm_fp8(M, attq, H, lo + L.wo8, lo + L.so, lo + L.bo, kActQuantScale, u, H, x, H, mrows, H, H, k,
                                    EPI_BIAS_RESIDUAL, qH, sH, sH, s, nullptr, 0, 0, 0, 1.f));
@@ -506,7 +559,7 @@ static int run_forward(const sp_model* M, const int32_t* ids, const int32_t* cu,
 
     const bool two_groups = with_head && !pt && k >= 2 && T >= two_groups_min_tokens() && !c.single_stream && M->aux;
     if (!two_groups)
-        return run_students(M, W, ids, cu, B, T, max_seqlen, 0, k, stop_layers, with_head, w, logits, s, pt);
+        return run_students(M, W, ids, cu, B, T, max_seqlen, 0, k, true, stop_layers, with_head, w, logits, s, pt);
 
     const int ka = (k + 1) / 2;
     float* lpart = (float*)(w + W.lpart);
@@ -514,8 +567,8 @@ static int run_forward(const sp_model* M, const int32_t* ids, const int32_t* cu,
     std::lock_guard<std::mutex> hold(*M->mu);       // one fork/join at a time on the model's stream and events
     if (hipEventRecord(M->ev_fork, s) != hipSuccess || hipStreamWaitEvent(M->aux, M->ev_fork, 0) != hipSuccess)
         return SP_EHIP;
-    int rc = run_students(M, W, ids, cu, B, T, max_seqlen, 0, ka, stop_layers, true, w, lpart, s, nullptr);
-    const int rc2 = run_students(M, W, ids, cu, B, T, max_seqlen, ka, k - ka, stop_layers, true, w, lpart + n, M->aux,
+    int rc = run_students(M, W, ids, cu, B, T, max_seqlen, 0, ka, false, stop_layers, true, w, lpart, s, nullptr);
+    const int rc2 = run_students(M, W, ids, cu, B, T, max_seqlen, ka, k - ka, false, stop_layers, true, w, lpart + n, M->aux,
                                  nullptr);
     // join even after an error, so that the auxiliary stream never runs on beyond the call
     if (hipEventRecord(M->ev_join, M->aux) != hipSuccess || hipStreamWaitEvent(s, M->ev_join, 0) != hipSuccess)

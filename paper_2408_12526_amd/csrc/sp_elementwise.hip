@@ -198,6 +198,48 @@ __global__ __launch_bounds__(256) void layernorm_kernel(const char* arena, size_
     }
 }
 
+// Sum of the slices of a split reduction + bias + residual, then LayerNorm: one wave per row.
+constexpr int kMaxSlices = 8;
+template <int MAXC>
+__global__ __launch_bounds__(256) void ln_slices_kernel(const char* arena, size_t student_stride, size_t g_off, size_t b_off,
+                                                        size_t bias_off, const float* __restrict__ part, size_t slice,
+                                                        size_t p_ss, int splits, const bf16* __restrict__ res,
+                                                        bf16* __restrict__ out, int rows, int nrows, int H, float eps)
+{
+    const int m = blockIdx.y, lane = threadIdx.x & 63;
+    const int row = blockIdx.x * 4 + (threadIdx.x >> 6);
+    if (row >= nrows) return;
+    const int nch = H >> 3;
+    const char* sb = arena + (size_t)m * student_stride;
+    float gg[MAXC][8], bb[MAXC][8];
+    load_gamma_beta<MAXC>((const float*)(sb + g_off), (const float*)(sb + b_off), nch, lane, gg, bb);
+    const float* bias = (const float*)(sb + bias_off);
+    const bf16* rrow = res + ((size_t)m * rows + row) * H;
+    const float* prow = part + (size_t)m * p_ss + (size_t)row * H;
+    float v[MAXC][8];
+#pragma unroll
+    for (int i = 0; i < MAXC; ++i) {
+        const int c = lane + 64 * i;
+        if (c < nch) {
+            float r8[8], b8[8], p8[kMaxSlices][8];            // all slices requested at once, added in ascending order
+            load8(rrow + c * 8, r8);
+            load8(bias + c * 8, b8);
+#pragma unroll
+            for (int sidx = 0; sidx < kMaxSlices; ++sidx)
+                if (sidx < splits) load8(prow + (size_t)sidx * slice + c * 8, p8[sidx]);
+#pragma unroll
+            for (int e = 0; e < 8; ++e) v[i][e] = r8[e] + b8[e];
+#pragma unroll
+            for (int sidx = 0; sidx < kMaxSlices; ++sidx)
+                if (sidx < splits) {
+#pragma unroll
+                    for (int e = 0; e < 8; ++e) v[i][e] += p8[sidx][e];
+                }
+        }
+    }
+    ln_row_store<bf16, MAXC>(v, nch, lane, H, gg, bb, eps, out + ((size_t)m * rows + row) * H);
+}
+
 // ---- head -------------------------------------------------------------------------
 // Stage 1: one workgroup = (group of kSeqPerWg sequences, student, slice of 64 pooler outputs).
 // pooled[n] = tanh(bp[n] + sum_i cls[i] Wp[i][n]); the slice's share of the classifier,
@@ -541,6 +583,21 @@ hipError_t launch_check_inputs(const int32_t* ids, const int32_t* cu, int B, int
     const int blocks = (T + 255) / 256 < 1024 ? (T + 255) / 256 : 1024;
     hipLaunchKernelGGL(check_inputs_kernel, dim3(blocks < 1 ? 1 : blocks), dim3(256), 0, s, ids, cu, B, T, max_seqlen,
                        vocab, flags);
+    return hipGetLastError();
+}
+
+hipError_t launch_ln_slices(const sp_model* M, const float* part, size_t slice, size_t p_ss, int splits, size_t bias_off,
+                            const void* residual, void* out, int rows, int nrows, int k, size_t g_off, size_t b_off,
+                            hipStream_t s)
+{
+    const sp_config& c = M->cfg;
+    if (!bf16_path(c) || splits < 1 || splits > kMaxSlices || c.hidden > 1024) return hipErrorInvalidValue;
+    dim3 grid((nrows + 3) / 4, k);
+#define SP_LNS(MAXC)                                                                                               \
+    hipLaunchKernelGGL((ln_slices_kernel<MAXC>), grid, dim3(256), 0, s, M->arena, M->L.student_stride, g_off, b_off, bias_off, \
+                       part, slice, p_ss, splits, (const bf16*)residual, (bf16*)out, rows, nrows, c.hidden, c.ln_eps)
+    if (c.hidden <= 512) SP_LNS(1); else SP_LNS(2);
+#undef SP_LNS
     return hipGetLastError();
 }
 

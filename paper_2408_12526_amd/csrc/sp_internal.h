@@ -222,7 +222,7 @@ hipError_t launch_layernorm(const sp_model* M, const void* u, void* out, int row
 
 // EPI_QKV (bf16 path only): bias; output columns >= n_split (the value projection) are written transposed,
 // out2[m][column - n_split][row], so that attention reads key-contiguous value tiles.
-enum Epilogue { EPI_BIAS = 0, EPI_BIAS_GELU = 1, EPI_BIAS_RESIDUAL = 2, EPI_QKV = 3, EPI_BIAS_TANH = 4 };
+enum Epilogue { EPI_BIAS = 0, EPI_BIAS_GELU = 1, EPI_BIAS_RESIDUAL = 2, EPI_QKV = 3, EPI_BIAS_TANH = 4, EPI_PARTIAL = 5 };
 
 // out[m][row][0..N) = epi(A[m][row][0..Kd) . W^T + bias), W stored [N][Kd] at w_off of each student.
 // lda / ldo / ldr are row strides in elements; residual may be null unless EPI_BIAS_RESIDUAL;
@@ -232,6 +232,15 @@ hipError_t launch_gemm(const sp_model* M, const void* A, int lda, size_t w_off, 
                        size_t a_student_stride, size_t o_student_stride, size_t r_student_stride, hipStream_t s,
                        void* out2 = nullptr, int n_split = 0, int ld2 = 0, size_t o2_student_stride = 0,
                        bool packed_out = false);   // packed_out (bf16): out in packed_layout(ldo)
+
+// Split reduction for launches of few tiles: part[sp][m][row][0..N) = A[m][row][sp*Kd/splits ..) . W^T (fp32, no bias), sp <
+// splits; slice: elements from slice to slice, p_student_stride from student to student.
+hipError_t launch_gemm_split(const sp_model* M, const void* A, int lda, size_t w_off, float* part, size_t slice, int mrows,
+                             int N, int Kd, int k, int splits, size_t a_student_stride, size_t p_student_stride, hipStream_t s);
+// out[m][row][:] = LN(sum_sp part[sp][m][row][:] + bias + residual[m][row][:]; g, b)
+hipError_t launch_ln_slices(const sp_model* M, const float* part, size_t slice, size_t p_ss, int splits, size_t bias_off,
+                            const void* residual, void* out, int rows, int nrows, int k, size_t g_off, size_t b_off,
+                            hipStream_t s);
 
 // The same projection on fp8 operands (SP_DTYPE_FP8; 256 x 256 tile only: mrows and N multiples of 256, Kd of 128).
 // A8: e4m3 codes of activation * a_qscale, [m][row][lda] bytes; weights at w_off (e4m3, [N][Kd] bytes) with fp32

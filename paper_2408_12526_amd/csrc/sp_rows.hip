@@ -253,15 +253,72 @@ struct RowsKArgs {
     int Tn, M, N, Kd, nfb, nfb8, nrb;
 };
 
+// Outputs are four neighbouring features of a row per thread and round: threads per row, rows per round, rounds.
+template <int TM, int TF>
+struct KsplitOut {
+    static constexpr int TPR = 4 * TF, RPR = 256 / TPR, ROUNDS = 16 * TM / RPR < 1 ? 1 : 16 * TM / RPR;
+};
+
+// what the last step needs (requested first)
+template <bool F32OUT, int TM, int TF>
+__device__ __forceinline__ void ksplit_inputs(const RowsKArgs& p, bf16x4 (&rv)[KsplitOut<TM, TF>::ROUNDS], f32x4& bias,
+                                              const char* sb, int m, int r0, int n0)
+{
+    using O = KsplitOut<TM, TF>;
+    const int f = 4 * ((int)threadIdx.x % O::TPR), rr = (int)threadIdx.x / O::TPR;
+    bias = *(const f32x4*)((const float*)(sb + p.b) + n0 + f);
+    if (!F32OUT) return;
+#pragma unroll
+    for (int i = 0; i < O::ROUNDS; ++i) {
+        int r = r0 + (rr + O::RPR * i) % (16 * TM);
+        r = r < p.M ? r : p.M - 1;
+        rv[i] = *(const bf16x4*)(p.res + (size_t)m * p.r_ss + (size_t)(p.r_first ? first_row(p.cu, r, p.Tn) : r) * p.ldr + n0 + f);
+    }
+}
+
+// the four waves' partial tiles through LDS, added in wave order, then bias and residual
+template <bool F32OUT, int TM, int TF>
+__device__ __forceinline__ void ksplit_finish(const RowsKArgs& p, float (*part)[16 * TM][16 * TF + 4], const f32x4 (&acc)[TF][TM],
+                                              const bf16x4 (&rv)[KsplitOut<TM, TF>::ROUNDS], f32x4 bias, int m, int r0, int n0)
+{
+    using O = KsplitOut<TM, TF>;
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, l16 = lane & 15, kg = lane >> 4;
+    const int f = 4 * ((int)threadIdx.x % O::TPR), rr = (int)threadIdx.x / O::TPR;
+#pragma unroll
+    for (int fi = 0; fi < TF; ++fi)
+#pragma unroll
+        for (int t = 0; t < TM; ++t) *(f32x4*)&part[wave][16 * t + l16][16 * fi + 4 * kg] = acc[fi][t];
+    __syncthreads();
+#pragma unroll
+    for (int i = 0; i < O::ROUNDS; ++i) {
+        const int rl = rr + O::RPR * i, r = r0 + rl;
+        if (rl >= 16 * TM || r >= p.M) continue;
+        f32x4 s = *(const f32x4*)&part[0][rl][f];
+#pragma unroll
+        for (int w = 1; w < 4; ++w) s += *(const f32x4*)&part[w][rl][f];
+        s += bias;
+        const size_t at = (size_t)m * p.o_ss + (size_t)r * p.ldo + n0 + f;
+        if (F32OUT) {
+#pragma unroll
+            for (int e = 0; e < 4; ++e) s[e] += (float)rv[i][e];
+            *(f32x4*)((float*)p.out + at) = s;
+        } else {
+            bf16x4 o;
+#pragma unroll
+            for (int e = 0; e < 4; ++e) o[e] = (bf16)s[e];
+            *(bf16x4*)((bf16*)p.out + at) = o;
+        }
+    }
+}
+
 template <bool F32OUT, int TM, int TF, int NS, bool EXACT>
 __global__ __launch_bounds__(256) void rows_ksplit_kernel(RowsKArgs p)
 {
-    constexpr int PP = 16 * TF + 4;
-    __shared__ __attribute__((aligned(16))) float part[4][16 * TM][PP];  // [wave][row][feature], padded
+    __shared__ __attribute__((aligned(16))) float part[4][16 * TM][16 * TF + 4];  // [wave][row][feature], padded
     const int fb = (int)blockIdx.x % p.nfb8, rm = (int)blockIdx.x / p.nfb8;
     if (fb >= p.nfb) return;
     const int m = rm / p.nrb, r0 = (rm % p.nrb) * 16 * TM;
-    const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const int l16 = lane & 15, kg = lane >> 4;
     const char* sb = p.arena + (size_t)m * p.ss;
     const int Kd = EXACT ? 128 * NS : p.Kd, n0 = fb * 16 * TF, kw = Kd >> 2, k0 = wave * kw;
@@ -276,20 +333,9 @@ __global__ __launch_bounds__(256) void rows_ksplit_kernel(RowsKArgs p)
         if (p.a_first) r = first_row(p.cu, r, p.Tn);
         ar[t] = ab + (size_t)(r >> 4) * p.al.rb + (size_t)(r & 15) * p.al.rs;
     }
-    // what the last step needs, requested first: outputs are four neighbouring features of a row per thread and round
-    constexpr int TPR = 4 * TF, RPR = 256 / TPR, NR = 16 * TM / RPR;     // threads per row, rows per round, rounds
-    constexpr int ROUNDS = NR < 1 ? 1 : NR;
-    const int f = 4 * (tid % TPR), rr = tid / TPR;
-    const f32x4 bias = *(const f32x4*)((const float*)(sb + p.b) + n0 + f);
-    bf16x4 rv[ROUNDS];
-    if (F32OUT) {
-#pragma unroll
-        for (int i = 0; i < ROUNDS; ++i) {
-            int r = r0 + (rr + RPR * i) % (16 * TM);
-            r = r < p.M ? r : p.M - 1;
-            rv[i] = *(const bf16x4*)(p.res + (size_t)m * p.r_ss + (size_t)(p.r_first ? first_row(p.cu, r, p.Tn) : r) * p.ldr + n0 + f);
-        }
-    }
+    bf16x4 rv[KsplitOut<TM, TF>::ROUNDS];
+    f32x4 bias;
+    ksplit_inputs<F32OUT, TM, TF>(p, rv, bias, sb, m, r0, n0);
     f32x4 acc[TF][TM];
 #pragma unroll
     for (int fi = 0; fi < TF; ++fi)
@@ -321,31 +367,7 @@ __global__ __launch_bounds__(256) void rows_ksplit_kernel(RowsKArgs p)
                 for (int fi = 0; fi < TF; ++fi) acc[fi][t] = mfma16(fw[fi][s], fa[t & 1][s], acc[fi][t]);   // rows: features
         }
     }
-#pragma unroll
-    for (int fi = 0; fi < TF; ++fi)
-#pragma unroll
-        for (int t = 0; t < TM; ++t) *(f32x4*)&part[wave][16 * t + l16][16 * fi + 4 * kg] = acc[fi][t];
-    __syncthreads();
-#pragma unroll
-    for (int i = 0; i < ROUNDS; ++i) {
-        const int rl = rr + RPR * i, r = r0 + rl;
-        if (rl >= 16 * TM || r >= p.M) continue;
-        f32x4 s = *(const f32x4*)&part[0][rl][f];
-#pragma unroll
-        for (int w = 1; w < 4; ++w) s += *(const f32x4*)&part[w][rl][f];
-        s += bias;
-        const size_t at = (size_t)m * p.o_ss + (size_t)r * p.ldo + n0 + f;
-        if (F32OUT) {
-#pragma unroll
-            for (int e = 0; e < 4; ++e) s[e] += (float)rv[i][e];
-            *(f32x4*)((float*)p.out + at) = s;
-        } else {
-            bf16x4 o;
-#pragma unroll
-            for (int e = 0; e < 4; ++e) o[e] = (bf16)s[e];
-            *(bf16x4*)((bf16*)p.out + at) = o;
-        }
-    }
+    ksplit_finish<F32OUT, TM, TF>(p, part, acc, rv, bias, m, r0, n0);
 }
 
 // -------------------------------------------------------------------------------------
