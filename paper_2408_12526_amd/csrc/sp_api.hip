@@ -167,8 +167,8 @@ static inline uint8_t f32_to_e4m3(float f)
     return (uint8_t)(sign | (code > 0x7e ? 0x7e : code));
 }
 
-// dst8[o][i] = e4m3(src[i][o] / scale[o]), scale[o] = max_i |src[i][o]| / 448 (1 for an all-zero column);
-// src is [n_in][n_out]
+// code (o, i) = e4m3(src[i][o] / scale[o]), scale[o] = max_i |src[i][o]| / 448 (1 for an all-zero column), in the operand
+// blocks of ArenaLayout; src is [n_in][n_out], n_in a multiple of 64 and n_out of 32
 static void quantize_transposed(uint8_t* dst8, float* scale, const float* src, size_t n_in, size_t n_out)
 {
     std::vector<float> amax(n_out, 0.f);
@@ -183,7 +183,11 @@ static void quantize_transposed(uint8_t* dst8, float* scale, const float* src, s
         for (size_t o0 = 0; o0 < n_out; o0 += T) {
             const size_t i1 = i0 + T < n_in ? i0 + T : n_in, o1 = o0 + T < n_out ? o0 + T : n_out;
             for (size_t o = o0; o < o1; ++o)
-                for (size_t i = i0; i < i1; ++i) dst8[o * n_in + i] = f32_to_e4m3(src[i * n_out + o] / scale[o]);
+                for (size_t i = i0; i < i1; ++i) {
+                    const size_t c = i >> 4 & 3;
+                    dst8[((o >> 5) * (n_in >> 6) + (i >> 6)) * 2048 + (c & 1) * 1024 + (c >> 1) * 512 + (o & 31) * 16 + (i & 15)] =
+                        f32_to_e4m3(src[i * n_out + o] / scale[o]);
+                }
         }
 }
 
@@ -290,10 +294,10 @@ static int run_students(const sp_model* M0, const WsLayout& W, const int32_t* id
     const sp_model* M = &shifted;
     const int H = c.hidden, F = c.ffn, rows = W.rows;
     // quantised students: the four projections of the all-token layers on fp8 operands (large calls only)
-    // (the fp8 kernel has one tile size, 256 x 256: widths that are not multiples of it stay on the bf16 path)
+    // (the fp8 kernel's tiles are 256 features wide: widths that are not multiples of it stay on the bf16 path)
     const bool fp8 = c.dtype == SP_DTYPE_FP8 && rows >= kFp8MinRows && W.xq && H % 256 == 0 && F % 256 == 0;
     // rows actually computed
-    const int mtile = fp8 || !bf16_path(c) ? 256 : 64;
+    const int mtile = !bf16_path(c) ? 256 : 64;
     const int mrows = !bf16_path(c) && T <= 256 ? (T + (T > 64 ? 127 : 63)) / (T > 64 ? 128 : 64) * (T > 64 ? 128 : 64)
                                                 : (T + mtile - 1) / mtile * mtile;
     const size_t ab = W.act_bytes;

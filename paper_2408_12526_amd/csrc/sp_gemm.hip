@@ -284,7 +284,9 @@ hipError_t launch_wreg_tile(const sp_model* M, GemmArgs a, int N, int k, hipStre
 // what a token costs at that height (a lower tile reads the weights more often: measured 1.1 at 96 tokens, 1.2 at 64, 1.7 at
 // 32, 1 at 128).  Measured against it, us at 128 / 96 / 64 / 32 tokens: 960 tokens x 4 students, 2304 features from 768:
 // 25.1 / 21.7 / 23.2 / 28.2; 18432 tokens, 1024 features from 4096: 175 / 155 / 185 / -; 640 tokens, 768 from 768: 15.3 / 13.0 / 11.2 / 8.8.
-inline int tile_height(int mrows, int N, int k)
+}  // namespace
+
+int gemm_tile_height(int mrows, int N, int k)
 {
     static const double cost[5] = {0, 1.7, 1.2, 1.1, 1.0};
     int best = 4;
@@ -297,12 +299,14 @@ inline int tile_height(int mrows, int N, int k)
     return best;
 }
 
+namespace {
+
 template <int EPI>
 hipError_t launch_bf16(const sp_model* M, const GemmArgs& a, int N, int k, hipStream_t s)
 {
     // (widths that are not multiples of 256: half the features, two waves)
     if (N % 256 || a.n_split % 256) return launch_wreg_tile<2, 2, EPI>(M, a, N, k, s);
-    switch (tile_height(a.mrows, N, k * a.splits)) {
+    switch (gemm_tile_height(a.mrows, N, k * a.splits)) {
         case 1: return launch_wreg_tile<1, 4, EPI>(M, a, N, k, s);
         case 2: return launch_wreg_tile<2, 4, EPI>(M, a, N, k, s);
         case 3: return launch_wreg_tile<3, 4, EPI>(M, a, N, k, s);

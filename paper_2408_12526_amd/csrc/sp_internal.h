@@ -166,7 +166,9 @@ struct ArenaLayout {
     size_t wqkv, bqkv, wo, bo, ln1g, ln1b, w1, b1, w2, b2, ln2g, ln2b;
     size_t wk_io;                  // the key projection once more with the roles exchanged: rows in, reduction index out (folded first-token queries)
     // SP_DTYPE_FP8 only (0 otherwise), relative to the start of a layer: the fused q|k|v, attention-output, FFN-up and
-    // FFN-down matrices once more as e4m3 codes, [out][in] bytes, and their per-output-feature scales (fp32)
+    // FFN-down matrices once more as e4m3 codes and their per-output-feature scales (fp32).  Codes lie in blocks of 32
+    // outputs x 64 inputs, [out / 32][in / 64][c % 2][c / 2][out % 32][in % 16] with c = in / 16 % 4: the two wave-loads of
+    // one matrix-instruction operand, 1 KB in a row each
     size_t wqkv8, sqkv, wo8, so, w18, s1, w28, s2;
     size_t wp, wp_t, bp, wc, bc;   // wp: [in][out] (column-parallel head kernel); wp_t: projection operand
     size_t student_stride;
@@ -242,8 +244,11 @@ hipError_t launch_ln_slices(const sp_model* M, const float* part, size_t slice, 
                             const void* residual, void* out, int rows, int nrows, int k, size_t g_off, size_t b_off,
                             hipStream_t s);
 
-// The same projection on fp8 operands (SP_DTYPE_FP8; 256 x 256 tile only: mrows and N multiples of 256, Kd of 128).
-// A8: e4m3 codes of activation * a_qscale, [m][row][lda] bytes; weights at w_off (e4m3, [N][Kd] bytes) with fp32
+// Tile height in blocks of 32 tokens (1 to 4) for a projection of mrows rows onto N features (a multiple of 256) of k students.
+int gemm_tile_height(int mrows, int N, int k);
+
+// The same projection on fp8 operands (SP_DTYPE_FP8: mrows a multiple of 64, N and Kd of 256).
+// A8: e4m3 codes of activation * a_qscale, [m][row][lda] bytes; weights at w_off (e4m3, operand blocks) with fp32
 // scales at s_off; epi is EPI_QKV (bf16 out, value third transposed into out2), EPI_BIAS_GELU (out: e4m3 codes of
 // gelu(.) * out_qscale, ldo bytes per row) or EPI_BIAS_RESIDUAL (bf16 out).  Student strides in bytes.
 hipError_t launch_gemm_fp8(const sp_model* M, const void* A8, int lda, size_t w_off, size_t s_off, size_t b_off,

@@ -263,3 +263,41 @@ def test_fp8_large_width(sp, oracle64):
     print(f"fp8 hidden 1024: rel err {e:.3e}", flush=True)
     assert e <= FP8_LOGITS_REL
     st.close()
+
+
+# K picks the tile height (32 K tokens) of the projections of 768 features at these row counts: q|k|v and FFN up at the first
+# width, attention output, FFN up and down at the second; one row beyond a tile of any height, and one short of 64
+@pytest.mark.parametrize("tokens", [2049, 2111])
+@pytest.mark.parametrize("K", [1, 2, 3, 4])
+@pytest.mark.parametrize("hidden", [256, 768])
+def test_fp8_tiles_of_every_height_at_their_edges(sp, oracle64, hidden, K, tokens):
+    """Every projection on the HIP path's own quantised input, the last rows and a sample of the others: bounds as in the stage
+    test (bf16 rounding of the outputs; e4m3 rounding of the GELU output)."""
+    shape = synth.StudentShape(K=K, layers=1, hidden=hidden, heads=hidden // 64, ffn=768, vocab=60, max_pos=128, classes=2, dtype="fp8")
+    rng = np.random.default_rng(tokens + K)
+    lengths = np.full(-(-tokens // 100), 100, dtype=np.int32)
+    lengths[-1] = tokens - 100 * (len(lengths) - 1)
+    ids, blob = synth.make_ids(rng, tokens, shape.vocab), synth.make_weights(rng, shape, std=0.05, ln_random=True)
+    st = sp.Students(sp.config_from_shape(shape, last_layer_all_tokens=True), blob)
+    d_ids, d_cu = torch.from_numpy(ids).cuda(), torch.from_numpy(sp.sp_pack(lengths)).cuda()
+    rows = np.unique(np.r_[np.arange(0, tokens, 61), np.arange(tokens - 130, tokens)])
+    names = ("xq", "qkv", "attq", "x1", "x1q", "gq", "x")
+    B = len(lengths)
+    ws = st.sp_forward_partial(d_ids, d_cu, 100, K, 0)
+    x0, xq0 = (st.read_activation(ws, n, tokens, B, K)[:, rows] for n in ("x", "xq"))
+    ws = st.sp_forward_partial(d_ids, d_cu, 100, K, 1)
+    got = {n: st.read_activation(ws, n, tokens, B, K)[:, rows] for n in names}
+    ow = dequantised_weights(blob, shape, range(1))
+    for m in range(K):
+        v = {n[3:]: w for n, w in synth.student_views(ow, shape, m).items() if n.startswith("l0.")}
+
+        def ln(u, which):
+            return np.stack([oracle64.layernorm(r, v[f"ln{which}_g"], v[f"ln{which}_b"], shape.ln_eps) for r in u])
+
+        qkv = oracle64.linear(xq0[m], np.concatenate([v["Wq"], v["Wk"], v["Wv"]], axis=1), np.concatenate([v["bq"], v["bk"], v["bv"]]))
+        assert rel_err(got["qkv"][m], qkv) < 1.2e-2
+        assert rel_err(got["x1"][m], ln(x0[m] + oracle64.linear(got["attq"][m], v["Wo"], v["bo"]), 1)) < 1.2e-2
+        g = torch.nn.functional.gelu(torch.from_numpy(oracle64.linear(got["x1q"][m], v["W1"], v["b1"]))).numpy()
+        assert (np.abs(got["gq"][m] - g) - 2.0 ** -4 * np.abs(g)).max() <= 2e-3 * np.abs(g).max()
+        assert rel_err(got["x"][m], ln(got["x1"][m] + oracle64.linear(got["gq"][m], v["W2"], v["b2"]), 2)) < 1.2e-2
+    st.close()
