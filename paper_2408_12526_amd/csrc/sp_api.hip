@@ -447,6 +447,8 @@ static int run_students(const sp_model* M0, const WsLayout& W, const int32_t* id
         }
         return SP_OK;
     }
+    // (the partial forwards of the tests read the buffers between the projections)
+    const bool f32_layer = with_head && f32_layer_supported(c, (long)T * k);
     SP_TRY(launch_embed_ln(M, ids, cu, B, T, rows, mrows, k, x, att, s, xq, kActQuantScale, attq));
     SP_MARK(SP_PHASE_EMBED);
     for (int l = 0; l < stop_layers; ++l) {
@@ -483,7 +485,7 @@ static int run_students(const sp_model* M0, const WsLayout& W, const int32_t* id
         else if (bf16_path(c))
             SP_TRY(launch_gemm(M, x, H, lo + L.wqkv, lo + L.bqkv, qkv, 3 * H, nullptr, 0, mrows, 3 * H, H, k, EPI_QKV,
                                sH, s3H, 0, s, vt, 2 * H, rows, sH));
-        else
+        else if (l == 0 || !f32_layer)                      // (else the previous layer's launch has left q|k|v)
             SP_TRY(launch_gemm(M, x, H, lo + L.wqkv, lo + L.bqkv, qkv, 3 * H, nullptr, 0, mrows, 3 * H, H, k, EPI_BIAS,
                                sH, s3H, 0, s));
         SP_MARK(SP_PHASE_QKV);
@@ -492,6 +494,11 @@ static int run_students(const sp_model* M0, const WsLayout& W, const int32_t* id
         SP_TRY(launch_attention(M, qkv, vt, fp8 && with_head ? nullptr : att, cu, B, T, max_seqlen, rows, k, s, attq,
                                 kActQuantScale));
         SP_MARK(SP_PHASE_ATTENTION);
+        if (f32_layer) {
+            SP_TRY(launch_f32_layer(M, lo, att, x, l + 1 < stop_layers ? qkv : nullptr, T, rows, k, s));
+            SP_MARK(SP_PHASE_FFN_DOWN);
+            continue;
+        }
         if (bf16_path(c) && !fp8) {
             int rc = project_ln(att, H, sH, lo + L.wo, lo + L.bo, x, x1, lo + L.ln1g, lo + L.ln1b, SP_PHASE_OPROJ);
             if (rc != SP_OK) return rc;

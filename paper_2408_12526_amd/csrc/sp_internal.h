@@ -291,6 +291,12 @@ hipError_t launch_attention_first(const sp_model* M, const void* qkv, const void
 hipError_t launch_rows_ln_out(const sp_model* M, size_t g_off, size_t b_off, const float* u, size_t u_ss, void* out,
                               size_t o_ss, int nrows, int k, hipStream_t s);
 
+// ---- fp32 path, calls of few rows (sp_rows_f32.hip): x = LN(x1 + FFN(x1)), x1 = LN(x + att Wo + bo), of T rows per student in
+// one launch, and q|k|v of the next layer from the new x (qkv_next null: there is none)
+bool f32_layer_supported(const sp_config& c, long rows_of_all_students);
+hipError_t launch_f32_layer(const sp_model* M, size_t lo, const void* att, void* x, void* qkv_next, int T, int rows, int k,
+                            hipStream_t s);
+
 // att[m][t][h*64..] = softmax(q k^T / 8) v inside each sequence; qkv rows are [q | k | v] of width 3H.
 // bf16 path: the values are read from vt[m][H][rows] (transposed) instead of the third slice of qkv.
 // attq (may be null, bf16 path only): the output once more as e4m3 codes of value * qscale, [m][rows][H] bytes.

@@ -51,3 +51,26 @@ def test_first_token_rows_of_many_sequences(oracle64, hidden, nseq, length):
     shape = synth.StudentShape(K=3, layers=2, hidden=hidden, heads=hidden // 64, ffn=4 * hidden, vocab=60, max_pos=16, classes=2,
                                dtype="bf16")
     _run(oracle64, shape, (length,) * nseq, (1, 3), hidden + nseq)
+
+
+@pytest.mark.parametrize("ffn,layers", [(128, 1), (512, 2), (768, 3)])
+@pytest.mark.parametrize("lengths,k", [((1,), 1), ((2,), 2), ((3, 4), 2), ((27, 8, 32, 19), 2), ((64,) * 4, 2), ((64, 64, 64, 64, 1), 2),
+                                       ((57,) * 9, 1)])
+def test_fp32_layer_in_one_launch(oracle64, ffn, layers, lengths, k):
+    """Two rows per workgroup: one row, odd counts, the last call on one launch per layer (512 rows of all students) and the
+    first on separate ones; with and without a next layer.  fp32 sums of at most 768 terms, each within a few 1e-7 of its size."""
+    from paper_2408_12526_amd import sp
+    shape = synth.StudentShape(K=2, layers=layers, hidden=128, heads=2, ffn=ffn, vocab=60, max_pos=64, classes=3, dtype="fp32")
+    rng = np.random.default_rng(ffn + sum(lengths))
+    lengths = np.array(lengths, dtype=np.int32)
+    ids = synth.make_ids(rng, int(lengths.sum()), shape.vocab)
+    blob = synth.make_weights(rng, shape, std=0.04, ln_random=True)
+    cu = sp.sp_pack(lengths)
+    st = sp.Students(sp.config_from_shape(shape), blob)
+    got = st.sp_forward(torch.from_numpy(ids).cuda(), torch.from_numpy(cu).cuda(), int(lengths.max()), k).double().cpu().numpy()
+    cfg = OracleConfig(shape.K, shape.layers, shape.hidden, shape.heads, shape.ffn, shape.vocab, shape.max_pos, shape.classes,
+                       shape.ln_eps)
+    want = oracle64.forward(cfg, blob, ids, cu, k)
+    err = np.abs(got - want).max() / max(np.abs(want).max(), 1e-3)
+    assert err <= 1e-5, f"{err:.3e}"
+    st.close()
