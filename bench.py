@@ -706,7 +706,7 @@ def main():
         # the ffn_up phase is exactly one launch of this kernel per step (HIP events around it, on the launch stream)
         tr = tracked_traffic()
         fresh = bool(tr and tr.get("matches_this_build"))
-        rec["roofline"] = {"kernel": "gemm_bf16_kernel<256,256,BIAS_GELU> (FFN up-projection + GELU, all-token layer)",
+        rec["roofline"] = {"kernel": "gemm_wreg_kernel<4,4,BIAS_GELU> (FFN up-projection + GELU, all-token layer)",
                            "bound": "mfma",
                            "achieved": d["tflops"], "peak": PEAK_BF16_TFLOPS, "unit": "TFLOP/s", "frac": d["frac"],
                            "traffic": (tr["read_bytes"] + tr["written_bytes"]) if tr else None,

@@ -148,7 +148,7 @@ constexpr int kRowsMaxSeqs = 256;     // most sequences whose first-token rows d
 // 35.4 us for a layer's embedding, q|k|v and FFN up against 38, 352 rows 40 against 38; hidden 256: 528 rows 17.5 against 26).
 constexpr long kRowsLnMaxElems = 262144;
 constexpr int kRowsU = 1024;          // fp32 rows per student of the few-row projections' scratch (four regions of 256)
-constexpr int kFirstOnlyMinTokens = 1024;   // smallest call whose last layer runs on the first-token rows only
+constexpr int kFirstOnlyMinTokens = 1024;   // smallest call whose first-token rows have buffers of their own
 // fp8 projections: activations are quantised as e4m3(value * kActQuantScale) by the kernel that produces them
 // (LayerNorm outputs and GELU outputs are of order one: 448 / 16 = 28 before saturation, 2^-6 / 16 = 1e-3 before the
 // subnormal range), and only calls that compute at least kFp8MinRows rows use them

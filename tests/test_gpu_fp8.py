@@ -180,7 +180,7 @@ def test_fp8_mode_keeps_small_calls_on_the_bf16_path(sp, oracle64):
 
 
 def test_fp8_mode_keeps_other_widths_on_the_bf16_path(sp, oracle64):
-    """The fp8 kernel's one tile is 256 x 256: quantised students whose widths are not multiples of 256 (hidden 384
+    """The fp8 kernel's tiles are 256 features wide: quantised students whose widths are not multiples of 256 (hidden 384
     here) run large calls in bf16 as well and must meet the bf16 bound against the bf16 oracle weights."""
     shape = synth.StudentShape(K=2, layers=2, hidden=384, heads=6, ffn=640, vocab=300, max_pos=320, classes=3, dtype="fp8")
     lengths, ids, blob, cu = make_case(sp, 64, 40, shape)

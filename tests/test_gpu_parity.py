@@ -315,8 +315,8 @@ LARGE_OTHER = {
                                        classes=2, dtype="bf16"),
     "512D_ffn1280": synth.StudentShape(K=2, layers=2, hidden=512, heads=8, ffn=1280, vocab=1000, max_pos=128,
                                        classes=3, dtype="bf16"),
-    # reduction depth 128 (two k-tiles): such projections go to the 128 x 128 tile even in large calls; the shortest
-    # reduction the large tile meets is depth 256 (four k-tiles: the 256-wide student above)
+    # reduction depth 128 (two k-tiles), features in half tiles; the shortest whole tile
+    # meets depth 256 (four k-tiles: the 256-wide student above)
     "128D_ffn256": synth.StudentShape(K=3, layers=2, hidden=128, heads=2, ffn=256, vocab=1000, max_pos=128,
                                       classes=2, dtype="bf16"),
 }
@@ -324,7 +324,7 @@ LARGE_OTHER = {
 
 @pytest.mark.parametrize("name", list(LARGE_OTHER))
 def test_large_calls_on_other_widths(sp, oracle64, name):
-    """Calls of more than 2048 tokens (the 256 x 256 projection tiles, the long-call LayerNorm and embedding paths) on
+    """Calls of more than 2048 tokens (the projection tiles of large launches, the long-call LayerNorm and embedding paths) on
     widths other than the workloads'.  The oracle checks a sample of the sequences (sequences are independent)."""
     shape = LARGE_OTHER[name]
     rng = np.random.default_rng(37)
