@@ -375,7 +375,10 @@ __global__ __launch_bounds__(256) void rows_ksplit_kernel(RowsKArgs p)
 // (student, head, 16 sequences).  q_h = x[first token] Wq_h^T + bq_h (sixteen of the head's 64 features per wave),
 // exchanged through LDS as bf16, then q~_h = Wk_h q_h (a quarter of the H features per wave, reduction over 64).  Both
 // weight slices (64 x H each) are requested at once, so the two products cost one memory round trip: 9-13 us for four
-// students and up to 32 sequences where gathering the rows and two launches took 22 us.
+// students and up to 32 sequences where gathering the rows and two launches took 22 us.  The weights fill the register file
+// of a compute unit, so a launch of more workgroups than that repeats the round trip: there a workgroup takes several blocks
+// of 16 sequences, the weights staying in its registers.  Eight students and 256 sequences: 88 us with one block each, about 40
+// with eight.
 // A-operand row i of block j of a pair of blocks stands for feature 8 (i / 4) + 4 (j % 2) + i % 4 of the pair's 32, so
 // that a lane ends with eight neighbouring features and writes 16 bytes.
 // -------------------------------------------------------------------------------------
@@ -389,34 +392,38 @@ struct FoldQArgs {
     size_t q_ss;
     bf16* qt;                         // [student][qt_ss], row stride heads * H
     size_t qt_ss;
-    int Tn, M, H, heads, heads8, nrb;
+    int Tn, M, H, heads, heads8, nrb, rpw;                  // nrb: groups of rpw blocks of 16 sequences
 };
 
 template <int NS, bool EXACT>
 __global__ __launch_bounds__(256) void fold_query_kernel(FoldQArgs p)
 {
     constexpr int QP = 64 * 2 + 16;                         // bytes per staged query row
-    __shared__ __attribute__((aligned(16))) char qbuf[16 * QP];
+    __shared__ __attribute__((aligned(16))) char qbuf[2][16 * QP];   // (the next block's queries do not wait for this one's readers)
     const int h = (int)blockIdx.x % p.heads8, rm = (int)blockIdx.x / p.heads8;
     if (h >= p.heads) return;
-    const int m = rm / p.nrb, r = (rm % p.nrb) * 16 + (threadIdx.x & 15);   // this lane's sequence
+    const int m = rm / p.nrb, rb = (rm % p.nrb) * p.rpw * 16;
+    const int re = rb + p.rpw * 16 < p.M ? rb + p.rpw * 16 : p.M;
     const int H = EXACT ? 32 * NS : p.H, lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const int l16 = lane & 15, kg = lane >> 4;
     const char* sb = p.arena + (size_t)m * p.ss;
     const int n0 = h * 64 + wave * 16;
     // (!EXACT: steps beyond H repeat the last one with zero weights)
     auto at = [&](int s) { return EXACT || 32 * s < H ? 32 * s : H - 32; };
-    const bf16* xr = p.x + (size_t)m * p.x_ss + (size_t)first_row(p.cu, r < p.M ? r : p.M - 1, p.Tn) * H + 8 * kg;
     bf16x8 fw[NS], fx[NS];
+    auto load_x = [&](int r) {                              // the row of this lane's sequence
+        const bf16* xr = p.x + (size_t)m * p.x_ss + (size_t)first_row(p.cu, r < p.M ? r : p.M - 1, p.Tn) * H + 8 * kg;
+#pragma unroll
+        for (int s = 0; s < NS; ++s) fx[s] = *(const bf16x8*)(xr + at(s));
+    };
     const bf16* wp = (const bf16*)(sb + p.wq) + (size_t)n0 * H + kg * 128 + l16 * 8;
 #pragma unroll
     for (int s = 0; s < NS; ++s) {
         fw[s] = *(const bf16x8*)(wp + 16 * at(s));
         if (!EXACT && 32 * s >= H) fw[s] = bf16x8{};
     }
-#pragma unroll
-    for (int s = 0; s < NS; ++s) fx[s] = *(const bf16x8*)(xr + at(s));
-    f32x4 acc = *(const f32x4*)((const float*)(sb + p.bq) + n0 + 4 * kg);
+    load_x(rb + l16);
+    const f32x4 bias = *(const f32x4*)((const float*)(sb + p.bq) + n0 + 4 * kg);
     // key slice: this wave's H / 4 features in pairs of 16-row blocks, two reduction steps each
     const int hq = H >> 2, f0 = wave * hq;                  // (a multiple of 32)
     const int prow = 8 * (l16 >> 2) + (l16 & 3);
@@ -429,27 +436,33 @@ __global__ __launch_bounds__(256) void fold_query_kernel(FoldQArgs p)
         for (int s = 0; s < 2; ++s)                         // (a pair beyond the quarter repeats the first; it is not stored)
             fk[j][s] = *(const bf16x8*)(kp + (size_t)(EXACT || (j >> 1) * 32 < hq ? (j >> 1) * 32 : 0) * H + 32 * (j & 1) + 512 * s);
     __builtin_amdgcn_sched_barrier(0);
+    for (int r0 = rb, buf = 0; r0 < re; r0 += 16, buf ^= 1) {
+        const int r = r0 + l16;                             // this lane's sequence
+        f32x4 acc = bias;
 #pragma unroll
-    for (int s = 0; s < NS; ++s) acc = mfma16(fw[s], fx[s], acc);
-    bf16x4 o4;
+        for (int s = 0; s < NS; ++s) acc = mfma16(fw[s], fx[s], acc);
+        __builtin_amdgcn_sched_barrier(0);
+        if (r0 + 16 < re) load_x(r + 16);                   // in flight during the exchange and the second product
+        bf16x4 o4;
 #pragma unroll
-    for (int e = 0; e < 4; ++e) o4[e] = (bf16)acc[e];
-    *(bf16x4*)(qbuf + l16 * QP + (wave * 16 + 4 * kg) * 2) = o4;
-    if (r < p.M) *(bf16x4*)(p.q + (size_t)m * p.q_ss + (size_t)r * H + n0 + 4 * kg) = o4;
-    __syncthreads();
-    bf16x8 fq[2];
+        for (int e = 0; e < 4; ++e) o4[e] = (bf16)acc[e];
+        *(bf16x4*)(qbuf[buf] + l16 * QP + (wave * 16 + 4 * kg) * 2) = o4;
+        if (r < p.M) *(bf16x4*)(p.q + (size_t)m * p.q_ss + (size_t)r * H + n0 + 4 * kg) = o4;
+        barrier_lds();
+        bf16x8 fq[2];
 #pragma unroll
-    for (int s = 0; s < 2; ++s) fq[s] = *(const bf16x8*)(qbuf + l16 * QP + (4 * s + kg) * 16);
-    bf16* dst = p.qt + (size_t)m * p.qt_ss + ((size_t)r * p.heads + h) * H + f0 + 8 * kg;
+        for (int s = 0; s < 2; ++s) fq[s] = *(const bf16x8*)(qbuf[buf] + l16 * QP + (4 * s + kg) * 16);
+        bf16* dst = p.qt + (size_t)m * p.qt_ss + ((size_t)r * p.heads + h) * H + f0 + 8 * kg;
 #pragma unroll
-    for (int j = 0; j < NS / 2; j += 2) {
-        f32x4 a = {0.f, 0.f, 0.f, 0.f}, b = a;
+        for (int j = 0; j < NS / 2; j += 2) {
+            f32x4 a = {0.f, 0.f, 0.f, 0.f}, b = a;
 #pragma unroll
-        for (int s = 0; s < 2; ++s) { a = mfma16(fk[j][s], fq[s], a); b = mfma16(fk[j + 1][s], fq[s], b); }
-        bf16x8 o;
+            for (int s = 0; s < 2; ++s) { a = mfma16(fk[j][s], fq[s], a); b = mfma16(fk[j + 1][s], fq[s], b); }
+            bf16x8 o;
 #pragma unroll
-        for (int e = 0; e < 4; ++e) { o[e] = (bf16)a[e]; o[4 + e] = (bf16)b[e]; }
-        if (r < p.M && (EXACT || 16 * j < hq)) *(bf16x8*)(dst + 16 * j) = o;
+            for (int e = 0; e < 4; ++e) { o[e] = (bf16)a[e]; o[4 + e] = (bf16)b[e]; }
+            if (r < p.M && (EXACT || 16 * j < hq)) *(bf16x8*)(dst + 16 * j) = o;
+        }
     }
 }
 
@@ -749,7 +762,10 @@ hipError_t launch_fold_query(const sp_model* M, size_t lo, const void* x, int ro
     a.x = (const bf16*)x; a.x_ss = (size_t)rows * c.hidden; a.cu = cu;
     a.q = (bf16*)q; a.q_ss = q_ss; a.qt = (bf16*)qt; a.qt_ss = qt_ss;
     a.Tn = T; a.M = B; a.H = c.hidden; a.heads = c.heads; a.heads8 = up8(c.heads);
-    a.nrb = (B + 15) / 16;
+    // (one workgroup per compute unit: the fewest blocks per workgroup that need no second round)
+    const int blocks = (B + 15) / 16, groups = 256 / (c.heads * k) < 1 ? 1 : 256 / (c.heads * k);
+    a.rpw = (blocks + groups - 1) / groups;
+    a.nrb = (blocks + a.rpw - 1) / a.rpw;
     const dim3 grid((unsigned)(a.heads8 * a.nrb * k));
 #define SP_GO(NS, X) hipLaunchKernelGGL((fold_query_kernel<NS, X>), grid, dim3(256), 0, s, a)
     if (a.H == 256) SP_GO(8, true);
