@@ -347,7 +347,7 @@ static int run_students(const sp_model* M0, const WsLayout& W, const int32_t* id
             const size_t p_ss = (size_t)rows * H, slice = p_ss * k;
             SP_TRY(launch_gemm_split(M, A, Kd, w_off, ps, slice, mrows, H, Kd, k, splits, a_ss, p_ss, s));
             SP_MARK(phase);
-            SP_TRY(launch_ln_slices(M, ps, slice, p_ss, splits, b_off, res, out, rows, T, k, g_off, be_off, s));
+            SP_TRY(launch_ln_slices(M, ps, slice, p_ss, splits, b_off, res, out, rows, T, mrows, k, g_off, be_off, s));
         } else {
             SP_TRY(launch_gemm(M, A, Kd, w_off, b_off, u, H, res, H, mrows, H, Kd, k, EPI_BIAS_RESIDUAL, a_ss, sH, sH, s));
             SP_MARK(phase);

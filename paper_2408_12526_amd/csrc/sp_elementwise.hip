@@ -198,18 +198,26 @@ __global__ __launch_bounds__(256) void layernorm_kernel(const char* arena, size_
     }
 }
 
-// Sum of the slices of a split reduction + bias + residual, then LayerNorm: one wave per row.
+// Sum of the slices of a split reduction + bias + residual, then LayerNorm: one wave per row.  Rows T..mrows become zero:
+// attention multiplies the values of up to seven of them by zero probabilities, so what the next layer forms there
+// must be finite, and the operands of this projection need not be (the slices lie over the attention output's padding rows).
 constexpr int kMaxSlices = 8;
 template <int MAXC>
 __global__ __launch_bounds__(256) void ln_slices_kernel(const char* arena, size_t student_stride, size_t g_off, size_t b_off,
                                                         size_t bias_off, const float* __restrict__ part, size_t slice,
                                                         size_t p_ss, int splits, const bf16* __restrict__ res,
-                                                        bf16* __restrict__ out, int rows, int nrows, int H, float eps)
+                                                        bf16* __restrict__ out, int rows, int T, int mrows, int H, float eps)
 {
     const int m = blockIdx.y, lane = threadIdx.x & 63;
     const int row = blockIdx.x * 4 + (threadIdx.x >> 6);
-    if (row >= nrows) return;
+    if (row >= mrows) return;
     const int nch = H >> 3;
+    bf16* orow = out + ((size_t)m * rows + row) * H;
+    if (row >= T) {
+        const float zero8[8] = {0, 0, 0, 0, 0, 0, 0, 0};
+        for (int c = lane; c < nch; c += 64) store8(orow + c * 8, zero8);
+        return;
+    }
     const char* sb = arena + (size_t)m * student_stride;
     float gg[MAXC][8], bb[MAXC][8];
     load_gamma_beta<MAXC>((const float*)(sb + g_off), (const float*)(sb + b_off), nch, lane, gg, bb);
@@ -237,7 +245,7 @@ __global__ __launch_bounds__(256) void ln_slices_kernel(const char* arena, size_
                 }
         }
     }
-    ln_row_store<bf16, MAXC>(v, nch, lane, H, gg, bb, eps, out + ((size_t)m * rows + row) * H);
+    ln_row_store<bf16, MAXC>(v, nch, lane, H, gg, bb, eps, orow);
 }
 
 // ---- head -------------------------------------------------------------------------
@@ -587,15 +595,15 @@ hipError_t launch_check_inputs(const int32_t* ids, const int32_t* cu, int B, int
 }
 
 hipError_t launch_ln_slices(const sp_model* M, const float* part, size_t slice, size_t p_ss, int splits, size_t bias_off,
-                            const void* residual, void* out, int rows, int nrows, int k, size_t g_off, size_t b_off,
+                            const void* residual, void* out, int rows, int T, int mrows, int k, size_t g_off, size_t b_off,
                             hipStream_t s)
 {
     const sp_config& c = M->cfg;
     if (!bf16_path(c) || splits < 1 || splits > kMaxSlices || c.hidden > 1024) return hipErrorInvalidValue;
-    dim3 grid((nrows + 3) / 4, k);
+    dim3 grid((mrows + 3) / 4, k);
 #define SP_LNS(MAXC)                                                                                               \
     hipLaunchKernelGGL((ln_slices_kernel<MAXC>), grid, dim3(256), 0, s, M->arena, M->L.student_stride, g_off, b_off, bias_off, \
-                       part, slice, p_ss, splits, (const bf16*)residual, (bf16*)out, rows, nrows, c.hidden, c.ln_eps)
+                       part, slice, p_ss, splits, (const bf16*)residual, (bf16*)out, rows, T, mrows, c.hidden, c.ln_eps)
     if (c.hidden <= 512) SP_LNS(1); else SP_LNS(2);
 #undef SP_LNS
     return hipGetLastError();

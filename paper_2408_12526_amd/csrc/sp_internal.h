@@ -239,9 +239,9 @@ hipError_t launch_gemm(const sp_model* M, const void* A, int lda, size_t w_off, 
 // splits; slice: elements from slice to slice, p_student_stride from student to student.
 hipError_t launch_gemm_split(const sp_model* M, const void* A, int lda, size_t w_off, float* part, size_t slice, int mrows,
                              int N, int Kd, int k, int splits, size_t a_student_stride, size_t p_student_stride, hipStream_t s);
-// out[m][row][:] = LN(sum_sp part[sp][m][row][:] + bias + residual[m][row][:]; g, b)
+// out[m][row][:] = LN(sum_sp part[sp][m][row][:] + bias + residual[m][row][:]; g, b) for row < T, zero for T <= row < mrows
 hipError_t launch_ln_slices(const sp_model* M, const float* part, size_t slice, size_t p_ss, int splits, size_t bias_off,
-                            const void* residual, void* out, int rows, int nrows, int k, size_t g_off, size_t b_off,
+                            const void* residual, void* out, int rows, int T, int mrows, int k, size_t g_off, size_t b_off,
                             hipStream_t s);
 
 // Tile height in blocks of 32 tokens (1 to 4) for a projection of mrows rows onto N features (a multiple of 256) of k students.
