@@ -81,12 +81,13 @@ __global__ __launch_bounds__(64 * NW, 2) void gemm_wreg_kernel(GemmArgs p)
     const int Kd = p.Kd, nk = (EPI == EPI_PARTIAL ? p.Kper : Kd) >> 6;
 
     // activations: thread -> (row tid / 8 + 8 NW i, chunk tid % 8) of a k-tile; rows beyond mrows repeat the last one
-    const bf16* Ag = p.A + (size_t)m * p.a_ss + (EPI == EPI_PARTIAL ? sp * p.Kper : 0);
+    // (64-bit base of the tile, 32-bit offsets inside it: a buffer may hold more than 2^32 elements)
+    const bf16* Ag = p.A + (size_t)m * p.a_ss + (size_t)m0 * p.lda + (EPI == EPI_PARTIAL ? sp * p.Kper : 0);
     unsigned aoff[NA], adst[NA];
 #pragma unroll
     for (int i = 0; i < NA; ++i) {
         const int r = (tid >> 3) + 8 * NW * i;
-        const int rr = m0 + r < p.mrows ? m0 + r : p.mrows - 1;
+        const int rr = m0 + r < p.mrows ? r : p.mrows - 1 - m0;
         aoff[i] = (unsigned)rr * (unsigned)p.lda + (tid & 7) * 8;
         adst[i] = r * 8 + ((tid & 7) ^ ((r >> 1) & 7));
     }

@@ -71,14 +71,15 @@ __global__ __launch_bounds__(256, 2) void gemm_fp8_kernel(Fp8Args p)
     const int Kd = p.Kd, nk = Kd >> 7;
 
     // activations: thread -> (row tid / 8 + 32 i, chunk tid % 8) of a k-tile; rows beyond mrows repeat the last one
-    const unsigned char* Ag = p.A + (size_t)m * p.a_ss;
+    // (64-bit base of the tile, 32-bit offsets inside it: a buffer may hold more than 2^32 elements)
+    const unsigned char* Ag = p.A + (size_t)m * p.a_ss + (size_t)m0 * p.lda;
     // (the swizzle key repeats every 16 rows, so one LDS address serves a thread's pieces)
     unsigned aoff[NA];
     const unsigned adst = (tid >> 3) * 8 + ((tid & 7) ^ ((tid >> 4) & 7));
 #pragma unroll
     for (int i = 0; i < NA; ++i) {
         const int r = (tid >> 3) + 32 * i;
-        const int rr = m0 + r < p.mrows ? m0 + r : p.mrows - 1;
+        const int rr = m0 + r < p.mrows ? r : p.mrows - 1 - m0;
         aoff[i] = (unsigned)rr * (unsigned)p.lda + (tid & 7) * 16;
     }
     // weights: operand blocks of 32 features x 64 reduction elements, 2 KB, lane after lane in both halves

@@ -245,6 +245,30 @@ def test_fp8_call_whose_buffers_pass_four_gib(sp, oracle64):
     st.close()
 
 
+@pytest.mark.parametrize("dtype", ["bf16", "fp8"])
+def test_one_student_whose_ffn_activations_pass_two_to_the_32_elements(sp, oracle64, dtype):
+    """2070 sequences of up to 512 tokens at FFN 4096: element offsets inside one student's FFN activations need more than 32
+    bits from token 2^20 on.  Sequences on both sides of that token, the first and the last against the oracle."""
+    shape = synth.StudentShape(K=1, layers=2, hidden=256, heads=4, ffn=4096, vocab=500, max_pos=512, classes=2, dtype=dtype)
+    rng = np.random.default_rng(20)
+    lengths = np.full(2070, 512, dtype=np.int32)
+    lengths[::9] = 500
+    B, T = len(lengths), int(lengths.sum())
+    cu = sp.sp_pack(lengths)
+    edge = int(np.searchsorted(cu, 2**20, side="right")) - 1
+    assert T * shape.ffn > 2**32 and edge + 4 < B
+    ids, blob = synth.make_ids(rng, T, shape.vocab), synth.make_weights(rng, shape, std=0.04, ln_random=True)
+    st = sp.Students(sp.config_from_shape(shape), blob)
+    got = st.sp_forward(torch.from_numpy(ids).cuda(), torch.from_numpy(cu).cuda(), 512, 1).cpu().numpy().astype(np.float64)
+    picks = [0, edge - 1, edge, edge + 1, B - 1]
+    sub_ids = np.concatenate([ids[cu[b]:cu[b + 1]] for b in picks])
+    sub_cu = np.concatenate([[0], np.cumsum(lengths[picks])]).astype(np.int32)
+    ow = dequantised_weights(blob, shape, range(1)) if dtype == "fp8" else torch.from_numpy(blob).bfloat16().float().numpy()
+    e = rel_err(got[picks], oracle64.forward(ocfg(shape), ow, sub_ids, sub_cu, 1))
+    assert np.isfinite(got).all() and e <= (FP8_LOGITS_REL if dtype == "fp8" else 3e-2), f"{e:.3e}"
+    st.close()
+
+
 def test_fp8_large_width(sp, oracle64):
     """Quantised students at the large width (hidden 1024, 16 heads, FFN 4096: reduction depths 1024 and 4096, four and
     sixteen 256-wide feature tiles), sequences of up to 300 tokens, every sequence against the oracle."""
