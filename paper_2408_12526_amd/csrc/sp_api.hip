@@ -282,11 +282,12 @@ struct PhaseTimer {
 
 // The forward of students [m0, m0 + k) of the model (k >= 1), all of it enqueued on stream s.  Every buffer of the
 // workspace is sliced per student, so groups of students can run side by side on different streams.  With
-// with_head the group's z rows are written; logits (the group's own sum, in student order) only if non-null.  sole: no
-// other group runs beside this one (m0 is 0), so the buffers of the students beyond it are free.
+// with_head the group's z rows are written; logits (the group's own sum, in student order) only if non-null.
+// k_call: active students of the whole call.  The rules that choose between kernels of different rounding go by it and by
+// may_split, never by the group's k, so that a call has the same bits as one group and as two.
 static int run_students(const sp_model* M0, const WsLayout& W, const int32_t* ids, const int32_t* cu, int B, int T,
-                        int max_seqlen, int m0, int k, bool sole, int stop_layers, bool with_head, char* w, float* logits,
-                        hipStream_t s, PhaseTimer* pt)
+                        int max_seqlen, int m0, int k, int k_call, bool may_split, int stop_layers, bool with_head, char* w,
+                        float* logits, hipStream_t s, PhaseTimer* pt)
 {
     const sp_config& c = M0->cfg;
     sp_model shifted = *M0;                 // launchers address student i of the group as arena + i * stride
@@ -334,7 +335,8 @@ static int run_students(const sp_model* M0, const WsLayout& W, const int32_t* id
                           size_t be_off, int phase) -> int {
         int splits = 1;
         const long tiles = (long)((mrows + 63) / 64) * (H / 256) * k;
-        if (sole && with_head && H % 256 == 0 && tiles < 256) {   // (partial forwards keep the buffers for the tests)
+        // (calls that may run as two groups have no room for slices; partial forwards keep the buffers for the tests)
+        if (may_split && with_head && H % 256 == 0 && tiles < 256) {
             const int room = (A == att ? 2 : 3) * c.K / k;
             for (int sp : {2, 3, 4, 6, 8})
                 if (sp <= room && (Kd / 64) % (2 * sp) == 0 && Kd / sp >= 256) {
@@ -359,7 +361,7 @@ static int run_students(const sp_model* M0, const WsLayout& W, const int32_t* id
     // g = gelu(LN(uo; ln1) W1^T + b1) of n rows: fused while the rows of all students are few, else a LayerNorm launch and
     // the tile kernel
     auto ffn_up = [&](size_t lo, int n, void* x1r, size_t x1_ss, void* gr, size_t g_ss, bool packed) -> hipError_t {
-        if ((long)n * k * H <= kRowsLnMaxElems)
+        if ((long)n * k_call * H <= kRowsLnMaxElems)
             return launch_rows_ffn_up(M, lo, uo, u_ss, n, x1r, x1_ss, gr, g_ss, packed ? packed_layout(F) : rows_layout(F), k, s);
         const hipError_t e = launch_rows_ln_out(M, lo + L.ln1g, lo + L.ln1b, uo, u_ss, x1r, x1_ss, n, k, s);
         if (e != hipSuccess) return e;
@@ -391,7 +393,7 @@ static int run_students(const sp_model* M0, const WsLayout& W, const int32_t* id
         // Many rows over all students: the tile kernel with a split reduction for the two projections onto the hidden width as
         // well (hidden 768, 960 rows, us for both projections of a layer and their LayerNorms: 31.4 against 34.7; 352 rows 22.6
         // against 23.1; hidden 1024, 768 rows: 43.4 against 50.9)
-        const bool tiles_from_here = H % 256 == 0 && (long)T * k * H > 2 * kRowsLnMaxElems;
+        const bool tiles_from_here = H % 256 == 0 && (long)T * k_call * H > 2 * kRowsLnMaxElems;
         // (the partial forwards of the tests read the FFN activations row by row)
         const RowsLayout gl = with_head ? packed_layout(F) : rows_layout(F);
         if (stop_layers == 0) {
@@ -400,7 +402,7 @@ static int run_students(const sp_model* M0, const WsLayout& W, const int32_t* id
         }
         for (int l = 0; l < stop_layers; ++l) {
             const size_t lo = L.layer0 + (size_t)l * L.layer_stride, pl = lo - L.layer_stride;
-            if ((long)T * k * H <= kRowsLnMaxElems) {
+            if ((long)T * k_call * H <= kRowsLnMaxElems) {
                 SP_TRY(launch_rows_qkv(M, lo, l ? ud : nullptr, u_ss, l ? pl + L.ln2g : L.emb_g, l ? pl + L.ln2b : L.emb_b,
                                        ids, cu, B, T, x, qkv, vt, rows, k, s));
             } else {
@@ -448,7 +450,7 @@ static int run_students(const sp_model* M0, const WsLayout& W, const int32_t* id
         return SP_OK;
     }
     // (the partial forwards of the tests read the buffers between the projections)
-    const bool f32_layer = with_head && f32_layer_supported(c, (long)T * k);
+    const bool f32_layer = with_head && f32_layer_supported(c, (long)T * k_call);
     SP_TRY(launch_embed_ln(M, ids, cu, B, T, rows, mrows, k, x, att, s, xq, kActQuantScale, attq));
     SP_MARK(SP_PHASE_EMBED);
     for (int l = 0; l < stop_layers; ++l) {
@@ -568,9 +570,10 @@ static int run_forward(const sp_model* M, const int32_t* ids, const int32_t* cu,
     if (ws_bytes < W.end) return SP_ENOMEM;
     char* w = (char*)ws;
 
-    const bool two_groups = with_head && !pt && k >= 2 && T >= two_groups_min_tokens() && !c.single_stream && M->aux;
+    const bool large = k >= 2 && T >= two_groups_min_tokens();
+    const bool two_groups = with_head && !pt && large && !c.single_stream && M->aux;
     if (!two_groups)
-        return run_students(M, W, ids, cu, B, T, max_seqlen, 0, k, true, stop_layers, with_head, w, logits, s, pt);
+        return run_students(M, W, ids, cu, B, T, max_seqlen, 0, k, k, !large, stop_layers, with_head, w, logits, s, pt);
 
     const int ka = (k + 1) / 2;
     float* lpart = (float*)(w + W.lpart);
@@ -578,9 +581,9 @@ static int run_forward(const sp_model* M, const int32_t* ids, const int32_t* cu,
     std::lock_guard<std::mutex> hold(*M->mu);       // one fork/join at a time on the model's stream and events
     if (hipEventRecord(M->ev_fork, s) != hipSuccess || hipStreamWaitEvent(M->aux, M->ev_fork, 0) != hipSuccess)
         return SP_EHIP;
-    int rc = run_students(M, W, ids, cu, B, T, max_seqlen, 0, ka, false, stop_layers, true, w, lpart, s, nullptr);
-    const int rc2 = run_students(M, W, ids, cu, B, T, max_seqlen, ka, k - ka, false, stop_layers, true, w, lpart + n, M->aux,
-                                 nullptr);
+    int rc = run_students(M, W, ids, cu, B, T, max_seqlen, 0, ka, k, false, stop_layers, true, w, lpart, s, nullptr);
+    const int rc2 = run_students(M, W, ids, cu, B, T, max_seqlen, ka, k - ka, k, false, stop_layers, true, w, lpart + n,
+                                 M->aux, nullptr);
     // join even after an error, so that the auxiliary stream never runs on beyond the call
     if (hipEventRecord(M->ev_join, M->aux) != hipSuccess || hipStreamWaitEvent(s, M->ev_join, 0) != hipSuccess)
         return SP_EHIP;

@@ -104,3 +104,27 @@ def test_nothing_in_the_workspace_has_to_be_finite(oracle64, hidden, ffn, layers
     err = np.abs(got - want).max() / max(np.abs(want).max(), 1e-3)
     assert err <= 3e-2, f"{err:.3e}"
     st.close()
+
+
+# (hidden, students, sequences of 60 tokens): the first-token rows of all students are beyond the fused LayerNorm's limit, those
+# of one group are not
+@pytest.mark.parametrize("hidden,K,nseq", [(768, 3, 140), (768, 2, 200), (1024, 4, 138)])
+@pytest.mark.parametrize("dtype", ["bf16", "fp8"])
+def test_one_group_of_students_or_two_give_the_same_bits(hidden, K, nseq, dtype):
+    """Which kernel takes the first-token rows goes by the call, not by the group of students it runs for: logits of a large call
+    are the same bits on one stream and on two, for every number of active students."""
+    from paper_2408_12526_amd import sp
+    shape = synth.StudentShape(K=K, layers=2, hidden=hidden, heads=hidden // 64, ffn=1024, vocab=500, max_pos=64, classes=4, dtype=dtype)
+    rng = np.random.default_rng(hidden + K)
+    lengths = np.full(nseq, 60, dtype=np.int32)
+    ids = torch.from_numpy(synth.make_ids(rng, int(lengths.sum()), shape.vocab)).cuda()
+    assert ids.numel() >= 8192
+    cu = torch.from_numpy(sp.sp_pack(lengths)).cuda()
+    blob = synth.make_weights(rng, shape, std=0.04, ln_random=True)
+    two = sp.Students(sp.config_from_shape(shape), blob)
+    one = sp.Students(sp.config_from_shape(shape, single_stream=True), blob)
+    for k in range(2, K + 1):
+        a, b = two.sp_forward(ids, cu, 60, k), one.sp_forward(ids, cu, 60, k)
+        assert torch.equal(a, b), f"k_active {k}: {(a - b).abs().max().item():.3e}"
+    two.close()
+    one.close()
