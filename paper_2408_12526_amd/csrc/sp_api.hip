@@ -105,10 +105,9 @@ WsLayout make_ws_layout(const sp_config& c, int total_tokens, int batch)
     // compact buffers for the first-token rows of the last layer (never used by calls of fewer than
     // kFirstOnlyMinTokens tokens: those get none)
     const size_t crows = total_tokens >= kFirstOnlyMinTokens ? align_up((size_t)batch, kRowPad) : 0;
-    W.cx = take(K * crows * H * ab);
+    W.cu0 = take(K * crows * H * 2 * ab);
     W.cq = take(K * crows * H * ab);
     W.catt = take(K * crows * H * ab);
-    W.cu_ = take(K * crows * H * ab);
     W.cx1 = take(K * crows * H * ab);
     W.cg = take(K * crows * F * ab);
     W.cqt = take(K * crows * (size_t)c.heads * H * ab);
@@ -323,10 +322,14 @@ static int run_students(const sp_model* M0, const WsLayout& W, const int32_t* id
                             (T >= kFirstOnlyMinTokens ||
                              ((size_t)B * c.heads <= (size_t)3 * rows && (size_t)B * c.heads * H <= (size_t)rows * F));
     const int crows = W.crows;
-    // fp32 rows of the few-row projections: four regions of 256 rows per student
-    const size_t u_ss = (size_t)kRowsU * H;
-    float* uo = (float*)(w + W.part) + (size_t)m0 * u_ss;   // after the attention-output projection
-    float *ud = uo + (size_t)256 * H, *pooled = uo + (size_t)512 * H;   // after the FFN; pooled first-token rows
+    // fp32 rows of the few-row projections: after the attention-output projection, after the FFN, pooled.  Calls of up to
+    // kRowsMaxTokens tokens: regions of kRowsMaxTokens rows of the scratch.  The folded last layer has as many rows as
+    // sequences: the first rows in its own buffer (fewer than kFirstOnlyMinTokens tokens: the scratch, which holds that many
+    // rows), the second over the folded queries, which nobody reads any more, and the pooled ones over the first.
+    struct FirstRows { float *o, *d, *pooled; size_t o_ss, d_ss; };
+    float* const part = (float*)(w + W.part) + (size_t)m0 * kRowsU * H;
+    const size_t part_ss = (size_t)kRowsU * H;
+    const FirstRows small{part, part + (size_t)kRowsMaxTokens * H, part + (size_t)2 * kRowsMaxTokens * H, part_ss, part_ss};
     // Projection onto the hidden width, residual and LayerNorm of the T token rows (bf16): out = LN(A W^T + b + res).  A launch
     // of fewer than a tile per compute unit splits the reduction range over workgroups; the fp32 slices go into the buffers
     // that are free at that point (q|k|v and values, and behind them the attention output and the pre-LayerNorm rows once
@@ -358,9 +361,10 @@ static int run_students(const sp_model* M0, const WsLayout& W, const int32_t* id
         SP_MARK(SP_PHASE_LAYERNORM);
         return SP_OK;
     };
-    // g = gelu(LN(uo; ln1) W1^T + b1) of n rows: fused while the rows of all students are few, else a LayerNorm launch and
+    // g = gelu(LN(u; ln1) W1^T + b1) of n rows: fused while the rows of all students are few, else a LayerNorm launch and
     // the tile kernel
-    auto ffn_up = [&](size_t lo, int n, void* x1r, size_t x1_ss, void* gr, size_t g_ss, bool packed) -> hipError_t {
+    auto ffn_up = [&](size_t lo, int n, const float* uo, size_t u_ss, void* x1r, size_t x1_ss, void* gr, size_t g_ss,
+                      bool packed) -> hipError_t {
         if ((long)n * k_call * H <= kRowsLnMaxElems)
             return launch_rows_ffn_up(M, lo, uo, u_ss, n, x1r, x1_ss, gr, g_ss, packed ? packed_layout(F) : rows_layout(F), k, s);
         const hipError_t e = launch_rows_ln_out(M, lo + L.ln1g, lo + L.ln1b, uo, u_ss, x1r, x1_ss, n, k, s);
@@ -368,28 +372,27 @@ static int run_students(const sp_model* M0, const WsLayout& W, const int32_t* id
         return launch_gemm(M, x1r, H, lo + L.w1, lo + L.b1, gr, F, nullptr, 0, (n + 63) / 64 * 64, F, H, k, EPI_BIAS_GELU,
                            x1_ss * ab, g_ss * ab, 0, s, nullptr, 0, 0, 0, packed);
     };
-    // Last layer of n sequences (at most kRowsMaxSeqs) from sequence b0 on, from the attention output of their first tokens:
-    // A holds token rows (a_first) or one row per sequence; x1c and gc are scratch of one row per sequence.  ss: student
-    // strides, elements.
-    auto first_rows_tail = [&](size_t lo, int b0, int n, const bf16* A, size_t a_ss, bool a_first, bf16* x1c, size_t x1c_ss,
+    // Last layer from the attention output of the first tokens: A holds token rows (a_first) or one row per sequence; x1c and gc
+    // are scratch of one row per sequence.  ss: student strides, elements.
+    auto first_rows_tail = [&](size_t lo, const FirstRows& f, const bf16* A, size_t a_ss, bool a_first, bf16* x1c, size_t x1c_ss,
                                bf16* gc, size_t gc_ss) -> int {
         const size_t sT = (size_t)rows * H;
-        SP_TRY(launch_rows_residual(M, lo + L.wo, lo + L.bo, A, a_ss, rows_layout(H), H, a_first, (const bf16*)x, sT, true, uo,
-                                    u_ss, cu + b0, T, n, k, s));
+        SP_TRY(launch_rows_residual(M, lo + L.wo, lo + L.bo, A, a_ss, rows_layout(H), H, a_first, (const bf16*)x, sT, true, f.o,
+                                    f.o_ss, cu, T, B, k, s));
         SP_MARK(SP_PHASE_LAST_FIRST);
-        SP_TRY(ffn_up(lo, n, x1c, x1c_ss, gc, gc_ss, true));
+        SP_TRY(ffn_up(lo, B, f.o, f.o_ss, x1c, x1c_ss, gc, gc_ss, true));
         SP_MARK(SP_PHASE_LAST_FIRST);
-        SP_TRY(launch_rows_residual(M, lo + L.w2, lo + L.b2, gc, gc_ss, packed_layout(F), F, false, x1c, x1c_ss, false, ud,
-                                    u_ss, cu + b0, T, n, k, s));
+        SP_TRY(launch_rows_residual(M, lo + L.w2, lo + L.b2, gc, gc_ss, packed_layout(F), F, false, x1c, x1c_ss, false, f.d,
+                                    f.d_ss, cu, T, B, k, s));
         SP_MARK(SP_PHASE_LAST_FIRST);
-        SP_TRY(launch_rows_pooler(M, lo, ud, u_ss, n, pooled, u_ss, k, s));
-        SP_TRY(launch_head_classify(M, pooled, n, B, kRowsU, k, z + (size_t)b0 * c.classes,
-                                    logits ? logits + (size_t)b0 * c.classes : nullptr, s));
+        SP_TRY(launch_rows_pooler(M, lo, f.d, f.d_ss, B, f.pooled, f.o_ss, k, s));
+        SP_TRY(launch_head_classify(M, f.pooled, f.o_ss, B, k, z, logits, s));
         SP_MARK(SP_PHASE_HEAD);
         return SP_OK;
     };
     if (bf16_path(c) && T <= kRowsMaxTokens) {
-        const size_t sT = (size_t)rows * H, sG = (size_t)rows * F;
+        const size_t sT = (size_t)rows * H, sG = (size_t)rows * F, u_ss = part_ss;
+        float *uo = small.o, *ud = small.d;
         // Many rows over all students: the tile kernel with a split reduction for the two projections onto the hidden width as
         // well (hidden 768, 960 rows, us for both projections of a layer and their LayerNorms: 31.4 against 34.7; 352 rows 22.6
         // against 23.1; hidden 1024, 768 rows: 43.4 against 50.9)
@@ -417,7 +420,7 @@ static int run_students(const sp_model* M0, const WsLayout& W, const int32_t* id
             if (with_head && !c.last_layer_all_tokens && l == c.layers - 1) {
                 SP_TRY(launch_attention_first(M, qkv, vt, att, cu, B, T, max_seqlen, rows, k, s));
                 SP_MARK(SP_PHASE_LAST_FIRST);
-                return first_rows_tail(lo, 0, B, (const bf16*)att, sT, true, (bf16*)x1, sT, (bf16*)g, sG);
+                return first_rows_tail(lo, small, (const bf16*)att, sT, true, (bf16*)x1, sT, (bf16*)g, sG);
             }
             SP_TRY(launch_attention(M, qkv, vt, att, cu, B, T, max_seqlen, rows, k, s));
             SP_MARK(SP_PHASE_ATTENTION);
@@ -433,7 +436,7 @@ static int run_students(const sp_model* M0, const WsLayout& W, const int32_t* id
             SP_TRY(launch_rows_residual(M, lo + L.wo, lo + L.bo, (const bf16*)att, sT, rows_layout(H), H, false,
                                         (const bf16*)x, sT, false, uo, u_ss, cu, T, T, k, s));
             SP_MARK(SP_PHASE_OPROJ);
-            SP_TRY(ffn_up(lo, T, x1, sT, g, sG, with_head));
+            SP_TRY(ffn_up(lo, T, uo, u_ss, x1, sT, g, sG, with_head));
             SP_MARK(SP_PHASE_FFN_UP);
             SP_TRY(launch_rows_residual(M, lo + L.w2, lo + L.b2, (const bf16*)g, sG, gl, F, false, (const bf16*)x1, sT, false,
                                         ud, u_ss, cu, T, T, k, s));
@@ -457,7 +460,7 @@ static int run_students(const sp_model* M0, const WsLayout& W, const int32_t* id
         const size_t lo = L.layer0 + (size_t)l * L.layer_stride;
         if (first_only && l == c.layers - 1) {
             const bool own = T >= kFirstOnlyMinTokens;
-            const size_t sT = (size_t)rows * H, sC = (size_t)crows * H, hH = (size_t)c.heads * H;
+            const size_t sT = (size_t)rows * H, sC = (size_t)crows * H;
             const size_t s1 = own ? sC : sT, sq = own ? sC * c.heads : 3 * sT, sx = own ? sC * c.heads : (size_t)rows * F;
             const size_t sg = (size_t)(own ? crows : rows) * F;
             bf16* q1 = own ? (bf16*)(w + W.cq) + m0 * sC : (bf16*)vt;
@@ -466,20 +469,15 @@ static int run_students(const sp_model* M0, const WsLayout& W, const int32_t* id
             bf16* xb1 = own ? (bf16*)(w + W.cxb) + m0 * sx : (bf16*)g;
             bf16* x11 = own ? (bf16*)(w + W.cx1) + m0 * sC : (bf16*)x1;
             bf16* g1 = own ? (bf16*)(w + W.cg) + m0 * sg : (bf16*)g;
-            for (int b0 = 0; b0 < B; b0 += kRowsMaxSeqs) {
-                const int n = B - b0 < kRowsMaxSeqs ? B - b0 : kRowsMaxSeqs;
-                SP_TRY(launch_fold_query(M, lo, x, rows, cu + b0, T, n, q1 + (size_t)b0 * H, s1, qt1 + b0 * hH, sq, k, s));
-                SP_MARK(SP_PHASE_LAST_FIRST);
-                SP_TRY(launch_attention_first_fold(M, x, qt1 + b0 * hH, sq, xb1 + b0 * hH, sx, cu + b0, n, T, max_seqlen, rows,
-                                                   k, s));
-                SP_MARK(SP_PHASE_LAST_FIRST);
-                SP_TRY(launch_rows_head_values(M, lo, xb1 + b0 * hH, sx, att1 + (size_t)b0 * H, s1, n, k, s));
-                SP_MARK(SP_PHASE_LAST_FIRST);
-                const int rc = first_rows_tail(lo, b0, n, att1 + (size_t)b0 * H, s1, false, x11 + (size_t)b0 * H, s1,
-                                               g1 + (size_t)b0 * F, sg);
-                if (rc != SP_OK) return rc;
-            }
-            return SP_OK;
+            const FirstRows f = own ? FirstRows{(float*)(w + W.cu0) + m0 * sC, (float*)qt1, (float*)(w + W.cu0) + m0 * sC, sC, sq / 2}
+                                    : FirstRows{part, (float*)qt1, part, part_ss, sq / 2};
+            SP_TRY(launch_fold_query(M, lo, x, rows, cu, T, B, q1, s1, qt1, sq, k, s));
+            SP_MARK(SP_PHASE_LAST_FIRST);
+            SP_TRY(launch_attention_first_fold(M, x, qt1, sq, xb1, sx, cu, B, T, max_seqlen, rows, k, s));
+            SP_MARK(SP_PHASE_LAST_FIRST);
+            SP_TRY(launch_rows_head_values(M, lo, xb1, sx, att1, s1, B, k, s));
+            SP_MARK(SP_PHASE_LAST_FIRST);
+            return first_rows_tail(lo, f, att1, s1, false, x11, s1, g1, sg);
         }
         if (fp8)
             SP_TRY(launch_gemm_fp8(M, xq, H, lo + L.wqkv8, lo + L.sqkv, lo + L.bqkv, kActQuantScale, qkv, 3 * H, nullptr, 0,

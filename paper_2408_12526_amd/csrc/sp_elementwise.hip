@@ -447,8 +447,8 @@ __global__ void sum_students_kernel(const float* __restrict__ z, int n, int k, f
 // (a pass per class, a chain of dependent iterations each, took 11.6 us for one sequence and eight students).
 template <int CB>
 __global__ __launch_bounds__(256) void head_classify_kernel(const char* arena, size_t student_stride, size_t wc_off,
-                                                            size_t bc_off, const float* __restrict__ pooled, int zrows,
-                                                            int prows, int H, int C, int k, float* __restrict__ z,
+                                                            size_t bc_off, const float* __restrict__ pooled, size_t p_ss,
+                                                            int B, int H, int C, int k, float* __restrict__ z,
                                                             float* __restrict__ logits)
 {
     __shared__ float zs[64][16];                 // [student][class]
@@ -456,7 +456,7 @@ __global__ __launch_bounds__(256) void head_classify_kernel(const char* arena, s
     for (int m = wave; m < k; m += 4) {
         const char* sb = arena + (size_t)m * student_stride;
         const bf16* Wc = (const bf16*)(sb + wc_off);
-        const float* p = pooled + ((size_t)m * prows + b) * H;
+        const float* p = pooled + (size_t)m * p_ss + (size_t)b * H;
         for (int c0 = 0; c0 < C; c0 += CB) {
             float pv[16];
             bf16 wv[16][CB];
@@ -477,7 +477,7 @@ __global__ __launch_bounds__(256) void head_classify_kernel(const char* arena, s
                 if (lane == 0 && c0 + c < C) {
                     const float v = acc[c] + ((const float*)(sb + bc_off))[c0 + c];
                     zs[m][c0 + c] = v;
-                    z[((size_t)m * zrows + b) * C + c0 + c] = v;
+                    z[((size_t)m * B + b) * C + c0 + c] = v;
                 }
             }
         }
@@ -492,14 +492,14 @@ __global__ __launch_bounds__(256) void head_classify_kernel(const char* arena, s
 
 }  // namespace
 
-hipError_t launch_head_classify(const sp_model* M, const float* pooled, int n, int zrows, int prows, int k, float* z,
-                                float* logits, hipStream_t s)
+hipError_t launch_head_classify(const sp_model* M, const float* pooled, size_t p_ss, int B, int k, float* z, float* logits,
+                                hipStream_t s)
 {
     const sp_config& c = M->cfg;
     if (!bf16_path(c) || k > 64 || c.hidden > 1024 || c.hidden % 64) return hipErrorInvalidValue;
 #define SP_CLASSIFY(CB)                                                                                             \
-    hipLaunchKernelGGL(head_classify_kernel<CB>, dim3((unsigned)n), dim3(256), 0, s, M->arena, M->L.student_stride, M->L.wc, \
-                       M->L.bc, pooled, zrows, prows, c.hidden, c.classes, k, z, logits)
+    hipLaunchKernelGGL(head_classify_kernel<CB>, dim3((unsigned)B), dim3(256), 0, s, M->arena, M->L.student_stride, M->L.wc, \
+                       M->L.bc, pooled, p_ss, B, c.hidden, c.classes, k, z, logits)
     if (c.classes <= 2) SP_CLASSIFY(2); else SP_CLASSIFY(4);
 #undef SP_CLASSIFY
     return hipGetLastError();

@@ -142,12 +142,11 @@ __device__ inline void barrier_lds()
 
 constexpr int kRowPad = 256;  // activation rows per student are padded to a multiple of this
 constexpr int kRowsMaxTokens = 256;   // largest call whose all-token layers run on the few-row projections
-constexpr int kRowsMaxSeqs = 256;     // most sequences whose first-token rows do
 // Most elements (rows of all students x hidden width) that the fused LayerNorm + projection kernels take: every workgroup
 // repeats the statistics of its rows, and beyond this a LayerNorm launch and the tile kernel are faster (hidden 768: 256 rows
 // 35.4 us for a layer's embedding, q|k|v and FFN up against 38, 352 rows 40 against 38; hidden 256: 528 rows 17.5 against 26).
 constexpr long kRowsLnMaxElems = 262144;
-constexpr int kRowsU = 1024;          // fp32 rows per student of the few-row projections' scratch (four regions of 256)
+constexpr int kRowsU = 1024;          // fp32 rows per student of the few-row projections' scratch
 constexpr int kFirstOnlyMinTokens = 1024;   // smallest call whose first-token rows have buffers of their own
 // fp8 projections: activations are quantised as e4m3(value * kActQuantScale) by the kernel that produces them
 // (LayerNorm outputs and GELU outputs are of order one: 448 / 16 = 28 before saturation, 2^-6 / 16 = 1e-3 before the
@@ -179,7 +178,7 @@ ArenaLayout make_arena_layout(const sp_config& c);
 // Workspace carve-up for one call.
 struct WsLayout {
     size_t x, qkv, vt, att, u, x1, g, z, zpart, end;
-    size_t cx, cq, catt, cu_, cx1, cg;   // first-token rows only: [K][crows][H] (cg: [F]), last layer
+    size_t cu0, cq, catt, cx1, cg;       // first-token rows only: [K][crows][H] (cu0: fp32; cg: [F]), last layer
     size_t cqt, cxb;                     // folded queries / weighted mean rows: [K][crows][heads][H]
     size_t part;                         // fp32 rows between the few-row projections: [K][kRowsU][H]
     size_t lpart;                        // per-group logit sums when two groups of students run side by side: [2][B][C]
@@ -312,10 +311,10 @@ hipError_t launch_attention_first_fold(const sp_model* M, const void* x, const v
                                        size_t xb_ss, const int32_t* cu, int B, int T, int max_seqlen, int rows, int k,
                                        hipStream_t s);
 
-// Head on fp32 pooled rows of n sequences: z[m][b][c] = pooled[m][b] . Wc + bc; logits[b][c] = sum_{m<k} z[m][b][c] (m
-// ascending; not written if null).  Student strides: prows pooled rows, zrows rows of z.
-hipError_t launch_head_classify(const sp_model* M, const float* pooled, int n, int zrows, int prows, int k, float* z,
-                                float* logits, hipStream_t s);
+// Head on fp32 pooled rows (p_ss: elements from student to student): z[m][b][c] = pooled[m][b] . Wc + bc; logits[b][c] =
+// sum_{m<k} z[m][b][c] (m ascending; not written if null).
+hipError_t launch_head_classify(const sp_model* M, const float* pooled, size_t p_ss, int B, int k, float* z, float* logits,
+                                hipStream_t s);
 
 // flags[0] |= SP_BAD_* bits for the inputs of a forward (flags[0] is cleared first, on the same stream).
 hipError_t launch_check_inputs(const int32_t* ids, const int32_t* cu, int B, int T, int max_seqlen, int vocab,
