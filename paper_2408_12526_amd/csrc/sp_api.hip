@@ -390,6 +390,26 @@ static int run_students(const sp_model* M0, const WsLayout& W, const int32_t* id
         SP_MARK(SP_PHASE_HEAD);
         return SP_OK;
     };
+    // The same from one row per sequence where the rows are many: the tile kernels, whose bare sums the LayerNorm launches
+    // (and the classifier) finish.  xf: scratch like x1c.  Rows behind the last sequence are computed and never read.
+    auto first_rows_tail_tiles = [&](size_t lo, const FirstRows& f, const bf16* A, size_t a_ss, bf16* x1c, size_t x1c_ss, bf16* gc,
+                                     size_t gc_ss, bf16* xf, size_t xf_ss) -> int {
+        const int mr = (B + 63) / 64 * 64;
+        SP_TRY(launch_gemm_split(M, A, H, lo + L.wo, f.o, 0, mr, H, H, k, 1, a_ss * ab, f.o_ss, s));
+        SP_TRY(launch_rows_ln_add(M, lo + L.ln1g, lo + L.ln1b, f.o, f.o_ss, lo + L.bo, x, (size_t)rows * H, cu, T, x1c, x1c_ss, B, k,
+                                  s));
+        SP_MARK(SP_PHASE_LAST_FIRST);
+        SP_TRY(launch_gemm(M, x1c, H, lo + L.w1, lo + L.b1, gc, F, nullptr, 0, mr, F, H, k, EPI_BIAS_GELU, x1c_ss * ab, gc_ss * ab,
+                           0, s));
+        SP_MARK(SP_PHASE_LAST_FIRST);
+        SP_TRY(launch_gemm_split(M, gc, F, lo + L.w2, f.d, 0, mr, H, F, k, 1, gc_ss * ab, f.d_ss, s));
+        SP_TRY(launch_rows_ln_add(M, lo + L.ln2g, lo + L.ln2b, f.d, f.d_ss, lo + L.b2, x1c, x1c_ss, nullptr, T, xf, xf_ss, B, k, s));
+        SP_MARK(SP_PHASE_LAST_FIRST);
+        SP_TRY(launch_gemm_split(M, xf, H, L.wp_t, f.pooled, 0, mr, H, H, k, 1, xf_ss * ab, f.o_ss, s));
+        SP_TRY(launch_head_classify(M, f.pooled, f.o_ss, B, k, z, logits, s, true));
+        SP_MARK(SP_PHASE_HEAD);
+        return SP_OK;
+    };
     if (bf16_path(c) && T <= kRowsMaxTokens) {
         const size_t sT = (size_t)rows * H, sG = (size_t)rows * F, u_ss = part_ss;
         float *uo = small.o, *ud = small.d;
@@ -477,6 +497,8 @@ static int run_students(const sp_model* M0, const WsLayout& W, const int32_t* id
             SP_MARK(SP_PHASE_LAST_FIRST);
             SP_TRY(launch_rows_head_values(M, lo, xb1, sx, att1, s1, B, k, s));
             SP_MARK(SP_PHASE_LAST_FIRST);
+            if (own && (long)B * k_call * H > kRowsTilesElems)
+                return first_rows_tail_tiles(lo, f, att1, s1, x11, s1, g1, sg, xb1, sx);
             return first_rows_tail(lo, f, att1, s1, false, x11, s1, g1, sg);
         }
         if (fp8)

@@ -445,9 +445,10 @@ __global__ void sum_students_kernel(const float* __restrict__ z, int n, int k, f
 // Classifier on pooled rows and the cross-student sum: one workgroup per sequence, wave w takes students w, w + 4, ...
 // One pass over the row for CB classes at a time and all its loads requested together: a student is one memory round trip
 // (a pass per class, a chain of dependent iterations each, took 11.6 us for one sequence and eight students).
-template <int CB>
+// BARE: the rows are the pooler's sums, bias and tanh are applied here.
+template <int CB, bool BARE>
 __global__ __launch_bounds__(256) void head_classify_kernel(const char* arena, size_t student_stride, size_t wc_off,
-                                                            size_t bc_off, const float* __restrict__ pooled, size_t p_ss,
+                                                            size_t bc_off, size_t bp_off, const float* __restrict__ pooled, size_t p_ss,
                                                             int B, int H, int C, int k, float* __restrict__ z,
                                                             float* __restrict__ logits)
 {
@@ -464,6 +465,7 @@ __global__ __launch_bounds__(256) void head_classify_kernel(const char* arena, s
             for (int i = 0; i < 16; ++i) {       // hidden <= 1024, a multiple of 64; pieces beyond it count as zero
                 const int n = lane + (64 * i < H ? 64 * i : 0);
                 pv[i] = p[n];
+                if (BARE) pv[i] = tanhf(pv[i] + ((const float*)(sb + bp_off))[n]);
 #pragma unroll
                 for (int c = 0; c < CB; ++c) wv[i][c] = Wc[(size_t)n * C + (c0 + c < C ? c0 + c : C - 1)];
             }
@@ -493,14 +495,15 @@ __global__ __launch_bounds__(256) void head_classify_kernel(const char* arena, s
 }  // namespace
 
 hipError_t launch_head_classify(const sp_model* M, const float* pooled, size_t p_ss, int B, int k, float* z, float* logits,
-                                hipStream_t s)
+                                hipStream_t s, bool bare)
 {
     const sp_config& c = M->cfg;
     if (!bf16_path(c) || k > 64 || c.hidden > 1024 || c.hidden % 64) return hipErrorInvalidValue;
-#define SP_CLASSIFY(CB)                                                                                             \
-    hipLaunchKernelGGL(head_classify_kernel<CB>, dim3((unsigned)B), dim3(256), 0, s, M->arena, M->L.student_stride, M->L.wc, \
-                       M->L.bc, pooled, p_ss, B, c.hidden, c.classes, k, z, logits)
-    if (c.classes <= 2) SP_CLASSIFY(2); else SP_CLASSIFY(4);
+#define SP_CLASSIFY(CB, BARE)                                                                                       \
+    hipLaunchKernelGGL((head_classify_kernel<CB, BARE>), dim3((unsigned)B), dim3(256), 0, s, M->arena, M->L.student_stride, \
+                       M->L.wc, M->L.bc, M->L.bp, pooled, p_ss, B, c.hidden, c.classes, k, z, logits)
+    if (bare) { if (c.classes <= 2) SP_CLASSIFY(2, true); else SP_CLASSIFY(4, true); }
+    else { if (c.classes <= 2) SP_CLASSIFY(2, false); else SP_CLASSIFY(4, false); }
 #undef SP_CLASSIFY
     return hipGetLastError();
 }

@@ -146,6 +146,11 @@ constexpr int kRowsMaxTokens = 256;   // largest call whose all-token layers run
 // repeats the statistics of its rows, and beyond this a LayerNorm launch and the tile kernel are faster (hidden 768: 256 rows
 // 35.4 us for a layer's embedding, q|k|v and FFN up against 38, 352 rows 40 against 38; hidden 256: 528 rows 17.5 against 26).
 constexpr long kRowsLnMaxElems = 262144;
+// First-token rows (elements as above) beyond which all their projections take the tile kernel, whose bare sums the LayerNorm
+// launches finish.  Measured, us for the two residual projections, the FFN up-projection, pooler and classifier, few-row kernels
+// against this: hidden 768: 2048 rows 108 / 113, 4096 rows 183 / 141, 8192 rows 349 / 221; hidden 1024, 1536 rows: 124 / 126;
+// hidden 256: 3072 rows 51 / 60, 12288 rows 115 / 110.
+constexpr long kRowsTilesElems = 1L << 21;
 constexpr int kRowsU = 1024;          // fp32 rows per student of the few-row projections' scratch
 constexpr int kFirstOnlyMinTokens = 1024;   // smallest call whose first-token rows have buffers of their own
 // fp8 projections: activations are quantised as e4m3(value * kActQuantScale) by the kernel that produces them
@@ -290,6 +295,11 @@ hipError_t launch_attention_first(const sp_model* M, const void* qkv, const void
 hipError_t launch_rows_ln_out(const sp_model* M, size_t g_off, size_t b_off, const float* u, size_t u_ss, void* out,
                               size_t o_ss, int nrows, int k, hipStream_t s);
 
+// out = LN(u + bias + residual), bf16 rows; the residual of row r is row r of res, or row cu[r] of T (cu not null)
+hipError_t launch_rows_ln_add(const sp_model* M, size_t g_off, size_t b_off, const float* u, size_t u_ss, size_t bias_off,
+                              const void* res, size_t r_ss, const int32_t* cu, int T, void* out, size_t o_ss, int nrows, int k,
+                              hipStream_t s);
+
 // ---- fp32 path, calls of few rows (sp_rows_f32.hip): x = LN(x1 + FFN(x1)), x1 = LN(x + att Wo + bo), of T rows per student in
 // one launch, and q|k|v of the next layer from the new x (qkv_next null: there is none)
 bool f32_layer_supported(const sp_config& c, long rows_of_all_students);
@@ -312,9 +322,9 @@ hipError_t launch_attention_first_fold(const sp_model* M, const void* x, const v
                                        hipStream_t s);
 
 // Head on fp32 pooled rows (p_ss: elements from student to student): z[m][b][c] = pooled[m][b] . Wc + bc; logits[b][c] =
-// sum_{m<k} z[m][b][c] (m ascending; not written if null).
+// sum_{m<k} z[m][b][c] (m ascending; not written if null).  bare: the rows are tanh's argument without the pooler's bias.
 hipError_t launch_head_classify(const sp_model* M, const float* pooled, size_t p_ss, int B, int k, float* z, float* logits,
-                                hipStream_t s);
+                                hipStream_t s, bool bare = false);
 
 // flags[0] |= SP_BAD_* bits for the inputs of a forward (flags[0] is cleared first, on the same stream).
 hipError_t launch_check_inputs(const int32_t* ids, const int32_t* cu, int B, int T, int max_seqlen, int vocab,

@@ -580,23 +580,40 @@ __global__ __launch_bounds__(256) void attention_first_kernel(const bf16* __rest
     att[((size_t)m * rows + t0) * H + h * 64 + lane] = (bf16)(o / l);
 }
 
-// fp32 rows -> LayerNorm -> bf16 rows, one wave per row (the end of a forward that stops after an all-token layer)
-template <int MAXC>
+// fp32 rows -> LayerNorm -> bf16 rows, one wave per row.  ADD: the rows are bare sums of a projection, bias and residual are
+// added first (residual row r, or the token row cu[r]).
+struct RowsAdd {
+    size_t bias;                      // byte offset into a student slab
+    const bf16* res;
+    size_t r_ss;
+    const int32_t* cu;                // null: residual row r
+    int Tn;
+};
+template <int MAXC, bool ADD>
 __global__ __launch_bounds__(256) void rows_ln_kernel(const char* arena, size_t ss, size_t g_off, size_t b_off,
-                                                      const float* __restrict__ u, size_t u_ss, bf16* __restrict__ out,
-                                                      size_t o_ss, int M, int H, float eps)
+                                                      const float* __restrict__ u, size_t u_ss, RowsAdd add,
+                                                      bf16* __restrict__ out, size_t o_ss, int M, int H, float eps)
 {
     const int m = blockIdx.y, lane = threadIdx.x & 63, row = blockIdx.x * 4 + (threadIdx.x >> 6);
     if (row >= M) return;
     const char* sb = arena + (size_t)m * ss;
     const float* ur = u + (size_t)m * u_ss + (size_t)row * H;
+    const bf16* rr = ADD ? add.res + (size_t)m * add.r_ss + (size_t)(add.cu ? first_row(add.cu, row, add.Tn) : row) * H : nullptr;
     f32x4 v[MAXC];
     float s = 0.f;
 #pragma unroll
     for (int c = 0; c < MAXC; ++c) {
         const int e0 = 4 * (lane + 64 * c);
         v[c] = f32x4{0.f, 0.f, 0.f, 0.f};
-        if (e0 < H) v[c] = *(const f32x4*)(ur + e0);
+        if (e0 < H) {
+            v[c] = *(const f32x4*)(ur + e0);
+            if (ADD) {
+                const f32x4 b = *(const f32x4*)((const float*)(sb + add.bias) + e0);
+                const bf16x4 r = *(const bf16x4*)(rr + e0);
+#pragma unroll
+                for (int e = 0; e < 4; ++e) v[c][e] = v[c][e] + b[e] + (float)r[e];
+            }
+        }
 #pragma unroll
         for (int e = 0; e < 4; ++e) s += v[c][e];
     }
@@ -792,17 +809,34 @@ hipError_t launch_attention_first(const sp_model* M, const void* qkv, const void
     return hipGetLastError();
 }
 
-hipError_t launch_rows_ln_out(const sp_model* M, size_t g_off, size_t b_off, const float* u, size_t u_ss, void* out,
-                              size_t o_ss, int nrows, int k, hipStream_t s)
+namespace {
+template <bool ADD>
+hipError_t launch_rows_ln_any(const sp_model* M, size_t g_off, size_t b_off, const float* u, size_t u_ss, const RowsAdd& add,
+                              void* out, size_t o_ss, int nrows, int k, hipStream_t s)
 {
     const sp_config& c = M->cfg;
     if (!bf16_path(c) || nrows < 1) return hipErrorInvalidValue;
     const dim3 grid((unsigned)((nrows + 3) / 4), (unsigned)k);
-#define SP_GO(MAXC) hipLaunchKernelGGL(rows_ln_kernel<MAXC>, grid, dim3(256), 0, s, M->arena, M->L.student_stride, g_off, b_off, \
-                                       u, u_ss, (bf16*)out, o_ss, nrows, c.hidden, c.ln_eps)
+#define SP_GO(MAXC) hipLaunchKernelGGL((rows_ln_kernel<MAXC, ADD>), grid, dim3(256), 0, s, M->arena, M->L.student_stride, g_off, \
+                                       b_off, u, u_ss, add, (bf16*)out, o_ss, nrows, c.hidden, c.ln_eps)
     if (c.hidden <= 256) SP_GO(1); else SP_GO(4);
 #undef SP_GO
     return hipGetLastError();
+}
+}  // namespace
+
+hipError_t launch_rows_ln_out(const sp_model* M, size_t g_off, size_t b_off, const float* u, size_t u_ss, void* out,
+                              size_t o_ss, int nrows, int k, hipStream_t s)
+{
+    return launch_rows_ln_any<false>(M, g_off, b_off, u, u_ss, RowsAdd{}, out, o_ss, nrows, k, s);
+}
+
+hipError_t launch_rows_ln_add(const sp_model* M, size_t g_off, size_t b_off, const float* u, size_t u_ss, size_t bias_off,
+                              const void* res, size_t r_ss, const int32_t* cu, int T, void* out, size_t o_ss, int nrows, int k,
+                              hipStream_t s)
+{
+    return launch_rows_ln_any<true>(M, g_off, b_off, u, u_ss, RowsAdd{bias_off, (const bf16*)res, r_ss, cu, T}, out, o_ss, nrows,
+                                    k, s);
 }
 
 }  // namespace sp
