@@ -16,6 +16,7 @@
 // One sequence of 64 tokens, hidden 768, one student: twelve launches, 57 us a call, where fifteen launches took 84.
 // Rounding points: operands bf16, accumulation fp32, the rows before a LayerNorm stay fp32, x, x1, g, the attention
 // output and the final hidden state are rounded to bf16.
+#include <atomic>
 #include <type_traits>
 
 #include "sp_internal.h"
@@ -377,8 +378,10 @@ __global__ __launch_bounds__(256) void rows_ksplit_kernel(RowsKArgs p)
 // weight slices (64 x H each) are requested at once, so the two products cost one memory round trip: 9-13 us for four
 // students and up to 32 sequences where gathering the rows and two launches took 22 us.  The weights fill the register file
 // of a compute unit, so a launch of more workgroups than that repeats the round trip: there a workgroup takes several blocks
-// of 16 sequences, the weights staying in its registers.  Eight students and 256 sequences: 88 us with one block each, about 40
-// with eight.
+// of 16 sequences, the weights staying in its registers.  Its token rows, a quarter per wave, go through registers into one of
+// two LDS buffers, two blocks ahead, and its results through LDS out in whole row pieces.  What bounds it then is the way of
+// rows and results through memory.  us at hidden 768, each wave fetching all rows when it needs them / this: eight students, 256
+// sequences 41 / 29; four, 1024 sequences 118 / 71; two, 4096 sequences 259 / 148.
 // A-operand row i of block j of a pair of blocks stands for feature 8 (i / 4) + 4 (j % 2) + i % 4 of the pair's 32, so
 // that a lane ends with eight neighbouring features and writes 16 bytes.
 // -------------------------------------------------------------------------------------
@@ -395,37 +398,67 @@ struct FoldQArgs {
     int Tn, M, H, heads, heads8, nrb, rpw;                  // nrb: groups of rpw blocks of 16 sequences
 };
 
-template <int NS, bool EXACT>
+constexpr int kFoldQPitch = 64 * 2 + 16;                    // bytes per staged query row
+constexpr int fold_x_pitch(int ns) { return ns * 64 + 16; } // bytes per staged token row
+constexpr int fold_o_pitch(int ns) { return ns * 16 + 16; } // bytes per row of a wave's staged output
+constexpr size_t fold_query_smem(int ns)
+{
+    return 2 * 16 * (size_t)(fold_x_pitch(ns) + kFoldQPitch) + 4 * 16 * (size_t)fold_o_pitch(ns);
+}
+
+template <int NS>
 __global__ __launch_bounds__(256) void fold_query_kernel(FoldQArgs p)
 {
-    constexpr int QP = 64 * 2 + 16;                         // bytes per staged query row
-    __shared__ __attribute__((aligned(16))) char qbuf[2][16 * QP];   // (the next block's queries do not wait for this one's readers)
+    constexpr int H = 32 * NS, XP = fold_x_pitch(NS), QP = kFoldQPitch;
+    constexpr int CPR = H / 8, NL = 4 * CPR / 64;           // 16-byte chunks of a row; chunks a lane moves (a wave: four rows)
+    constexpr int OP = fold_o_pitch(NS), CO = NS, NO = CO / 4;   // 16-byte chunks of a staged output row; chunks a lane stores
+    extern __shared__ __attribute__((aligned(16))) char fold_lds[];
+    char *const xbuf = fold_lds, *const qbuf = fold_lds + 2 * 16 * XP;
+    char* const obuf = qbuf + 2 * 16 * QP + (threadIdx.x >> 6) * 16 * OP;   // wave-private
     const int h = (int)blockIdx.x % p.heads8, rm = (int)blockIdx.x / p.heads8;
     if (h >= p.heads) return;
     const int m = rm / p.nrb, rb = (rm % p.nrb) * p.rpw * 16;
     const int re = rb + p.rpw * 16 < p.M ? rb + p.rpw * 16 : p.M;
-    const int H = EXACT ? 32 * NS : p.H, lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const int l16 = lane & 15, kg = lane >> 4;
     const char* sb = p.arena + (size_t)m * p.ss;
     const int n0 = h * 64 + wave * 16;
-    // (!EXACT: steps beyond H repeat the last one with zero weights)
-    auto at = [&](int s) { return EXACT || 32 * s < H ? 32 * s : H - 32; };
-    bf16x8 fw[NS], fx[NS];
-    auto load_x = [&](int r) {                              // the row of this lane's sequence
-        const bf16* xr = p.x + (size_t)m * p.x_ss + (size_t)first_row(p.cu, r < p.M ? r : p.M - 1, p.Tn) * H + 8 * kg;
+    const bf16* xs = p.x + (size_t)m * p.x_ss;
+    // this wave's four of a block's sixteen rows: chunk lane + 64 i of the four together (rows beyond the last sequence repeat it)
+    bf16x8 xr[2][NL];                                       // two blocks in flight: a block's set by its number's last bit
+    // (The rows' token indices come through the scalar path: vector loads would be waited for together with the stores before
+    // them, which put several microseconds between two blocks.)
+    auto load_x = [&](int r0, auto set) {
+        const auto* cu = (const __attribute__((address_space(4))) int32_t*)p.cu;
+        int t[4];
 #pragma unroll
-        for (int s = 0; s < NS; ++s) fx[s] = *(const bf16x8*)(xr + at(s));
+        for (int q = 0; q < 4; ++q) {
+            const int r = r0 + 4 * wave + q, v = cu[r < p.M ? r : p.M - 1];
+            t[q] = v < 0 ? 0 : (v >= p.Tn ? p.Tn - 1 : v);
+        }
+#pragma unroll
+        for (int i = 0; i < NL; ++i) {
+            const int c = lane + 64 * i, q = c / CPR;
+            xr[set()][i] = *(const bf16x8*)(xs + (size_t)(q == 0 ? t[0] : q == 1 ? t[1] : q == 2 ? t[2] : t[3]) * H + (c % CPR) * 8);
+        }
     };
+    auto write_x = [&](auto set) {
+#pragma unroll
+        for (int i = 0; i < NL; ++i) {
+            const int c = lane + 64 * i;
+            *(bf16x8*)(xbuf + (set() * 16 + 4 * wave + c / CPR) * XP + (c % CPR) * 16) = xr[set()][i];
+        }
+    };
+    constexpr std::integral_constant<int, 0> S0{};
+    constexpr std::integral_constant<int, 1> S1{};
+    load_x(rb, S0);
+    bf16x8 fw[NS];
     const bf16* wp = (const bf16*)(sb + p.wq) + (size_t)n0 * H + kg * 128 + l16 * 8;
 #pragma unroll
-    for (int s = 0; s < NS; ++s) {
-        fw[s] = *(const bf16x8*)(wp + 16 * at(s));
-        if (!EXACT && 32 * s >= H) fw[s] = bf16x8{};
-    }
-    load_x(rb + l16);
+    for (int s = 0; s < NS; ++s) fw[s] = *(const bf16x8*)(wp + 512 * s);
     const f32x4 bias = *(const f32x4*)((const float*)(sb + p.bq) + n0 + 4 * kg);
     // key slice: this wave's H / 4 features in pairs of 16-row blocks, two reduction steps each
-    const int hq = H >> 2, f0 = wave * hq;                  // (a multiple of 32)
+    const int f0 = wave * (H / 4);                          // (a multiple of 32)
     const int prow = 8 * (l16 >> 2) + (l16 & 3);
     // (rows prow and prow + 4 of a pair lie in the same block of sixteen)
     const bf16* kp = (const bf16*)(sb + p.wk) + (size_t)(f0 + (prow & 16)) * H + (size_t)(h * 8 + kg) * 128 + (prow & 15) * 8;
@@ -433,26 +466,38 @@ __global__ __launch_bounds__(256) void fold_query_kernel(FoldQArgs p)
 #pragma unroll
     for (int j = 0; j < NS / 2; ++j)
 #pragma unroll
-        for (int s = 0; s < 2; ++s)                         // (a pair beyond the quarter repeats the first; it is not stored)
-            fk[j][s] = *(const bf16x8*)(kp + (size_t)(EXACT || (j >> 1) * 32 < hq ? (j >> 1) * 32 : 0) * H + 32 * (j & 1) + 512 * s);
+        for (int s = 0; s < 2; ++s) fk[j][s] = *(const bf16x8*)(kp + (size_t)(j >> 1) * 32 * H + 32 * (j & 1) + 512 * s);
     __builtin_amdgcn_sched_barrier(0);
-    for (int r0 = rb, buf = 0; r0 < re; r0 += 16, buf ^= 1) {
+    write_x(S0);
+    if (rb + 16 < re) load_x(rb + 16, S1);
+    if (rb + 32 < re) load_x(rb + 32, S0);
+    barrier_lds();
+    // A block's rows are in LDS when its turn begins.  During it the next one's, two turns in flight, are put down and their
+    // registers requested again for the block two after that.  Either buffer's readers are behind a barrier by then.
+    auto block = [&](int r0, auto set, auto other) {
+        constexpr int buf = decltype(set)::value;
         const int r = r0 + l16;                             // this lane's sequence
-        f32x4 acc = bias;
+        f32x4 acc = bias, acc1 = {0.f, 0.f, 0.f, 0.f};
+        const char* xrow = xbuf + (buf * 16 + l16) * XP + 16 * kg;
 #pragma unroll
-        for (int s = 0; s < NS; ++s) acc = mfma16(fw[s], fx[s], acc);
-        __builtin_amdgcn_sched_barrier(0);
-        if (r0 + 16 < re) load_x(r + 16);                   // in flight during the exchange and the second product
+        for (int s = 0; s < NS; s += 2) {
+            acc = mfma16(fw[s], *(const bf16x8*)(xrow + 64 * s), acc);
+            acc1 = mfma16(fw[s + 1], *(const bf16x8*)(xrow + 64 * (s + 1)), acc1);
+        }
+        acc += acc1;
         bf16x4 o4;
 #pragma unroll
         for (int e = 0; e < 4; ++e) o4[e] = (bf16)acc[e];
-        *(bf16x4*)(qbuf[buf] + l16 * QP + (wave * 16 + 4 * kg) * 2) = o4;
+        *(bf16x4*)(qbuf + (buf * 16 + l16) * QP + (wave * 16 + 4 * kg) * 2) = o4;
+        if (r0 + 16 < re) {
+            write_x(other);
+            if (r0 + 48 < re) load_x(r0 + 48, other);
+        }
         if (r < p.M) *(bf16x4*)(p.q + (size_t)m * p.q_ss + (size_t)r * H + n0 + 4 * kg) = o4;
         barrier_lds();
         bf16x8 fq[2];
 #pragma unroll
-        for (int s = 0; s < 2; ++s) fq[s] = *(const bf16x8*)(qbuf[buf] + l16 * QP + (4 * s + kg) * 16);
-        bf16* dst = p.qt + (size_t)m * p.qt_ss + ((size_t)r * p.heads + h) * H + f0 + 8 * kg;
+        for (int s = 0; s < 2; ++s) fq[s] = *(const bf16x8*)(qbuf + (buf * 16 + l16) * QP + (4 * s + kg) * 16);
 #pragma unroll
         for (int j = 0; j < NS / 2; j += 2) {
             f32x4 a = {0.f, 0.f, 0.f, 0.f}, b = a;
@@ -461,8 +506,23 @@ __global__ __launch_bounds__(256) void fold_query_kernel(FoldQArgs p)
             bf16x8 o;
 #pragma unroll
             for (int e = 0; e < 4; ++e) { o[e] = (bf16)a[e]; o[4 + e] = (bf16)b[e]; }
-            if (r < p.M && (EXACT || 16 * j < hq)) *(bf16x8*)(dst + 16 * j) = o;
+            *(bf16x8*)(obuf + l16 * OP + 32 * j + 16 * kg) = o;
         }
+        __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+        __builtin_amdgcn_wave_barrier();
+#pragma unroll
+        for (int i = 0; i < NO; ++i) {
+            const int c = lane + 64 * i, ro = r0 + c / CO;
+            if (ro < p.M)
+                *(bf16x8*)(p.qt + (size_t)m * p.qt_ss + ((size_t)ro * p.heads + h) * H + f0 + (c % CO) * 8) =
+                    *(const bf16x8*)(obuf + (c / CO) * OP + (c % CO) * 16);
+        }
+        __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+        __builtin_amdgcn_wave_barrier();
+    };
+    for (int r0 = rb; r0 < re; r0 += 32) {
+        block(r0, S0, S1);
+        if (r0 + 16 < re) block(r0 + 16, S1, S0);
     }
 }
 
@@ -688,6 +748,23 @@ hipError_t launch_rows_k(RowsKArgs a, int k, hipStream_t s)
     return hipGetLastError();
 }
 
+template <int NS>
+hipError_t launch_fold(const FoldQArgs& a, int k, hipStream_t s)
+{
+    constexpr size_t smem = fold_query_smem(NS);
+    auto kern = fold_query_kernel<NS>;
+    if (smem > 48 * 1024) {
+        static std::atomic<bool> raised{false};             // per instantiation; the attribute is sticky for the process
+        if (!raised.load(std::memory_order_acquire)) {
+            const hipError_t e = hipFuncSetAttribute((const void*)kern, hipFuncAttributeMaxDynamicSharedMemorySize, (int)smem);
+            if (e != hipSuccess) return e;
+            raised.store(true, std::memory_order_release);
+        }
+    }
+    hipLaunchKernelGGL(kern, dim3((unsigned)(a.heads8 * a.nrb * k)), dim3(256), smem, s, a);
+    return hipGetLastError();
+}
+
 RowsLnArgs ln_args(const sp_model* M, size_t w, size_t b, size_t g, size_t beta)
 {
     RowsLnArgs a{};
@@ -783,14 +860,13 @@ hipError_t launch_fold_query(const sp_model* M, size_t lo, const void* x, int ro
     const int blocks = (B + 15) / 16, groups = 256 / (c.heads * k) < 1 ? 1 : 256 / (c.heads * k);
     a.rpw = (blocks + groups - 1) / groups;
     a.nrb = (blocks + a.rpw - 1) / a.rpw;
-    const dim3 grid((unsigned)(a.heads8 * a.nrb * k));
-#define SP_GO(NS, X) hipLaunchKernelGGL((fold_query_kernel<NS, X>), grid, dim3(256), 0, s, a)
-    if (a.H == 256) SP_GO(8, true);
-    else if (a.H == 768) SP_GO(24, true);
-    else if (a.H == 1024) SP_GO(32, true);
-    else SP_GO(32, false);
-#undef SP_GO
-    return hipGetLastError();
+    switch (a.H) {                                          // (the folded attention's widths)
+        case 256: return launch_fold<8>(a, k, s);
+        case 512: return launch_fold<16>(a, k, s);
+        case 768: return launch_fold<24>(a, k, s);
+        case 1024: return launch_fold<32>(a, k, s);
+        default: return hipErrorInvalidValue;
+    }
 }
 
 hipError_t launch_attention_first(const sp_model* M, const void* qkv, const void* vt, void* att, const int32_t* cu, int B,
