@@ -282,10 +282,10 @@ struct PhaseTimer {
 // The forward of students [m0, m0 + k) of the model (k >= 1), all of it enqueued on stream s.  Every buffer of the
 // workspace is sliced per student, so groups of students can run side by side on different streams.  With
 // with_head the group's z rows are written; logits (the group's own sum, in student order) only if non-null.
-// k_call: active students of the whole call.  The rules that choose between kernels of different rounding go by it and by
-// may_split, never by the group's k, so that a call has the same bits as one group and as two.
+// k_rule, may_split: what the rules that choose between kernels of different rounding go by, never the group's own k, so
+// that a call has the same bits as one group and as two.
 static int run_students(const sp_model* M0, const WsLayout& W, const int32_t* ids, const int32_t* cu, int B, int T,
-                        int max_seqlen, int m0, int k, int k_call, bool may_split, int stop_layers, bool with_head, char* w,
+                        int max_seqlen, int m0, int k, int k_rule, bool may_split, int stop_layers, bool with_head, char* w,
                         float* logits, hipStream_t s, PhaseTimer* pt)
 {
     const sp_config& c = M0->cfg;
@@ -365,7 +365,7 @@ static int run_students(const sp_model* M0, const WsLayout& W, const int32_t* id
     // the tile kernel
     auto ffn_up = [&](size_t lo, int n, const float* uo, size_t u_ss, void* x1r, size_t x1_ss, void* gr, size_t g_ss,
                       bool packed) -> hipError_t {
-        if ((long)n * k_call * H <= kRowsLnMaxElems)
+        if ((long)n * k_rule * H <= kRowsLnMaxElems)
             return launch_rows_ffn_up(M, lo, uo, u_ss, n, x1r, x1_ss, gr, g_ss, packed ? packed_layout(F) : rows_layout(F), k, s);
         const hipError_t e = launch_rows_ln_out(M, lo + L.ln1g, lo + L.ln1b, uo, u_ss, x1r, x1_ss, n, k, s);
         if (e != hipSuccess) return e;
@@ -416,7 +416,7 @@ static int run_students(const sp_model* M0, const WsLayout& W, const int32_t* id
         // Many rows over all students: the tile kernel with a split reduction for the two projections onto the hidden width as
         // well (hidden 768, 960 rows, us for both projections of a layer and their LayerNorms: 31.4 against 34.7; 352 rows 22.6
         // against 23.1; hidden 1024, 768 rows: 43.4 against 50.9)
-        const bool tiles_from_here = H % 256 == 0 && (long)T * k_call * H > 2 * kRowsLnMaxElems;
+        const bool tiles_from_here = H % 256 == 0 && (long)T * k_rule * H > 2 * kRowsLnMaxElems;
         // (the partial forwards of the tests read the FFN activations row by row)
         const RowsLayout gl = with_head ? packed_layout(F) : rows_layout(F);
         if (stop_layers == 0) {
@@ -425,7 +425,7 @@ static int run_students(const sp_model* M0, const WsLayout& W, const int32_t* id
         }
         for (int l = 0; l < stop_layers; ++l) {
             const size_t lo = L.layer0 + (size_t)l * L.layer_stride, pl = lo - L.layer_stride;
-            if ((long)T * k_call * H <= kRowsLnMaxElems) {
+            if ((long)T * k_rule * H <= kRowsLnMaxElems) {
                 SP_TRY(launch_rows_qkv(M, lo, l ? ud : nullptr, u_ss, l ? pl + L.ln2g : L.emb_g, l ? pl + L.ln2b : L.emb_b,
                                        ids, cu, B, T, x, qkv, vt, rows, k, s));
             } else {
@@ -473,7 +473,7 @@ static int run_students(const sp_model* M0, const WsLayout& W, const int32_t* id
         return SP_OK;
     }
     // (the partial forwards of the tests read the buffers between the projections)
-    const bool f32_layer = with_head && f32_layer_supported(c, (long)T * k_call);
+    const bool f32_layer = with_head && f32_layer_supported(c, (long)T * k_rule);
     SP_TRY(launch_embed_ln(M, ids, cu, B, T, rows, mrows, k, x, att, s, xq, kActQuantScale, attq));
     SP_MARK(SP_PHASE_EMBED);
     for (int l = 0; l < stop_layers; ++l) {
@@ -497,7 +497,7 @@ static int run_students(const sp_model* M0, const WsLayout& W, const int32_t* id
             SP_MARK(SP_PHASE_LAST_FIRST);
             SP_TRY(launch_rows_head_values(M, lo, xb1, sx, att1, s1, B, k, s));
             SP_MARK(SP_PHASE_LAST_FIRST);
-            if (own && (long)B * k_call * H > kRowsTilesElems)
+            if (own && (long)B * k_rule * H > kRowsTilesElems)
                 return first_rows_tail_tiles(lo, f, att1, s1, x11, s1, g1, sg, xb1, sx);
             return first_rows_tail(lo, f, att1, s1, false, x11, s1, g1, sg);
         }
@@ -591,18 +591,18 @@ static int run_forward(const sp_model* M, const int32_t* ids, const int32_t* cu,
     char* w = (char*)ws;
 
     const bool large = k >= 2 && T >= two_groups_min_tokens();
+    const int ka = (k + 1) / 2, k_rule = large ? ka : k;    // (students of the larger group)
     const bool two_groups = with_head && !pt && large && !c.single_stream && M->aux;
     if (!two_groups)
-        return run_students(M, W, ids, cu, B, T, max_seqlen, 0, k, k, !large, stop_layers, with_head, w, logits, s, pt);
+        return run_students(M, W, ids, cu, B, T, max_seqlen, 0, k, k_rule, !large, stop_layers, with_head, w, logits, s, pt);
 
-    const int ka = (k + 1) / 2;
     float* lpart = (float*)(w + W.lpart);
     const size_t n = (size_t)B * c.classes;
     std::lock_guard<std::mutex> hold(*M->mu);       // one fork/join at a time on the model's stream and events
     if (hipEventRecord(M->ev_fork, s) != hipSuccess || hipStreamWaitEvent(M->aux, M->ev_fork, 0) != hipSuccess)
         return SP_EHIP;
-    int rc = run_students(M, W, ids, cu, B, T, max_seqlen, 0, ka, k, false, stop_layers, true, w, lpart, s, nullptr);
-    const int rc2 = run_students(M, W, ids, cu, B, T, max_seqlen, ka, k - ka, k, false, stop_layers, true, w, lpart + n,
+    int rc = run_students(M, W, ids, cu, B, T, max_seqlen, 0, ka, k_rule, false, stop_layers, true, w, lpart, s, nullptr);
+    const int rc2 = run_students(M, W, ids, cu, B, T, max_seqlen, ka, k - ka, k_rule, false, stop_layers, true, w, lpart + n,
                                  M->aux, nullptr);
     // join even after an error, so that the auxiliary stream never runs on beyond the call
     if (hipEventRecord(M->ev_join, M->aux) != hipSuccess || hipStreamWaitEvent(s, M->ev_join, 0) != hipSuccess)
