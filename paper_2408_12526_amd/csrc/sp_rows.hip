@@ -69,23 +69,23 @@ struct RowsLnArgs {
 enum RowsPrologue { PRO_LN = 0, PRO_EMBED = 1 };
 
 // (No branches between the loads: behind one, the compiler waits for everything in flight at the first use.)
-template <int PRO, int EPI, int NS, bool EXACT>
+template <int PRO, int EPI, int NS>
 __global__ __launch_bounds__(256) void rows_ln_gemm_kernel(RowsLnArgs p)
 {
-    constexpr int NC = NS / 8;                              // chunks of four elements per lane and row
+    constexpr int H = 32 * NS, NC = (NS + 7) / 8;           // NC: chunks of four elements per lane and row
     constexpr int PITCH = NS * 64 + 16;                     // bytes per LDS row: sixteen rows, one chunk: 16 bank groups
     constexpr int RW = 4;                                   // rows a wave normalises
     __shared__ __attribute__((aligned(16))) char rowbuf[16 * PITCH];
     const int fb = (int)blockIdx.x % p.nfb8, rm = (int)blockIdx.x / p.nfb8;
     if (fb >= p.nfb) return;
     const int m = rm / p.nrb, r0 = (rm % p.nrb) * 16;
-    const int H = EXACT ? 32 * NS : p.H, lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const int l16 = lane & 15, kg = lane >> 4;
     const char* sb = p.arena + (size_t)m * p.ss;
     const int n0 = fb * 64 + wave * 16;
-    // element of chunk c of a row for this lane; chunks beyond H (!EXACT) repeat the last one and count as zero
-    auto el = [&](int c) { const int e = 4 * (lane + 64 * c); return EXACT || e < H ? e : H - 4; };
-    auto in_row = [&](int c) { return EXACT || 4 * (lane + 64 * c) < H; };
+    // element of chunk c of a row for this lane; chunks beyond H (its last half chunk of 128) repeat the last one and do not count
+    auto in_row = [&](int c) { return 256 * (c + 1) <= H || 4 * (lane + 64 * c) < H; };
+    auto el = [&](int c) { return in_row(c) ? 4 * (lane + 64 * c) : H - 4; };
     // rows beyond M repeat the last one; what comes of them is written where no result looks
     auto row_of = [&](int r) { return r < p.M ? r : p.M - 1; };
 
@@ -139,7 +139,7 @@ __global__ __launch_bounds__(256) void rows_ln_gemm_kernel(RowsLnArgs p)
     {
         const bf16* wp = (const bf16*)(sb + p.w) + (size_t)n0 * H + kg * 128 + l16 * 8;
 #pragma unroll
-        for (int s = 0; s < NS; ++s) fw[s] = *(const bf16x8*)(wp + 16 * (EXACT || 32 * s < H ? 32 * s : H - 32));
+        for (int s = 0; s < NS; ++s) fw[s] = *(const bf16x8*)(wp + 512 * s);
     }
     const bool transposed = EPI == EPI_QKV && fb * 64 >= p.n_split;    // (uniform: n_split is a multiple of 64)
     f32x4 acc;
@@ -188,8 +188,8 @@ __global__ __launch_bounds__(256) void rows_ln_gemm_kernel(RowsLnArgs p)
         for (int c = 0; c < NC; ++c) {
             bf16x4 o;
 #pragma unroll
-            for (int e = 0; e < 4; ++e) o[e] = (bf16)(in_row(c) ? gg[c][e] * ((v[i][c][e] - mean[i]) * inv[i]) + bb[c][e] : 0.f);
-            *(bf16x4*)(rowbuf + (wave * RW + i) * PITCH + 8 * (lane + 64 * c)) = o;
+            for (int e = 0; e < 4; ++e) o[e] = (bf16)(gg[c][e] * ((v[i][c][e] - mean[i]) * inv[i]) + bb[c][e]);
+            if (in_row(c)) *(bf16x4*)(rowbuf + (wave * RW + i) * PITCH + 8 * (lane + 64 * c)) = o;
         }
     barrier_lds();
 
@@ -710,14 +710,56 @@ hipError_t launch_rows_ln(RowsLnArgs a, int k, hipStream_t s)
     a.nfb8 = up8(a.nfb);
     a.nrb = (a.M + 15) / 16;
     const dim3 grid((unsigned)(a.nfb8 * a.nrb * k));
-    // (an instance per hidden width of the usual shapes; any other width up to 1024 takes the clamped one)
-#define SP_GO(NS, X) hipLaunchKernelGGL((rows_ln_gemm_kernel<PRO, EPI, NS, X>), grid, dim3(256), 0, s, a)
-    if (a.H == 256) SP_GO(8, true);
-    else if (a.H == 768) SP_GO(24, true);
-    else if (a.H == 1024) SP_GO(32, true);
-    else SP_GO(32, false);
+    // (an instance for every hidden width there is: multiples of 128 up to 1024)
+#define SP_GO(NS) case 32 * NS: hipLaunchKernelGGL((rows_ln_gemm_kernel<PRO, EPI, NS>), grid, dim3(256), 0, s, a); break
+    switch (a.H) {
+        SP_GO(4); SP_GO(8); SP_GO(12); SP_GO(16); SP_GO(20); SP_GO(24); SP_GO(28); SP_GO(32);
+        default: return hipErrorInvalidValue;
+    }
 #undef SP_GO
     return hipGetLastError();
+}
+
+// A wave's quarter of the reduction range has Kd / 128 steps of 32.  Up to eight (every hidden width): one pass of an instance of
+// that length.  FFN depths: one pass of 24 steps, or of 32 where the rows are few enough for the registers; any other depth takes
+// passes of 10, 12, 14 or 16 steps, whichever makes them cheapest: a pass costs a memory round trip, about six steps, and the
+// steps that it has, the unused ones of the last pass among them.  Instances for listed depths only, and 16-step passes for all
+// others, cost depth 640 three times its loads (four students, 200 rows, one launch: 19.9 us against 7.2 now).
+template <bool F32OUT, int TM, int TF>
+hipError_t launch_rows_k_tile(const RowsKArgs& a, dim3 grid, hipStream_t s)
+{
+#define SP_GO(NS, X) hipLaunchKernelGGL((rows_ksplit_kernel<F32OUT, TM, TF, NS, X>), grid, dim3(256), 0, s, a)
+    const int steps = a.Kd / 128;
+    switch (steps) {
+        case 1: SP_GO(1, true); return hipGetLastError();
+        case 2: SP_GO(2, true); return hipGetLastError();
+        case 3: SP_GO(3, true); return hipGetLastError();
+        case 4: SP_GO(4, true); return hipGetLastError();
+        case 5: SP_GO(5, true); return hipGetLastError();
+        case 6: SP_GO(6, true); return hipGetLastError();
+        case 7: SP_GO(7, true); return hipGetLastError();
+        case 8: SP_GO(8, true); return hipGetLastError();
+        default: break;
+    }
+    if constexpr (F32OUT) {
+        if (steps == 24) { SP_GO(24, true); return hipGetLastError(); }
+        if constexpr (TM == 1)
+            if (steps == 32) { SP_GO(32, true); return hipGetLastError(); }
+        int best = 0, least = 0;
+        for (int ns : {16, 14, 12, 10}) {
+            const int cost = (steps + ns - 1) / ns * (ns + 6);
+            if (!best || cost < least) { best = ns; least = cost; }
+        }
+        switch (best) {
+            case 10: SP_GO(10, false); break;
+            case 12: SP_GO(12, false); break;
+            case 14: SP_GO(14, false); break;
+            default: SP_GO(16, false); break;
+        }
+        return hipGetLastError();
+    }
+#undef SP_GO
+    return hipErrorInvalidValue;                            // (bf16 outputs: the value projection, as deep as the hidden width)
 }
 
 template <bool F32OUT>
@@ -734,18 +776,10 @@ hipError_t launch_rows_k(RowsKArgs a, int k, hipStream_t s)
     a.nfb8 = up8(a.nfb);
     a.nrb = (a.M + 16 * tm - 1) / (16 * tm);
     const dim3 grid((unsigned)(a.nfb8 * a.nrb * k));
-#define SP_GO(TM, TF, NS, X) hipLaunchKernelGGL((rows_ksplit_kernel<F32OUT, TM, TF, NS, X>), grid, dim3(256), 0, s, a)
-#define SP_NS(TM, TF) do { if (a.Kd == 256) SP_GO(TM, TF, 2, true); else if (a.Kd == 768) SP_GO(TM, TF, 6, true); \
-                           else if (a.Kd == 1024) SP_GO(TM, TF, 8, true); else if (a.Kd == 3072) SP_GO(TM, TF, 24, true); \
-                           else if (a.Kd == 4096 && TM == 1) SP_GO(TM, TF, (TM == 1 ? 32 : 16), (TM == 1)); \
-                           else SP_GO(TM, TF, 16, false); } while (0)
-    if (tm == 1 && tf == 1) SP_NS(1, 1);
-    else if (tm == 1) SP_NS(1, 2);
-    else if (tm == 2) SP_NS(2, 2);
-    else SP_NS(4, 2);
-#undef SP_NS
-#undef SP_GO
-    return hipGetLastError();
+    if (tm == 1 && tf == 1) return launch_rows_k_tile<F32OUT, 1, 1>(a, grid, s);
+    if (tm == 1) return launch_rows_k_tile<F32OUT, 1, 2>(a, grid, s);
+    if (tm == 2) return launch_rows_k_tile<F32OUT, 2, 2>(a, grid, s);
+    return launch_rows_k_tile<F32OUT, 4, 2>(a, grid, s);
 }
 
 template <int NS>

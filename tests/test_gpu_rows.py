@@ -32,8 +32,8 @@ def _run(oracle64, shape, lengths, ks, seed):
     st.close()
 
 
-# widths with an instance of their own (256, 768, 1024) and between them; reduction depths of one and several passes
-@pytest.mark.parametrize("hidden,ffn", [(128, 128), (256, 1024), (384, 640), (768, 3072), (896, 2176), (1024, 4096)])
+# every hidden width; reduction depths of one pass and of several, with and without unused steps in the last
+@pytest.mark.parametrize("hidden,ffn", [(128, 128), (256, 1024), (384, 640), (512, 1536), (640, 2560), (768, 3072), (896, 2176), (1024, 4096)])
 @pytest.mark.parametrize("lengths", [(1,), (15,), (16,), (17,), (5, 28), (57, 58), (64, 1, 63), (9,) * 20, (250, 6)])
 def test_small_calls_on_every_width(oracle64, hidden, ffn, lengths):
     """Row blocks of sixteen just missed, met and passed, both sides of the fused LayerNorm's limit, one and several steps
@@ -106,9 +106,9 @@ def test_nothing_in_the_workspace_has_to_be_finite(oracle64, hidden, ffn, layers
     st.close()
 
 
-# (hidden, students, sequences of 60 tokens): the first-token rows of all students are beyond the fused LayerNorm's limit, those
-# of one group are not
-@pytest.mark.parametrize("hidden,K,nseq", [(768, 3, 140), (768, 2, 200), (1024, 4, 138)])
+# (hidden, students, sequences of 60 tokens): the first-token rows of all students and those of a group, or those of the two
+# groups of an odd number, lie on different sides of a limit between kernels
+@pytest.mark.parametrize("hidden,K,nseq", [(768, 3, 140), (768, 2, 200), (1024, 4, 138), (768, 5, 140), (1024, 6, 900)])
 @pytest.mark.parametrize("dtype", ["bf16", "fp8"])
 def test_one_group_of_students_or_two_give_the_same_bits(hidden, K, nseq, dtype):
     """Which kernel takes the first-token rows goes by the call, not by the group of students it runs for: logits of a large call
