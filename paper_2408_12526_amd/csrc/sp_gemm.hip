@@ -287,26 +287,38 @@ hipError_t launch_wreg_tile(const sp_model* M, GemmArgs a, int N, int k, hipStre
 // 25.1 / 21.7 / 23.2 / 28.2; 18432 tokens, 1024 features from 4096: 175 / 155 / 185 / -; 640 tokens, 768 from 768: 15.3 / 13.0 / 11.2 / 8.8.
 }  // namespace
 
-int gemm_tile_height(int mrows, int N, int k)
+// wide: tiles side by side; round: how many the chip takes at once; tallest: the largest height there is
+static int tile_height(int mrows, long wide, long round, int tallest)
 {
     static const double cost[5] = {0, 1.7, 1.2, 1.1, 1.0};
-    int best = 4;
+    int best = tallest;
     double least = 0;
-    for (int tm = 4; tm >= 1; --tm) {
-        const long tiles = (long)((mrows + 32 * tm - 1) / (32 * tm)) * (N / 256) * k;
-        const double t = (double)((tiles + 255) / 256) * tm * cost[tm];
-        if (tm == 4 || t < least) { best = tm; least = t; }
+    for (int tm = tallest; tm >= 1; --tm) {
+        const double t = (double)(((mrows + 32 * tm - 1) / (32 * tm) * wide + round - 1) / round) * tm * cost[tm];
+        if (tm == tallest || t < least) { best = tm; least = t; }
     }
     return best;
 }
+
+int gemm_tile_height(int mrows, int N, int k) { return tile_height(mrows, (long)(N / 256) * k, 256, 4); }
 
 namespace {
 
 template <int EPI>
 hipError_t launch_bf16(const sp_model* M, const GemmArgs& a, int N, int k, hipStream_t s)
 {
-    // (widths that are not multiples of 256: half the features, two waves)
-    if (N % 256 || a.n_split % 256) return launch_wreg_tile<2, 2, EPI>(M, a, N, k, s);
+    // Widths that are not multiples of 256: half the features, two waves, so a round is twice as many workgroups; 96 tokens (128
+    // do not fit the registers: 665 us where these take 471) only from two rounds on.  Measured, us, 64 tokens always / this: 14521
+    // tokens x 4 students, hidden 896: q|k|v 322 / 289, attention output 144 / 127, FFN down 507 / 471; calls of few tiles are
+    // chains of k-tiles that a lower tile shortens: 1851 tokens, hidden 384: attention output 7.5 / 5.9, FFN down from 640 10 / 8.
+    if (N % 256 || a.n_split % 256) {
+        const long wide = (long)(N / 128) * k * a.splits;
+        switch (tile_height(a.mrows, wide, 512, (a.mrows + 95) / 96 * wide >= 1024 ? 3 : 2)) {
+            case 1: return launch_wreg_tile<1, 2, EPI>(M, a, N, k, s);
+            case 2: return launch_wreg_tile<2, 2, EPI>(M, a, N, k, s);
+            default: return launch_wreg_tile<3, 2, EPI>(M, a, N, k, s);
+        }
+    }
     switch (gemm_tile_height(a.mrows, N, k * a.splits)) {
         case 1: return launch_wreg_tile<1, 4, EPI>(M, a, N, k, s);
         case 2: return launch_wreg_tile<2, 4, EPI>(M, a, N, k, s);
@@ -521,7 +533,7 @@ hipError_t launch_gelu_probe(const float* x, float* y, long n, hipStream_t s)
 hipError_t launch_gemm_split(const sp_model* M, const void* A, int lda, size_t w_off, float* part, size_t slice, int mrows,
                              int N, int Kd, int k, int splits, size_t a_student_stride, size_t p_student_stride, hipStream_t s)
 {
-    if (!bf16_path(M->cfg) || mrows % 64 || N % 256 || splits < 1 || Kd % (128 * splits)) return hipErrorInvalidValue;
+    if (!bf16_path(M->cfg) || mrows % 64 || N % 128 || splits < 1 || Kd % (128 * splits)) return hipErrorInvalidValue;
     const GemmArgs a{(const bf16*)A, a_student_stride / 2, M->arena, M->L.student_stride, w_off, 0, (bf16*)part, p_student_stride,
                      nullptr, 0, nullptr, 0, rows_layout(N), lda, 0, 0, 0, Kd, Kd / splits, splits, mrows, 0, 0, 0, 0, slice};
     return launch_bf16<EPI_PARTIAL>(M, a, N, k, s);

@@ -81,7 +81,8 @@ def test_fp32_layer_in_one_launch(oracle64, ffn, layers, lengths, k):
 @pytest.mark.parametrize("hidden,ffn,layers,K,k,all_tokens,lengths",
                          [(512, 640, 3, 2, 2, False, (100, 37, 150, 62)), (768, 640, 2, 2, 2, True, (200, 90, 5)),
                           (1024, 128, 3, 1, 1, False, (64, 64, 64, 65, 64)), (256, 1024, 3, 4, 1, True, (90, 200, 13)),
-                          (768, 3072, 3, 2, 1, True, (301, 12, 90)), (768, 384, 2, 5, 5, False, (100, 53))])
+                          (768, 3072, 3, 2, 1, True, (301, 12, 90)), (768, 384, 2, 5, 5, False, (100, 53)),
+                          (384, 1536, 3, 2, 1, False, (301, 12, 90)), (640, 2560, 3, 1, 1, True, (77, 200, 13))])
 def test_nothing_in_the_workspace_has_to_be_finite(oracle64, hidden, ffn, layers, K, k, all_tokens, lengths):
     """Padding rows reach attention with probability zero, which is no help against what is not a number: a workspace full of
     NaN gives what the oracle gives, for the last sequence too (token counts that are no multiple of eight)."""
@@ -128,3 +129,73 @@ def test_one_group_of_students_or_two_give_the_same_bits(hidden, K, nseq, dtype)
         assert torch.equal(a, b), f"k_active {k}: {(a - b).abs().max().item():.3e}"
     two.close()
     one.close()
+
+
+def _stages(oracle64, shape, weights, m, x0, att, got):
+    """Largest relative errors of x1, g and x of a one-layer student against the layer's pieces applied to what the GPU had."""
+    v = {n[3:]: w for n, w in synth.student_views(weights, shape, m).items() if n.startswith("l0.")}
+
+    def ln(u, which):
+        return np.stack([oracle64.layernorm(r, v[f"ln{which}_g"], v[f"ln{which}_b"], shape.ln_eps) for r in u])
+
+    def rel(a, b):
+        return np.abs(a - b).max() / np.abs(b).max()
+
+    g = torch.nn.functional.gelu(torch.from_numpy(oracle64.linear(got["x1"][m], v["W1"], v["b1"]))).numpy()
+    return (rel(got["x1"][m], ln(x0[m] + oracle64.linear(att[m], v["Wo"], v["bo"]), 1)), rel(got["g"][m], g),
+            rel(got["x"][m], ln(got["x1"][m] + oracle64.linear(got["g"][m], v["W2"], v["b2"]), 2)))
+
+
+# one student of K: as many slices as the buffers of the others leave room for.  Slices of the two projections: 3 and 8, 3 and 6, 2
+# and 3, 1 and 4, 1 and 6 (tiles of half the features), 1 and 2
+@pytest.mark.parametrize("hidden,ffn,K", [(768, 3072, 8), (768, 3072, 2), (768, 3072, 1), (256, 1024, 2), (384, 1536, 2), (128, 512, 1)])
+def test_split_reductions_stage_by_stage(oracle64, hidden, ffn, K):
+    """A whole forward with every token in its one layer leaves x1, g and x of that layer: each against the oracle's piece applied
+    to the stage before it (the attention output, which the slices overwrite, from a forward that stops after the layer)."""
+    from paper_2408_12526_amd import sp
+    shape = synth.StudentShape(K=K, layers=1, hidden=hidden, heads=hidden // 64, ffn=ffn, vocab=60, max_pos=208, classes=2, dtype="bf16")
+    rng = np.random.default_rng(hidden + K)
+    lengths = np.array((101, 13, 199), dtype=np.int32)
+    T, B = int(lengths.sum()), 3
+    ids, blob, cu = synth.make_ids(rng, T, shape.vocab), synth.make_weights(rng, shape, std=0.05, ln_random=True), sp.sp_pack(lengths)
+    weights = torch.from_numpy(blob).bfloat16().float().numpy()
+    st = sp.Students(sp.config_from_shape(shape, last_layer_all_tokens=True), blob)
+    d_ids, d_cu = torch.from_numpy(ids).cuda(), torch.from_numpy(cu).cuda()
+    x0 = st.read_activation(st.sp_forward_partial(d_ids, d_cu, 199, 1, 0), "x", T, B, 1)
+    att = st.read_activation(st.sp_forward_partial(d_ids, d_cu, 199, 1, 1), "att", T, B, 1)
+    st.sp_forward(d_ids, d_cu, 199, 1)
+    got = {n: st.read_activation(st.workspace(T, B), n, T, B, 1) for n in ("x1", "g", "x")}
+    # (one bf16 rounding of each output: the operands are what the GPU had)
+    assert max(_stages(oracle64, shape, weights, 0, x0, att, got)) < 1.2e-2
+    st.close()
+
+
+# K picks the tile heights: hidden 256 and 768 as in the test of the fp8 tiles; hidden 384 tiles of half the features, 32 tokens
+# for the attention output and 64 for q|k|v at K = 1, 64 and 96 at K = 7
+@pytest.mark.parametrize("tokens", [2049, 2111])
+@pytest.mark.parametrize("hidden,ffn,K", [(256, 768, 1), (256, 768, 2), (256, 768, 3), (256, 768, 4), (768, 768, 1), (768, 768, 2),
+                                          (768, 768, 3), (768, 768, 4), (384, 640, 1), (384, 640, 7)])
+def test_tiles_of_every_height_at_their_edges(oracle64, hidden, ffn, K, tokens):
+    """Every projection on the HIP path's own input, the last rows and a sample of the others: one row beyond a tile of any height,
+    and one short of 64."""
+    from paper_2408_12526_amd import sp
+    shape = synth.StudentShape(K=K, layers=1, hidden=hidden, heads=hidden // 64, ffn=ffn, vocab=60, max_pos=128, classes=2, dtype="bf16")
+    rng = np.random.default_rng(tokens + K)
+    lengths = np.full(-(-tokens // 100), 100, dtype=np.int32)
+    lengths[-1] = tokens - 100 * (len(lengths) - 1)
+    B = len(lengths)
+    ids, blob, cu = synth.make_ids(rng, tokens, shape.vocab), synth.make_weights(rng, shape, std=0.05, ln_random=True), sp.sp_pack(lengths)
+    weights = torch.from_numpy(blob).bfloat16().float().numpy()
+    st = sp.Students(sp.config_from_shape(shape, last_layer_all_tokens=True), blob)
+    d_ids, d_cu = torch.from_numpy(ids).cuda(), torch.from_numpy(cu).cuda()
+    rows = np.unique(np.r_[np.arange(0, tokens, 61), np.arange(tokens - 130, tokens)])
+    x0 = st.read_activation(st.sp_forward_partial(d_ids, d_cu, 100, K, 0), "x", tokens, B, K)[:, rows]
+    ws = st.sp_forward_partial(d_ids, d_cu, 100, K, 1)
+    got = {n: st.read_activation(ws, n, tokens, B, K)[:, rows] for n in ("qkv", "att", "x1", "g", "x")}
+    for m in range(K):
+        v = synth.student_views(weights, shape, m)
+        qkv = oracle64.linear(x0[m], np.concatenate([v["l0.Wq"], v["l0.Wk"], v["l0.Wv"]], axis=1),
+                              np.concatenate([v["l0.bq"], v["l0.bk"], v["l0.bv"]]))
+        assert np.abs(got["qkv"][m] - qkv).max() / np.abs(qkv).max() < 1.2e-2
+        assert max(_stages(oracle64, shape, weights, m, x0, got["att"], got)) < 1.2e-2
+    st.close()
