@@ -78,10 +78,13 @@ typedef struct {
                          them for the first tokens only.  1: every token goes
                          through the whole last layer (what a stock BERT does; the fp32 path always does). */
     int32_t single_stream;
-                      /* 0 (default): a call with >= 2048 tokens and k_active >= 2 runs the active students
+                      /* 0 (default): a call with >= 8192 tokens and k_active >= 2 runs the active students
                          as two groups side by side, the second on a stream the model owns, forked from and
                          joined to the caller's stream with events (the call stays asynchronous and can be
                          captured in a graph; the logits are bit-identical to the single-stream result).
+                         In such large calls a student's term has the same bits for every k_active; smaller
+                         calls choose their kernels by the rows of all active students, so there the term
+                         of a student may differ between two k_active by roundings of its arithmetic.
                          1: everything is enqueued on the caller's stream. */
 } sp_config;
 

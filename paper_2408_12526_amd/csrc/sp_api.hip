@@ -282,8 +282,7 @@ struct PhaseTimer {
 // The forward of students [m0, m0 + k) of the model (k >= 1), all of it enqueued on stream s.  Every buffer of the
 // workspace is sliced per student, so groups of students can run side by side on different streams.  With
 // with_head the group's z rows are written; logits (the group's own sum, in student order) only if non-null.
-// k_rule, may_split: what the rules that choose between kernels of different rounding go by, never the group's own k, so
-// that a call has the same bits as one group and as two.
+// k_rule, may_split: what the rules that choose between kernels of different rounding go by, never the group's own k.
 static int run_students(const sp_model* M0, const WsLayout& W, const int32_t* ids, const int32_t* cu, int B, int T,
                         int max_seqlen, int m0, int k, int k_rule, bool may_split, int stop_layers, bool with_head, char* w,
                         float* logits, hipStream_t s, PhaseTimer* pt)
@@ -593,9 +592,12 @@ static int run_forward(const sp_model* M, const int32_t* ids, const int32_t* cu,
     if (ws_bytes < W.end) return SP_ENOMEM;
     char* w = (char*)ws;
 
-    const bool large = k >= 2 && T >= two_groups_min_tokens();
-    const int ka = (k + 1) / 2, k_rule = large ? ka : k;    // (students of the larger group)
-    const bool two_groups = with_head && !pt && large && !c.single_stream && M->aux;
+    // Large calls: kernels by the model's students, not by how many are active, so that a student's term has the same bits
+    // whatever k and however the students are grouped.  (Smaller calls go by the active ones: a call pruned to one student would
+    // otherwise run on kernels for eight.)
+    const bool large = T >= two_groups_min_tokens();
+    const int ka = (k + 1) / 2, k_rule = large ? (c.K + 1) / 2 : k;
+    const bool two_groups = with_head && !pt && large && k >= 2 && !c.single_stream && M->aux;
     if (!two_groups)
         return run_students(M, W, ids, cu, B, T, max_seqlen, 0, k, k_rule, !large, stop_layers, with_head, w, logits, s, pt);
 

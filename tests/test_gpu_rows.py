@@ -107,13 +107,14 @@ def test_nothing_in_the_workspace_has_to_be_finite(oracle64, hidden, ffn, layers
     st.close()
 
 
-# (hidden, students, sequences of 60 tokens): the first-token rows of all students and those of a group, or those of the two
-# groups of an odd number, lie on different sides of a limit between kernels
-@pytest.mark.parametrize("hidden,K,nseq", [(768, 3, 140), (768, 2, 200), (1024, 4, 138), (768, 5, 140), (1024, 6, 900)])
+# (hidden, students, sequences of 60 tokens): the first-token rows of all students and of a group, of the two groups of an odd
+# number, or of few and of all students, lie on different sides of a limit between kernels; few tiles for one student
+@pytest.mark.parametrize("hidden,K,nseq", [(768, 3, 140), (768, 2, 200), (1024, 4, 138), (768, 5, 140), (1024, 6, 900),
+                                            (256, 3, 150)])
 @pytest.mark.parametrize("dtype", ["bf16", "fp8"])
 def test_one_group_of_students_or_two_give_the_same_bits(hidden, K, nseq, dtype):
-    """Which kernel takes the first-token rows goes by the call, not by the group of students it runs for: logits of a large call
-    are the same bits on one stream and on two, for every number of active students."""
+    """Which kernels a large call takes goes by its tokens and sequences and the model, not by the group of students at hand nor by
+    how many are active: its logits are the same bits on one stream and on two, and the sum of the same terms for every k."""
     from paper_2408_12526_amd import sp
     shape = synth.StudentShape(K=K, layers=2, hidden=hidden, heads=hidden // 64, ffn=1024, vocab=500, max_pos=64, classes=4, dtype=dtype)
     rng = np.random.default_rng(hidden + K)
@@ -124,9 +125,14 @@ def test_one_group_of_students_or_two_give_the_same_bits(hidden, K, nseq, dtype)
     blob = synth.make_weights(rng, shape, std=0.04, ln_random=True)
     two = sp.Students(sp.config_from_shape(shape), blob)
     one = sp.Students(sp.config_from_shape(shape, single_stream=True), blob)
-    for k in range(2, K + 1):
-        a, b = two.sp_forward(ids, cu, 60, k), one.sp_forward(ids, cu, 60, k)
+    two.sp_forward(ids, cu, 60, K)
+    z = torch.from_numpy(two.read_activation(two.workspace(ids.numel(), nseq), "z", ids.numel(), nseq, K)).float()
+    total = torch.zeros(nseq, 4)
+    for k in range(1, K + 1):
+        total = total + z[k - 1]
+        a, b = two.sp_forward(ids, cu, 60, k).cpu(), one.sp_forward(ids, cu, 60, k).cpu()
         assert torch.equal(a, b), f"k_active {k}: {(a - b).abs().max().item():.3e}"
+        assert torch.equal(a, total), f"k_active {k}, terms: {(a - total).abs().max().item():.3e}"
     two.close()
     one.close()
 
