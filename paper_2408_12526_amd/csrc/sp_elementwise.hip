@@ -349,7 +349,7 @@ __global__ __launch_bounds__(256) void head_pool_kernel(const char* arena, size_
     const int nseq = (B - b0) < kSeqPerWg ? (B - b0) : kSeqPerWg;
     const char* sb = arena + (size_t)m * student_stride;
     for (int s = 0; s < nseq; ++s) {
-        int r = cu ? cu[b0 + s] : b0 + s;    // packed layout: first token of the sequence; compact layout: row b
+        int r = cu[b0 + s];                  // first token of the sequence
         r = r < 0 ? 0 : (r >= Tn ? Tn - 1 : r);
         const T* src = x + ((size_t)m * rows + r) * H;
         for (int i = tid; i < H; i += 256) xs[s * H + i] = (float)src[i];

@@ -333,7 +333,7 @@ hipError_t launch_check_inputs(const int32_t* ids, const int32_t* cu, int B, int
 // logits[i] = sum_{m<k} z[m][i], m ascending (i < n).
 hipError_t launch_sum_students(const float* z, int n, int k, float* logits, hipStream_t s);
 
-// z[m][b][c] = tanh(x[m][cu[b]] Wp + bp) Wc + bc (row b itself if cu is null) ; logits[b][c] = sum_{m<k} z[m][b][c] (m ascending).
+// z[m][b][c] = tanh(x[m][cu[b]] Wp + bp) Wc + bc ; logits[b][c] = sum_{m<k} z[m][b][c] (m ascending).
 hipError_t launch_head(const sp_model* M, const void* x, const int32_t* cu, int B, int T, int rows, int k, float* z,
                        float* zpart, float* logits, hipStream_t s);
 

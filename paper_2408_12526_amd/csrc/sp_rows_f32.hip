@@ -174,12 +174,13 @@ __global__ __launch_bounds__(64 * kWaves) void f32_layer_kernel(F32LayerArgs p)
 
 }  // namespace
 
-// Every workgroup reads the layer's weights, so the kernel is for narrow students (1 MB of weights: 7 us at the L2's rate; the
-// separate launches spread them over the chip) and for calls of at most one workgroup per compute unit.
+// Every workgroup reads the layer's weights, so the kernel is for narrow students (1 MB of weights, i.e. hidden 128 with an FFN of up
+// to 768: 7 us at the L2's rate; the separate launches spread them over the chip) and for calls of at most one workgroup per
+// compute unit.
 bool f32_layer_supported(const sp_config& c, long rows_of_all_students)
 {
     const size_t H = c.hidden, F = c.ffn;
-    return !bf16_path(c) && H % 128 == 0 && F % 128 == 0 && H <= 256 && (4 * H * H + 2 * H * F) * sizeof(float) <= (1u << 20) &&
+    return !bf16_path(c) && H == 128 && F % 128 == 0 && (4 * H * H + 2 * H * F) * sizeof(float) <= (1u << 20) &&
            rows_of_all_students <= 256 * kRows;
 }
 
