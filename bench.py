@@ -715,7 +715,7 @@ def main():
                            "traffic_written": tr["written_bytes"] if tr else None,
                            "traffic_source": os.path.relpath(TRAFFIC_PROFILE, ROOT) if tr else None,
                            "traffic_measured_on_this_build": fresh, "build_id": kernel_build_id(),
-                           "algorithmic_bytes": 8 * 14848 * (H + F) * 2 + 8 * H * F * 2,
+                           "algorithmic_bytes": 8 * 14784 * (H + F) * 2 + 8 * H * F * 2,
                            "algorithmic_flops": gf["ffn_up"], "launch_ms": d["ms"]}
     rec["cpu_baseline"] = cpu
     print(json.dumps(rec))
