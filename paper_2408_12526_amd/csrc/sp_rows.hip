@@ -731,17 +731,20 @@ hipError_t launch_rows_k_tile(const RowsKArgs& a, dim3 grid, hipStream_t s)
 #define SP_GO(NS, X) hipLaunchKernelGGL((rows_ksplit_kernel<F32OUT, TM, TF, NS, X>), grid, dim3(256), 0, s, a)
     const int steps = a.Kd / 128;
     switch (steps) {
-        case 1: SP_GO(1, true); return hipGetLastError();
         case 2: SP_GO(2, true); return hipGetLastError();
-        case 3: SP_GO(3, true); return hipGetLastError();
         case 4: SP_GO(4, true); return hipGetLastError();
-        case 5: SP_GO(5, true); return hipGetLastError();
         case 6: SP_GO(6, true); return hipGetLastError();
-        case 7: SP_GO(7, true); return hipGetLastError();
         case 8: SP_GO(8, true); return hipGetLastError();
         default: break;
     }
     if constexpr (F32OUT) {
+        switch (steps) {
+            case 1: SP_GO(1, true); return hipGetLastError();
+            case 3: SP_GO(3, true); return hipGetLastError();
+            case 5: SP_GO(5, true); return hipGetLastError();
+            case 7: SP_GO(7, true); return hipGetLastError();
+            default: break;
+        }
         if (steps == 24) { SP_GO(24, true); return hipGetLastError(); }
         if constexpr (TM == 1)
             if (steps == 32) { SP_GO(32, true); return hipGetLastError(); }
@@ -759,7 +762,7 @@ hipError_t launch_rows_k_tile(const RowsKArgs& a, dim3 grid, hipStream_t s)
         return hipGetLastError();
     }
 #undef SP_GO
-    return hipErrorInvalidValue;                            // (bf16 outputs: the value projection, as deep as the hidden width)
+    return hipErrorInvalidValue;                            // (bf16 outputs: the value projection, as deep as the folded attention's widths)
 }
 
 template <bool F32OUT>
