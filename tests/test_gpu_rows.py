@@ -43,7 +43,7 @@ def test_small_calls_on_every_width(oracle64, hidden, ffn, lengths):
     _run(oracle64, shape, lengths, (1, 5), 7 * hidden + sum(lengths))
 
 
-@pytest.mark.parametrize("nseq,length", [(33, 8), (64, 9), (255, 3), (256, 5), (257, 5), (300, 4), (600, 2), (1041, 3), (1500, 3)])
+@pytest.mark.parametrize("nseq,length", [(33, 8), (64, 9), (255, 3), (256, 5), (257, 5), (300, 3), (300, 4), (511, 2), (600, 2), (1041, 3), (1500, 3)])
 @pytest.mark.parametrize("hidden", [256, 512, 768, 1024])
 def test_first_token_rows_of_many_sequences(oracle64, hidden, nseq, length):
     """The folded last layer at row blocks of every tile, on few and on many sequences; below 1024 tokens its rows share the
