@@ -10,16 +10,6 @@ namespace sp {
 namespace {
 
 constexpr int kD = 64;          // head width
-constexpr int kQPerWg = 256;    // queries per workgroup of the long-sequence body: 4 waves x 2 blocks of 32
-constexpr int kKeyTile = 64;    // keys staged in LDS per step
-constexpr int kKStride = kKeyTile + 1;   // 16-byte units per k-group of the key tile
-constexpr int kVStride = 68;    // bf16 elements per row of the transposed value tile (136 B)
-constexpr int kOutPitch = kD * 2 + 16;   // bytes per staged output row
-constexpr int kLongKBytes = 8 * kKStride * 16, kLongVBytes = kD * kVStride * 2;
-constexpr int kLongTileBytes = kLongKBytes + kLongVBytes;   // one buffer of the key/value tile
-constexpr int kLongLdsBytes = 2 * kLongTileBytes;
-static_assert(kLongTileBytes % 16 == 0 && 4 * 32 * kOutPitch <= kLongLdsBytes, "the output tiles reuse the key/value buffers");
-
 // 2^x by the hardware instruction alone.  (exp2f() wraps it in a range test, a scaling and an ldexp so that results
 // below 2^-126 come out as denormals: four more instructions per value, which a softmax numerator does not need;
 // arguments here are <= 0, and what underflows is flushed to zero.)
@@ -42,460 +32,289 @@ __device__ inline uint2 chunk_to_fp8(uint4 c, float qscale)
 }
 
 // -------------------------------------------------------------------------------------
-// bf16 body on the matrix cores for long sequences.  One workgroup = (student, sequence, head, block of 256
-// queries); wave w owns queries q0 + 64 w .. + 63 as two blocks of 32, which share every key and value fragment
-// it reads from LDS.  Per 64-key tile and query block:
-//   S^T = K Q^T      (A operand: key rows from LDS, B operand: the block's queries, kept in
-//                     registers for the whole kernel)
-//   online softmax   per query = per lane column; a query's keys sit in 16 accumulator
-//                    registers of two lanes (l and l + 32); the 1/sqrt(d) log2(e) factor rides in the
-//                    fused multiply-add in front of the exponential
-//   O^T += V^T P^T   (A operand: transposed value tile from LDS; B operand: the
-//                     probabilities, which already sit in the B-operand register layout
-//                     once the reduction slots of V^T are enumerated in the same key order)
-// The key/value tiles are double-buffered in LDS and travel through registers: tile t + 2 is requested from
-// memory and tile t + 1 written to the idle buffer while tile t is multiplied; one barrier per tile, which
-// waits for LDS traffic only (the loads stay in flight across it).
+// bf16 kernel on the matrix cores (v_mfma_f32_32x32x16_bf16, fp32 accumulate).  A workgroup takes 128 queries of one sequence
+// and head, a wave 32 of them.  Keys and values go through LDS in tiles of 64 keys that the four waves share; per block of 32 keys:
+//   S^T = K Q^T      (A operand: key rows from LDS, B operand: the queries, in registers throughout)
+//   online softmax   a query is a lane column, its keys sit in the registers of lanes l and l + 32; the
+//                    1/sqrt(d) log2(e) factor rides in the multiply-add in front of the exponential
+//   O^T += V^T P^T   (A operand: transposed value tile from LDS; B operand: the probabilities as they are)
+// The tiles are double-buffered and travel through registers, keys and values in turn: the next tile's keys are put down once
+// the scores are formed and its values requested, the values put down at the end and the keys of the tile after it requested; one
+// barrier per tile, which waits for LDS traffic only.  Rows of eight 16-byte slots, slot = chunk ^ ((row / 2) % 8).
+//
+// The running maximum moves per tile of 64 keys, in sequences of up to 128 tokens per block of 32.
+//
+// Work item i belongs to the last sequence b with cu[b] / 128 + b <= i: a sequence of L tokens gets at least ceil(L / 128)
+// consecutive numbers, T / 128 + B numbers are enough for any lengths, and which sequence it is takes one look at 64 boundaries
+// by the whole wave (two looks beyond 64 sequences).
+//
+// What bounds it: vector instructions (about seven issue slots per score, four of them the exponential) and the read of
+// queries, keys and values, neither saturated: a wave's chain of products, maximum, exponentials and products is issued in
+// order, so waves in flight are what counts.  Hence 32 queries a wave and 127 registers, four waves per SIMD (with 64 queries a
+// wave a key fragment served two products, but two waves per SIMD was all the registers held).  us per launch, a wave per
+// sequence and head up to 128 tokens and 64 queries per wave above / this: 64 sequences of 64-512 tokens, 16 heads, one student
+// 84 / 66, six 466 / 335; 256 sequences of 8-256, 12 heads, eight students 238 / 214, two 65 / 54; 32 of 16-128, four students
+// 31 / 21; one of 64, one student 9.9 / 6.9.  Tried: keys and values in flight together (141 registers, three waves) 65, 357, 237,
+// 60, 22 and 6.6; two heads per workgroup side by side where a sequence fits one tile: 382 for the second where one head took 340.
+// A reference that moves only when it is outgrown by 2^8 saves most rescaling (317 for the second), but then the largest
+// probability is no longer 1 and is rounded: up to 1.2 times the error against 64 bits on sharp distributions.
 // -------------------------------------------------------------------------------------
-__device__ __forceinline__ void attention_long_body(char* lds, int bid, const bf16* __restrict__ qkv,
-                                                    const bf16* __restrict__ vt, bf16* __restrict__ att,
-                                                    const int32_t* __restrict__ cu, int B, int Tn, int rows, int H,
-                                                    int heads, int max_seqlen, int nqc, int min_len,
-                                                    unsigned char* __restrict__ attq, float qscale)
+constexpr int kQItem = 128;     // queries of a work item: four waves x 32
+constexpr int kKeyTile = 64;    // keys staged in LDS per step
+constexpr int kNarrowLen = 128; // longest sequence whose softmax goes by blocks of 32 keys
+constexpr int kTileBytes = kKeyTile * kD * 2;       // keys: rows of 64 dimensions; values: rows of 64 keys; eight 16-byte slots each
+constexpr int kOutPitch = kD * 2 + 16;              // bytes per staged output row
+constexpr int kAttnLdsBytes = 4 * kTileBytes;       // two buffers of a key and a value tile
+static_assert(4 * 32 * kOutPitch <= kAttnLdsBytes && (2 * kTileBytes & (2 * kTileBytes - 1)) == 0, "the output tiles reuse the key/value buffers; offsets change buffers by an exclusive or");
+
+struct AttnArgs {
+    const bf16 *qkv, *vt;
+    bf16* att;                        // null: the fp8 copy alone
+    unsigned char* attq;              // null: none
+    const int32_t* cu;
+    float qscale;
+    int B, Tn, rows, H, heads, max_seqlen;
+    int items, run;                   // work items per head; neighbouring items that stay on one XCD
+};
+
+// Sequence b of work item i and its boundaries (every lane takes part; i and the result are uniform).
+__device__ __forceinline__ void sequence_of_item(const int32_t* __restrict__ cu, int B, int i, int lane, int& b, int& c0, int& c1)
 {
+    int base = 0, span = B;
+    for (;;) {
+        const int step = (span + 63) >> 6, off = lane * step;
+        const bool in = off < span;
+        const int at = base + (in ? off : 0), v0 = cu[at], v1 = cu[at + 1];
+        const int n = __popcll(__ballot(in && (v0 >> 7) + at <= i)), last = n > 0 ? n - 1 : 0;
+        base += last * step;
+        if (step == 1) {
+            b = base;
+            c0 = __builtin_amdgcn_readlane(v0, last);
+            c1 = __builtin_amdgcn_readlane(v1, last);
+            return;
+        }
+        span = step < span - last * step ? step : span - last * step;
+    }
+}
+
+__global__ __launch_bounds__(256, 4) void attention_bf16_kernel(AttnArgs p)
+{
+    __shared__ __attribute__((aligned(16))) char lds[kAttnLdsBytes];
     const int m = blockIdx.y;
-    // (sequence, head) pairs go round the XCDs one by one (the few long sequences of a serving batch are spread evenly:
-    // a contiguous run of sequences per XCD left them unevenly loaded and was measured 1.5x slower), but the query
-    // blocks of one pair stay on one XCD (workgroup id mod 8), so that its keys and values are fetched into one L2
-    const int xcd = bid & 7, y = bid >> 3;
-    const int qc = y % nqc, pair = (y / nqc) * 8 + xcd;
-    if (pair >= B * heads) return;
-    const int h = pair % heads;
-    const int b = pair / heads;
-    int t0 = cu[b], t1 = cu[b + 1];
-    t0 = t0 < 0 ? 0 : (t0 > Tn - 1 ? Tn - 1 : t0);
+    // workgroup id mod 8 selects the XCD: runs of neighbouring items (they share lines of the token-contiguous value rows)
+    // stay on one XCD, the runs go round the XCDs, another way for every student
+    const int xcd = ((int)blockIdx.x + m) & 7, y = (int)blockIdx.x >> 3;
+    const int h = y % p.heads, s = y / p.heads, item = ((s / p.run) * 8 + xcd) * p.run + s % p.run;
+    if (item >= p.items) return;
+    const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    int b, t0, t1;
+    sequence_of_item(p.cu, p.B, item, lane, b, t0, t1);
+    const int q0 = (item - ((t0 >> 7) + b)) * kQItem;
+    t0 = t0 < 0 ? 0 : (t0 > p.Tn - 1 ? p.Tn - 1 : t0);
     int L = t1 - t0;
     L = L < 1 ? 1 : L;
-    L = L > max_seqlen ? max_seqlen : L;
-    L = L > Tn - t0 ? Tn - t0 : L;
-    const int q0 = qc * kQPerWg;
-    if (q0 >= L || L <= min_len) return;            // whole workgroup leaves together
+    L = L > p.max_seqlen ? p.max_seqlen : L;
+    L = L > p.Tn - t0 ? p.Tn - t0 : L;
+    if (q0 < 0 || q0 >= L) return;                  // (the whole workgroup)
 
-    const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int j = lane & 31, g = lane >> 5;
+    const int H = p.H, rows = p.rows;
     const size_t ld = (size_t)3 * H;
-    const bf16* base = qkv + ((size_t)m * rows + t0) * ld + h * kD;
-    const int qw = q0 + wave * 64;                  // the wave's first query
-    const int g4 = 4 * g;
-
-    // queries: B operand of S^T = K Q^T, four k-steps of 16 over d
-    bf16x8 qf[2][4];
-    f32x16 o[2][2];
-    float mrun[2], lrun[2];                         // running maximum (raw scores) and sum of a query's half of the keys
-#pragma unroll
-    for (int qb = 0; qb < 2; ++qb) {
-        const int q = qw + 32 * qb + j;
-#pragma unroll
-        for (int s = 0; s < 4; ++s) {
-            uint4 t = {0, 0, 0, 0};
-            if (q < L) t = *(const uint4*)(base + (size_t)q * ld + 16 * s + 8 * g);
-            qf[qb][s] = __builtin_bit_cast(bf16x8, t);
-        }
-#pragma unroll
-        for (int db = 0; db < 2; ++db)
-#pragma unroll
-            for (int e = 0; e < 16; ++e) o[qb][db][e] = 0.f;
-        mrun[qb] = -INFINITY;
-        lrun[qb] = 0.f;
-    }
+    const bf16* base = p.qkv + ((size_t)m * rows + t0) * ld + h * kD;
+    // Key tiles start at a token index that is a multiple of 8, so that the values can be fetched 16 bytes at a time; tokens in
+    // front of the sequence are masked.
+    const int lead = t0 & 7;
+    const bf16* vbase = p.vt + ((size_t)m * H + h * kD) * rows + (t0 - lead);
+    const int vlast = (L + lead - 1) & ~7;          // last chunk of eight tokens that holds one of the sequence
     const float sl2 = 0.125f * 1.44269504088896341f;   // 1/sqrt(64) * log2(e)
 
-    // Key tiles start at a token index that is a multiple of 8, so that the transposed values (token-contiguous
-    // rows) can be fetched 16 bytes at a time; tokens in front of the sequence are masked below.
-    const int lead = t0 & 7;
-    const bf16* vbase = vt + ((size_t)m * H + h * kD) * rows + (t0 - lead);
+    // 16-byte pieces of a tile per thread: rows tid / 8 and tid / 8 + 32, chunk tid % 8 in slot (tid % 8) ^ ((row / 2) % 8).  What lies
+    // outside the sequence repeats its first or last row (chunk): finite values that get probability zero.
     const int lrow = tid >> 3, lc = tid & 7;
-    uint4 kreg[2], vreg[2];
-    auto fetch = [&](int kt0) {                     // what lies beyond the sequence is zero-filled
+    int dst = lrow * 128 + ((lc ^ ((lrow >> 1) & 7)) << 4);
+    auto fetch_keys = [&](int kt0, bf16x8 (&r)[2]) {
 #pragma unroll
-        for (int p = 0; p < 2; ++p) {
-            const int r = lrow + 32 * p;            // key of the tile, or head dimension
-            kreg[p] = uint4{0, 0, 0, 0};
-            vreg[p] = uint4{0, 0, 0, 0};
-            if (kt0 + r >= 0 && kt0 + r < L) kreg[p] = *(const uint4*)(base + (ptrdiff_t)(kt0 + r) * (ptrdiff_t)ld + H + lc * 8);
-            if (kt0 + lc * 8 < L) vreg[p] = *(const uint4*)(vbase + (size_t)r * rows + (kt0 + lead) + lc * 8);
+        for (int i = 0; i < 2; ++i) {
+            int key = kt0 + lrow + 32 * i;
+            key = key < 0 ? 0 : (key < L ? key : L - 1);
+            r[i] = *(const bf16x8*)(base + ((unsigned)key * (unsigned)ld + (unsigned)(H + lc * 8)));
         }
     };
-    auto stage = [&](int buf) {                     // registers -> LDS buffer: keys [d-group of 8][key], values [d][key]
-        uint4* sK = (uint4*)(lds + buf * kLongTileBytes);
-        bf16* sVt = (bf16*)(lds + buf * kLongTileBytes + kLongKBytes);
+    auto fetch_values = [&](int kt0, bf16x8 (&r)[2]) {
+        const int c = kt0 + lead + lc * 8;
 #pragma unroll
-        for (int p = 0; p < 2; ++p) {
-            const int r = lrow + 32 * p;
-            sK[lc * kKStride + r] = kreg[p];
-            uint2* vd = (uint2*)(sVt + r * kVStride + lc * 8);
-            vd[0] = uint2{vreg[p].x, vreg[p].y};
-            vd[1] = uint2{vreg[p].z, vreg[p].w};
+        for (int i = 0; i < 2; ++i) r[i] = *(const bf16x8*)(vbase + ((unsigned)(lrow + 32 * i) * (unsigned)rows + (unsigned)(c < vlast ? c : vlast)));
+    };
+    // (values: the two halves of a lane's share of a reduction step, four keys each, side by side: half p of chunk c goes to half
+    // c % 2 of slot (c - c % 2 + p) ^ ...)
+    int vdst = kTileBytes + lrow * 128 + (((lc & 6) ^ ((lrow >> 1) & 7)) << 4) + 8 * (lc & 1);
+    auto stage_keys = [&](int to, const bf16x8 (&r)[2]) {
+#pragma unroll
+        for (int i = 0; i < 2; ++i) *(bf16x8*)(lds + to + i * 32 * 128) = r[i];
+    };
+    auto stage_values = [&](int to, const bf16x8 (&r)[2]) {
+#pragma unroll
+        for (int i = 0; i < 2; ++i) {
+            *(bf16x4*)(lds + to + i * 32 * 128) = bf16x4{r[i][0], r[i][1], r[i][2], r[i][3]};
+            *(bf16x4*)(lds + (to ^ 16) + i * 32 * 128) = bf16x4{r[i][4], r[i][5], r[i][6], r[i][7]};
         }
     };
-    const bool act1 = qw + 32 < L;                  // the wave's second query block exists (wave-uniform)
-    const bool act0 = qw < L;
-    fetch(-lead);
-    stage(0);
-    if (-lead + kKeyTile < L) fetch(-lead + kKeyTile);
-    barrier_lds();
-    int buf = 0;
-    for (int kt0 = -lead; kt0 < L; kt0 += kKeyTile, buf ^= 1) {
-        const uint4* sK = (const uint4*)(lds + buf * kLongTileBytes);
-        const bf16* sVt = (const bf16*)(lds + buf * kLongTileBytes + kLongKBytes);
-        if (act0) {
-            // scores of the wave's query blocks against the 64 keys: two 32x32 blocks each
-            f32x16 sc[2][2];
+    const int q = q0 + 32 * wave;                   // the wave's first query
+    bf16x8 qf[4], moving[2];
+    f32x16 o[2];
+    float mrun = -INFINITY, lrun = 0.f;             // running maximum (raw scores); sum over this lane's keys
+    // LDS offsets of this lane's row in the current buffer, slot g; slot g + 2 n is at offset ^ 32 n
+    int krow = j * 128 + ((g ^ ((j >> 1) & 7)) << 4), vrow = kTileBytes + krow;
+    auto scores = [&](int kb) {
+        f32x16 sc;
 #pragma unroll
-            for (int qb = 0; qb < 2; ++qb)
+        for (int e = 0; e < 16; ++e) sc[e] = 0.f;
 #pragma unroll
-                for (int kb = 0; kb < 2; ++kb)
+        for (int s4 = 0; s4 < 4; ++s4) {
+            const bf16x8 kf = *(const bf16x8*)(lds + (krow ^ (32 * s4)) + kb * 32 * 128);
+            sc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(kf, qf[s4], sc, 0, 0, 0);
+        }
+        return sc;
+    };
+    // Accumulator register v of this lane is key 8 (v / 4) + 4 g + v % 4 of its block.  Only the first and the last block of a
+    // sequence have keys to mask (k0: the block's first key, at least -7).
+    auto mask = [&](f32x16& sc, int k0) {
+        if (k0 >= 0 && k0 + 32 <= L) return;
+        const int g4 = 4 * g;
 #pragma unroll
-                    for (int e = 0; e < 16; ++e) sc[qb][kb][e] = 0.f;
+        for (int v = 0; v < 16; ++v) {
+            const int c = 8 * (v >> 2) + (v & 3);
+            bool ok = g4 < L - k0 - c;
+            if (v < 4) ok = ok && g4 >= -k0 - c;
+            if (!ok) sc[v] = -INFINITY;
+        }
+    };
+    // New maximum of the queries; what the sums so far have to be multiplied by (no rescaling where no maximum moves).
+    auto rescale = [&](float mx) {
+        mx = max_across_halves(mx);
+        float alpha = 1.f;
+        if (__any(mx > mrun)) {
+            mx = fmaxf(mx, mrun);
+            alpha = exp2_raw((mrun - mx) * sl2);    // first block: exp2(-inf) = 0
+            mrun = mx;
 #pragma unroll
-            for (int kb = 0; kb < 2; ++kb)
+            for (int db = 0; db < 2; ++db)
 #pragma unroll
-                for (int s = 0; s < 4; ++s) {
-                    const bf16x8 kf = __builtin_bit_cast(bf16x8, sK[(2 * s + g) * kKStride + kb * 32 + j]);
-                    sc[0][kb] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(kf, qf[0][s], sc[0][kb], 0, 0, 0);
-                    if (act1) sc[1][kb] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(kf, qf[1][s], sc[1][kb], 0, 0, 0);
-                }
-            // accumulator register v of this lane is key 8*(v/4) + 4*g + v%4 of its block; only the first and the
-            // last tile of a sequence have keys to mask
-            const bool edge = kt0 < 0 || kt0 + kKeyTile > L;
-            bf16x8 pf[2][2][2];
+                for (int e = 0; e < 16; ++e) o[db][e] *= alpha;
+        }
+        return alpha;
+    };
+    // probabilities of a block, and its values weighted with them: reduction slot e of step s2 is the key of register 8 s2 + e
+    auto weigh = [&](const f32x16& sc, int kb, float& psum) {
+        const float nm = -mrun * sl2;
+        bf16x8 pf[2];
 #pragma unroll
-            for (int qb = 0; qb < 2; ++qb) {
-                if (qb == 1 && !act1) continue;
-                float mx = mrun[qb];
-                if (edge) {
-                    // key kt0 + c + 4 g with c = 32 kb + 8 (v / 4) + v % 4 is valid if 0 <= key < L: the upper bound is
-                    // one comparison of the lane's 4 g with a uniform value; only the first four registers of block 0
-                    // can lie in front of the sequence (kt0 >= -7)
+        for (int v = 0; v < 16; ++v) {
+            const float e = exp2_raw(fmaf(sc[v], sl2, nm));
+            psum += e;
+            pf[v >> 3][v & 7] = (bf16)e;
+        }
 #pragma unroll
-                    for (int kb = 0; kb < 2; ++kb)
+        for (int s2 = 0; s2 < 2; ++s2)
 #pragma unroll
-                        for (int v = 0; v < 16; ++v) {
-                            const int c = kb * 32 + 8 * (v >> 2) + (v & 3);
-                            bool ok = g4 < L - kt0 - c;
-                            if (kb == 0 && v < 4) ok = ok && g4 >= -kt0 - c;
-                            if (!ok) sc[qb][kb][v] = -INFINITY;
-                        }
-                }
-#pragma unroll
-                for (int kb = 0; kb < 2; ++kb)
-#pragma unroll
-                    for (int v = 0; v < 16; ++v) mx = fmaxf(mx, sc[qb][kb][v]);
-                mx = max_across_halves(mx);                 // the other half of the query's keys
-                const float alpha = exp2_raw((mrun[qb] - mx) * sl2);   // first tile: exp2(-inf) = 0
-                mrun[qb] = mx;
-                const float nm = -mx * sl2;
-                float psum = 0.f;
-#pragma unroll
-                for (int kb = 0; kb < 2; ++kb)
-#pragma unroll
-                    for (int v = 0; v < 16; ++v) {
-                        const float p = exp2_raw(fmaf(sc[qb][kb][v], sl2, nm));
-                        psum += p;
-                        pf[qb][kb][v >> 3][v & 7] = (bf16)p;
-                    }
-                lrun[qb] = lrun[qb] * alpha + psum;
-#pragma unroll
-                for (int db = 0; db < 2; ++db)
-#pragma unroll
-                    for (int e = 0; e < 16; ++e) o[qb][db][e] *= alpha;
+            for (int db = 0; db < 2; ++db) {
+                const bf16x8 vf = *(const bf16x8*)(lds + (vrow ^ (64 * kb + 32 * s2)) + db * 32 * 128);
+                o[db] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(vf, pf[s2], o[db], 0, 0, 0);
             }
-            // O^T += V^T P^T.  Reduction slot e of k-step s2 in block kb is key
-            // 32*kb + 16*s2 + 8*(e/4) + 4*g + e%4, the key held by register 8*s2 + e above.
+    };
+    auto maximum = [](const f32x16& sc) {
+        float mx = sc[0];
 #pragma unroll
-            for (int kb = 0; kb < 2; ++kb)
-#pragma unroll
-                for (int s2 = 0; s2 < 2; ++s2) {
-                    const int kbase = kb * 32 + 16 * s2 + 4 * g;
-#pragma unroll
-                    for (int db = 0; db < 2; ++db) {
-                        const bf16* vr = sVt + (db * 32 + j) * kVStride + kbase;
-                        const bf16x4 lo = *(const bf16x4*)vr, hi = *(const bf16x4*)(vr + 8);
-                        const bf16x8 vf = {lo[0], lo[1], lo[2], lo[3], hi[0], hi[1], hi[2], hi[3]};
-                        o[0][db] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(vf, pf[0][kb][s2], o[0][db], 0, 0, 0);
-                        if (act1) o[1][db] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(vf, pf[1][kb][s2], o[1][db], 0, 0, 0);
-                    }
+        for (int v = 1; v < 16; ++v) mx = fmaxf(mx, sc[v]);
+        return mx;
+    };
+    const bool wide = L > kNarrowLen;
+    auto tile = [&](int kt0) {
+        const bool more = kt0 + kKeyTile < L, two = kt0 + 32 < L;
+        // (the other buffer is idle since the barrier of the previous tile)
+        auto next_keys = [&] {                      // keys of the next tile down, its values requested
+            if (!more) return;
+            stage_keys(dst ^ 2 * kTileBytes, moving);
+            fetch_values(kt0 + kKeyTile, moving);
+        };
+        if (q < L) {
+            f32x16 s0 = scores(0), s1;
+            if (two) s1 = scores(1);
+            next_keys();
+            mask(s0, kt0);
+            float mx = maximum(s0), mx1 = -INFINITY;
+            if (two) {
+                mask(s1, kt0 + 32);
+                mx1 = maximum(s1);
+            }
+            if (wide) mx = fmaxf(mx, mx1);
+            float alpha = rescale(mx), psum = 0.f;
+            weigh(s0, 0, psum);
+            if (two) {
+                if (!wide) {
+                    lrun = lrun * alpha + psum;
+                    psum = 0.f;
+                    alpha = rescale(mx1);
                 }
+                weigh(s1, 1, psum);
+            }
+            lrun = lrun * alpha + psum;
+        } else {
+            next_keys();
         }
-        if (kt0 + kKeyTile < L) {
-            stage(buf ^ 1);                         // (idle since the barrier of the previous tile)
-            if (kt0 + 2 * kKeyTile < L) fetch(kt0 + 2 * kKeyTile);
+        if (more) {
+            stage_values(vdst ^ 2 * kTileBytes, moving);
+            if (kt0 + 2 * kKeyTile < L) fetch_keys(kt0 + 2 * kKeyTile, moving);
         }
         barrier_lds();
-    }
-
-    // Each 32 x 64 output block leaves through a wave-private LDS tile (the key/value buffers are idle now) as whole
-    // 128-byte rows.
-    char* stg = lds + wave * (32 * kOutPitch);
+        dst ^= 2 * kTileBytes;
+        vdst ^= 2 * kTileBytes;
+        krow ^= 2 * kTileBytes;
+        vrow ^= 2 * kTileBytes;
+    };
+    {
+        bf16x8 k0[2], v0[2];
+        fetch_keys(-lead, k0);
+        fetch_values(-lead, v0);
+        const int r = q + j < L ? q + j : L - 1;
 #pragma unroll
-    for (int qb = 0; qb < 2; ++qb) {
-        const int qs = qw + 32 * qb;                // first query of the block
-        if (qs >= L) continue;
-        const float inv = 1.0f / sum_across_halves(lrun[qb]);
+        for (int s4 = 0; s4 < 4; ++s4) qf[s4] = *(const bf16x8*)(base + (size_t)r * ld + 16 * s4 + 8 * g);
+        if (kKeyTile - lead < L) fetch_keys(kKeyTile - lead, moving);
 #pragma unroll
         for (int db = 0; db < 2; ++db)
 #pragma unroll
-            for (int v4 = 0; v4 < 4; ++v4) {
-                bf16x4 w;
-#pragma unroll
-                for (int e = 0; e < 4; ++e) w[e] = (bf16)(o[qb][db][4 * v4 + e] * inv);
-                *(bf16x4*)(stg + j * kOutPitch + (db * 32 + 8 * v4 + 4 * g) * 2) = w;
-            }
-        __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-        __builtin_amdgcn_wave_barrier();
-        const int orow = lane >> 3, oc = lane & 7;
-        const size_t doff = ((size_t)m * rows + t0 + qs) * H + h * kD + oc * 8;
-#pragma unroll
-        for (int r0 = 0; r0 < 32; r0 += 8)
-            if (qs + r0 + orow < L) {
-                const uint4 c = *(const uint4*)(stg + (r0 + orow) * kOutPitch + oc * 16);
-                if (att) *(uint4*)(att + doff + (size_t)(r0 + orow) * H) = c;   // (null: the fp8 copy alone)
-                if (attq) *(uint2*)(attq + doff + (size_t)(r0 + orow) * H) = chunk_to_fp8(c, qscale);   // fp8 copy
-            }
-        __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
-        __builtin_amdgcn_wave_barrier();            // the tile is rewritten by the next block
+            for (int e = 0; e < 16; ++e) o[db][e] = 0.f;
+        stage_keys(dst, k0);
+        stage_values(vdst, v0);
     }
-}
+    barrier_lds();
+    for (int kt0 = -lead; kt0 < L; kt0 += kKeyTile) tile(kt0);
+    if (q >= L) return;
 
-
-// -------------------------------------------------------------------------------------
-// bf16 kernel for short sequences (the common case of the serving workloads: tens of tokens).  One wave = one
-// (student, sequence, head); the four waves of a workgroup take four heads of the same sequence and never
-// synchronise with each other: each wave stages its 32-key tiles in a private slice of LDS.  Same arithmetic as
-// the kernel above (S^T = K Q^T, online softmax per lane column, O^T += V^T P^T), 32 queries per pass; the next
-// key tile is fetched into registers while the current one is multiplied.
-// -------------------------------------------------------------------------------------
-constexpr int kSKey = 32;                 // keys per tile
-constexpr int kSKStride = kSKey + 1;      // 16-byte units per d-group of the key tile
-constexpr int kSVStride = 36;             // bf16 elements per row of the transposed value tile (72 B)
-static_assert(kD * kSVStride * 2 == 32 * (kSVStride * 4) && kSVStride * 4 >= kD * 2 + 16, "the value slice doubles as the 32 x 64 output staging tile");
-
-// QB: blocks of 32 queries a wave carries through one pass over the keys.  Every pass re-reads the sequence's keys and
-// values, and between the passes of a dozen waves per compute unit they do not survive in the L2 (measured: the bytes
-// fetched from beyond the L2 are those of one read of the queries plus one read of keys and values PER PASS), so
-// QB = 2 halves the passes of sequences of more than 32 tokens; it costs the registers of a second set of queries and
-// output accumulators (two waves per SIMD instead of three).
-constexpr int kShortKBytes = 8 * kSKStride * 16, kShortVBytes = kD * kSVStride * 2;   // per wave
-constexpr int kShortLdsBytes = 4 * (kShortKBytes + kShortVBytes);
-
-template <int QB>
-__device__ __forceinline__ void attention_short_body(char* lds, int bid, const bf16* __restrict__ qkv,
-                                                     const bf16* __restrict__ vt, bf16* __restrict__ att,
-                                                     const int32_t* __restrict__ cu, int B, int Tn, int rows, int H,
-                                                     int heads, int max_seqlen, int ngroups, int max_len,
-                                                     unsigned char* __restrict__ attq, float qscale)
-{
-    const int m = blockIdx.y;
-    // XCD-aware order (workgroup id mod 8 selects the XCD): each XCD takes a contiguous run of sequences, so that
-    // the lines of the token-contiguous value rows which neighbouring sequences share are fetched into one L2
-    const int total = B * ngroups, chunk = (total + 7) >> 3;
-    const int lin = (bid & 7) * chunk + (bid >> 3);
-    if ((bid >> 3) >= chunk || lin >= total) return;
-    const int b = lin / ngroups, hg = lin % ngroups;
-    const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-    const int h = hg * 4 + wave;
-    int t0 = cu[b], t1 = cu[b + 1];
-    t0 = t0 < 0 ? 0 : (t0 > Tn - 1 ? Tn - 1 : t0);
-    int L = t1 - t0;
-    L = L < 1 ? 1 : L;
-    L = L > max_seqlen ? max_seqlen : L;
-    L = L > Tn - t0 ? Tn - t0 : L;
-    if (L > max_len || h >= heads) return;         // long sequences belong to the cooperative kernel
-    uint4* sK = (uint4*)(lds + wave * kShortKBytes);
-    bf16* sVt = (bf16*)(lds + 4 * kShortKBytes + wave * kShortVBytes);
-
-    const int j = lane & 31, g = lane >> 5;
-    const int g4 = 4 * g;
-    const size_t ld = (size_t)3 * H;
-    const bf16* base = qkv + ((size_t)m * rows + t0) * ld + h * kD;
-    const float sl2 = 0.125f * 1.44269504088896341f;
-    const int lkey = lane >> 3, lc = lane & 7;      // key loader: 8 keys x 8 sixteen-byte chunks per instruction
-    const int vrow = lane >> 2, vc = lane & 3;      // value loader: 16 head dimensions x 4 chunks of 8 keys
-    // key tiles start at a token index that is a multiple of 8 (16-byte fetches of the token-contiguous values);
-    // tokens in front of the sequence are masked
-    const int lead = t0 & 7;
-    const bf16* vbase = vt + ((size_t)m * H + h * kD) * rows + (t0 - lead);
-
-    for (int q0 = 0; q0 < L; q0 += 32 * QB) {
-        // query block qb covers queries q0 + 32 qb .. + 31; it is skipped as a whole (wave-uniform) if it lies beyond
-        // the sequence
-        bf16x8 qf[QB][4];
-        f32x16 o[QB][2];
-        float mrun[QB], lrun[QB];
+    // The 32 x 64 output block leaves through a wave-private LDS tile (the key/value buffers are idle) as whole 128-byte rows.
+    int ln = tid;
+    asm volatile("" : "+v"(ln));                    // (what follows from it is not kept through the loop)
+    const int stg = wave * (32 * kOutPitch), oq = ln & 31, og = ln >> 5 & 1, orow = ln >> 3 & 7, oc = ln & 7;
+    const float inv = 1.0f / sum_across_halves(lrun);
 #pragma unroll
-        for (int qb = 0; qb < QB; ++qb) {
-            const int q = q0 + 32 * qb + j;
+    for (int db = 0; db < 2; ++db)
 #pragma unroll
-            for (int s = 0; s < 4; ++s) {
-                uint4 t = {0, 0, 0, 0};
-                if (q < L) t = *(const uint4*)(base + (size_t)q * ld + 16 * s + 8 * g);
-                qf[qb][s] = __builtin_bit_cast(bf16x8, t);
-            }
+        for (int v4 = 0; v4 < 4; ++v4) {
+            bf16x4 w;
 #pragma unroll
-            for (int db = 0; db < 2; ++db)
-#pragma unroll
-                for (int e = 0; e < 16; ++e) o[qb][db][e] = 0.f;
-            mrun[qb] = -INFINITY;
-            lrun[qb] = 0.f;
+            for (int e = 0; e < 4; ++e) w[e] = (bf16)(o[db][4 * v4 + e] * inv);
+            *(bf16x4*)(lds + stg + oq * kOutPitch + (db * 32 + 8 * v4 + 4 * og) * 2) = w;
         }
-
-        uint4 kreg[4], vreg[4];
-        auto fetch = [&](int kt0) {                  // kt0: first key of the tile relative to the sequence start
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+    const size_t at = ((size_t)m * rows + t0 + q) * H + h * kD + oc * 8;
 #pragma unroll
-            for (int p = 0; p < 4; ++p) {
-                const int key = kt0 + p * 8 + lkey;
-                kreg[p] = uint4{0, 0, 0, 0};
-                vreg[p] = uint4{0, 0, 0, 0};
-                if (key >= 0 && key < L) kreg[p] = *(const uint4*)(base + (ptrdiff_t)key * (ptrdiff_t)ld + H + lc * 8);
-                if (kt0 + vc * 8 < L) vreg[p] = *(const uint4*)(vbase + (size_t)(p * 16 + vrow) * rows + (kt0 + lead) + vc * 8);
-            }
-        };
-        fetch(-lead);
-        for (int kt0 = -lead; kt0 < L; kt0 += kSKey) {
-            // registers -> this wave's LDS slice (what lies beyond the sequence was fetched as zeros)
-#pragma unroll
-            for (int p = 0; p < 4; ++p) {
-                sK[lc * kSKStride + p * 8 + lkey] = kreg[p];
-                uint2* vd = (uint2*)(sVt + (p * 16 + vrow) * kSVStride + vc * 8);
-                vd[0] = uint2{vreg[p].x, vreg[p].y};
-                vd[1] = uint2{vreg[p].z, vreg[p].w};
-            }
-            if (kt0 + kSKey < L) fetch(kt0 + kSKey);
-            __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-            __builtin_amdgcn_wave_barrier();
-
-#pragma unroll
-            for (int qb = 0; qb < QB; ++qb) {
-                if (qb > 0 && q0 + 32 * qb >= L) continue;
-                f32x16 sc;
-#pragma unroll
-                for (int e = 0; e < 16; ++e) sc[e] = 0.f;
-#pragma unroll
-                for (int s = 0; s < 4; ++s) {
-                    const uint4 t = sK[(2 * s + g) * kSKStride + j];
-                    sc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8, t), qf[qb][s], sc, 0, 0, 0);
-                }
-                float mx = mrun[qb];
-#pragma unroll
-                for (int v = 0; v < 16; ++v) {
-                    // key kt0 + c + 4 g, c = 8 (v / 4) + v % 4, is valid if 0 <= key < L: one comparison of the lane's
-                    // 4 g with a uniform value; only the first four registers can lie in front of the sequence
-                    const int c = 8 * (v >> 2) + (v & 3);
-                    bool ok = g4 < L - kt0 - c;
-                    if (v < 4) ok = ok && g4 >= -kt0 - c;
-                    const float sv = ok ? sc[v] : -INFINITY;
-                    sc[v] = sv;
-                    mx = fmaxf(mx, sv);
-                }
-                mx = max_across_halves(mx);
-                // (running maximum on the raw scores; the 1/sqrt(d) log2(e) factor rides in the multiply-add in front of
-                // the exponential)
-                const float alpha = exp2_raw((mrun[qb] - mx) * sl2);
-                mrun[qb] = mx;
-                const float nm = -mx * sl2;
-                float psum = 0.f;
-                bf16x8 pf[2];
-#pragma unroll
-                for (int v = 0; v < 16; ++v) {
-                    const float p = exp2_raw(fmaf(sc[v], sl2, nm));
-                    psum += p;
-                    pf[v >> 3][v & 7] = (bf16)p;
-                }
-                lrun[qb] = lrun[qb] * alpha + psum;
-#pragma unroll
-                for (int db = 0; db < 2; ++db)
-#pragma unroll
-                    for (int e = 0; e < 16; ++e) o[qb][db][e] *= alpha;
-#pragma unroll
-                for (int s2 = 0; s2 < 2; ++s2) {
-                    const int kbase = 16 * s2 + 4 * g;
-#pragma unroll
-                    for (int db = 0; db < 2; ++db) {
-                        const bf16* vr = sVt + (db * 32 + j) * kSVStride + kbase;
-                        const bf16x4 lo = *(const bf16x4*)vr, hi = *(const bf16x4*)(vr + 8);
-                        const bf16x8 vf = {lo[0], lo[1], lo[2], lo[3], hi[0], hi[1], hi[2], hi[3]};
-                        o[qb][db] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(vf, pf[s2], o[qb][db], 0, 0, 0);
-                    }
-                }
-            }
-            __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
-            __builtin_amdgcn_wave_barrier();       // the slice is rewritten at the top of the next iteration
+    for (int r0 = 0; r0 < 32; r0 += 8)
+        if (q + r0 + orow < L) {
+            const uint4 c = *(const uint4*)(lds + stg + (r0 + orow) * kOutPitch + oc * 16);
+            if (p.att) *(uint4*)(p.att + at + (size_t)(r0 + orow) * H) = c;   // (null: the fp8 copy alone)
+            if (p.attq) *(uint2*)(p.attq + at + (size_t)(r0 + orow) * H) = chunk_to_fp8(c, p.qscale);
         }
-        // A 32 x 64 output block leaves through this wave's (now idle) value slice, so that a store instruction
-        // writes eight whole 128-byte rows (eight-byte pieces of 32 rows per instruction are several times slower
-        // on the way to memory).
-#pragma unroll
-        for (int qb = 0; qb < QB; ++qb) {
-            const int qs = q0 + 32 * qb;                    // first query of the block
-            if (qb > 0 && qs >= L) continue;
-            const float inv = 1.0f / sum_across_halves(lrun[qb]);
-            char* stg = (char*)sVt;                         // 32 rows of 144 bytes = the whole slice
-#pragma unroll
-            for (int db = 0; db < 2; ++db)
-#pragma unroll
-                for (int v4 = 0; v4 < 4; ++v4) {
-                    bf16x4 w;
-#pragma unroll
-                    for (int e = 0; e < 4; ++e) w[e] = (bf16)(o[qb][db][4 * v4 + e] * inv);
-                    *(bf16x4*)(stg + j * (kSVStride * 4) + (db * 32 + 8 * v4 + 4 * g) * 2) = w;
-                }
-            __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-            __builtin_amdgcn_wave_barrier();
-            const int orow = lane >> 3, oc = lane & 7;
-            const size_t doff = ((size_t)m * rows + t0 + qs) * H + h * kD + oc * 8;
-#pragma unroll
-            for (int r0 = 0; r0 < 32; r0 += 8)
-                if (qs + r0 + orow < L) {
-                    const uint4 c = *(const uint4*)(stg + (r0 + orow) * (kSVStride * 4) + oc * 16);
-                    if (att) *(uint4*)(att + doff + (size_t)(r0 + orow) * H) = c;   // (null: the fp8 copy alone)
-                    if (attq) *(uint2*)(attq + doff + (size_t)(r0 + orow) * H) = chunk_to_fp8(c, qscale);   // fp8 copy
-                }
-            __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
-            __builtin_amdgcn_wave_barrier();                // the slice is rewritten by the next block / pass
-        }
-    }
-}
-
-template <int QB>
-__global__ __launch_bounds__(256, QB == 1 ? 3 : 2) void attention_bf16_short_kernel(
-    const bf16* __restrict__ qkv, const bf16* __restrict__ vt, bf16* __restrict__ att, const int32_t* __restrict__ cu,
-    int B, int Tn, int rows, int H, int heads, int max_seqlen, int ngroups, int max_len,
-    unsigned char* __restrict__ attq, float qscale)
-{
-    __shared__ __attribute__((aligned(16))) char lds[kShortLdsBytes];
-    attention_short_body<QB>(lds, (int)blockIdx.x, qkv, vt, att, cu, B, Tn, rows, H, heads, max_seqlen, ngroups, max_len,
-                             attq, qscale);
-}
-
-// Batches with sequences on both sides of the split: one launch.  The first nlong workgroup ids (a multiple of 8, so
-// the id-to-XCD relation of both bodies is kept) are the cooperative kernel's (sequence, head, query block) items,
-// most of which leave at once; the rest are the per-wave kernel's.  The few long items start first and run beside
-// the many short ones instead of in a launch of their own that cannot fill the chip.
-__global__ __launch_bounds__(256, 2) void attention_bf16_kernel(const bf16* __restrict__ qkv, const bf16* __restrict__ vt,
-                                                                bf16* __restrict__ att, const int32_t* __restrict__ cu,
-                                                                int B, int Tn, int rows, int H, int heads,
-                                                                int max_seqlen, int nqc, int ngroups, int split_len,
-                                                                int nlong, unsigned char* __restrict__ attq,
-                                                                float qscale)
-{
-    constexpr int kBytes = kLongLdsBytes > kShortLdsBytes ? kLongLdsBytes : kShortLdsBytes;
-    __shared__ __attribute__((aligned(16))) char lds[kBytes];
-    const int bid = (int)blockIdx.x;
-    if (bid < nlong)
-        attention_long_body(lds, bid, qkv, vt, att, cu, B, Tn, rows, H, heads, max_seqlen, nqc, split_len, attq, qscale);
-    else
-        attention_short_body<2>(lds, bid - nlong, qkv, vt, att, cu, B, Tn, rows, H, heads, max_seqlen, ngroups,
-                                split_len, attq, qscale);
 }
 
 // -------------------------------------------------------------------------------------
@@ -794,30 +613,13 @@ hipError_t launch_attention(const sp_model* M, const void* qkv, const void* vt, 
     if (c.hidden / c.heads != kD) return hipErrorInvalidValue;
     if (!att && !(attq && bf16_path(c))) return hipErrorInvalidValue;   // (no bf16 output: the fp8 copy alone)
     if (bf16_path(c)) {
-        // Sequences of up to 128 tokens: one wave per (sequence, head); longer ones: one workgroup per (sequence,
-        // head, 128 queries) sharing the key/value tiles.  Each kernel skips the other's sequences.  (Giving the long
-        // sequences of a serving batch to the per-wave kernel as well was measured slower: a 256-token sequence is 72
-        // tile iterations in one wave, a long tail behind the ~5 of a typical one.)
-        const int kShortLen = 128;
-        const int ngroups = (c.heads + 3) / 4;
-        const unsigned nshort = (unsigned)((B * ngroups + 7) / 8 * 8);
-        if (max_seqlen > kShortLen) {
-            const int nqc = (max_seqlen + kQPerWg - 1) / kQPerWg;
-            const unsigned nlong = (unsigned)((B * c.heads + 7) / 8 * 8 * nqc);
-            hipLaunchKernelGGL(attention_bf16_kernel, dim3(nlong + nshort, k), dim3(256), 0, s, (const bf16*)qkv,
-                               (const bf16*)vt, (bf16*)att, cu, B, T, rows, c.hidden, c.heads, max_seqlen, nqc, ngroups,
-                               kShortLen, (int)nlong, (unsigned char*)attq, qscale);
-        } else if (max_seqlen > 32) {
-            // two query blocks per pass wherever a sequence can have more than one (burst workload: 0.330 -> 0.280 ms
-            // for the attention phase; four blocks, one wave per SIMD: 0.353 ms)
-            hipLaunchKernelGGL(attention_bf16_short_kernel<2>, dim3(nshort, k), dim3(256), 0, s, (const bf16*)qkv,
-                               (const bf16*)vt, (bf16*)att, cu, B, T, rows, c.hidden, c.heads, max_seqlen, ngroups,
-                               kShortLen, (unsigned char*)attq, qscale);
-        } else {
-            hipLaunchKernelGGL(attention_bf16_short_kernel<1>, dim3(nshort, k), dim3(256), 0, s, (const bf16*)qkv,
-                               (const bf16*)vt, (bf16*)att, cu, B, T, rows, c.hidden, c.heads, max_seqlen, ngroups,
-                               kShortLen, (unsigned char*)attq, qscale);
-        }
+        // Runs of neighbouring items that stay on one XCD: 1, 2, 4, 8 and 16 measured 208 / 208 / 207 / 210 / 211 us on 371 items of
+        // short sequences (eight students), 325 / 322 / 326 / 328 / 347 on 208 of long ones (six); few items go round one by one.
+        AttnArgs a{(const bf16*)qkv, (const bf16*)vt, (bf16*)att, (unsigned char*)attq, cu, qscale, B, T, rows, c.hidden, c.heads,
+                   max_seqlen, T / kQItem + B, 1};
+        a.run = a.items < 128 ? 1 : (a.items < 256 ? 2 : 4);
+        const int nitems = (a.items + 8 * a.run - 1) / (8 * a.run) * (8 * a.run);
+        hipLaunchKernelGGL(attention_bf16_kernel, dim3((unsigned)(nitems * c.heads), k), dim3(256), 0, s, a);
     } else {
         const int nqc = (max_seqlen + 63) / 64;
         dim3 grid((unsigned)(B * c.heads * nqc), k);

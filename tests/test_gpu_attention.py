@@ -1,0 +1,42 @@
+"""All-token attention (bf16 path) at the edges of its key tiles and work items.  Needs an MI355X."""
+import numpy as np
+import pytest
+import torch
+
+from paper_2408_12526_amd import synth
+
+pytestmark = pytest.mark.gpu
+
+CASES = {
+    # a tile's and an item's last token and the one behind it, behind sequences that shift the first key tile by 0 to 7 tokens
+    "tile_edges": (1, 56, 57, 1, 58, 63, 64, 2, 65, 71, 72, 3, 120, 121, 127, 128, 129, 1, 136, 192, 193, 255, 256, 1, 257, 32, 33),
+    # one, two and three looks at the boundaries; empty work items
+    "64_sequences": (3, 130, 1, 40) * 16,
+    "65_sequences": (3, 130, 1, 40) * 16 + (129,),
+    "4097_sequences": (1,) * 2000 + (2,) * 2096 + (300,),
+}
+
+
+@pytest.mark.parametrize("name", list(CASES))
+@pytest.mark.parametrize("qk_std", [0.12, 0.6])         # 0.6: scores that outgrow the first block's maximum by far more than 2^8
+def test_attention_at_tile_and_item_edges(oracle64, name, qk_std):
+    """Attention output against the oracle's attention on the queries, keys and values that the projection left: one rounding of
+    the probabilities and one of the output, relative to the tensor's largest magnitude (the bound of the stage tests)."""
+    from paper_2408_12526_amd import sp
+    shape = synth.StudentShape(K=2, layers=1, hidden=128, heads=2, ffn=128, vocab=100, max_pos=320, classes=2, dtype="bf16")
+    lengths = np.array(CASES[name], np.int32)
+    rng = np.random.default_rng(len(lengths))
+    ids, blob = synth.make_ids(rng, int(lengths.sum()), shape.vocab), synth.make_weights(rng, shape, std=0.08, qk_std=qk_std)
+    st = sp.Students(sp.config_from_shape(shape), blob)
+    cu, k, H = sp.sp_pack(lengths), shape.K, shape.hidden
+    T, B = int(cu[-1]), len(lengths)
+    ws = st.sp_forward_partial(torch.from_numpy(ids).cuda(), torch.from_numpy(cu).cuda(), int(lengths.max()), k, 1)
+    qkv, att = st.read_activation(ws, "qkv", T, B, k), st.read_activation(ws, "att", T, B, k)
+    pick = range(B) if B < 200 else np.r_[0:50, 1980:2020, B - 50:B]
+    for m in range(k):
+        for b in pick:
+            a = qkv[m][cu[b]:cu[b + 1]]
+            want = oracle64.attention(a[:, :H], a[:, H:2 * H], a[:, 2 * H:], shape.heads)
+            err = np.abs(att[m][cu[b]:cu[b + 1]] - want).max() / np.abs(want).max()
+            assert err < 1.2e-2, f"student {m}, sequence {b} of {lengths[b]} tokens at {cu[b]}: {err:.3e}"
+    st.close()
