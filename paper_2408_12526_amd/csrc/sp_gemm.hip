@@ -14,15 +14,15 @@ __device__ inline float gelu_erf(float u) { return 0.5f * u * (1.0f + erff(u * 0
 
 // -------------------------------------------------------------------------------------
 // bf16 MFMA kernel with the weights in registers (v_mfma_f32_32x32x16_bf16): tile 32 TM tokens x 64 NW features, NW waves,
-// each with all the tile's tokens and 64 features of its own; two workgroups per compute unit.
+// each with all the tile's tokens and 64 features of its own; two workgroups per compute unit.  D: k-tiles of weights in flight.
 //
 // Operand roles are swapped with respect to the textbook picture: the weights are the MFMA "A" operand (rows = output
 // features) and the activations the "B" operand (columns = tokens), so a lane of the 32x32 accumulator owns one token and
 // runs of four consecutive features.
 //   * weights: a feature's weights are used by one wave only, so they go from memory straight to its registers, in operand
 //     blocks (see ArenaLayout: a load is 256-byte runs).  A step's registers are requested again, for the next k-tile of 64
-//     reduction elements, as soon as its matrix instructions are issued: four steps (1024 matrix-core cycles at 128 tokens) to
-//     arrive, twice that while the other workgroup has the matrix cores.
+//     reduction elements (D = 2: the one after), as soon as its matrix instructions are issued: four steps (1024 matrix-core
+//     cycles at 128 tokens) to arrive, twice that while the other workgroup has the matrix cores.
 //   * activations: through registers into one of two LDS stages (rows of eight 16-byte slots; slot s of row r holds chunk
 //     s ^ ((r >> 1) & 7): no bank conflicts), one barrier per k-tile that waits for LDS traffic only, requested two k-tiles
 //     ahead.  Ordinary loads throughout: with direct-to-LDS loads in flight the compiler waits for everything before the
@@ -58,9 +58,10 @@ struct GemmArgs {
     size_t slice;                     // EPI_PARTIAL: elements between the slices of a split reduction
 };
 
-template <int TM, int NW, int EPI>
-__global__ __launch_bounds__(64 * NW, 2) void gemm_wreg_kernel(GemmArgs p)
+template <int TM, int NW, int D, int EPI>
+__global__ __launch_bounds__(64 * NW, D > 1 ? 1 : 2) void gemm_wreg_kernel(GemmArgs p)
 {
+    static_assert(D == 1 || D == 2, "the k-tiles are an even number");
     constexpr int BM = 32 * TM, BN = 64 * NW, NA = TM * 4 / NW;   // NA: 16-byte pieces of an activation k-tile per thread
     constexpr int STAGE = BM * 8;                           // 16-byte units
     constexpr int TKEY = TM == 3 ? 3 : TM * 4 - 1;          // swizzle of the transposed staging: bits of the chunk
@@ -95,19 +96,19 @@ __global__ __launch_bounds__(64 * NW, 2) void gemm_wreg_kernel(GemmArgs p)
     const bf16* Wg = (const bf16*)(sb + p.w_off) + (size_t)(nf >> 4) * 16 * Kd + (EPI == EPI_PARTIAL ? (size_t)sp * p.Kper * 16 : 0);
     const unsigned wlane = (unsigned)((j31 >> 4) * 16 * Kd + g * 128 + (j31 & 15) * 8);
 
-    bf16x8 w[4][2];
-    u32x4 ar[NA];
-    auto load_a = [&](int kt) {
+    bf16x8 w[D][4][2];
+    u32x4 ar[D][NA];
+    auto load_a = [&](int kt, int slot) {
 #pragma unroll
-        for (int i = 0; i < NA; ++i) ar[i] = *(const u32x4*)(Ag + kt * 64 + aoff[i]);
+        for (int i = 0; i < NA; ++i) ar[slot][i] = *(const u32x4*)(Ag + kt * 64 + aoff[i]);
     };
-    auto load_w = [&](int kt, int s) {
+    auto load_w = [&](int kt, int slot, int s) {
 #pragma unroll
-        for (int i = 0; i < 2; ++i) w[s][i] = *(const bf16x8*)(Wg + (size_t)i * 32 * Kd + kt * 1024 + s * 256 + wlane);
+        for (int i = 0; i < 2; ++i) w[slot][s][i] = *(const bf16x8*)(Wg + (size_t)i * 32 * Kd + kt * 1024 + s * 256 + wlane);
     };
-    auto write_a = [&](int buf) {
+    auto write_a = [&](int buf, int slot) {
 #pragma unroll
-        for (int i = 0; i < NA; ++i) *(u32x4*)(smem + buf * STAGE + adst[i]) = ar[i];
+        for (int i = 0; i < NA; ++i) *(u32x4*)(smem + buf * STAGE + adst[i]) = ar[slot][i];
     };
     int xoff[TM];
 #pragma unroll
@@ -117,7 +118,7 @@ __global__ __launch_bounds__(64 * NW, 2) void gemm_wreg_kernel(GemmArgs p)
     auto frag = [&](int buf, int s, int t) { return *(const bf16x8*)(smem + buf * STAGE + xoff[t] + ((2 * s + g) ^ xkey)); };
 
     f32x16 acc[2][TM];
-    load_a(0);
+    load_a(0, 0);
     {
         const float* bias = (const float*)(sb + p.b_off) + nf + 4 * g;
 #pragma unroll
@@ -133,17 +134,27 @@ __global__ __launch_bounds__(64 * NW, 2) void gemm_wreg_kernel(GemmArgs p)
     }
     __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
-    for (int s = 0; s < 4; ++s) load_w(0, s);
+    for (int s = 0; s < 4; ++s) load_w(0, 0, s);
     __builtin_amdgcn_sched_barrier(0);
-    write_a(0);
+#pragma unroll
+    for (int d = 1; d < D; ++d) {
+        load_a(d, d);
+#pragma unroll
+        for (int s = 0; s < 4; ++s) load_w(d, d, s);
+        __builtin_amdgcn_sched_barrier(0);
+    }
+    write_a(0, 0);
     __builtin_amdgcn_sched_barrier(0);
-    load_a(1);
+    load_a(D < nk ? D : nk - 1, 0);
     barrier_lds();
 #pragma unroll
     for (int t = 0; t < TM; ++t) fx[0][t] = frag(0, 0, t);
 
-    auto ktile = [&](int j, int buf, auto next_c, auto next2_c) {
-        constexpr bool NEXT = decltype(next_c)::value, NEXT2 = decltype(next2_c)::value;
+    // One k-tile: j, slot = j % D.  W: k-tile j + D exists; AW, AL: so do j + 1 and j + 1 + D.
+    auto ktile = [&](int j, auto slot_c, auto w_c, auto aw_c, auto al_c) {
+        constexpr int slot = decltype(slot_c)::value, next = (slot + 1) % D;
+        constexpr bool W = decltype(w_c)::value, AW = decltype(aw_c)::value, AL = decltype(al_c)::value;
+        const int buf = D % 2 == 0 ? slot & 1 : j & 1;
 #pragma unroll
         for (int s = 0; s < 4; ++s) {
             if (s == 3) barrier_lds();
@@ -151,28 +162,48 @@ __global__ __launch_bounds__(64 * NW, 2) void gemm_wreg_kernel(GemmArgs p)
 #pragma unroll
             for (int t = 0; t < TM; ++t) {
                 if (s < 3) fx[(s + 1) & 1][t] = frag(buf, s + 1, t);
-                else if (NEXT) fx[0][t] = frag(buf ^ 1, 0, t);
+                else if (AW) fx[0][t] = frag(buf ^ 1, 0, t);
 #pragma unroll
-                for (int i = 0; i < 2; ++i) acc[i][t] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(w[s][i], fx[s & 1][t], acc[i][t], 0, 0, 0);
+                for (int i = 0; i < 2; ++i) acc[i][t] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(w[slot][s][i], fx[s & 1][t], acc[i][t], 0, 0, 0);
                 __builtin_amdgcn_sched_barrier(0);
             }
-            if (NEXT) load_w(j + 1, s);
-            if (s == 1 && NEXT) {
-                write_a(buf ^ 1);
-                if (NEXT2) load_a(j + 2);
+            if (W) load_w(j + D, slot, s);
+            if (s == 1 && AW) {
+                write_a(buf ^ 1, next);
+                if (AL) load_a(j + 1 + D, next);
             }
             __builtin_amdgcn_sched_barrier(0);
         }
     };
+    // D k-tiles from j on (nk is a multiple of D)
+    auto ktiles = [&](int j, auto w_c, auto al_c) {
+        constexpr bool W = decltype(w_c)::value, AL = decltype(al_c)::value;
+        auto one = [&](auto slot_c) {
+            constexpr int slot = decltype(slot_c)::value;
+            constexpr bool last = slot == D - 1;
+            ktile(j + slot, slot_c, w_c, std::bool_constant<W || !last>{}, std::bool_constant<W && (AL || !last)>{});
+        };
+        one(std::integral_constant<int, 0>{});
+        if constexpr (D > 1) one(std::integral_constant<int, 1>{});
+    };
     constexpr std::true_type Y{};
     constexpr std::false_type N{};
     int j = 0;
-    for (; j + 2 < nk; j += 2) {                            // (nk is even)
-        ktile(j, 0, Y, Y);
-        ktile(j + 1, 1, Y, Y);
+    if constexpr (D == 1) {
+        for (; j + 2 < nk; j += 2) {                        // (nk is even)
+            ktiles(j, Y, Y);
+            ktiles(j + 1, Y, Y);
+        }
+        ktiles(j, Y, N);
+        ktiles(j + 1, N, N);
+    } else {
+        for (; j + 2 * D < nk; j += D) ktiles(j, Y, Y);
+        if (j + D < nk) {
+            ktiles(j, Y, N);
+            j += D;
+        }
+        ktiles(j, N, N);
     }
-    ktile(j, 0, Y, N);
-    ktile(j + 1, 1, N, N);
 
     // ---- epilogue: accumulator element v of lane l in block (i, t): token 32 t + l % 32, feature 32 i + 8 (v / 4) +
     // 4 (l / 32) + v % 4.  Each wave stages its tile in its own slice of LDS and stores whole row segments.
@@ -259,11 +290,11 @@ __global__ __launch_bounds__(64 * NW, 2) void gemm_wreg_kernel(GemmArgs p)
     }
 }
 
-template <int TM, int NW, int EPI>
+template <int TM, int NW, int D, int EPI>
 hipError_t launch_wreg_tile(const sp_model* M, GemmArgs a, int N, int k, hipStream_t s)
 {
     constexpr size_t smem = (size_t)32 * TM * 128 * (NW < 2 ? 2 : NW);
-    auto kern = gemm_wreg_kernel<TM, NW, EPI>;
+    auto kern = gemm_wreg_kernel<TM, NW, D, EPI>;
     if (smem > 48 * 1024) {
         static std::atomic<bool> raised{false};
         if (!raised.load(std::memory_order_acquire)) {
@@ -314,16 +345,26 @@ hipError_t launch_bf16(const sp_model* M, const GemmArgs& a, int N, int k, hipSt
     if (N % 256 || a.n_split % 256) {
         const long wide = (long)(N / 128) * k * a.splits;
         switch (tile_height(a.mrows, wide, 512, (a.mrows + 95) / 96 * wide >= 1024 ? 3 : 2)) {
-            case 1: return launch_wreg_tile<1, 2, EPI>(M, a, N, k, s);
-            case 2: return launch_wreg_tile<2, 2, EPI>(M, a, N, k, s);
-            default: return launch_wreg_tile<3, 2, EPI>(M, a, N, k, s);
+            case 1: return launch_wreg_tile<1, 2, 1, EPI>(M, a, N, k, s);
+            case 2: return launch_wreg_tile<2, 2, 1, EPI>(M, a, N, k, s);
+            default: return launch_wreg_tile<3, 2, 1, EPI>(M, a, N, k, s);
         }
     }
+    // Few tiles: a workgroup is alone on its compute unit, and what a launch takes is its chain of k-tiles, each of which waits for
+    // its weights.  Half the features per tile bring twice the workgroups, and two k-tiles of weights are in flight: 32 tokens
+    // while those are at most a workgroup per compute unit, 64 (the weights read half as often) while that holds there.  us, 32 x
+    // 256 with one k-tile in flight / 32 x 128 / 64 x 128: 2304 features from 768, 192 rows x 2 students 8.3 / 5.9 / 8.2, 64 x 4 8.3 /
+    // 5.9 / 8.0, 64 x 8 12.1 / 12.1 / 10.2; 3072 features, 256 rows x 1 8.4 / 6.5 / 9.0, 64 x 8 14.0 / 14.0 / 12.6; with one k-tile in
+    // flight 32 x 128 takes 7.7 for the first.  (Four in flight: no change.  Taller tiles of 256 features, alone or two to a unit:
+    // none from two in flight, -4 to +25 %.)
+    const long half = (long)(N / 128) * k * a.splits;
+    if ((a.mrows + 31) / 32 * half <= 256) return launch_wreg_tile<1, 2, 2, EPI>(M, a, N, k, s);
+    if ((a.mrows + 63) / 64 * half <= 256) return launch_wreg_tile<2, 2, 2, EPI>(M, a, N, k, s);
     switch (gemm_tile_height(a.mrows, N, k * a.splits)) {
-        case 1: return launch_wreg_tile<1, 4, EPI>(M, a, N, k, s);
-        case 2: return launch_wreg_tile<2, 4, EPI>(M, a, N, k, s);
-        case 3: return launch_wreg_tile<3, 4, EPI>(M, a, N, k, s);
-        default: return launch_wreg_tile<4, 4, EPI>(M, a, N, k, s);
+        case 1: return launch_wreg_tile<1, 4, 1, EPI>(M, a, N, k, s);
+        case 2: return launch_wreg_tile<2, 4, 1, EPI>(M, a, N, k, s);
+        case 3: return launch_wreg_tile<3, 4, 1, EPI>(M, a, N, k, s);
+        default: return launch_wreg_tile<4, 4, 1, EPI>(M, a, N, k, s);
     }
 }
 
