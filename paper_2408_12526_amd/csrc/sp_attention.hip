@@ -525,16 +525,21 @@ __global__ __launch_bounds__(512, HEADS == 16 ? 2 : 4) void attention_first_fold
 }
 
 // -------------------------------------------------------------------------------------
-// fp32 kernel: one workgroup per (student, sequence, head, block of 64 queries); four neighbouring lanes share a query,
-// sixteen of the head's 64 dimensions each (the score is summed over the quad, every lane rescales and accumulates its
-// own sixteen output dimensions).  Keys and values come through LDS in chunks of 64 tokens; all lanes of a wave read
-// the same key row (a broadcast).  Online softmax in registers, exact exponentials and division.
+// fp32 kernel: one workgroup per (student, sequence, head, block of 256 / LQ queries); LQ neighbouring lanes share a query,
+// 64 / LQ of the head's dimensions each (a score is summed over them, every lane rescales and accumulates its own output
+// dimensions).  Keys and values come through LDS in chunks of 64 tokens; the queries of a wave read the same key row (a
+// broadcast).  Online softmax in registers by blocks of eight keys, whose scores do not wait for one another; exact
+// exponentials and division.
+// Bound by latency in small calls (two launches of them are a third of the smallest fp32 call): a chain of keys per query, so
+// sixteen lanes share one while the workgroups are few; four (fewer instructions in all) where they fill the chip.  us, key by key
+// with four lanes / this: two students, four sequences of 8-32 tokens 10.8 / 6.0.
 // -------------------------------------------------------------------------------------
+template <int LQ>
 __global__ __launch_bounds__(256) void attention_f32_kernel(const float* __restrict__ qkv, float* __restrict__ att,
                                                             const int32_t* __restrict__ cu, int B, int Tn, int rows,
                                                             int H, int heads, int max_seqlen, int nqc)
 {
-    constexpr int KC = 64, DP = kD / 4;                     // keys per chunk; dimensions per lane
+    constexpr int KC = 64, DP = kD / LQ, QW = 256 / LQ, KB = 8;   // keys per chunk; dimensions per lane; queries per workgroup; keys per block
     __shared__ __attribute__((aligned(16))) float Ks[KC][kD], Vs[KC][kD];
     const int m = blockIdx.y;
     int idx = blockIdx.x;
@@ -547,8 +552,8 @@ __global__ __launch_bounds__(256) void attention_f32_kernel(const float* __restr
     L = L < 1 ? 1 : L;
     L = L > max_seqlen ? max_seqlen : L;
     L = L > Tn - t0 ? Tn - t0 : L;
-    if (qc * 64 >= L) return;                               // (uniform over the workgroup)
-    const int tid = threadIdx.x, part = tid & 3, q = qc * 64 + (tid >> 2);
+    if (qc * QW >= L) return;                               // (uniform over the workgroup)
+    const int tid = threadIdx.x, part = tid % LQ, q = qc * QW + tid / LQ;
     const bool live = q < L;
     const size_t ld = (size_t)3 * H;
     const float* base = qkv + ((size_t)m * rows + t0) * ld + h * kD;
@@ -573,25 +578,45 @@ __global__ __launch_bounds__(256) void attention_f32_kernel(const float* __restr
             }
         }
         __syncthreads();
-        for (int key = 0; key < nk; ++key) {
-            float sdot = 0.f;
+        for (int k0 = 0; k0 < nk; k0 += KB) {
+            float s[KB], mx = mrun;                         // (keys behind the last one repeat it, with probability zero)
 #pragma unroll
-            for (int e4 = 0; e4 < DP; e4 += 4) {
-                const f32x4 kv = *(const f32x4*)&Ks[key][DP * part + e4];
+            for (int i = 0; i < KB; ++i) {
+                const int key = k0 + i < nk ? k0 + i : nk - 1;
+                s[i] = 0.f;
 #pragma unroll
-                for (int e = 0; e < 4; ++e) sdot = fmaf(qv[e4 + e], kv[e], sdot);
+                for (int e4 = 0; e4 < DP; e4 += 4) {
+                    const f32x4 kv = *(const f32x4*)&Ks[key][DP * part + e4];
+#pragma unroll
+                    for (int e = 0; e < 4; ++e) s[i] = fmaf(qv[e4 + e], kv[e], s[i]);
+                }
             }
-            sdot += dpp_moved<kDppPair>(sdot);              // the four lanes of a query: every one ends with the whole sum
-            sdot += dpp_moved<kDppQuad>(sdot);
-            sdot *= 0.125f;
-            const float mx = fmaxf(mrun, sdot);
-            const float alpha = expf(mrun - mx), p = expf(sdot - mx);
-            lrun = lrun * alpha + p;
 #pragma unroll
-            for (int e4 = 0; e4 < DP; e4 += 4) {
-                const f32x4 vv = *(const f32x4*)&Vs[key][DP * part + e4];
+            for (int i = 0; i < KB; ++i) {                  // over the lanes of a query: every one ends with the whole sum
+                s[i] += dpp_moved<kDppPair>(s[i]);
+                s[i] += dpp_moved<kDppQuad>(s[i]);
+                if (LQ == 16) {
+                    s[i] += dpp_moved<kDppHalfRowMirror>(s[i]);
+                    s[i] += dpp_moved<kDppRowMirror>(s[i]);
+                }
+                s[i] *= 0.125f;
+                mx = fmaxf(mx, s[i]);
+            }
+            const float alpha = expf(mrun - mx);
+            lrun *= alpha;
 #pragma unroll
-                for (int e = 0; e < 4; ++e) o[e4 + e] = o[e4 + e] * alpha + p * vv[e];
+            for (int e = 0; e < DP; ++e) o[e] *= alpha;
+#pragma unroll
+            for (int i = 0; i < KB; ++i) {
+                const int key = k0 + i < nk ? k0 + i : nk - 1;
+                const float p = k0 + i < nk ? expf(s[i] - mx) : 0.f;
+                lrun += p;
+#pragma unroll
+                for (int e4 = 0; e4 < DP; e4 += 4) {
+                    const f32x4 vv = *(const f32x4*)&Vs[key][DP * part + e4];
+#pragma unroll
+                    for (int e = 0; e < 4; ++e) o[e4 + e] = fmaf(p, vv[e], o[e4 + e]);
+                }
             }
             mrun = mx;
         }
@@ -621,10 +646,14 @@ hipError_t launch_attention(const sp_model* M, const void* qkv, const void* vt, 
         const int nitems = (a.items + 8 * a.run - 1) / (8 * a.run) * (8 * a.run);
         hipLaunchKernelGGL(attention_bf16_kernel, dim3((unsigned)(nitems * c.heads), k), dim3(256), 0, s, a);
     } else {
-        const int nqc = (max_seqlen + 63) / 64;
-        dim3 grid((unsigned)(B * c.heads * nqc), k);
-        hipLaunchKernelGGL(attention_f32_kernel, grid, dim3(256), 0, s, (const float*)qkv, (float*)att, cu, B, T, rows,
-                           c.hidden, c.heads, max_seqlen, nqc);
+        // (sixteen lanes per query: four times the workgroups; up to about two of them per compute unit)
+        const int nq16 = (max_seqlen + 15) / 16, nq4 = (max_seqlen + 63) / 64;
+        if ((long)B * c.heads * nq16 * k <= 512)
+            hipLaunchKernelGGL(attention_f32_kernel<16>, dim3((unsigned)(B * c.heads * nq16), k), dim3(256), 0, s, (const float*)qkv,
+                               (float*)att, cu, B, T, rows, c.hidden, c.heads, max_seqlen, nq16);
+        else
+            hipLaunchKernelGGL(attention_f32_kernel<4>, dim3((unsigned)(B * c.heads * nq4), k), dim3(256), 0, s, (const float*)qkv,
+                               (float*)att, cu, B, T, rows, c.hidden, c.heads, max_seqlen, nq4);
     }
     return hipGetLastError();
 }

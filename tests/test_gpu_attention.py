@@ -40,3 +40,26 @@ def test_attention_at_tile_and_item_edges(oracle64, name, qk_std):
             err = np.abs(att[m][cu[b]:cu[b + 1]] - want).max() / np.abs(want).max()
             assert err < 1.2e-2, f"student {m}, sequence {b} of {lengths[b]} tokens at {cu[b]}: {err:.3e}"
     st.close()
+
+
+@pytest.mark.parametrize("copies", [1, 3])               # sixteen lanes per query; four
+def test_fp32_attention_at_block_and_chunk_edges(oracle64, copies):
+    """Blocks of eight keys, chunks of 64 and blocks of 16 or 64 queries just missed, met and passed; sharp scores.  fp32 sums of up
+    to 129 terms against fp64: a few units of 2^-24 of the largest value."""
+    from paper_2408_12526_amd import sp
+    shape = synth.StudentShape(K=2, layers=1, hidden=128, heads=2, ffn=128, vocab=100, max_pos=160, classes=2, dtype="fp32")
+    lengths = np.array((1, 7, 8, 9, 15, 16, 17, 63, 64, 65, 128, 129) * copies, np.int32)
+    rng = np.random.default_rng(copies)
+    ids, blob = synth.make_ids(rng, int(lengths.sum()), shape.vocab), synth.make_weights(rng, shape, std=0.08, qk_std=0.4)
+    st = sp.Students(sp.config_from_shape(shape), blob)
+    cu, k, H = sp.sp_pack(lengths), shape.K, shape.hidden
+    T, B = int(cu[-1]), len(lengths)
+    ws = st.sp_forward_partial(torch.from_numpy(ids).cuda(), torch.from_numpy(cu).cuda(), int(lengths.max()), k, 1)
+    qkv, att = st.read_activation(ws, "qkv", T, B, k), st.read_activation(ws, "att", T, B, k)
+    for m in range(k):
+        for b in range(B):
+            a = qkv[m][cu[b]:cu[b + 1]]
+            want = oracle64.attention(a[:, :H], a[:, H:2 * H], a[:, 2 * H:], shape.heads)
+            err = np.abs(att[m][cu[b]:cu[b + 1]] - want).max() / np.abs(want).max()
+            assert err < 2e-5, f"student {m}, sequence {b} of {lengths[b]} tokens: {err:.3e}"
+    st.close()
