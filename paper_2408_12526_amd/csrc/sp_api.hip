@@ -476,7 +476,8 @@ static int run_students(const sp_model* M0, const WsLayout& W, const int32_t* id
     }
     // (the partial forwards of the tests read the buffers between the projections)
     const bool f32_layer = with_head && f32_layer_supported(c, (long)T * k_rule);
-    SP_TRY(launch_embed_ln(M, ids, cu, B, T, rows, mrows, k, x, att, s, xq, kActQuantScale, attq));
+    if (f32_layer) SP_TRY(launch_f32_embed(M, L.layer0, ids, cu, B, T, x, qkv, rows, k, s));
+    else SP_TRY(launch_embed_ln(M, ids, cu, B, T, rows, mrows, k, x, att, s, xq, kActQuantScale, attq));
     SP_MARK(SP_PHASE_EMBED);
     for (int l = 0; l < stop_layers; ++l) {
         const size_t lo = L.layer0 + (size_t)l * L.layer_stride;
@@ -509,7 +510,7 @@ static int run_students(const sp_model* M0, const WsLayout& W, const int32_t* id
         else if (bf16_path(c))
             SP_TRY(launch_gemm(M, x, H, lo + L.wqkv, lo + L.bqkv, qkv, 3 * H, nullptr, 0, mrows, 3 * H, H, k, EPI_QKV,
                                sH, s3H, 0, s, vt, 2 * H, rows, sH));
-        else if (l == 0 || !f32_layer)                      // (else the previous layer's launch has left q|k|v)
+        else if (!f32_layer)                                // (else the launch before has left q|k|v)
             SP_TRY(launch_gemm(M, x, H, lo + L.wqkv, lo + L.bqkv, qkv, 3 * H, nullptr, 0, mrows, 3 * H, H, k, EPI_BIAS,
                                sH, s3H, 0, s));
         SP_MARK(SP_PHASE_QKV);
@@ -518,6 +519,13 @@ static int run_students(const sp_model* M0, const WsLayout& W, const int32_t* id
         SP_TRY(launch_attention(M, qkv, vt, fp8 && with_head ? nullptr : att, cu, B, T, max_seqlen, rows, k, s, attq,
                                 kActQuantScale));
         SP_MARK(SP_PHASE_ATTENTION);
+        if (f32_layer && l == c.layers - 1 && !c.last_layer_all_tokens) {
+            SP_TRY(launch_f32_last(M, lo, att, x, cu, B, T, rows, k, z, s));
+            SP_MARK(SP_PHASE_LAST_FIRST);
+            if (logits) SP_TRY(launch_sum_students(z, B * c.classes, k, logits, s));
+            SP_MARK(SP_PHASE_HEAD);
+            return SP_OK;
+        }
         if (f32_layer) {
             SP_TRY(launch_f32_layer(M, lo, att, x, l + 1 < stop_layers ? qkv : nullptr, T, rows, k, s));
             SP_MARK(SP_PHASE_FFN_DOWN);

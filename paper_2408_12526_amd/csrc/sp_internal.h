@@ -300,11 +300,18 @@ hipError_t launch_rows_ln_add(const sp_model* M, size_t g_off, size_t b_off, con
                               const void* res, size_t r_ss, const int32_t* cu, int T, void* out, size_t o_ss, int nrows, int k,
                               hipStream_t s);
 
-// ---- fp32 path, calls of few rows (sp_rows_f32.hip): x = LN(x1 + FFN(x1)), x1 = LN(x + att Wo + bo), of T rows per student in
-// one launch, and q|k|v of the next layer from the new x (qkv_next null: there is none)
+// ---- fp32 path, calls of few rows (sp_rows_f32.hip), a launch each:
 bool f32_layer_supported(const sp_config& c, long rows_of_all_students);
+// x = LN(embedding) of T rows per student, and q|k|v of the layer at lo from them
+hipError_t launch_f32_embed(const sp_model* M, size_t lo, const int32_t* ids, const int32_t* cu, int B, int T, void* x, void* qkv,
+                            int rows, int k, hipStream_t s);
+// x = LN(x1 + FFN(x1)), x1 = LN(x + att Wo + bo), of T rows per student, and q|k|v of the next layer from the new x (qkv_next null:
+// there is none)
 hipError_t launch_f32_layer(const sp_model* M, size_t lo, const void* att, void* x, void* qkv_next, int T, int rows, int k,
                             hipStream_t s);
+// the same of the first token of every sequence, then z[m][b][c] = tanh(x Wp + bp) Wc + bc
+hipError_t launch_f32_last(const sp_model* M, size_t lo, const void* att, void* x, const int32_t* cu, int B, int T, int rows, int k,
+                           float* z, hipStream_t s);
 
 // att[m][t][h*64..] = softmax(q k^T / 8) v inside each sequence; qkv rows are [q | k | v] of width 3H.
 // bf16 path: the values are read from vt[m][H][rows] (transposed) instead of the third slice of qkv.

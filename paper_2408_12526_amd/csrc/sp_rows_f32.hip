@@ -1,37 +1,51 @@
-// fp32 path, calls of few rows: everything of an encoder layer that follows the attention, and the q|k|v projection of the
-// next layer, in one launch.
+// fp32 path, calls of few rows: a launch from one attention to the next.  What it starts with is the embedding or everything of an
+// encoder layer that follows the attention; what it ends with is the q|k|v projection of the next layer, or, in the last layer, which
+// then has the first token of every sequence as its rows, pooler and classifier.
 //
 // Such a call is a chain of dependent launches of 4-6 us that leave the chip idle: five per layer after the attention and one
 // for q|k|v.  All of it is row-wise, so a workgroup takes two rows through the whole chain with the rows in LDS and reads
 // the layer's weights (768 KB at 128 x 512) from the L2, which is what bounds it: about 64 bytes per cycle and compute unit.
 //   * sixteen lanes share an output feature and read 256 bytes in a row of its weights ([out][in]); eight waves x four
-//     features per step, four steps (eight wave-loads) at a time, the next eight in flight, also across the barriers between
-//     the projections;
+//     features x four make a block of 128 features x 128 reduction elements, eight wave-loads per wave; the next three blocks are
+//     in flight, also across the barriers between the projections (one in flight: twice the time, a block waits for its
+//     memory round trip).  The order of the blocks is fixed at compile time, an instance per FFN width.
 //   * a lane's partial sums are added over the sixteen lanes by four data-parallel-primitive adds; then one lane per output
 //     applies bias, GELU or residual.  Biases and LayerNorm parameters come through LDS, so nothing waits behind the weights.
-// Measured, two students of 2 layers x 128 wide on 86 tokens: 19 launches, 83.6 us a call -> 8 launches, 57.7 us; relative difference
-// from the separate launches' logits 1.9e-7.
+// Measured, two students of 2 layers x 128 wide on 86 tokens: separate launches, 19 of them, 83.6 us a call; one launch per layer after
+// the attention, a block of weights in flight, and embedding, first q|k|v, pooler and classifier apart, 8 launches, 51 us; this, 6
+// launches, 38.8 us (a layer 14.4 -> 11.8 us, the last one 13.0 -> 10.2).
+#include <type_traits>
+#include <utility>
+
 #include "sp_internal.h"
 
 namespace sp {
 
 namespace {
 
-constexpr int kWaves = 8, kRows = 2;
+constexpr int kWaves = 8, kRows = 2, H = 128;             // (see f32_layer_supported)
+constexpr int kAhead = 4;                                   // blocks of weights in registers
+
+enum { FROM_EMBEDDING, FROM_ATTENTION };                   // what the rows come from
+enum { TO_QKV, TO_ROWS, TO_CLASSES };                       // and what is made of them: q|k|v, x alone, the students' classifier outputs
 
 struct F32LayerArgs {
     const char* arena;
-    size_t ss, wo, bo, g1, be1, w1, b1, w2, b2, g2, be2, wqkv, bqkv;   // byte offsets into a student slab
+    size_t ss, wo, bo, g1, be1, w1, b1, w2, b2, g2, be2;    // byte offsets into a student slab (FROM_EMBEDDING: g2, be2 alone)
+    size_t wn, bn;                    // what follows the last LayerNorm: q|k|v or the pooler, [out][in]
+    size_t wc, bc, tok, pos;
     const float* att;
-    float *x, *qkv;                   // student strides: rows x H, rows x H, rows x 3 H
-    int T, rows, H, F;
+    float *x, *qkv, *z;               // student strides: rows x H, rows x H, rows x 3 H, M x C
+    const int32_t *ids, *cu;
+    int M, Tn, rows, B, C, V, P;      // M: rows to compute (tokens, or first tokens of sequences)
     float eps;
 };
 
-// Eight wave-loads: features f0 + 32 i (i < 4) of this lane group, reduction elements kc and kc + 64 on
-__device__ inline void load_weights(f32x4 (&w)[8], const float* W, int K, int step, int kc, int lane, int wave)
+// A block of a matrix with reduction depth K: features f0 + 32 i + 4 wave + lane / 16 (i < 4), reduction elements k0 + 4 (lane % 16)
+// and 64 more
+__device__ __forceinline__ void load_block(f32x4 (&w)[8], const float* W, int K, int f0, int k0, int lane, int wave)
 {
-    const float* p = W + (size_t)(step * 32 + wave * 4 + (lane >> 4)) * K + kc + (lane & 15) * 4;
+    const float* p = W + (size_t)(f0 + wave * 4 + (lane >> 4)) * K + k0 + (lane & 15) * 4;
 #pragma unroll
     for (int i = 0; i < 4; ++i) {
         w[2 * i] = *(const f32x4*)(p + (size_t)i * 32 * K);
@@ -39,164 +53,254 @@ __device__ inline void load_weights(f32x4 (&w)[8], const float* W, int K, int st
     }
 }
 
-// emit(feature, row, sum) of xs[row][K] . W[feature][K] for N features (N and K multiples of 128).  w holds the first eight
-// wave-loads of W on entry and those of Wn (reduction depth Kn), the next product's weights, on return.
-template <class Emit>
-__device__ inline void product(f32x4 (&w)[8], const float* W, int N, int K, const float* Wn, int Kn, const float* xs, int lane,
-                               int wave, Emit emit)
+__device__ __forceinline__ void multiply_block(const f32x4 (&w)[8], const float* xs, int pitch, int lane, float (&acc)[kRows][4])
 {
-    const int l16 = lane & 15, steps = N / 32;
-    float acc[kRows][4];
+    const int l16 = lane & 15;
+#pragma unroll
+    for (int r = 0; r < kRows; ++r) {
+        const f32x4 xa = *(const f32x4*)(xs + r * pitch + l16 * 4), xb = *(const f32x4*)(xs + r * pitch + 64 + l16 * 4);
+#pragma unroll
+        for (int i = 0; i < 4; ++i)
+#pragma unroll
+            for (int e = 0; e < 4; ++e) {
+                acc[r][i] = fmaf(w[2 * i][e], xa[e], acc[r][i]);
+                acc[r][i] = fmaf(w[2 * i + 1][e], xb[e], acc[r][i]);
+            }
+    }
+}
+
+// emit(feature - f0, row, sum over the sixteen lanes) and zero the sums
+template <class Emit>
+__device__ __forceinline__ void finish_block(float (&acc)[kRows][4], int lane, int wave, Emit emit)
+{
+    const int l16 = lane & 15;
+    float out = 0.f;                                        // lane l16 = 4 r + i of the group takes row r, step i
 #pragma unroll
     for (int r = 0; r < kRows; ++r)
 #pragma unroll
-        for (int i = 0; i < 4; ++i) acc[r][i] = 0.f;
-    int s = 0, kc = 0;
-    const int its = steps / 4 * (K / 128);
-    for (int it = 0; it < its; ++it) {
-        const bool wrap = kc + 128 == K, last = it + 1 == its;
-        const int s1 = last ? 0 : wrap ? s + 4 : s, kc1 = wrap ? 0 : kc + 128;
-        f32x4 wn[8];
-        load_weights(wn, last ? Wn : W, last ? Kn : K, s1, kc1, lane, wave);
-#pragma unroll
-        for (int r = 0; r < kRows; ++r) {
-            const f32x4 xa = *(const f32x4*)(xs + r * K + kc + l16 * 4), xb = *(const f32x4*)(xs + r * K + kc + 64 + l16 * 4);
-#pragma unroll
-            for (int i = 0; i < 4; ++i)
-#pragma unroll
-                for (int e = 0; e < 4; ++e) {
-                    acc[r][i] = fmaf(w[2 * i][e], xa[e], acc[r][i]);
-                    acc[r][i] = fmaf(w[2 * i + 1][e], xb[e], acc[r][i]);
-                }
+        for (int i = 0; i < 4; ++i) {
+            float v = acc[r][i];
+            v += dpp_moved<kDppPair>(v);
+            v += dpp_moved<kDppQuad>(v);
+            v += dpp_moved<kDppHalfRowMirror>(v);
+            v += dpp_moved<kDppRowMirror>(v);
+            out = l16 == 4 * r + i ? v : out;
+            acc[r][i] = 0.f;
         }
-        if (wrap) {
-            float out = 0.f;                                // lane l16 = 4 r + i of the group takes row r, step s + i
-#pragma unroll
-            for (int r = 0; r < kRows; ++r)
-#pragma unroll
-                for (int i = 0; i < 4; ++i) {
-                    float v = acc[r][i];
-                    v += dpp_moved<kDppPair>(v);
-                    v += dpp_moved<kDppQuad>(v);
-                    v += dpp_moved<kDppHalfRowMirror>(v);
-                    v += dpp_moved<kDppRowMirror>(v);
-                    out = l16 == 4 * r + i ? v : out;
-                    acc[r][i] = 0.f;
-                }
-            if (l16 < 4 * kRows) emit((s + (l16 & 3)) * 32 + wave * 4 + (lane >> 4), l16 >> 2, out);
-        }
-        s = s1;
-        kc = kc1;
-#pragma unroll
-        for (int i = 0; i < 8; ++i) w[i] = wn[i];
-    }
+    if (l16 < 4 * kRows) emit((l16 & 3) * 32 + wave * 4 + (lane >> 4), l16 >> 2, out);
 }
 
-// LayerNorm of a row of H <= 256 values in LDS, in place, by one wave; dst (may be null): the row once more
-__device__ inline void layernorm_row(float* v, const float* g, const float* b, int H, float eps, int lane, float* dst)
+// LayerNorm of a row in LDS, in place, by one wave; dst (may be null): the row once more
+__device__ inline void layernorm_row(float* v, const float* g, const float* b, float eps, int lane, float* dst)
 {
-    float x[4], s = 0.f, q = 0.f;
-#pragma unroll
-    for (int i = 0; i < 4; ++i) {
-        x[i] = lane + 64 * i < H ? v[lane + 64 * i] : 0.f;
-        s += x[i];
-    }
-    const float inv_h = __builtin_amdgcn_rcpf((float)H), mean = wave_sum(s) * inv_h;
-#pragma unroll
-    for (int i = 0; i < 4; ++i) {
-        const float d = x[i] - mean;
-        if (lane + 64 * i < H) q += d * d;
-    }
-    const float inv = __builtin_amdgcn_rsqf(wave_sum(q) * inv_h + eps);
-#pragma unroll
-    for (int i = 0; i < 4; ++i) {
-        const int c = lane + 64 * i;
-        if (c < H) {
-            const float o = g[c] * ((x[i] - mean) * inv) + b[c];
-            v[c] = o;
-            if (dst) dst[c] = o;
-        }
+    const float x0 = v[lane], x1 = v[lane + 64];
+    const float inv_h = 1.0f / H, mean = wave_sum(x0 + x1) * inv_h;
+    const float d0 = x0 - mean, d1 = x1 - mean, inv = __builtin_amdgcn_rsqf(wave_sum(d0 * d0 + d1 * d1) * inv_h + eps);
+    const float o0 = g[lane] * (d0 * inv) + b[lane], o1 = g[lane + 64] * (d1 * inv) + b[lane + 64];
+    v[lane] = o0;
+    v[lane + 64] = o1;
+    if (dst) {
+        dst[lane] = o0;
+        dst[lane + 64] = o1;
     }
 }
 
+// f(0) ... f(N - 1), the number as a constant
+template <class Fn, int... I>
+__device__ __forceinline__ void each_of(std::integer_sequence<int, I...>, Fn f) { (f(std::integral_constant<int, I>{}), ...); }
+template <int N, class Fn>
+__device__ __forceinline__ void each(Fn f) { each_of(std::make_integer_sequence<int, N>{}, f); }
+
+template <int FROM, int TO, int FB>
+constexpr int f32_layer_floats()                            // of LDS; see the kernel's carve-up
+{
+    return kRows * H + 2 * H + (TO == TO_QKV ? 3 : 1) * H + (FROM == FROM_EMBEDDING ? 0 : kRows * (H + 128 * FB) + 4 * H + 128 * FB);
+}
+
+// FB: FFN width / 128
+template <int FROM, int TO, int FB>
 __global__ __launch_bounds__(64 * kWaves) void f32_layer_kernel(F32LayerArgs p)
 {
-    extern __shared__ float lds[];
-    const int H = p.H, F = p.F, m = blockIdx.y, r0 = blockIdx.x * kRows;
+    __shared__ __attribute__((aligned(16))) float lds[f32_layer_floats<FROM, TO, FB>()];
+    constexpr int F = 128 * FB, NB = TO == TO_QKV ? 3 * H : H;         // NB: biases of what follows the last LayerNorm
+    constexpr int BODY = FROM == FROM_EMBEDDING ? 0 : 1 + 2 * FB, BLOCKS = BODY + (TO == TO_QKV ? 3 : TO == TO_CLASSES ? 1 : 0);
+    const int m = blockIdx.y, r0 = blockIdx.x * kRows;
     const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-    float *xa = lds, *xr = xa + kRows * H, *xg = xr + kRows * H, *bo = xg + kRows * F, *g1 = bo + H, *be1 = g1 + H, *b1 = be1 + H;
-    float *b2 = b1 + F, *g2 = b2 + H, *be2 = g2 + H, *bq = be2 + H;
+    float *xa = lds, *g2 = xa + kRows * H, *be2 = g2 + H, *bn = be2 + H, *xr = bn + NB, *bo = xr + kRows * H, *g1 = bo + H;
+    float *be1 = g1 + H, *b2 = be1 + H, *b1 = b2 + H, *xg = b1 + F;
     const char* sb = p.arena + (size_t)m * p.ss;
-    const bool tail = p.qkv != nullptr;
-    const float *Wo = (const float*)(sb + p.wo), *W1 = (const float*)(sb + p.w1), *W2 = (const float*)(sb + p.w2);
-    const float* Wq = tail ? (const float*)(sb + p.wqkv) : W2;          // (nothing follows: a load that nobody uses)
 
     auto fill = [&](float* dst, size_t off, int n) {
         for (int i = tid; i < n; i += 64 * kWaves) dst[i] = ((const float*)(sb + off))[i];
     };
-    for (int i = tid; i < kRows * H; i += 64 * kWaves) {
-        const int r = i / H, row = r0 + r < p.T ? r0 + r : p.T - 1;
-        const size_t at = ((size_t)m * p.rows + row) * H + (i - r * H);
-        xa[i] = p.att[at];
-        xr[i] = p.x[at];
+    // token row of row r (rows beyond the last one repeat it)
+    auto token = [&](int r) {
+        r = r < p.M ? r : p.M - 1;
+        if (TO != TO_CLASSES) return r;
+        const int t = p.cu[r];
+        return t < 0 ? 0 : (t < p.Tn ? t : p.Tn - 1);
+    };
+    f32x4 w[kAhead][8];
+    float acc[kRows][4] = {};
+    // blocks in order: Wo; W1 feature block by feature block; W2 along its reduction; then q|k|v or the pooler
+    auto request = [&](auto i_c) {
+        constexpr int i = decltype(i_c)::value;
+        if constexpr (i >= BLOCKS) return;
+        else if constexpr (i >= BODY) load_block(w[i % kAhead], (const float*)(sb + p.wn), H, (i - BODY) * 128, 0, lane, wave);
+        else if constexpr (i == 0) load_block(w[0], (const float*)(sb + p.wo), H, 0, 0, lane, wave);
+        else if constexpr (i <= FB) load_block(w[i % kAhead], (const float*)(sb + p.w1), H, (i - 1) * 128, 0, lane, wave);
+        else load_block(w[i % kAhead], (const float*)(sb + p.w2), F, 0, (i - 1 - FB) * 128, lane, wave);
+    };
+    auto multiply = [&](auto i_c, const float* xs, int pitch) {
+        constexpr int i = decltype(i_c)::value;
+        multiply_block(w[i % kAhead], xs, pitch, lane, acc);
+        request(std::integral_constant<int, i + kAhead>{});
+    };
+
+    if constexpr (FROM == FROM_EMBEDDING) {
+        if (wave < kRows) {                                 // a wave per row: its sequence starts at the last boundary up to it
+            const int row = token(r0 + wave), id = p.ids[row];
+            int start = 0;
+            for (int b0 = 0; b0 < p.B; b0 += 64) {
+                const int cv = b0 + lane < p.B ? p.cu[b0 + lane] : 0x7fffffff, n = __popcll(__ballot(cv <= row));
+                if (n > 0) start = __builtin_amdgcn_readlane(cv, n - 1);
+            }
+            int at = row - start;
+            at = at < 0 ? 0 : (at < p.P ? at : p.P - 1);
+            const float* te = (const float*)(sb + p.tok) + (size_t)(id < 0 ? 0 : (id < p.V ? id : p.V - 1)) * H;
+            const float* pe = (const float*)(sb + p.pos) + (size_t)at * H;
+#pragma unroll
+            for (int c = lane; c < H; c += 64) xa[wave * H + c] = te[c] + pe[c];
+        }
+    } else {
+        for (int i = tid; i < kRows * H; i += 64 * kWaves) {
+            const int r = i / H;
+            const size_t at = ((size_t)m * p.rows + token(r0 + r)) * H + (i - r * H);
+            xa[i] = p.att[at];
+            xr[i] = p.x[at];
+        }
+        fill(bo, p.bo, H);
+        fill(g1, p.g1, H);
+        fill(be1, p.be1, H);
+        fill(b1, p.b1, F);
+        fill(b2, p.b2, H);
     }
-    fill(bo, p.bo, H);
-    fill(g1, p.g1, H);
-    fill(be1, p.be1, H);
-    fill(b1, p.b1, F);
-    fill(b2, p.b2, H);
     fill(g2, p.g2, H);
     fill(be2, p.be2, H);
-    if (tail) fill(bq, p.bqkv, 3 * H);
-    f32x4 w[8];
-    load_weights(w, Wo, H, 0, 0, lane, wave);
+    if (TO != TO_ROWS) fill(bn, p.bn, NB);
+    __builtin_amdgcn_sched_barrier(0);
+    each<kAhead>(request);
+    __builtin_amdgcn_sched_barrier(0);
     barrier_lds();
-    product(w, Wo, H, H, W1, H, xa, lane, wave, [&](int f, int r, float v) { xr[r * H + f] = v + bo[f] + xr[r * H + f]; });
-    barrier_lds();
-    if (wave < kRows) layernorm_row(xr + wave * H, g1, be1, H, p.eps, lane, nullptr);
-    barrier_lds();
-    product(w, W1, F, H, W2, F, xr, lane, wave, [&](int f, int r, float v) {
-        const float u = v + b1[f];
-        xg[r * F + f] = 0.5f * u * (1.0f + erff(u * 0.70710678118654752f));
-    });
-    barrier_lds();
-    product(w, W2, H, F, Wq, tail ? H : F, xg, lane, wave, [&](int f, int r, float v) { xa[r * H + f] = v + b2[f] + xr[r * H + f]; });
-    barrier_lds();
+    if constexpr (FROM == FROM_ATTENTION) {
+        multiply(std::integral_constant<int, 0>{}, xa, H);
+        finish_block(acc, lane, wave, [&](int f, int r, float v) { xr[r * H + f] = v + bo[f] + xr[r * H + f]; });
+        barrier_lds();
+        if (wave < kRows) layernorm_row(xr + wave * H, g1, be1, p.eps, lane, nullptr);
+        barrier_lds();
+        each<FB>([&](auto i) {
+            multiply(std::integral_constant<int, 1 + decltype(i)::value>{}, xr, H);
+            finish_block(acc, lane, wave, [&](int f, int r, float v) {
+                const float u = v + b1[i() * 128 + f];
+                xg[r * F + i() * 128 + f] = 0.5f * u * (1.0f + erff(u * 0.70710678118654752f));
+            });
+        });
+        barrier_lds();
+        each<FB>([&](auto i) { multiply(std::integral_constant<int, 1 + FB + decltype(i)::value>{}, xg + i() * 128, F); });
+        finish_block(acc, lane, wave, [&](int f, int r, float v) { xa[r * H + f] = v + b2[f] + xr[r * H + f]; });
+        barrier_lds();
+    }
     if (wave < kRows)
-        layernorm_row(xa + wave * H, g2, be2, H, p.eps, lane,
-                      r0 + wave < p.T ? p.x + ((size_t)m * p.rows + r0 + wave) * H : nullptr);
-    if (!tail) return;
+        layernorm_row(xa + wave * H, g2, be2, p.eps, lane,
+                      r0 + wave < p.M ? p.x + ((size_t)m * p.rows + token(r0 + wave)) * H : nullptr);
+    if constexpr (TO == TO_ROWS) return;
     barrier_lds();
-    product(w, Wq, 3 * H, H, Wq, H, xa, lane, wave, [&](int f, int r, float v) {
-        if (r0 + r < p.T) p.qkv[((size_t)m * p.rows + r0 + r) * 3 * H + f] = v + bq[f];
-    });
+    if constexpr (TO == TO_QKV) {
+        each<3>([&](auto i) {
+            multiply(std::integral_constant<int, BODY + decltype(i)::value>{}, xa, H);
+            finish_block(acc, lane, wave, [&](int f, int r, float v) {
+                if (r0 + r < p.M) p.qkv[((size_t)m * p.rows + r0 + r) * 3 * H + i() * 128 + f] = v + bn[i() * 128 + f];
+            });
+        });
+    }
+    if constexpr (TO == TO_CLASSES) {
+        multiply(std::integral_constant<int, BODY>{}, xa, H);
+        finish_block(acc, lane, wave, [&](int f, int r, float v) { xr[r * H + f] = tanhf(v + bn[f]); });
+        barrier_lds();
+        if (wave < kRows && r0 + wave < p.M)
+            for (int c = 0; c < p.C; ++c) {
+                const float* wc = (const float*)(sb + p.wc) + c;
+                const float v = wave_sum(xr[wave * H + lane] * wc[(size_t)lane * p.C] + xr[wave * H + lane + 64] * wc[(size_t)(lane + 64) * p.C]) +
+                                ((const float*)(sb + p.bc))[c];
+                if (lane == 0) p.z[((size_t)m * p.M + r0 + wave) * p.C + c] = v;
+            }
+    }
+}
+
+template <int FROM, int TO>
+hipError_t launch(const sp_model* M, const F32LayerArgs& a, int k, hipStream_t s)
+{
+    const dim3 grid((a.M + kRows - 1) / kRows, k);
+#define SP_GO(FB) case FB: hipLaunchKernelGGL((f32_layer_kernel<FROM, TO, FB>), grid, dim3(64 * kWaves), 0, s, a); break
+    switch (FROM == FROM_EMBEDDING ? 1 : M->cfg.ffn / 128) {
+        SP_GO(1);
+        default: return hipErrorInvalidValue;
+        case 2: case 3: case 4: case 5: case 6:
+            if constexpr (FROM != FROM_EMBEDDING)
+                switch (M->cfg.ffn / 128) { SP_GO(2); SP_GO(3); SP_GO(4); SP_GO(5); SP_GO(6); }
+    }
+#undef SP_GO
+    return hipGetLastError();
+}
+
+F32LayerArgs layer_args(const sp_model* M, size_t lo, const void* att, void* x, const int32_t* cu, int B, int T, int rows)
+{
+    const sp_config& c = M->cfg;
+    const ArenaLayout& L = M->L;
+    F32LayerArgs a{};
+    a.arena = M->arena; a.ss = L.student_stride;
+    a.wo = lo + L.wo; a.bo = lo + L.bo; a.g1 = lo + L.ln1g; a.be1 = lo + L.ln1b; a.w1 = lo + L.w1; a.b1 = lo + L.b1;
+    a.w2 = lo + L.w2; a.b2 = lo + L.b2; a.g2 = lo + L.ln2g; a.be2 = lo + L.ln2b;
+    a.att = (const float*)att; a.x = (float*)x; a.cu = cu;
+    a.M = T; a.Tn = T; a.rows = rows; a.B = B; a.C = c.classes; a.V = c.vocab; a.P = c.max_pos; a.eps = c.ln_eps;
+    return a;
 }
 
 }  // namespace
 
-// Every workgroup reads the layer's weights, so the kernel is for narrow students (1 MB of weights, i.e. hidden 128 with an FFN of up
-// to 768: 7 us at the L2's rate; the separate launches spread them over the chip) and for calls of at most one workgroup per
+// Every workgroup reads the layer's weights, so the kernel is for narrow students (hidden 128 with an FFN of up to 768, 1 MB of
+// weights: 7 us at the L2's rate; the separate launches spread them over the chip) and for calls of at most one workgroup per
 // compute unit.
 bool f32_layer_supported(const sp_config& c, long rows_of_all_students)
 {
-    const size_t H = c.hidden, F = c.ffn;
-    return !bf16_path(c) && H == 128 && F % 128 == 0 && (4 * H * H + 2 * H * F) * sizeof(float) <= (1u << 20) &&
-           rows_of_all_students <= 256 * kRows;
+    return !bf16_path(c) && c.hidden == H && c.ffn % 128 == 0 && c.ffn <= 768 && rows_of_all_students <= 256 * kRows;
+}
+
+hipError_t launch_f32_embed(const sp_model* M, size_t lo, const int32_t* ids, const int32_t* cu, int B, int T, void* x, void* qkv,
+                            int rows, int k, hipStream_t s)
+{
+    const ArenaLayout& L = M->L;
+    F32LayerArgs a = layer_args(M, lo, nullptr, x, cu, B, T, rows);
+    a.g2 = L.emb_g; a.be2 = L.emb_b; a.wn = lo + L.wqkv; a.bn = lo + L.bqkv; a.tok = L.tok; a.pos = L.pos; a.ids = ids;
+    a.qkv = (float*)qkv;
+    return launch<FROM_EMBEDDING, TO_QKV>(M, a, k, s);
 }
 
 hipError_t launch_f32_layer(const sp_model* M, size_t lo, const void* att, void* x, void* qkv_next, int T, int rows, int k,
                             hipStream_t s)
 {
-    const sp_config& c = M->cfg;
-    const ArenaLayout& L = M->L;
-    const size_t nx = lo + L.layer_stride;
-    const F32LayerArgs a{M->arena, L.student_stride, lo + L.wo, lo + L.bo, lo + L.ln1g, lo + L.ln1b, lo + L.w1, lo + L.b1,
-                         lo + L.w2, lo + L.b2, lo + L.ln2g, lo + L.ln2b, nx + L.wqkv, nx + L.bqkv, (const float*)att, (float*)x,
-                         (float*)qkv_next, T, rows, c.hidden, c.ffn, c.ln_eps};
-    const size_t smem = sizeof(float) * ((size_t)kRows * (2 * c.hidden + c.ffn) + 9 * (size_t)c.hidden + c.ffn);
-    if (smem > 48 * 1024) return hipErrorInvalidValue;
-    hipLaunchKernelGGL(f32_layer_kernel, dim3((T + kRows - 1) / kRows, k), dim3(64 * kWaves), smem, s, a);
-    return hipGetLastError();
+    F32LayerArgs a = layer_args(M, lo, att, x, nullptr, 0, T, rows);
+    if (!qkv_next) return launch<FROM_ATTENTION, TO_ROWS>(M, a, k, s);
+    a.wn = lo + M->L.layer_stride + M->L.wqkv; a.bn = lo + M->L.layer_stride + M->L.bqkv; a.qkv = (float*)qkv_next;
+    return launch<FROM_ATTENTION, TO_QKV>(M, a, k, s);
+}
+
+hipError_t launch_f32_last(const sp_model* M, size_t lo, const void* att, void* x, const int32_t* cu, int B, int T, int rows, int k,
+                           float* z, hipStream_t s)
+{
+    F32LayerArgs a = layer_args(M, lo, att, x, cu, B, T, rows);
+    a.M = B; a.wn = M->L.wp_t; a.bn = M->L.bp; a.wc = M->L.wc; a.bc = M->L.bc; a.z = z;
+    return launch<FROM_ATTENTION, TO_CLASSES>(M, a, k, s);
 }
 
 }  // namespace sp
