@@ -77,26 +77,6 @@ struct AttnArgs {
     int items, run;                   // work items per head; neighbouring items that stay on one XCD
 };
 
-// Sequence b of work item i and its boundaries (every lane takes part; i and the result are uniform).
-__device__ __forceinline__ void sequence_of_item(const int32_t* __restrict__ cu, int B, int i, int lane, int& b, int& c0, int& c1)
-{
-    int base = 0, span = B;
-    for (;;) {
-        const int step = (span + 63) >> 6, off = lane * step;
-        const bool in = off < span;
-        const int at = base + (in ? off : 0), v0 = cu[at], v1 = cu[at + 1];
-        const int n = __popcll(__ballot(in && (v0 >> 7) + at <= i)), last = n > 0 ? n - 1 : 0;
-        base += last * step;
-        if (step == 1) {
-            b = base;
-            c0 = __builtin_amdgcn_readlane(v0, last);
-            c1 = __builtin_amdgcn_readlane(v1, last);
-            return;
-        }
-        span = step < span - last * step ? step : span - last * step;
-    }
-}
-
 __global__ __launch_bounds__(256, 4) void attention_bf16_kernel(AttnArgs p)
 {
     __shared__ __attribute__((aligned(16))) char lds[kAttnLdsBytes];
@@ -107,8 +87,8 @@ __global__ __launch_bounds__(256, 4) void attention_bf16_kernel(AttnArgs p)
     const int h = y % p.heads, s = y / p.heads, item = ((s / p.run) * 8 + xcd) * p.run + s % p.run;
     if (item >= p.items) return;
     const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-    int b, t0, t1;
-    sequence_of_item(p.cu, p.B, item, lane, b, t0, t1);
+    int t0, t1;
+    const int b = last_sequence(p.cu, p.B, lane, [&](int i, int c) { return (c >> 7) + i <= item; }, t0, t1);
     const int q0 = (item - ((t0 >> 7) + b)) * kQItem;
     t0 = t0 < 0 ? 0 : (t0 > p.Tn - 1 ? p.Tn - 1 : t0);
     int L = t1 - t0;

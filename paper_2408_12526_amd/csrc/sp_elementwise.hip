@@ -116,21 +116,13 @@ __global__ __launch_bounds__(256) void embed_ln_kernel(const char* arena, size_t
     const char* sb = arena + (size_t)m * student_stride;
     float gg[MAXC][8], bb[MAXC][8];
     load_gamma_beta<MAXC>((const float*)(sb + g_off), (const float*)(sb + b_off), nch, lane, gg, bb);
-    // Token id and position of the wave's rows, found by one lane per row before any row is fetched (rpw <= 64):
-    // the sequence of a row is the largest b with cu[b] <= row.  The row loop then has no dependent index loads.
-    int my_id = 0, my_pos = 0;
-    if (lane < rpw && row0 + lane < Tn) {
-        const int row = row0 + lane;
-        my_id = ids[row];
-        int lo = 0, hi = B;
-        while (hi - lo > 1) {
-            const int mid = (lo + hi) >> 1;
-            if (cu[mid] <= row) lo = mid; else hi = mid;
-        }
-        my_pos = row - cu[lo];
-        my_pos = my_pos < 0 ? 0 : (my_pos >= P ? P - 1 : my_pos);
-        my_id = my_id < 0 ? 0 : (my_id >= V ? V - 1 : my_id);
-    }
+    // Token ids and sequence starts of the wave's rows, a lane each (rpw < 64), before any row is fetched, so that the row loop has
+    // no dependent index loads: the sequence of the first row, then what begins in the rows behind it.
+    const int first = row0 < Tn ? row0 : Tn - 1;
+    int my_id = row0 + lane < Tn ? ids[row0 + lane] : 0, c0, c1;
+    my_id = my_id < 0 ? 0 : (my_id >= V ? V - 1 : my_id);
+    const int b = last_sequence(cu, B, lane, [&](int, int c) { return c <= first; }, c0, c1);
+    const int begin = lane == 0 ? c0 : lane == 1 ? c1 : rpw > 1 && b + lane < B ? cu[b + lane] : 0x7fffffff;
 #pragma unroll 2
     for (int r = 0; r < rpw; ++r) {
         const int row = row0 + r;
@@ -150,7 +142,9 @@ __global__ __launch_bounds__(256) void embed_ln_kernel(const char* arena, size_t
                 }
             continue;
         }
-        const int id = __builtin_amdgcn_readlane(my_id, r), pos = __builtin_amdgcn_readlane(my_pos, r);
+        const int id = __builtin_amdgcn_readlane(my_id, r), nb = __popcll(__ballot(begin <= row));
+        int pos = row - __builtin_amdgcn_readlane(begin, nb > 0 ? nb - 1 : 0);
+        pos = pos < 0 ? 0 : (pos >= P ? P - 1 : pos);
         const T* te = (const T*)(sb + tok_off) + (size_t)id * H;
         const T* pe = (const T*)(sb + pos_off) + (size_t)pos * H;
         float v[MAXC][8];
@@ -442,19 +436,20 @@ __global__ void sum_students_kernel(const float* __restrict__ z, int n, int k, f
     logits[i] = total;
 }
 
-// Classifier on pooled rows and the cross-student sum: one workgroup per sequence, wave w takes students w, w + 4, ...
+// Classifier on pooled rows and the cross-student sum: one workgroup per sequence, a wave per student (up to kClassifyWaves).
 // One pass over the row for CB classes at a time and all its loads requested together: a student is one memory round trip
 // (a pass per class, a chain of dependent iterations each, took 11.6 us for one sequence and eight students).
 // BARE: the rows are the pooler's sums, bias and tanh are applied here.
+constexpr int kClassifyWaves = 8;
 template <int CB, bool BARE>
-__global__ __launch_bounds__(256) void head_classify_kernel(const char* arena, size_t student_stride, size_t wc_off,
+__global__ __launch_bounds__(64 * kClassifyWaves) void head_classify_kernel(const char* arena, size_t student_stride, size_t wc_off,
                                                             size_t bc_off, size_t bp_off, const float* __restrict__ pooled, size_t p_ss,
                                                             int B, int H, int C, int k, float* __restrict__ z,
                                                             float* __restrict__ logits)
 {
     __shared__ float zs[64][16];                 // [student][class]
     const int b = blockIdx.x, lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-    for (int m = wave; m < k; m += 4) {
+    for (int m = wave; m < k; m += (int)(blockDim.x >> 6)) {
         const char* sb = arena + (size_t)m * student_stride;
         const bf16* Wc = (const bf16*)(sb + wc_off);
         const float* p = pooled + (size_t)m * p_ss + (size_t)b * H;
@@ -500,7 +495,7 @@ hipError_t launch_head_classify(const sp_model* M, const float* pooled, size_t p
     const sp_config& c = M->cfg;
     if (!bf16_path(c) || k > 64 || c.hidden > 1024 || c.hidden % 64) return hipErrorInvalidValue;
 #define SP_CLASSIFY(CB, BARE)                                                                                       \
-    hipLaunchKernelGGL((head_classify_kernel<CB, BARE>), dim3((unsigned)B), dim3(256), 0, s, M->arena, M->L.student_stride, \
+    hipLaunchKernelGGL((head_classify_kernel<CB, BARE>), dim3((unsigned)B), dim3(64 * (k < kClassifyWaves ? k : kClassifyWaves)), 0, s, M->arena, M->L.student_stride, \
                        M->L.wc, M->L.bc, M->L.bp, pooled, p_ss, B, c.hidden, c.classes, k, z, logits)
     if (bare) { if (c.classes <= 2) SP_CLASSIFY(2, true); else SP_CLASSIFY(4, true); }
     else { if (c.classes <= 2) SP_CLASSIFY(2, false); else SP_CLASSIFY(4, false); }

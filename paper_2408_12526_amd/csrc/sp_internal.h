@@ -138,6 +138,26 @@ __device__ inline void barrier_lds()
     asm volatile("" ::: "memory");
 }
 
+// The last sequence b for which in(b, cu[b]) holds (true up to some b, at least for 0), and its boundaries.  The whole wave looks at
+// 64 boundaries at once, so 64 sequences take one round trip to memory and 4096 take two, where halving takes six and twelve.
+template <class In>
+__device__ __forceinline__ int last_sequence(const int32_t* __restrict__ cu, int B, int lane, In in, int& c0, int& c1)
+{
+    int base = 0, span = B;
+    for (;;) {
+        const int step = (span + 63) >> 6, off = lane * step;
+        const int at = base + (off < span ? off : 0), v0 = cu[at], v1 = cu[at + 1];
+        const int n = __popcll(__ballot(off < span && in(at, v0))), last = n > 0 ? n - 1 : 0;
+        base += last * step;
+        if (step == 1) {
+            c0 = __builtin_amdgcn_readlane(v0, last);
+            c1 = __builtin_amdgcn_readlane(v1, last);
+            return base;
+        }
+        span = step < span - last * step ? step : span - last * step;
+    }
+}
+
 #endif  // __HIPCC__
 
 constexpr int kRowPad = 256;  // activation rows per student are padded to a multiple of this
