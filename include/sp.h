@@ -213,8 +213,9 @@ int sp_check_inputs(const sp_model* model, const int32_t* token_ids, const int32
  *   g    [rows][F]  GELU(FFN up-projection)
  *   z    float32 [K][batch][C] per-student classifier outputs before the sum
  * and, written only when the last layer ran on the first-token rows (see
- * sp_config.last_layer_all_tokens; `x` then still holds the last layer's input), per
- * student first_rows rows, row b = sequence b:
+ * sp_config.last_layer_all_tokens; `x` then holds the last layer's input, or, where that
+ * layer reads the other rows before their LayerNorm, row b = its input for the first token
+ * of sequence b), per student first_rows rows, row b = sequence b:
  *   first_q    [first_rows][H]  the last layer's queries of the first tokens
  *   first_att  [first_rows][H]  its attention output for the first tokens */
 typedef struct {

@@ -333,8 +333,9 @@ static int run_students(const sp_model* M0, const WsLayout& W, const int32_t* id
     // of fewer than a tile per compute unit splits the reduction range over workgroups; the fp32 slices go into the buffers
     // that are free at that point (q|k|v and values, and behind them the attention output and the pre-LayerNorm rows once
     // the output projection is done), and the LayerNorm adds them.
+    // raw (not null): the caller can do with the rows before the LayerNorm (in u); set if that is what it gets.
     auto project_ln = [&](const char* A, int Kd, size_t a_ss, size_t w_off, size_t b_off, const char* res, char* out, size_t g_off,
-                          size_t be_off, int phase) -> int {
+                          size_t be_off, int phase, bool* raw = nullptr) -> int {
         int splits = 1;
         const long tiles = (long)((mrows + 63) / 64) * (H / (H % 256 ? 128 : 256)) * k;
         // Tiles of half the features: only reductions that are deep for their tiles gain (hidden 384, depth 1536, 33 tiles: 14.7 us
@@ -358,6 +359,7 @@ static int run_students(const sp_model* M0, const WsLayout& W, const int32_t* id
         } else {
             SP_TRY(launch_gemm(M, A, Kd, w_off, b_off, u, H, res, H, mrows, H, Kd, k, EPI_BIAS_RESIDUAL, a_ss, sH, sH, s));
             SP_MARK(phase);
+            if (raw) { *raw = true; return SP_OK; }
             SP_TRY(launch_layernorm(M, u, out, rows, mrows, k, g_off, be_off, s));
         }
         SP_MARK(SP_PHASE_LAYERNORM);
@@ -374,12 +376,12 @@ static int run_students(const sp_model* M0, const WsLayout& W, const int32_t* id
         return launch_gemm(M, x1r, H, lo + L.w1, lo + L.b1, gr, F, nullptr, 0, (n + 63) / 64 * 64, F, H, k, EPI_BIAS_GELU,
                            x1_ss * ab, g_ss * ab, 0, s, nullptr, 0, 0, 0, packed);
     };
-    // Last layer from the attention output of the first tokens: A holds token rows (a_first) or one row per sequence; x1c and gc
-    // are scratch of one row per sequence.  ss: student strides, elements.
-    auto first_rows_tail = [&](size_t lo, const FirstRows& f, const bf16* A, size_t a_ss, bool a_first, bf16* x1c, size_t x1c_ss,
-                               bf16* gc, size_t gc_ss) -> int {
+    // Last layer from the attention output of the first tokens: A and x hold token rows (a_first, x_first) or one row per
+    // sequence; x1c and gc are scratch of one row per sequence.  ss: student strides, elements.
+    auto first_rows_tail = [&](size_t lo, const FirstRows& f, const bf16* A, size_t a_ss, bool a_first, bool x_first, bf16* x1c,
+                               size_t x1c_ss, bf16* gc, size_t gc_ss) -> int {
         const size_t sT = (size_t)rows * H;
-        SP_TRY(launch_rows_residual(M, lo + L.wo, lo + L.bo, A, a_ss, rows_layout(H), H, a_first, (const bf16*)x, sT, true, f.o,
+        SP_TRY(launch_rows_residual(M, lo + L.wo, lo + L.bo, A, a_ss, rows_layout(H), H, a_first, (const bf16*)x, sT, x_first, f.o,
                                     f.o_ss, cu, T, B, k, s));
         SP_MARK(SP_PHASE_LAST_FIRST);
         SP_TRY(ffn_up(lo, B, f.o, f.o_ss, x1c, x1c_ss, gc, gc_ss, true));
@@ -394,12 +396,12 @@ static int run_students(const sp_model* M0, const WsLayout& W, const int32_t* id
     };
     // The same from one row per sequence where the rows are many: the tile kernels, whose bare sums the LayerNorm launches
     // (and the classifier) finish.  xf: scratch like x1c.  Rows behind the last sequence are computed and never read.
-    auto first_rows_tail_tiles = [&](size_t lo, const FirstRows& f, const bf16* A, size_t a_ss, bf16* x1c, size_t x1c_ss, bf16* gc,
-                                     size_t gc_ss, bf16* xf, size_t xf_ss) -> int {
+    auto first_rows_tail_tiles = [&](size_t lo, const FirstRows& f, const bf16* A, size_t a_ss, bool x_first, bf16* x1c, size_t x1c_ss,
+                                     bf16* gc, size_t gc_ss, bf16* xf, size_t xf_ss) -> int {
         const int mr = (B + 63) / 64 * 64;
         SP_TRY(launch_gemm_split(M, A, H, lo + L.wo, f.o, 0, mr, H, H, k, 1, a_ss * ab, f.o_ss, s));
-        SP_TRY(launch_rows_ln_add(M, lo + L.ln1g, lo + L.ln1b, f.o, f.o_ss, lo + L.bo, x, (size_t)rows * H, cu, T, x1c, x1c_ss, B, k,
-                                  s));
+        SP_TRY(launch_rows_ln_add(M, lo + L.ln1g, lo + L.ln1b, f.o, f.o_ss, lo + L.bo, x, (size_t)rows * H, x_first ? cu : nullptr, T, x1c,
+                                  x1c_ss, B, k, s));
         SP_MARK(SP_PHASE_LAST_FIRST);
         SP_TRY(launch_gemm(M, x1c, H, lo + L.w1, lo + L.b1, gc, F, nullptr, 0, mr, F, H, k, EPI_BIAS_GELU, x1c_ss * ab, gc_ss * ab,
                            0, s));
@@ -442,7 +444,7 @@ static int run_students(const sp_model* M0, const WsLayout& W, const int32_t* id
             if (with_head && !c.last_layer_all_tokens && l == c.layers - 1) {
                 SP_TRY(launch_attention_first(M, qkv, vt, att, cu, B, T, max_seqlen, rows, k, s));
                 SP_MARK(SP_PHASE_LAST_FIRST);
-                return first_rows_tail(lo, small, (const bf16*)att, sT, true, (bf16*)x1, sT, (bf16*)g, sG);
+                return first_rows_tail(lo, small, (const bf16*)att, sT, true, true, (bf16*)x1, sT, (bf16*)g, sG);
             }
             SP_TRY(launch_attention(M, qkv, vt, att, cu, B, T, max_seqlen, rows, k, s));
             SP_MARK(SP_PHASE_ATTENTION);
@@ -479,8 +481,14 @@ static int run_students(const sp_model* M0, const WsLayout& W, const int32_t* id
     if (f32_layer) SP_TRY(launch_f32_embed(M, L.layer0, ids, cu, B, T, x, qkv, rows, k, s));
     else SP_TRY(launch_embed_ln(M, ids, cu, B, T, rows, mrows, k, x, att, s, xq, kActQuantScale, attq));
     SP_MARK(SP_PHASE_EMBED);
+    // Where the folded last layer follows, the rows stay as they are before the LayerNorm (see attention_first_fold_kernel) and only
+    // the first tokens' are normalised, into the first B rows of x: a read and a write of every row less, for a longer fold.  us a
+    // call, with the LayerNorm of all rows / this: hidden 768, 5.2 k tokens, eight students 876 / 858, quantised 666 / 633; 14.3 k
+    // tokens, eight 2152 / 2111, one 344 / 340; hidden 256, 4.3 k, three 122.4 / 122.7; hidden 1024, 19.5 k, six 3530 / 3474.
+    bool raw = false;
     for (int l = 0; l < stop_layers; ++l) {
-        const size_t lo = L.layer0 + (size_t)l * L.layer_stride;
+        const size_t lo = L.layer0 + (size_t)l * L.layer_stride, pl = lo - L.layer_stride;
+        const bool fold_next = first_only && l == c.layers - 2;
         if (first_only && l == c.layers - 1) {
             const bool own = T >= kFirstOnlyMinTokens;
             const size_t sT = (size_t)rows * H, sC = (size_t)crows * H;
@@ -494,15 +502,20 @@ static int run_students(const sp_model* M0, const WsLayout& W, const int32_t* id
             bf16* g1 = own ? (bf16*)(w + W.cg) + m0 * sg : (bf16*)g;
             const FirstRows f = own ? FirstRows{(float*)(w + W.cu0) + m0 * sC, (float*)qt1, (float*)(w + W.cu0) + m0 * sC, sC, sq / 2}
                                     : FirstRows{part, (float*)qt1, part, part_ss, sq / 2};
-            SP_TRY(launch_fold_query(M, lo, x, rows, cu, T, B, q1, s1, qt1, sq, k, s));
+            if (raw) {
+                SP_TRY(launch_layernorm_first(M, u, x, rows, cu, B, T, k, pl + L.ln2g, pl + L.ln2b, s));
+                SP_MARK(SP_PHASE_LAST_FIRST);
+            }
+            SP_TRY(launch_fold_query(M, lo, x, rows, raw ? nullptr : cu, T, B, q1, s1, qt1, sq, k, s));
             SP_MARK(SP_PHASE_LAST_FIRST);
-            SP_TRY(launch_attention_first_fold(M, x, qt1, sq, xb1, sx, cu, B, T, max_seqlen, rows, k, s));
+            SP_TRY(launch_attention_first_fold(M, raw ? u : x, qt1, sq, xb1, sx, cu, B, T, max_seqlen, rows, k, s, raw, pl + L.ln2g,
+                                               pl + L.ln2b));
             SP_MARK(SP_PHASE_LAST_FIRST);
             SP_TRY(launch_rows_head_values(M, lo, xb1, sx, att1, s1, B, k, s));
             SP_MARK(SP_PHASE_LAST_FIRST);
             if (own && (long)B * k_rule * H > kRowsTilesElems)
-                return first_rows_tail_tiles(lo, f, att1, s1, x11, s1, g1, sg, xb1, sx);
-            return first_rows_tail(lo, f, att1, s1, false, x11, s1, g1, sg);
+                return first_rows_tail_tiles(lo, f, att1, s1, !raw, x11, s1, g1, sg, xb1, sx);
+            return first_rows_tail(lo, f, att1, s1, false, !raw, x11, s1, g1, sg);
         }
         if (fp8)
             SP_TRY(launch_gemm_fp8(M, xq, H, lo + L.wqkv8, lo + L.sqkv, lo + L.bqkv, kActQuantScale, qkv, 3 * H, nullptr, 0,
@@ -536,7 +549,8 @@ static int run_students(const sp_model* M0, const WsLayout& W, const int32_t* id
             if (rc != SP_OK) return rc;
             SP_TRY(launch_gemm(M, x1, H, lo + L.w1, lo + L.b1, g, F, nullptr, 0, mrows, F, H, k, EPI_BIAS_GELU, sH, sF, 0, s));
             SP_MARK(SP_PHASE_FFN_UP);
-            rc = project_ln(g, F, sF, lo + L.w2, lo + L.b2, x1, x, lo + L.ln2g, lo + L.ln2b, SP_PHASE_FFN_DOWN);
+            rc = project_ln(g, F, sF, lo + L.w2, lo + L.b2, x1, x, lo + L.ln2g, lo + L.ln2b, SP_PHASE_FFN_DOWN,
+                            fold_next ? &raw : nullptr);
             if (rc != SP_OK) return rc;
             continue;
         }
@@ -561,6 +575,7 @@ static int run_students(const sp_model* M0, const WsLayout& W, const int32_t* id
         else
             SP_TRY(launch_gemm(M, g, F, lo + L.w2, lo + L.b2, u, H, x1, H, mrows, H, F, k, EPI_BIAS_RESIDUAL, sF, sH, sH, s));
         SP_MARK(SP_PHASE_FFN_DOWN);
+        if (fold_next) { raw = true; continue; }
         SP_TRY(launch_layernorm(M, u, x, rows, mrows, k, lo + L.ln2g, lo + L.ln2b, s, xq, kActQuantScale));
         SP_MARK(SP_PHASE_LAYERNORM);
     }

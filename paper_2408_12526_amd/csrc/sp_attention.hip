@@ -309,6 +309,7 @@ __global__ __launch_bounds__(256, 4) void attention_bf16_kernel(AttnArgs p)
 // -------------------------------------------------------------------------------------
 
 typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
+typedef float f32x2 __attribute__((ext_vector_type(2)));
 
 // Maximum / sum over the four lanes l % 16 + {0, 16, 32, 48} (every lane active).
 __device__ inline float max_across_rows(float v)
@@ -348,35 +349,58 @@ __device__ inline float sum_across_rows(float v)
 // start-up and barrier waits are covered by the other.
 //   qt   [m][b][head][H]   folded queries (row stride HEADS * H)
 //   xbar [m][b][head][H]   output
+//
+// RAW: the token rows are u, before their LayerNorm x = g (u - mu) r + b (mu and r = 1 / deviation, per token), which nobody else
+// needs of all tokens, so that the LayerNorm launch (a read and a write of every row) falls away:
+//     q~ . x_t = r_t ((g q~) . u_t - mu_t sum(g q~)) + const,    sum_t p_t x_t = g (a - mean(a)) + b sum_t p_t,  a = sum_t p_t r_t u_t.
+// Sums and squares of the rows come from the matrix cores (a product with ones, the diagonal of the rows' product with themselves)
+// and cross the waves with the partial scores.  sum(g q~) and mean(a) are formed from the rounded g q~ and p r that the products
+// use, so that a mean common to the row cancels to fp32; E[u^2] - mu^2 loses (mu / deviation)^2 2^-23 of the variance, less than the
+// rounding of u to bf16 has lost ((mu / deviation) 2^-9 of the deviation) for any mean below 2^14 deviations.  One rounding
+// (of x) fewer than before.
 constexpr int kFoldWaves = 8;
-template <int HEADS>
+template <int HEADS, bool RAW>
 struct FoldLds {
     static constexpr int H = HEADS * kD, FW = H / kFoldWaves;   // features per wave
     static constexpr int SCP = 36;                          // pitch of a head's 32 scores (floats)
     static constexpr size_t slab_bytes = (size_t)32 * FW * 2;   // per wave: 32 tokens x FW features
-    static constexpr size_t bytes = kFoldWaves * (slab_bytes + 16 * 32 * 4) + (size_t)16 * SCP * 4;
+    static constexpr size_t stats = kFoldWaves * (slab_bytes + 16 * 32 * 4) + (size_t)16 * SCP * 4;
+    static constexpr size_t bytes = stats + (RAW ? 32 * kFoldWaves * 8 + 32 * 4 + kFoldWaves * 16 * 4 : 0);
     static_assert(FW % 32 == 0 && HEADS <= 16 && bytes <= 160 * 1024, "whole reduction steps per wave, heads in one block");
 };
 
-template <int HEADS>
-__global__ __launch_bounds__(512, HEADS == 16 ? 2 : 4) void attention_first_fold_kernel(const bf16* __restrict__ x,
-                                                                      const bf16* __restrict__ qt,
-                                                                      bf16* __restrict__ xbar,
-                                                                      const int32_t* __restrict__ cu, int B, int Tn,
-                                                                      int rows, size_t qt_ss, size_t xb_ss,
-                                                                      int max_seqlen)
+struct FoldArgs {
+    const bf16 *x, *qt;
+    bf16* xbar;
+    size_t qt_ss, xb_ss;
+    const int32_t* cu;
+    int Tn, rows, max_seqlen;
+    const char* arena;                // RAW: scale and shift (byte offsets into a student slab)
+    size_t ss, g, b;
+    float eps;
+};
+
+template <int HEADS, bool RAW>
+__global__ __launch_bounds__(512, HEADS == 16 ? 2 : 4) void attention_first_fold_kernel(FoldArgs p)
 {
-    using F = FoldLds<HEADS>;
+    using F = FoldLds<HEADS, RAW>;
     constexpr int H = F::H, FW = F::FW, SCP = F::SCP, NW = kFoldWaves;
     constexpr int KS = FW / 32;                             // 32-feature steps (scores) = 32-feature blocks (output)
     constexpr int PITCH = FW * 2;                           // slab row, bytes
     extern __shared__ uint4 fold_smem[];
     float* part = (float*)((char*)fold_smem + NW * F::slab_bytes);   // [waves][16][32] partial score tiles
     float* sc = part + NW * 16 * 32;                        // [16][SCP] scores of the current tile, log2 units
+    float* stat = (float*)((char*)fold_smem + F::stats);    // [32][waves][2] sums and squares of the tile's rows
+    float* norm = stat + 32 * NW * 2;                       // [32] 1 / deviation
+    float* qsum = norm + 32;                                // [waves][16] sums of the scaled folded queries, later of the weighted rows
+    const bf16 *x = p.x, *qt = p.qt;
+    const int32_t* cu = p.cu;
+    const int Tn = p.Tn, rows = p.rows, max_seqlen = p.max_seqlen;
+    const size_t qt_ss = p.qt_ss;
     const int m = blockIdx.y, b = blockIdx.x;
     const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     char* slab = (char*)fold_smem + wave * F::slab_bytes;   // this wave's features of the tile: [token][FW / 8 chunks]
-    bf16* xb = xbar + (size_t)m * xb_ss + (size_t)b * HEADS * H;
+    bf16* xb = p.xbar + (size_t)m * p.xb_ss + (size_t)b * HEADS * H;
     int t0 = cu[b], t1 = cu[b + 1];
     t0 = t0 < 0 ? 0 : (t0 > Tn - 1 ? Tn - 1 : t0);
     int L = t1 - t0;
@@ -399,7 +423,22 @@ __global__ __launch_bounds__(512, HEADS == 16 ? 2 : 4) void attention_first_fold
                 for (int e = 0; e < 8; ++e) fq[st][e] = (bf16)0.f;
             }
         }
+        if (RAW) {
+            const float* gam = (const float*)(p.arena + (size_t)m * p.ss + p.g) + wave * FW + 8 * kg;
+#pragma unroll
+            for (int st = 0; st < KS; ++st) {
+                const f32x4 g0 = *(const f32x4*)(gam + 32 * st), g1 = *(const f32x4*)(gam + 32 * st + 4);
+#pragma unroll
+                for (int e = 0; e < 4; ++e) {
+                    fq[st][e] = (bf16)((float)fq[st][e] * g0[e]);
+                    fq[st][4 + e] = (bf16)((float)fq[st][4 + e] * g1[e]);
+                }
+            }
+        }
     }
+    bf16x8 ones;
+#pragma unroll
+    for (int e = 0; e < 8; ++e) ones[e] = (bf16)1.f;
     // token rows of a tile in operand layout: block nb holds tokens 16 nb + l16.  Rows beyond the sequence repeat its
     // last row (they get probability zero).
     bf16x8 xr[2][KS];
@@ -418,7 +457,13 @@ __global__ __launch_bounds__(512, HEADS == 16 ? 2 : 4) void attention_first_fold
     f32x4 acc[2 * KS];                                      // [block of 32 features][c]: feature 2 row + c, column = head
 #pragma unroll
     for (int a = 0; a < 2 * KS; ++a) acc[a] = f32x4{0.f, 0.f, 0.f, 0.f};
-    float mrun = -INFINITY, lrun = 0.f;
+    float mrun = -INFINITY, lrun = 0.f, qs = 0.f;            // qs: sum of this thread's head's scaled query
+    if (RAW) {
+        f32x4 a = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+        for (int st = 0; st < KS; ++st) a = __builtin_amdgcn_mfma_f32_16x16x32_bf16(fq[st], ones, a, 0, 0, 0);   // rows: heads, columns alike
+        if (l16 == 0) *(f32x4*)(qsum + wave * 16 + 4 * kg) = a;
+    }
     for (int tile = 0; tile < nt; ++tile) {
         // partial scores[head][token] over this wave's features
         f32x4 sa[2] = {f32x4{0.f, 0.f, 0.f, 0.f}, f32x4{0.f, 0.f, 0.f, 0.f}};
@@ -431,6 +476,20 @@ __global__ __launch_bounds__(512, HEADS == 16 ? 2 : 4) void attention_first_fold
         for (int nb = 0; nb < 2; ++nb)
 #pragma unroll
             for (int v = 0; v < 4; ++v) part[(wave * 16 + 4 * kg + v) * 32 + 16 * nb + l16] = sa[nb][v];
+        if (RAW) {
+#pragma unroll
+            for (int nb = 0; nb < 2; ++nb) {
+                f32x4 us = {0.f, 0.f, 0.f, 0.f}, uu = us;
+#pragma unroll
+                for (int st = 0; st < KS; ++st) {
+                    us = __builtin_amdgcn_mfma_f32_16x16x32_bf16(ones, xr[nb][st], us, 0, 0, 0);       // columns: tokens, rows alike
+                    uu = __builtin_amdgcn_mfma_f32_16x16x32_bf16(xr[nb][st], xr[nb][st], uu, 0, 0, 0);
+                }
+                // the square of token l16 is element l16 of its column: register l16 % 4 of lane group l16 / 4
+                const float sq = (l16 & 2) ? ((l16 & 1) ? uu[3] : uu[2]) : ((l16 & 1) ? uu[1] : uu[0]);
+                if (kg == l16 >> 2) *(f32x2*)(stat + ((16 * nb + l16) * NW + wave) * 2) = f32x2{us[0], sq};
+            }
+        }
         // the rows into the wave's slab: chunk ch of token r sits in slot ch ^ ((r / 2) % 4).  (The wave's previous
         // reads of the slab are behind it: LDS accesses of one wave execute in order.)
 #pragma unroll
@@ -446,6 +505,23 @@ __global__ __launch_bounds__(512, HEADS == 16 ? 2 : 4) void attention_first_fold
             float sum = 0.f;
 #pragma unroll
             for (int w = 0; w < NW; ++w) sum += part[(w * 16 + hh) * 32 + t];
+            if (RAW) {
+                if (tile == 0)
+#pragma unroll
+                    for (int w = 0; w < NW; ++w) qs += qsum[w * 16 + hh];
+                float s1 = 0.f, s2 = 0.f;
+#pragma unroll
+                for (int w = 0; w < NW; w += 2) {
+                    const f32x4 v = *(const f32x4*)(stat + (t * NW + w) * 2);
+                    s1 += v[0];
+                    s2 += v[1];
+                    s1 += v[2];
+                    s2 += v[3];
+                }
+                const float mu = s1 * (1.0f / H), var = fmaxf(s2 * (1.0f / H) - mu * mu, 0.f), r = __builtin_amdgcn_rsqf(var + p.eps);
+                sum = (sum - mu * qs) * r;
+                if (hh == 0) norm[t] = r;
+            }
             sc[hh * SCP + t] = tile * 32 + t < L ? sum * scale : -INFINITY;
         }
         barrier_lds();
@@ -453,12 +529,12 @@ __global__ __launch_bounds__(512, HEADS == 16 ? 2 : 4) void attention_first_fold
         // xbar^T[feature][head] += sum_t x[t][feature] p[head][t]
         const float* sr = sc + (l16 < HEADS ? l16 : 0) * SCP + 8 * kg;
         const f32x4 s0 = *(const f32x4*)sr, s1 = *(const f32x4*)(sr + 4);
-        float p[8];
+        float pr[8];
         float mx = -INFINITY;
 #pragma unroll
         for (int e = 0; e < 4; ++e) {
-            p[e] = s0[e];
-            p[4 + e] = s1[e];
+            pr[e] = s0[e];
+            pr[4 + e] = s1[e];
             mx = fmaxf(mx, fmaxf(s0[e], s1[e]));
         }
         mx = fmaxf(mrun, max_across_rows(mx));              // finite: the tile has at least one token of the sequence
@@ -467,15 +543,24 @@ __global__ __launch_bounds__(512, HEADS == 16 ? 2 : 4) void attention_first_fold
         float ls = 0.f;
 #pragma unroll
         for (int e = 0; e < 8; ++e) {
-            p[e] = exp2_raw(p[e] - mx);
-            ls += p[e];
+            pr[e] = exp2_raw(pr[e] - mx);
+            ls += pr[e];
         }
         lrun = fmaf(lrun, alpha, ls);
 #pragma unroll
         for (int a = 0; a < 2 * KS; ++a) acc[a] *= alpha;
         bf16x8 fp;
+        if (RAW) {
+            const f32x4 n0 = *(const f32x4*)(norm + 8 * kg), n1 = *(const f32x4*)(norm + 8 * kg + 4);
 #pragma unroll
-        for (int e = 0; e < 8; ++e) fp[e] = (bf16)(l16 < HEADS ? p[e] : 0.f);
+            for (int e = 0; e < 4; ++e) {
+                fp[e] = (bf16)(l16 < HEADS ? pr[e] * n0[e] : 0.f);
+                fp[4 + e] = (bf16)(l16 < HEADS ? pr[4 + e] * n1[e] : 0.f);
+            }
+        } else {
+#pragma unroll
+            for (int e = 0; e < 8; ++e) fp[e] = (bf16)(l16 < HEADS ? pr[e] : 0.f);
+        }
 #pragma unroll
         for (int gq = 0; gq < KS; ++gq) {
             bf16x2 xv[8];
@@ -492,13 +577,31 @@ __global__ __launch_bounds__(512, HEADS == 16 ? 2 : 4) void attention_first_fold
         }
     }
     const float inv = 1.0f / sum_across_rows(lrun);
+    const float *gam = (const float*)(p.arena + (size_t)m * p.ss + p.g) + wave * FW, *bet = (const float*)(p.arena + (size_t)m * p.ss + p.b) + wave * FW;
+    float common = 0.f;                                     // mean of the head's weighted row over the features
+    if (RAW) {
+        float t = 0.f;
+#pragma unroll
+        for (int a = 0; a < 2 * KS; ++a) t += acc[a][0] + acc[a][1] + (acc[a][2] + acc[a][3]);
+        t = sum_across_rows(t);
+        if (kg == 0) qsum[wave * 16 + l16] = t;             // (the queries' sums were read before the last tile's barriers)
+        barrier_lds();
+#pragma unroll
+        for (int w = 0; w < NW; ++w) common += qsum[w * 16 + l16];
+        common *= 1.0f / H;
+    }
     // lane: head l16; element v of acc[2 gq + c] is feature 32 gq + 2 (4 kg + v) + c of the wave's FW
     if (l16 < HEADS) {
 #pragma unroll
         for (int gq = 0; gq < KS; ++gq) {
             bf16x8 r;
 #pragma unroll
-            for (int i = 0; i < 8; ++i) r[i] = (bf16)(acc[2 * gq + (i & 1)][i >> 1] * inv);
+            for (int i = 0; i < 8; ++i) {
+                float v = acc[2 * gq + (i & 1)][i >> 1];
+                if (RAW) v = gam[32 * gq + 8 * kg + i] * ((v - common) * inv) + bet[32 * gq + 8 * kg + i];
+                else v *= inv;
+                r[i] = (bf16)v;
+            }
             *(bf16x8*)(xb + (size_t)l16 * H + wave * FW + 32 * gq + 8 * kg) = r;
         }
     }
@@ -646,15 +749,17 @@ bool attention_first_fold_supported(const sp_config& c, int max_seqlen)
 
 hipError_t launch_attention_first_fold(const sp_model* M, const void* x, const void* qt, size_t qt_ss, void* xbar,
                                        size_t xb_ss, const int32_t* cu, int B, int T, int max_seqlen, int rows, int k,
-                                       hipStream_t s)
+                                       hipStream_t s, bool raw, size_t g_off, size_t b_off)
 {
     const sp_config& c = M->cfg;
     if (!attention_first_fold_supported(c, max_seqlen)) return hipErrorInvalidValue;
+    const FoldArgs a{(const bf16*)x, (const bf16*)qt, (bf16*)xbar, qt_ss, xb_ss, cu, T, rows, max_seqlen, M->arena, M->L.student_stride,
+                     g_off, b_off, c.ln_eps};
     dim3 grid((unsigned)B, (unsigned)k);
-#define SP_FOLD(HEADS)                                                                                              \
+#define SP_FOLD(HEADS, RAW)                                                                                         \
     do {                                                                                                            \
-        auto kern = attention_first_fold_kernel<HEADS>;                                                             \
-        constexpr size_t smem = FoldLds<HEADS>::bytes;                                                              \
+        auto kern = attention_first_fold_kernel<HEADS, RAW>;                                                        \
+        constexpr size_t smem = FoldLds<HEADS, RAW>::bytes;                                                         \
         static std::atomic<bool> raised{false}; /* the attribute is sticky for the process */                      \
         if (smem > 48 * 1024 && !raised) {                                                                          \
             hipError_t e = hipFuncSetAttribute((const void*)kern, hipFuncAttributeMaxDynamicSharedMemorySize,      \
@@ -662,15 +767,16 @@ hipError_t launch_attention_first_fold(const sp_model* M, const void* x, const v
             if (e != hipSuccess) return e;                                                                          \
             raised = true;                                                                                          \
         }                                                                                                           \
-        hipLaunchKernelGGL(kern, grid, dim3(64 * kFoldWaves), smem, s, (const bf16*)x, (const bf16*)qt, (bf16*)xbar,  \
-                           cu, B, T, rows, qt_ss, xb_ss, max_seqlen);                                              \
+        hipLaunchKernelGGL(kern, grid, dim3(64 * kFoldWaves), smem, s, a);                                          \
     } while (0)
+#define SP_FOLD_ANY(HEADS) do { if (raw) SP_FOLD(HEADS, true); else SP_FOLD(HEADS, false); } while (0)
     switch (c.heads) {
-        case 4: SP_FOLD(4); break;
-        case 8: SP_FOLD(8); break;
-        case 12: SP_FOLD(12); break;
-        default: SP_FOLD(16); break;
+        case 4: SP_FOLD_ANY(4); break;
+        case 8: SP_FOLD_ANY(8); break;
+        case 12: SP_FOLD_ANY(12); break;
+        default: SP_FOLD_ANY(16); break;
     }
+#undef SP_FOLD_ANY
 #undef SP_FOLD
     return hipGetLastError();
 }

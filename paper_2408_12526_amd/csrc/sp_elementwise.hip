@@ -192,6 +192,27 @@ __global__ __launch_bounds__(256) void layernorm_kernel(const char* arena, size_
     }
 }
 
+// The first tokens' rows alone, one wave per row.
+template <int MAXC>
+__global__ __launch_bounds__(256) void layernorm_first_kernel(const char* arena, size_t student_stride, size_t g_off, size_t b_off,
+                                                              const bf16* __restrict__ u, bf16* __restrict__ out, int rows,
+                                                              const int32_t* __restrict__ cu, int B, int Tn, int H, float eps)
+{
+    const int m = blockIdx.y, lane = threadIdx.x & 63, b = blockIdx.x * 4 + (threadIdx.x >> 6);
+    if (b >= B) return;
+    const int nch = H >> 3;
+    const char* sb = arena + (size_t)m * student_stride;
+    float gg[MAXC][8], bb[MAXC][8], v[MAXC][8];
+    int row = cu[b];
+    row = row < 0 ? 0 : (row >= Tn ? Tn - 1 : row);
+    load_gamma_beta<MAXC>((const float*)(sb + g_off), (const float*)(sb + b_off), nch, lane, gg, bb);
+    const bf16* in = u + ((size_t)m * rows + row) * H;
+#pragma unroll
+    for (int i = 0; i < MAXC; ++i)
+        if (lane + 64 * i < nch) load8(in + (lane + 64 * i) * 8, v[i]);
+    ln_row_store<bf16, MAXC>(v, nch, lane, H, gg, bb, eps, out + ((size_t)m * rows + b) * H);
+}
+
 // Sum of the slices of a split reduction + bias + residual, then LayerNorm: one wave per row.  Rows T..mrows become zero:
 // attention multiplies the values of up to seven of them by zero probabilities, so what the next layer forms there
 // must be finite, and the operands of this projection need not be (the slices lie over the attention output's padding rows).
@@ -553,6 +574,19 @@ hipError_t launch_layernorm(const sp_model* M, const void* u, void* out, int row
         if (maxc <= 1) SP_LN(float, 1); else if (maxc == 2) SP_LN(float, 2); else SP_LN(float, 4);
     }
 #undef SP_LN
+    return hipGetLastError();
+}
+
+hipError_t launch_layernorm_first(const sp_model* M, const void* u, void* out, int rows, const int32_t* cu, int B, int T, int k,
+                                  size_t g_off, size_t b_off, hipStream_t s)
+{
+    const sp_config& c = M->cfg;
+    if (!bf16_path(c) || B < 1 || B > rows || c.hidden > 1024) return hipErrorInvalidValue;
+    const dim3 grid((unsigned)((B + 3) / 4), (unsigned)k);
+#define SP_GO(MAXC) hipLaunchKernelGGL(layernorm_first_kernel<MAXC>, grid, dim3(256), 0, s, M->arena, M->L.student_stride, g_off, \
+                                       b_off, (const bf16*)u, (bf16*)out, rows, cu, B, T, c.hidden, c.ln_eps)
+    if (c.hidden <= 512) SP_GO(1); else SP_GO(2);
+#undef SP_GO
     return hipGetLastError();
 }
 

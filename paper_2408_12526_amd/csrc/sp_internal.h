@@ -246,6 +246,10 @@ hipError_t launch_embed_ln(const sp_model* M, const int32_t* ids, const int32_t*
 hipError_t launch_layernorm(const sp_model* M, const void* u, void* out, int rows, int mrows, int k, size_t g_off,
                             size_t b_off, hipStream_t s, void* outq = nullptr, float qscale = 1.f);
 
+// out[m][b][:] = LN(u[m][cu[b]][:]; g, b) for b < B (bf16 path; the same arithmetic)
+hipError_t launch_layernorm_first(const sp_model* M, const void* u, void* out, int rows, const int32_t* cu, int B, int T, int k,
+                                  size_t g_off, size_t b_off, hipStream_t s);
+
 // EPI_QKV (bf16 path only): bias; output columns >= n_split (the value projection) are written transposed,
 // out2[m][column - n_split][row], so that attention reads key-contiguous value tiles.
 enum Epilogue { EPI_BIAS = 0, EPI_BIAS_GELU = 1, EPI_BIAS_RESIDUAL = 2, EPI_QKV = 3, EPI_BIAS_TANH = 4, EPI_PARTIAL = 5 };
@@ -305,7 +309,7 @@ hipError_t launch_rows_residual(const sp_model* M, size_t w_off, size_t b_off, c
 // att[b][h*64..] = Wv_h xbar[b][h] + bv_h
 hipError_t launch_rows_head_values(const sp_model* M, size_t lo, const void* xbar, size_t xb_ss, void* att, size_t att_ss,
                                    int nrows, int k, hipStream_t s);
-// q[b] = x[cu[b]] Wq^T + bq; qt[b][h] = Wk_h q[b][h]
+// q[b] = x[cu[b]] Wq^T + bq; qt[b][h] = Wk_h q[b][h]  (cu null: x[b])
 hipError_t launch_fold_query(const sp_model* M, size_t lo, const void* x, int rows, const int32_t* cu, int T, int B,
                              void* q, size_t q_ss, void* qt, size_t qt_ss, int k, hipStream_t s);
 // attention output of the first token of every sequence, at its token row
@@ -342,11 +346,11 @@ hipError_t launch_attention(const sp_model* M, const void* qkv, const void* vt, 
 
 // Attention of the first token of each sequence with folded queries: for sequence b and head h,
 // p = softmax_t(qt[m][b][h] . x[m][t] / 8) over the tokens t of the sequence and xbar[m][b][h][:] = sum_t p_t x[m][t][:].
-// qt and xbar are [m][.._ss elements], rows of [heads][H].
+// qt and xbar are [m][.._ss elements], rows of [heads][H].  raw: x holds rows before their LayerNorm (g_off, b_off).
 bool attention_first_fold_supported(const sp_config& c, int max_seqlen);
 hipError_t launch_attention_first_fold(const sp_model* M, const void* x, const void* qt, size_t qt_ss, void* xbar,
                                        size_t xb_ss, const int32_t* cu, int B, int T, int max_seqlen, int rows, int k,
-                                       hipStream_t s);
+                                       hipStream_t s, bool raw, size_t g_off, size_t b_off);
 
 // Head on fp32 pooled rows (p_ss: elements from student to student): z[m][b][c] = pooled[m][b] . Wc + bc; logits[b][c] =
 // sum_{m<k} z[m][b][c] (m ascending; not written if null).  bare: the rows are tanh's argument without the pooler's bias.

@@ -433,7 +433,7 @@ __global__ __launch_bounds__(256) void fold_query_kernel(FoldQArgs p)
         int t[4];
 #pragma unroll
         for (int q = 0; q < 4; ++q) {
-            const int r = r0 + 4 * wave + q, v = cu[r < p.M ? r : p.M - 1];
+            const int r = r0 + 4 * wave + q < p.M ? r0 + 4 * wave + q : p.M - 1, v = cu ? cu[r] : r;
             t[q] = v < 0 ? 0 : (v >= p.Tn ? p.Tn - 1 : v);
         }
 #pragma unroll

@@ -205,3 +205,39 @@ def test_tiles_of_every_height_at_their_edges(oracle64, hidden, ffn, K, tokens):
         assert np.abs(got["qkv"][m] - qkv).max() / np.abs(qkv).max() < 1.2e-2
         assert max(_stages(oracle64, shape, weights, m, x0, got["att"], got)) < 1.2e-2
     st.close()
+
+
+# 8192 tokens or more: no split reductions, so the folded last layer takes the rows before their LayerNorm
+@pytest.mark.parametrize("hidden,dtype", [(256, "bf16"), (512, "bf16"), (768, "bf16"), (1024, "bf16"), (768, "fp8")])
+@pytest.mark.parametrize("offset", [0.0, 6.0])
+def test_folded_last_layer_on_rows_before_their_layernorm(oracle64, hidden, dtype, offset):
+    """Against the oracle and the last layer on every token; a bias common to all features of the rows (their mean several times
+    their deviation) must cancel but for the rounding of the rows themselves, which grows by that factor on either way."""
+    from paper_2408_12526_amd import sp
+    shape = synth.StudentShape(K=2, layers=2, hidden=hidden, heads=hidden // 64, ffn=256, vocab=60, max_pos=256, classes=3, dtype=dtype)
+    rng = np.random.default_rng(hidden)
+    lengths = np.array((1, 2, 31, 32, 33, 64, 65, 256) + (60,) * 140, np.int32)
+    T = int(lengths.sum())
+    assert T >= 8192
+    ids, blob = synth.make_ids(rng, T, shape.vocab), synth.make_weights(rng, shape, std=0.04, ln_random=True)
+    for m in range(shape.K):
+        synth.student_views(blob, shape, m)["l0.b2"][:] += offset
+    cu, n = sp.sp_pack(lengths), 12                         # (the first twelve sequences against the oracle)
+    args = torch.from_numpy(ids).cuda(), torch.from_numpy(cu).cuda(), int(lengths.max()), shape.K
+    st = sp.Students(sp.config_from_shape(shape), blob)
+    got = st.sp_forward(*args).double().cpu().numpy()
+    x = st.read_activation(st.workspace(T, len(lengths)), "x", T, len(lengths), shape.K)
+    st.close()
+    st = sp.Students(sp.config_from_shape(shape, last_layer_all_tokens=True), blob)
+    full = st.sp_forward(*args).double().cpu().numpy()
+    x_full = st.read_activation(st.sp_forward_partial(*args, 1), "x", T, len(lengths), shape.K)
+    st.close()
+    assert np.array_equal(x[:, :len(lengths)], x_full[:, cu[:-1]])       # the first tokens' rows are the LayerNorm's, bit for bit
+    bound = {"bf16": 3e-2, "fp8": 1e-1}[dtype] * (1 if offset == 0 else 2)
+    assert np.isfinite(got).all() and np.abs(got - full).max() / np.abs(full).max() < bound
+    if dtype == "bf16":
+        ow = torch.from_numpy(blob).bfloat16().float().numpy()
+        cfg = OracleConfig(shape.K, shape.layers, shape.hidden, shape.heads, shape.ffn, shape.vocab, shape.max_pos, shape.classes, shape.ln_eps)
+        want = oracle64.forward(cfg, ow, ids[:cu[n]], cu[:n + 1], shape.K)
+        err = [np.abs(g[:n] - want).max() / np.abs(want).max() for g in (got, full)]
+        assert err[0] < bound and err[1] < bound, err
