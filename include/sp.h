@@ -76,15 +76,18 @@ typedef struct {
                          tokens: only where the call's buffers hold the folded queries); smaller bf16 calls form
                          the last layer's queries, keys and values of every token and compute everything after
                          them for the first tokens only.  1: every token goes
-                         through the whole last layer (what a stock BERT does; the fp32 path always does). */
+                         through the whole last layer (what a stock BERT does; so does the fp32 path but in
+                         calls of a few hundred rows of students of hidden 128, which compute everything after
+                         the last attention for the first tokens only). */
     int32_t single_stream;
-                      /* 0 (default): a call with >= 8192 tokens and k_active >= 2 runs the active students
-                         as two groups side by side, the second on a stream the model owns, forked from and
-                         joined to the caller's stream with events (the call stays asynchronous and can be
-                         captured in a graph; the logits are bit-identical to the single-stream result).
-                         In such large calls a student's term has the same bits for every k_active; smaller
-                         calls choose their kernels by the rows of all active students, so there the term
-                         of a student may differ between two k_active by roundings of its arithmetic.
+                      /* 0 (default): a call with k_active >= 2 and work enough (tokens x k_active x hidden >=
+                         20 Mi) runs the active students as two groups side by side, the second on a stream the
+                         model owns, forked from and joined to the caller's stream with events (the call stays
+                         asynchronous and can be captured in a graph; the logits are bit-identical to the
+                         single-stream result).
+                         In calls of >= 8192 tokens a student's term has the same bits for every k_active;
+                         smaller calls choose their kernels by the rows of all active students, so there the
+                         term of a student may differ between two k_active by roundings of its arithmetic.
                          1: everything is enqueued on the caller's stream. */
 } sp_config;
 

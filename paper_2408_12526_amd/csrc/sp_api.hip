@@ -588,18 +588,25 @@ static int run_students(const sp_model* M0, const WsLayout& W, const int32_t* id
     return SP_OK;
 }
 
-// Whole call: argument checks, then either all active students on the caller's stream, or, for large calls, two
+// Whole call: argument checks, then either all active students on the caller's stream, or, where there is work enough, two
 // halves of them side by side: the first on the caller's stream, the second on the model's auxiliary stream (forked
 // and joined with events, so the call stays asynchronous and capturable).  The matrix-core phases run at the
 // package power limit while the bandwidth-bound phases leave most of it unused; two groups of students drift out
-// of phase and fill each other's gaps (measured about 3 % on the burst workload; starting the second group late,
-// after the first group's first projection, measured no better).  The logits are summed over all
-// students in ascending order after the join, so the result does not depend on the grouping.
-static int two_groups_min_tokens()
-{
-    static const int v = [] { const char* e = getenv("SP_TWO_GROUPS_MIN_TOKENS"); return e ? atoi(e) : 8192; }();
-    return v;
-}
+// of phase and fill each other's gaps (starting the second group late, after the first group's first projection, measured no
+// better).  The logits are summed over all students in ascending order after the join, so the result does not depend on the
+// grouping.
+//
+// Work: tokens x active students x hidden width.  Fork and join cost about 20 us, and half the students fill the chip less well.  One
+// stream / two, us: 7 M (256 x 14.3 k tokens x 2) 168 / 183; 11 M (256 x 14.3 k x 3) 221 / 238; 13 M (768 x 8.5 k x 2) 392 / 406, (768 x
+// 4.3 k x 4) 401 / 426; 18.6 M (768 x 6 k x 4) 519 / 530; 22 M (768 x 14.3 k x 2) 586 / 592 and, of other lengths, 628 / 617, (1024 x
+// 10.6 k x 2) 726 / 720; 26 M (768 x 8.5 k x 4) 727 / 695, (1024 x 4.3 k x 6) 881 / 859; 27 M (768 x 4.3 k x 8) 739 / 723, quantised
+// 545 / 527; 37 M (768 x 6 k x 8) 1000 / 995; 40 M (1024 x 19.5 k x 2) 1219 / 1221; 88 M (768 x 14.3 k x 8) 2129 / 2150, quantised
+// 1491 / 1460.
+constexpr int64_t kTwoGroupsWork = 20 << 20;
+// Calls of at least this many tokens choose their kernels by the model's students, not by how many are active, and split no
+// reduction, so that a student's term has the same bits whatever k.  (Smaller calls go by the active ones: a call pruned to one student
+// would otherwise run on kernels for eight.)
+constexpr int kLargeTokens = 8192;
 
 static int run_forward(const sp_model* M, const int32_t* ids, const int32_t* cu, int B, int T, int max_seqlen, int k,
                        int stop_layers, bool with_head, void* ws, size_t ws_bytes, float* logits, hipStream_t s,
@@ -615,12 +622,10 @@ static int run_forward(const sp_model* M, const int32_t* ids, const int32_t* cu,
     if (ws_bytes < W.end) return SP_ENOMEM;
     char* w = (char*)ws;
 
-    // Large calls: kernels by the model's students, not by how many are active, so that a student's term has the same bits
-    // whatever k and however the students are grouped.  (Smaller calls go by the active ones: a call pruned to one student would
-    // otherwise run on kernels for eight.)
-    const bool large = T >= two_groups_min_tokens();
+    const bool large = T >= kLargeTokens;
     const int ka = (k + 1) / 2, k_rule = large ? (c.K + 1) / 2 : k;
-    const bool two_groups = with_head && !pt && large && k >= 2 && !c.single_stream && M->aux;
+    // (a call of that much work has more tiles than any that splits a reduction)
+    const bool two_groups = with_head && !pt && k >= 2 && (int64_t)T * k * c.hidden >= kTwoGroupsWork && !c.single_stream && M->aux;
     if (!two_groups)
         return run_students(M, W, ids, cu, B, T, max_seqlen, 0, k, k_rule, !large, stop_layers, with_head, w, logits, s, pt);
 

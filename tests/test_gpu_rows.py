@@ -207,6 +207,27 @@ def test_tiles_of_every_height_at_their_edges(oracle64, hidden, ffn, K, tokens):
     st.close()
 
 
+@pytest.mark.parametrize("hidden,K,nseq", [(768, 8, 68), (1024, 6, 68), (512, 13, 64)])
+@pytest.mark.parametrize("dtype", ["bf16", "fp8"])
+def test_two_groups_below_8192_tokens_give_the_same_bits(hidden, K, nseq, dtype):
+    """Calls whose work is enough for two groups of students although their tokens are fewer: the same logits on one stream."""
+    from paper_2408_12526_amd import sp
+    shape = synth.StudentShape(K=K, layers=2, hidden=hidden, heads=hidden // 64, ffn=512, vocab=500, max_pos=64, classes=3, dtype=dtype)
+    rng = np.random.default_rng(hidden + K)
+    lengths = np.full(nseq, 63, dtype=np.int32)
+    ids = torch.from_numpy(synth.make_ids(rng, int(lengths.sum()), shape.vocab)).cuda()
+    assert ids.numel() < 8192 and ids.numel() * K * hidden >= 20 << 20
+    cu = torch.from_numpy(sp.sp_pack(lengths)).cuda()
+    blob = synth.make_weights(rng, shape, std=0.04, ln_random=True)
+    two = sp.Students(sp.config_from_shape(shape), blob)
+    one = sp.Students(sp.config_from_shape(shape, single_stream=True), blob)
+    for k in (K, K - 1):
+        a, b = two.sp_forward(ids, cu, 63, k).cpu(), one.sp_forward(ids, cu, 63, k).cpu()
+        assert torch.equal(a, b), f"k_active {k}: {(a - b).abs().max().item():.3e}"
+    two.close()
+    one.close()
+
+
 # 8192 tokens or more: no split reductions, so the folded last layer takes the rows before their LayerNorm
 @pytest.mark.parametrize("hidden,dtype", [(256, "bf16"), (512, "bf16"), (768, "bf16"), (1024, "bf16"), (768, "fp8")])
 @pytest.mark.parametrize("offset", [0.0, 6.0])
