@@ -321,14 +321,14 @@ static int run_students(const sp_model* M0, const WsLayout& W, const int32_t* id
                             (T >= kFirstOnlyMinTokens ||
                              ((size_t)B * c.heads <= (size_t)3 * rows && (size_t)B * c.heads * H <= (size_t)rows * F));
     const int crows = W.crows;
-    // fp32 rows of the few-row projections: after the attention-output projection, after the FFN, pooled.  Calls of up to
-    // kRowsMaxTokens tokens: regions of kRowsMaxTokens rows of the scratch.  The folded last layer has as many rows as
-    // sequences: the first rows in its own buffer (fewer than kFirstOnlyMinTokens tokens: the scratch, which holds that many
-    // rows), the second over the folded queries, which nobody reads any more, and the pooled ones over the first.
+    // fp32 rows of the few-row projections: after the attention-output projection, after the FFN, and (many first tokens) the
+    // pooler's sums.  Calls of up to kRowsMaxTokens tokens: regions of kRowsMaxTokens rows of the scratch.  The folded last layer has
+    // as many rows as sequences: the first rows in its own buffer (fewer than kFirstOnlyMinTokens tokens: the scratch, which holds
+    // that many rows), the second over the folded queries, which nobody reads any more, and the sums over the first.
     struct FirstRows { float *o, *d, *pooled; size_t o_ss, d_ss; };
     float* const part = (float*)(w + W.part) + (size_t)m0 * kRowsU * H;
     const size_t part_ss = (size_t)kRowsU * H;
-    const FirstRows small{part, part + (size_t)kRowsMaxTokens * H, part + (size_t)2 * kRowsMaxTokens * H, part_ss, part_ss};
+    const FirstRows small{part, part + (size_t)kRowsMaxTokens * H, nullptr, part_ss, part_ss};
     // Projection onto the hidden width, residual and LayerNorm of the T token rows (bf16): out = LN(A W^T + b + res).  A launch
     // of fewer than a tile per compute unit splits the reduction range over workgroups; the fp32 slices go into the buffers
     // that are free at that point (q|k|v and values, and behind them the attention output and the pre-LayerNorm rows once
@@ -389,8 +389,8 @@ static int run_students(const sp_model* M0, const WsLayout& W, const int32_t* id
         SP_TRY(launch_rows_residual(M, lo + L.w2, lo + L.b2, gc, gc_ss, packed_layout(F), F, false, x1c, x1c_ss, false, f.d,
                                     f.d_ss, cu, T, B, k, s));
         SP_MARK(SP_PHASE_LAST_FIRST);
-        SP_TRY(launch_rows_pooler(M, lo, f.d, f.d_ss, B, f.pooled, f.o_ss, k, s));
-        SP_TRY(launch_head_classify(M, f.pooled, f.o_ss, B, k, z, logits, s));
+        SP_TRY(launch_rows_pooler(M, lo, f.d, f.d_ss, B, zpart, k, s));
+        SP_TRY(launch_head_sum(M, zpart, B, k, z, logits, s));
         SP_MARK(SP_PHASE_HEAD);
         return SP_OK;
     };
@@ -410,7 +410,7 @@ static int run_students(const sp_model* M0, const WsLayout& W, const int32_t* id
         SP_TRY(launch_rows_ln_add(M, lo + L.ln2g, lo + L.ln2b, f.d, f.d_ss, lo + L.b2, x1c, x1c_ss, nullptr, T, xf, xf_ss, B, k, s));
         SP_MARK(SP_PHASE_LAST_FIRST);
         SP_TRY(launch_gemm_split(M, xf, H, L.wp_t, f.pooled, 0, mr, H, H, k, 1, xf_ss * ab, f.o_ss, s));
-        SP_TRY(launch_head_classify(M, f.pooled, f.o_ss, B, k, z, logits, s, true));
+        SP_TRY(launch_head_classify(M, f.pooled, f.o_ss, B, k, z, logits, s));
         SP_MARK(SP_PHASE_HEAD);
         return SP_OK;
     };

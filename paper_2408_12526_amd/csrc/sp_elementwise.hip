@@ -418,6 +418,7 @@ __global__ __launch_bounds__(256) void head_pool_kernel(const char* arena, size_
 // 256 threads = 8 student lanes x 32 outputs: the students' slice sums run in parallel, the sum over students is taken
 // in order by the first lane of each output.
 constexpr int kSumStudents = 64;   // most students (sp_config.K is capped at this)
+constexpr int kMaxSlices64 = 16;   // most slices of 64 pooled features
 
 __global__ __launch_bounds__(256) void head_sum_kernel(const char* arena, size_t student_stride, size_t bc_off,
                                                        const float* __restrict__ zpart, int B, int C, int k, int nslice,
@@ -431,15 +432,18 @@ __global__ __launch_bounds__(256) void head_sum_kernel(const char* arena, size_t
     for (int m = my; m < k; m += 8) {
         float zm = 0.f;
         if (live) {
-#pragma unroll 4
-            for (int sl = 0; sl < nslice; ++sl) zm += zpart[((size_t)m * nslice + sl) * B * C + idx];
+            float part[kMaxSlices64];                       // all slices requested at once, added in ascending order
+#pragma unroll
+            for (int sl = 0; sl < kMaxSlices64; ++sl) part[sl] = zpart[((size_t)m * nslice + (sl < nslice ? sl : nslice - 1)) * B * C + idx];
+#pragma unroll
+            for (int sl = 0; sl < kMaxSlices64; ++sl) zm += sl < nslice ? part[sl] : 0.f;
             zm += ((const float*)(arena + (size_t)m * student_stride + bc_off))[c];
             z[(size_t)m * B * C + idx] = zm;
         }
         zs[m][ox] = zm;
     }
     __syncthreads();
-    if (my == 0 && live) {
+    if (logits && my == 0 && live) {
         float total = 0.f;
         for (int m = 0; m < k; ++m) total += zs[m][ox];
         logits[idx] = total;
@@ -457,12 +461,12 @@ __global__ void sum_students_kernel(const float* __restrict__ z, int n, int k, f
     logits[i] = total;
 }
 
-// Classifier on pooled rows and the cross-student sum: one workgroup per sequence, a wave per student (up to kClassifyWaves).
+// Classifier and the cross-student sum where the first tokens are many: one workgroup per sequence, a wave per student (up to kClassifyWaves).
 // One pass over the row for CB classes at a time and all its loads requested together: a student is one memory round trip
 // (a pass per class, a chain of dependent iterations each, took 11.6 us for one sequence and eight students).
-// BARE: the rows are the pooler's sums, bias and tanh are applied here.
+// The rows are the pooler's sums: bias and tanh are applied here.
 constexpr int kClassifyWaves = 8;
-template <int CB, bool BARE>
+template <int CB>
 __global__ __launch_bounds__(64 * kClassifyWaves) void head_classify_kernel(const char* arena, size_t student_stride, size_t wc_off,
                                                             size_t bc_off, size_t bp_off, const float* __restrict__ pooled, size_t p_ss,
                                                             int B, int H, int C, int k, float* __restrict__ z,
@@ -480,8 +484,7 @@ __global__ __launch_bounds__(64 * kClassifyWaves) void head_classify_kernel(cons
 #pragma unroll
             for (int i = 0; i < 16; ++i) {       // hidden <= 1024, a multiple of 64; pieces beyond it count as zero
                 const int n = lane + (64 * i < H ? 64 * i : 0);
-                pv[i] = p[n];
-                if (BARE) pv[i] = tanhf(pv[i] + ((const float*)(sb + bp_off))[n]);
+                pv[i] = tanhf(p[n] + ((const float*)(sb + bp_off))[n]);
 #pragma unroll
                 for (int c = 0; c < CB; ++c) wv[i][c] = Wc[(size_t)n * C + (c0 + c < C ? c0 + c : C - 1)];
             }
@@ -510,17 +513,26 @@ __global__ __launch_bounds__(64 * kClassifyWaves) void head_classify_kernel(cons
 
 }  // namespace
 
-hipError_t launch_head_classify(const sp_model* M, const float* pooled, size_t p_ss, int B, int k, float* z, float* logits,
-                                hipStream_t s, bool bare)
+hipError_t launch_head_classify(const sp_model* M, const float* sums, size_t p_ss, int B, int k, float* z, float* logits,
+                                hipStream_t s)
 {
     const sp_config& c = M->cfg;
     if (!bf16_path(c) || k > 64 || c.hidden > 1024 || c.hidden % 64) return hipErrorInvalidValue;
-#define SP_CLASSIFY(CB, BARE)                                                                                       \
-    hipLaunchKernelGGL((head_classify_kernel<CB, BARE>), dim3((unsigned)B), dim3(64 * (k < kClassifyWaves ? k : kClassifyWaves)), 0, s, M->arena, M->L.student_stride, \
-                       M->L.wc, M->L.bc, M->L.bp, pooled, p_ss, B, c.hidden, c.classes, k, z, logits)
-    if (bare) { if (c.classes <= 2) SP_CLASSIFY(2, true); else SP_CLASSIFY(4, true); }
-    else { if (c.classes <= 2) SP_CLASSIFY(2, false); else SP_CLASSIFY(4, false); }
+#define SP_CLASSIFY(CB)                                                                                             \
+    hipLaunchKernelGGL(head_classify_kernel<CB>, dim3((unsigned)B), dim3(64 * (k < kClassifyWaves ? k : kClassifyWaves)), 0, s, \
+                       M->arena, M->L.student_stride, M->L.wc, M->L.bc, M->L.bp, sums, p_ss, B, c.hidden, c.classes, k, z, logits)
+    if (c.classes <= 2) SP_CLASSIFY(2); else SP_CLASSIFY(4);
 #undef SP_CLASSIFY
+    return hipGetLastError();
+}
+
+hipError_t launch_head_sum(const sp_model* M, const float* zpart, int B, int k, float* z, float* logits, hipStream_t s)
+{
+    const sp_config& c = M->cfg;
+    const int n = B * c.classes, nslice = c.hidden / 64;
+    if (k > kSumStudents || nslice > kMaxSlices64) return hipErrorInvalidValue;
+    hipLaunchKernelGGL(head_sum_kernel, dim3((n + 31) / 32), dim3(256), 0, s, M->arena, M->L.student_stride, M->L.bc, zpart, B,
+                       c.classes, k, nslice, z, logits);
     return hipGetLastError();
 }
 
@@ -663,11 +675,7 @@ hipError_t launch_head(const sp_model* M, const void* x, const int32_t* cu, int 
                            L.wc, (const float*)x, cu, B, T, rows, c.hidden, c.classes, zpart);
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
-    const int n = B * c.classes;
-    if (k > kSumStudents) return hipErrorInvalidValue;
-    hipLaunchKernelGGL(head_sum_kernel, dim3((n + 31) / 32), dim3(256), 0, s, M->arena, L.student_stride, L.bc,
-                       zpart, B, c.classes, k, nslice, z, logits);
-    return hipGetLastError();
+    return launch_head_sum(M, zpart, B, k, z, logits, s);
 }
 
 }  // namespace sp

@@ -299,9 +299,9 @@ hipError_t launch_rows_qkv(const sp_model* M, size_t lo, const float* u, size_t 
 // g = gelu(LN(u; ln1) W1^T + b1), the normalised rows to x1 (row stride H)
 hipError_t launch_rows_ffn_up(const sp_model* M, size_t lo, const float* u, size_t u_ss, int nrows, void* x1, size_t x1_ss,
                               void* g, size_t g_ss, RowsLayout gl, int k, hipStream_t s);
-// pooled = tanh(LN(u; ln2) Wp + bp), fp32
-hipError_t launch_rows_pooler(const sp_model* M, size_t lo, const float* u, size_t u_ss, int nrows, float* pooled,
-                              size_t p_ss, int k, hipStream_t s);
+// zpart[m][n][r][c] = sum over the n-th 64 features of tanh(LN(u; ln2) Wp + bp) Wc (for launch_head_sum)
+hipError_t launch_rows_pooler(const sp_model* M, size_t lo, const float* u, size_t u_ss, int nrows, float* zpart, int k,
+                              hipStream_t s);
 // out[r] (fp32, H wide) = A[r or cu[r]] W^T + bias + res[r or cu[r]]; Kd columns of A
 hipError_t launch_rows_residual(const sp_model* M, size_t w_off, size_t b_off, const bf16* A, size_t a_ss, RowsLayout al,
                                 int Kd, bool a_first, const bf16* res, size_t r_ss, bool r_first, float* out, size_t o_ss,
@@ -352,10 +352,12 @@ hipError_t launch_attention_first_fold(const sp_model* M, const void* x, const v
                                        size_t xb_ss, const int32_t* cu, int B, int T, int max_seqlen, int rows, int k,
                                        hipStream_t s, bool raw, size_t g_off, size_t b_off);
 
-// Head on fp32 pooled rows (p_ss: elements from student to student): z[m][b][c] = pooled[m][b] . Wc + bc; logits[b][c] =
-// sum_{m<k} z[m][b][c] (m ascending; not written if null).  bare: the rows are tanh's argument without the pooler's bias.
-hipError_t launch_head_classify(const sp_model* M, const float* pooled, size_t p_ss, int B, int k, float* z, float* logits,
-                                hipStream_t s, bool bare = false);
+// Head on the pooler's sums without bias (fp32 rows, p_ss elements from student to student): z[m][b][c] = tanh(sums + bp) . Wc + bc;
+// logits[b][c] = sum_{m<k} z[m][b][c] (m ascending; not written if null).
+hipError_t launch_head_classify(const sp_model* M, const float* sums, size_t p_ss, int B, int k, float* z, float* logits,
+                                hipStream_t s);
+// z[m][b][c] = bc + sum over the H / 64 slices n of zpart[m][n][b][c]; logits as above
+hipError_t launch_head_sum(const sp_model* M, const float* zpart, int B, int k, float* z, float* logits, hipStream_t s);
 
 // flags[0] |= SP_BAD_* bits for the inputs of a forward (flags[0] is cleared first, on the same stream).
 hipError_t launch_check_inputs(const int32_t* ids, const int32_t* cu, int B, int T, int max_seqlen, int vocab,

@@ -63,9 +63,12 @@ struct RowsLnArgs {
     bf16* out2;                       // value third, transposed: [student][o2_ss], row stride ld2
     size_t o2_ss;
     int ld2, n_split;
+    size_t wc;                        // pooler: classifier, [in][out]; out: [student][feature block][row][class]
+    int C;
     int M, H, N, nfb, nfb8, nrb;
 };
 
+constexpr int kMaxClasses = 16;
 enum RowsPrologue { PRO_LN = 0, PRO_EMBED = 1 };
 
 // (No branches between the loads: behind one, the compiler waits for everything in flight at the first use.)
@@ -148,6 +151,14 @@ __global__ __launch_bounds__(256) void rows_ln_gemm_kernel(RowsLnArgs p)
         if (transposed) { const float bs = bias[l16]; acc = f32x4{bs, bs, bs, bs}; }
         else acc = *(const f32x4*)(bias + 4 * kg);
     }
+    // pooler: this lane's four features of the classifier's matrix, all of them if there are two classes
+    const bf16* wc = (const bf16*)(sb + p.wc) + (size_t)(n0 + 4 * kg) * p.C;
+    bf16x4 wc2[2];
+    if constexpr (EPI == EPI_BIAS_TANH) {
+        const bf16* at = (n0 + 4 * kg) * p.C + 8 <= H * p.C ? wc : wc - 4;      // (one class: the last lanes' eight would pass the end)
+        wc2[0] = *(const bf16x4*)at;
+        wc2[1] = *(const bf16x4*)(at + 4);
+    }
     __builtin_amdgcn_sched_barrier(0);
 
     if constexpr (PRO == PRO_EMBED) {
@@ -213,19 +224,42 @@ __global__ __launch_bounds__(256) void rows_ln_gemm_kernel(RowsLnArgs p)
         *(bf16x4*)(p.out2 + (size_t)m * p.o2_ss + (size_t)(n0 - p.n_split + l16) * p.ld2 + r0 + 4 * kg) = o;
         return;
     }
+    if constexpr (EPI == EPI_BIAS_TANH) {
+        // This workgroup's share of the classifier: 64 of the pooled features, so that the launch behind it adds a dozen numbers
+        // per output where it read every pooled row (and, with the classifier's matrix cold, took 6 us for eight students).
+        __shared__ float zs[4][16][kMaxClasses];
+        float t[4];
+#pragma unroll
+        for (int e = 0; e < 4; ++e) t[e] = tanhf(acc[e]);
+        for (int c = 0; c < p.C; ++c) {
+            float z = 0.f;
+#pragma unroll
+            for (int e = 0; e < 4; ++e) {
+                const float w2 = (float)(c ? wc2[e >> 1][2 * (e & 1) + 1] : wc2[e >> 1][2 * (e & 1)]);
+                z = __builtin_fmaf(t[e], p.C == 2 ? w2 : (float)wc[(size_t)e * p.C + c], z);
+            }
+            float a = z, b = z;                             // over the four lanes of a row: 16 features
+            swap_rows(a, b);
+            z = a + b;
+            a = z;
+            b = z;
+            swap_halves(a, b);
+            if (kg == 0) zs[wave][l16][c] = a + b;
+        }
+        __syncthreads();
+        for (int i = threadIdx.x; i < 16 * p.C; i += 256) {
+            const int r = i / p.C, c = i - r * p.C;
+            if (r0 + r < p.M)
+                ((float*)p.out)[(((size_t)m * p.nfb + fb) * p.M + r0 + r) * p.C + c] = (zs[0][r][c] + zs[1][r][c]) + (zs[2][r][c] + zs[3][r][c]);
+        }
+        return;
+    }
     const int f = n0 + 4 * kg;
     const size_t at = (size_t)m * p.o_ss + (size_t)(r0 / 16) * p.ol.rb + (size_t)l16 * p.ol.rs + (size_t)(f >> 3) * p.ol.cs + (f & 7);
-    if (EPI == EPI_BIAS_TANH) {
-        f32x4 o;
+    bf16x4 o;
 #pragma unroll
-        for (int e = 0; e < 4; ++e) o[e] = tanhf(acc[e]);
-        *(f32x4*)((float*)p.out + at) = o;
-    } else {
-        bf16x4 o;
-#pragma unroll
-        for (int e = 0; e < 4; ++e) o[e] = (bf16)(EPI == EPI_BIAS_GELU ? gelu_erf_fast(acc[e]) : acc[e]);
-        *(bf16x4*)((bf16*)p.out + at) = o;
-    }
+    for (int e = 0; e < 4; ++e) o[e] = (bf16)(EPI == EPI_BIAS_GELU ? gelu_erf_fast(acc[e]) : acc[e]);
+    *(bf16x4*)((bf16*)p.out + at) = o;
 }
 
 // -------------------------------------------------------------------------------------
@@ -841,14 +875,14 @@ hipError_t launch_rows_ffn_up(const sp_model* M, size_t lo, const float* u, size
     return launch_rows_ln<PRO_LN, EPI_BIAS_GELU>(a, k, s);
 }
 
-hipError_t launch_rows_pooler(const sp_model* M, size_t lo, const float* u, size_t u_ss, int nrows, float* pooled,
-                              size_t p_ss, int k, hipStream_t s)
+hipError_t launch_rows_pooler(const sp_model* M, size_t lo, const float* u, size_t u_ss, int nrows, float* zpart, int k,
+                              hipStream_t s)
 {
     const sp_config& c = M->cfg;
-    if (!bf16_path(c) || nrows < 1) return hipErrorInvalidValue;
+    if (!bf16_path(c) || nrows < 1 || c.classes > kMaxClasses) return hipErrorInvalidValue;
     RowsLnArgs a = ln_args(M, M->L.wp_t, M->L.bp, lo + M->L.ln2g, lo + M->L.ln2b);
     a.u = u; a.u_ss = u_ss;
-    a.out = pooled; a.o_ss = p_ss; a.ol = rows_layout(c.hidden);
+    a.out = zpart; a.wc = M->L.wc; a.C = c.classes;
     a.M = nrows; a.N = c.hidden;
     return launch_rows_ln<PRO_LN, EPI_BIAS_TANH>(a, k, s);
 }
