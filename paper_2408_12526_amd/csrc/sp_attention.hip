@@ -333,8 +333,8 @@ __device__ inline float sum_across_rows(float v)
     return a + b;
 }
 
-// One workgroup (eight waves) per (student, sequence); the sequence's token rows x are read from global memory once, in
-// tiles of 32 tokens, and every wave touches only its own eighth of the features (FW = H / 8 of them):
+// One workgroup (eight waves, four at hidden 256) per (student, sequence); the sequence's token rows x are read from global
+// memory once, in tiles of 32 tokens, and every wave touches only its own share of the features (FW = H / 8 of them):
 //   scores: heads x tokens on the matrix cores (16 x 16 x 32 shape: two blocks of 16 tokens, FW / 32 steps of 32
 //           features); the token rows arrive in registers in operand layout (lane: token l % 16, eight features); the
 //           waves' partial tiles are added in a fixed order through LDS;
@@ -358,15 +358,16 @@ __device__ inline float sum_across_rows(float v)
 // use, so that a mean common to the row cancels to fp32; E[u^2] - mu^2 loses (mu / deviation)^2 2^-23 of the variance, less than the
 // rounding of u to bf16 has lost ((mu / deviation) 2^-9 of the deviation) for any mean below 2^14 deviations.  One rounding
 // (of x) fewer than before.
-constexpr int kFoldWaves = 8;
 template <int HEADS, bool RAW>
 struct FoldLds {
-    static constexpr int H = HEADS * kD, FW = H / kFoldWaves;   // features per wave
+    // (four heads: a wave's 32 features would be mostly the exchange between the waves)
+    static constexpr int NW = HEADS == 4 ? 4 : 8;               // waves
+    static constexpr int H = HEADS * kD, FW = H / NW;           // features per wave
     static constexpr int SCP = 36;                          // pitch of a head's 32 scores (floats)
     static constexpr size_t slab_bytes = (size_t)32 * FW * 2;   // per wave: 32 tokens x FW features
-    static constexpr size_t stats = kFoldWaves * (slab_bytes + 16 * 32 * 4) + (size_t)16 * SCP * 4;
-    static constexpr size_t bytes = stats + (RAW ? 32 * kFoldWaves * 8 + 32 * 4 + kFoldWaves * 16 * 4 : 0);
-    static_assert(FW % 32 == 0 && HEADS <= 16 && bytes <= 160 * 1024, "whole reduction steps per wave, heads in one block");
+    static constexpr size_t stats = NW * (slab_bytes + 16 * 32 * 4) + (size_t)16 * SCP * 4;
+    static constexpr size_t bytes = stats + (RAW ? 32 * NW * 8 + 32 * 4 + NW * 16 * 4 : 0);
+    static_assert(FW % 32 == 0 && HEADS <= 2 * NW && bytes <= 160 * 1024, "whole reduction steps per wave, a thread per score of a tile");
 };
 
 struct FoldArgs {
@@ -381,10 +382,10 @@ struct FoldArgs {
 };
 
 template <int HEADS, bool RAW>
-__global__ __launch_bounds__(512, HEADS == 16 ? 2 : 4) void attention_first_fold_kernel(FoldArgs p)
+__global__ __launch_bounds__((64 * FoldLds<HEADS, RAW>::NW), (HEADS == 16 ? 2 : 4)) void attention_first_fold_kernel(FoldArgs p)
 {
     using F = FoldLds<HEADS, RAW>;
-    constexpr int H = F::H, FW = F::FW, SCP = F::SCP, NW = kFoldWaves;
+    constexpr int H = F::H, FW = F::FW, SCP = F::SCP, NW = F::NW;
     constexpr int KS = FW / 32;                             // 32-feature steps (scores) = 32-feature blocks (output)
     constexpr int PITCH = FW * 2;                           // slab row, bytes
     extern __shared__ uint4 fold_smem[];
@@ -501,7 +502,7 @@ __global__ __launch_bounds__(512, HEADS == 16 ? 2 : 4) void attention_first_fold
         if (tile + 1 < nt) load_tile(tile + 1);
         barrier_lds();
         {
-            const int hh = tid >> 5, t = tid & 31;          // 16 x 32 sums, one per thread, waves in a fixed order
+            const int hh = tid >> 5, t = tid & 31;          // 2 NW heads x 32 sums, one per thread, waves in a fixed order
             float sum = 0.f;
 #pragma unroll
             for (int w = 0; w < NW; ++w) sum += part[(w * 16 + hh) * 32 + t];
@@ -767,7 +768,7 @@ hipError_t launch_attention_first_fold(const sp_model* M, const void* x, const v
             if (e != hipSuccess) return e;                                                                          \
             raised = true;                                                                                          \
         }                                                                                                           \
-        hipLaunchKernelGGL(kern, grid, dim3(64 * kFoldWaves), smem, s, a);                                          \
+        hipLaunchKernelGGL(kern, grid, dim3((64 * FoldLds<HEADS, RAW>::NW)), smem, s, a);                                          \
     } while (0)
 #define SP_FOLD_ANY(HEADS) do { if (raw) SP_FOLD(HEADS, true); else SP_FOLD(HEADS, false); } while (0)
     switch (c.heads) {
