@@ -262,3 +262,27 @@ def test_folded_last_layer_on_rows_before_their_layernorm(oracle64, hidden, dtyp
         want = oracle64.forward(cfg, ow, ids[:cu[n]], cu[:n + 1], shape.K)
         err = [np.abs(g[:n] - want).max() / np.abs(want).max() for g in (got, full)]
         assert err[0] < bound and err[1] < bound, err
+
+
+# one, two and three looks at the boundaries; a row and several rows per wave; runs of the shortest sequences, a last wave that is partly filled
+@pytest.mark.parametrize("lengths", [(7,), (1,) * 64, (3, 1) * 32 + (2,), (1,) * 4095 + (9,), (1,) * 2500 + (5, 2) * 2100 + (64,) * 3, (63, 64, 1) * 100])
+@pytest.mark.parametrize("dtype", ["bf16", "fp32"])
+def test_embedding_finds_the_sequence_of_every_row(lengths, dtype):
+    """Token row + position row, then LayerNorm, of every row in fp64; the bound of the stage tests (one rounding of the output)."""
+    from paper_2408_12526_amd import sp
+    shape = synth.StudentShape(K=2, layers=1, hidden=128, heads=2, ffn=128, vocab=100, max_pos=64, classes=2, dtype=dtype)
+    rng = np.random.default_rng(len(lengths))
+    cu, T, B = sp.sp_pack(np.array(lengths, np.int32)), sum(lengths), len(lengths)
+    ids, blob = synth.make_ids(rng, T, shape.vocab), synth.make_weights(rng, shape, std=0.08, ln_random=True)
+    st = sp.Students(sp.config_from_shape(shape), blob)
+    x = st.read_activation(st.sp_forward_partial(torch.from_numpy(ids).cuda(), torch.from_numpy(cu).cuda(), max(lengths), 2, 0), "x", T, B, 2)
+    pos = np.arange(T) - np.repeat(cu[:-1], lengths)
+    for m in range(2):
+        v = synth.student_views(blob, shape, m)
+        tab = {n: (torch.from_numpy(v[n]).bfloat16() if dtype == "bf16" else torch.from_numpy(v[n])).double().numpy() for n in ("tok_emb", "pos_emb")}
+        u = tab["tok_emb"][ids] + tab["pos_emb"][pos]
+        d = u - u.mean(1, keepdims=True)
+        want = d / np.sqrt((d * d).mean(1, keepdims=True) + shape.ln_eps) * v["emb_ln_g"] + v["emb_ln_b"]
+        err = np.abs(x[m][:T] - want).max() / np.abs(want).max()
+        assert err < (1.2e-2 if dtype == "bf16" else 2e-5), f"student {m}: {err:.3e}"
+    st.close()
