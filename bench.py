@@ -229,6 +229,11 @@ def first_only_runs(shape, tokens, max_len):
     return shape.dtype == "bf16" and tokens >= 1024 and shape.heads % 4 == 0 and shape.heads <= 16   # (any length)
 
 
+def f32_last_first(shape, rows):
+    """Whether an fp32 call of `rows` rows of all students computes what follows its last attention for the first tokens only."""
+    return shape.dtype == "fp32" and shape.hidden == 128 and shape.ffn % 128 == 0 and shape.ffn <= 768 and rows <= 512
+
+
 def executed_flops(shape, lengths, k):
     """Flops one forward executes (projections on the real tokens, attention, the first-token last layer where it
     runs, pooler and classifier), and the weight bytes it has to stream at least once."""
@@ -240,6 +245,8 @@ def executed_flops(shape, lengths, k):
     flops = sum(gemm_flops(shape, T, k, full).values()) + attention_flops(shape, lengths, k, full)
     if fo:
         flops += last_first_work(shape, T, B, k)[0]
+    elif f32_last_first(shape, T * k):
+        flops -= k * 2 * (T - B) * (H * H + 2 * H * F)      # output projection and feed-forward
     flops += k * B * (2 * H * H + 2 * H * shape.classes)
     weights = k * (shape.layers * (4 * H * H + 2 * H * F) + H * H + H * shape.classes) * wb
     return flops, weights, fo
@@ -299,7 +306,8 @@ def per_config_table(sp, synth, torch, dev, calls_small, calls_large, warm):
                    "wall_us_p50": p50, "wall_us_p95": percentile(wall, 95), "device_us_p50": d50,
                    "device_us_p95": percentile(devt, 95), "sequences_per_s": B / p50 * 1e6,
                    "executed_flops": flops, "weight_bytes": wbytes,
-                   "last_layer": "first-token rows only" if fo else "every token"}
+                   "last_layer": "first-token rows only" if fo else
+                                 "first-token rows behind the attention" if f32_last_first(w.shape, T * k) else "every token"}
             if T < 1024:        # small calls: weight streaming (and launches) bound them, not arithmetic
                 row.update(bound="hbm", achieved=wbytes / d50 / 1e3, peak=PEAK_HBM_GBS, unit="GB/s (weights streamed once)",
                            frac=wbytes / d50 / 1e3 / PEAK_HBM_GBS)
@@ -544,7 +552,8 @@ def main():
         phases["attention"] = {"ms": acc["attention"], "bound": "mfma", "tflops": af / acc["attention"] / 1e9,
                                "frac": af / acc["attention"] / 1e9 / PEAK_BF16_TFLOPS}
         emb_bytes = 8 * T4 * (6 * H + 4)                      # two table rows read, one row written, bf16, + id
-        ln_bytes = 8 * T4 * full_layers * 2 * (4 * H)         # every LayerNorm reads a row and writes a row, bf16
+        # every LayerNorm reads a row and writes a row, bf16; the folded last layer takes its rows before theirs
+        ln_bytes = 8 * T4 * (2 * full_layers - (1 if acc["last_first"] > 0 else 0)) * (4 * H)
         head_bytes = 8 * (B4 * H * 2 + (H * H + H * w4.shape.classes) * 2)
         for n, b in (("embed", emb_bytes), ("layernorm", ln_bytes), ("head", head_bytes)):
             phases[n] = {"ms": acc[n], "bound": "hbm", "gbs": b / acc[n] / 1e6, "frac": b / acc[n] / 1e6 / PEAK_HBM_GBS}
