@@ -506,7 +506,7 @@ static int run_students(const sp_model* M0, const WsLayout& W, const int32_t* id
                 SP_TRY(launch_layernorm_first(M, u, x, rows, cu, B, T, k, pl + L.ln2g, pl + L.ln2b, s));
                 SP_MARK(SP_PHASE_LAST_FIRST);
             }
-            SP_TRY(launch_fold_query(M, lo, x, rows, raw ? nullptr : cu, T, B, q1, s1, qt1, sq, k, s));
+            SP_TRY(launch_fold_query(M, lo, x, rows, raw ? nullptr : cu, T, B, q1, s1, qt1, sq, k, s, raw, pl + L.ln2g));
             SP_MARK(SP_PHASE_LAST_FIRST);
             SP_TRY(launch_attention_first_fold(M, raw ? u : x, qt1, sq, xb1, sx, cu, B, T, max_seqlen, rows, k, s, raw, pl + L.ln2g,
                                                pl + L.ln2b));

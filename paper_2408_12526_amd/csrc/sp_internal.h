@@ -309,9 +309,9 @@ hipError_t launch_rows_residual(const sp_model* M, size_t w_off, size_t b_off, c
 // att[b][h*64..] = Wv_h xbar[b][h] + bv_h
 hipError_t launch_rows_head_values(const sp_model* M, size_t lo, const void* xbar, size_t xb_ss, void* att, size_t att_ss,
                                    int nrows, int k, hipStream_t s);
-// q[b] = x[cu[b]] Wq^T + bq; qt[b][h] = Wk_h q[b][h]  (cu null: x[b])
+// q[b] = x[cu[b]] Wq^T + bq; qt[b][h] = Wk_h q[b][h]  (cu null: x[b]).  scaled: qt times the scales at g_off, feature by feature
 hipError_t launch_fold_query(const sp_model* M, size_t lo, const void* x, int rows, const int32_t* cu, int T, int B,
-                             void* q, size_t q_ss, void* qt, size_t qt_ss, int k, hipStream_t s);
+                             void* q, size_t q_ss, void* qt, size_t qt_ss, int k, hipStream_t s, bool scaled, size_t g_off);
 // attention output of the first token of every sequence, at its token row
 hipError_t launch_attention_first(const sp_model* M, const void* qkv, const void* vt, void* att, const int32_t* cu, int B,
                                   int T, int max_seqlen, int rows, int k, hipStream_t s);
@@ -346,7 +346,8 @@ hipError_t launch_attention(const sp_model* M, const void* qkv, const void* vt, 
 
 // Attention of the first token of each sequence with folded queries: for sequence b and head h,
 // p = softmax_t(qt[m][b][h] . x[m][t] / 8) over the tokens t of the sequence and xbar[m][b][h][:] = sum_t p_t x[m][t][:].
-// qt and xbar are [m][.._ss elements], rows of [heads][H].  raw: x holds rows before their LayerNorm (g_off, b_off).
+// qt and xbar are [m][.._ss elements], rows of [heads][H].  raw: x holds rows before their LayerNorm (g_off, b_off), and qt carries
+// its scale.
 bool attention_first_fold_supported(const sp_config& c, int max_seqlen);
 hipError_t launch_attention_first_fold(const sp_model* M, const void* x, const void* qt, size_t qt_ss, void* xbar,
                                        size_t xb_ss, const int32_t* cu, int B, int T, int max_seqlen, int rows, int k,

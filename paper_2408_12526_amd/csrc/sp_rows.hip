@@ -429,6 +429,8 @@ struct FoldQArgs {
     size_t q_ss;
     bf16* qt;                         // [student][qt_ss], row stride heads * H
     size_t qt_ss;
+    size_t g;                         // scaled: what feature f of a folded query is multiplied with (fp32, byte offset into a student slab)
+    bool scaled;
     int Tn, M, H, heads, heads8, nrb, rpw;                  // nrb: groups of rpw blocks of 16 sequences
 };
 
@@ -437,7 +439,7 @@ constexpr int fold_x_pitch(int ns) { return ns * 64 + 16; } // bytes per staged 
 constexpr int fold_o_pitch(int ns) { return ns * 16 + 16; } // bytes per row of a wave's staged output
 constexpr size_t fold_query_smem(int ns)
 {
-    return 2 * 16 * (size_t)(fold_x_pitch(ns) + kFoldQPitch) + 4 * 16 * (size_t)fold_o_pitch(ns);
+    return 2 * 16 * (size_t)(fold_x_pitch(ns) + kFoldQPitch) + 4 * 16 * (size_t)fold_o_pitch(ns) + 32 * (size_t)ns * 4;
 }
 
 template <int NS>
@@ -449,6 +451,7 @@ __global__ __launch_bounds__(256) void fold_query_kernel(FoldQArgs p)
     extern __shared__ __attribute__((aligned(16))) char fold_lds[];
     char *const xbuf = fold_lds, *const qbuf = fold_lds + 2 * 16 * XP;
     char* const obuf = qbuf + 2 * 16 * QP + (threadIdx.x >> 6) * 16 * OP;   // wave-private
+    float* const gbuf = (float*)(qbuf + 2 * 16 * QP + 4 * 16 * OP);         // the H scales
     const int h = (int)blockIdx.x % p.heads8, rm = (int)blockIdx.x / p.heads8;
     if (h >= p.heads) return;
     const int m = rm / p.nrb, rb = (rm % p.nrb) * p.rpw * 16;
@@ -501,8 +504,11 @@ __global__ __launch_bounds__(256) void fold_query_kernel(FoldQArgs p)
     for (int j = 0; j < NS / 2; ++j)
 #pragma unroll
         for (int s = 0; s < 2; ++s) fk[j][s] = *(const bf16x8*)(kp + (size_t)(j >> 1) * 32 * H + 32 * (j & 1) + 512 * s);
+    f32x4 gv = {1.f, 1.f, 1.f, 1.f};
+    if (p.scaled && 4 * threadIdx.x < H) gv = *(const f32x4*)((const float*)(sb + p.g) + 4 * threadIdx.x);
     __builtin_amdgcn_sched_barrier(0);
     write_x(S0);
+    if (4 * threadIdx.x < H) *(f32x4*)(gbuf + 4 * threadIdx.x) = gv;
     if (rb + 16 < re) load_x(rb + 16, S1);
     if (rb + 32 < re) load_x(rb + 32, S0);
     barrier_lds();
@@ -537,6 +543,10 @@ __global__ __launch_bounds__(256) void fold_query_kernel(FoldQArgs p)
             f32x4 a = {0.f, 0.f, 0.f, 0.f}, b = a;
 #pragma unroll
             for (int s = 0; s < 2; ++s) { a = mfma16(fk[j][s], fq[s], a); b = mfma16(fk[j + 1][s], fq[s], b); }
+            if (p.scaled) {
+                a *= *(const f32x4*)(gbuf + f0 + 16 * j + 8 * kg);
+                b *= *(const f32x4*)(gbuf + f0 + 16 * j + 8 * kg + 4);
+            }
             bf16x8 o;
 #pragma unroll
             for (int e = 0; e < 4; ++e) { o[e] = (bf16)a[e]; o[4 + e] = (bf16)b[e]; }
@@ -918,11 +928,12 @@ hipError_t launch_rows_head_values(const sp_model* M, size_t lo, const void* xba
 }
 
 hipError_t launch_fold_query(const sp_model* M, size_t lo, const void* x, int rows, const int32_t* cu, int T, int B,
-                             void* q, size_t q_ss, void* qt, size_t qt_ss, int k, hipStream_t s)
+                             void* q, size_t q_ss, void* qt, size_t qt_ss, int k, hipStream_t s, bool scaled, size_t g_off)
 {
     const sp_config& c = M->cfg;
     if (!bf16_path(c) || c.heads * 64 != c.hidden || B < 1) return hipErrorInvalidValue;
     FoldQArgs a{};
+    a.scaled = scaled; a.g = g_off;
     a.arena = M->arena; a.ss = M->L.student_stride; a.wq = lo + M->L.wqkv; a.bq = lo + M->L.bqkv; a.wk = lo + M->L.wk_io;
     a.x = (const bf16*)x; a.x_ss = (size_t)rows * c.hidden; a.cu = cu;
     a.q = (bf16*)q; a.q_ss = q_ss; a.qt = (bf16*)qt; a.qt_ss = qt_ss;

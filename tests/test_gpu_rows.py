@@ -264,6 +264,52 @@ def test_folded_last_layer_on_rows_before_their_layernorm(oracle64, hidden, dtyp
         assert err[0] < bound and err[1] < bound, err
 
 
+# 8192 tokens or more, as above.  Scores spread about 4 (as in the stage test of the fold on normalised rows), first tokens that have all the
+# weight (sequences of one token), and rows whose mean is several times their deviation
+@pytest.mark.parametrize("hidden", [256, 512, 768, 1024])
+@pytest.mark.parametrize("offset", [0.0, 6.0, 30.0])
+def test_folded_attention_on_rows_before_their_layernorm_against_the_definition(hidden, offset):
+    """Its attention output against keys and values formed in fp64 from the rows before their LayerNorm (what the FFN's stages left,
+    rounded to bf16 as the fold reads them), and softmax attention of the HIP path's own queries over them."""
+    from paper_2408_12526_amd import sp
+    shape = synth.StudentShape(K=1, layers=2, hidden=hidden, heads=hidden // 64, ffn=256, vocab=300, max_pos=256, classes=2, dtype="bf16")
+    rng = np.random.default_rng(hidden)
+    lengths = np.array((1,) * 200 + (2, 31, 32, 33, 64, 65, 256, 129) + (60,) * 130, np.int32)
+    T, B = int(lengths.sum()), len(lengths)
+    assert T >= 8192
+    ids = synth.make_ids(rng, T, shape.vocab)
+    blob = synth.make_weights(rng, shape, std=0.04, ln_random=True, qk_std=1.92 / hidden ** 0.5)
+    v = synth.student_views(blob, shape, 0)
+    v["l0.b2"][:] += offset
+    cu = sp.sp_pack(lengths)
+    args = torch.from_numpy(ids).cuda(), torch.from_numpy(cu).cuda(), 256, 1
+    st = sp.Students(sp.config_from_shape(shape), blob)
+    st.sp_forward(*args)
+    q, got = (st.read_activation(st.workspace(T, B), n, T, B, 1)[0] for n in ("first_q", "first_att"))
+    ws = st.sp_forward_partial(*args, 1)
+    x1, g = (st.read_activation(ws, n, T, B, 1)[0] for n in ("x1", "g"))
+    st.close()
+    w = {n: (torch.from_numpy(a).bfloat16() if a.ndim == 2 else torch.from_numpy(a)).double().numpy() for n, a in v.items()}
+    u64 = torch.from_numpy(x1 + g @ w["l0.W2"] + w["l0.b2"])
+    u = u64.bfloat16().double().numpy()
+    d = u - u.mean(1, keepdims=True)
+    x = d / np.sqrt((d * d).mean(1, keepdims=True) + shape.ln_eps) * w["l0.ln2_g"] + w["l0.ln2_b"]
+    keys, values = x @ w["l1.Wk"] + w["l1.bk"], x @ w["l1.Wv"] + w["l1.bv"]
+    want = np.empty((B, hidden))
+    for b in range(B):
+        r = slice(cu[b], cu[b + 1])
+        s = np.einsum("hd,thd->ht", q[b].reshape(-1, 64), keys[r].reshape(-1, shape.heads, 64)) / 8
+        p = np.exp(s - s.max(1, keepdims=True))
+        want[b] = np.einsum("ht,thd->hd", p / p.sum(1, keepdims=True), values[r].reshape(-1, shape.heads, 64)).reshape(-1)
+    assert np.abs(got - want).max() / np.abs(want).max() < 1.2e-2
+    # One token: its weight is one, so the output has two roundings to bf16 (weighted row, value), 2^-8 0.378 of a vector's norm each and
+    # 2.1e-3 in quadrature.  One of the weight itself would be common to the whole vector: up to 3.9e-3 more.
+    # (Rows of which fp32 sums, within 2^-20, may round another way than fp64 ones are not looked at: a step of a mean of 30 is large.)
+    sure = ((u64 * (1 + 2.0 ** -20)).bfloat16() == (u64 * (1 - 2.0 ** -20)).bfloat16()).all(1).numpy()[:200]
+    one = (np.linalg.norm(got[:200] - want[:200], axis=1) / np.linalg.norm(want[:200], axis=1))[sure]
+    assert len(one) > 50 and one.max() < 3e-3, (len(one), one.max())
+
+
 # one, two and three looks at the boundaries; a row and several rows per wave; runs of the shortest sequences, a last wave that is partly filled
 @pytest.mark.parametrize("lengths", [(7,), (1,) * 64, (3, 1) * 32 + (2,), (1,) * 4095 + (9,), (1,) * 2500 + (5, 2) * 2100 + (64,) * 3, (63, 64, 1) * 100])
 @pytest.mark.parametrize("dtype", ["bf16", "fp32"])
