@@ -3,6 +3,7 @@
 #include <atomic>
 #include <type_traits>
 
+#include "sp_attn_offsets.h"
 #include "sp_internal.h"
 
 namespace sp {
@@ -46,11 +47,11 @@ __device__ inline uint2 chunk_to_fp8(uint4 c, float qscale)
 //
 // Work item i belongs to the last sequence b with cu[b] / 128 + b <= i: a sequence of L tokens gets at least ceil(L / 128)
 // consecutive numbers, T / 128 + B numbers are enough for any lengths, and which sequence it is takes one look at 64 boundaries
-// by the whole wave (two looks beyond 64 sequences).
+// by the whole wave (two beyond 64 sequences, three beyond 4096).
 //
 // What bounds it: vector instructions (about seven issue slots per score, four of them the exponential) and the read of
 // queries, keys and values, neither saturated: a wave's chain of products, maximum, exponentials and products is issued in
-// order, so waves in flight are what counts.  Hence 32 queries a wave and 127 registers, four waves per SIMD (with 64 queries a
+// order, so waves in flight are what counts.  Hence 32 queries a wave and 128 registers, four waves per SIMD (with 64 queries a
 // wave a key fragment served two products, but two waves per SIMD was all the registers held).  us per launch, a wave per
 // sequence and head up to 128 tokens and 64 queries per wave above / this: 64 sequences of 64-512 tokens, 16 heads, one student
 // 84 / 66, six 466 / 335; 256 sequences of 8-256, 12 heads, eight students 238 / 214, two 65 / 54; 32 of 16-128, four students
@@ -105,6 +106,7 @@ __global__ __launch_bounds__(256, 4) void attention_bf16_kernel(AttnArgs p)
     // front of the sequence are masked.
     const int lead = t0 & 7;
     const bf16* vbase = p.vt + ((size_t)m * H + h * kD) * rows + (t0 - lead);
+    const bf16* vrows = vbase + value_row_offset(threadIdx.x >> 3, rows);
     const int vlast = (L + lead - 1) & ~7;          // last chunk of eight tokens that holds one of the sequence
     const float sl2 = 0.125f * 1.44269504088896341f;   // 1/sqrt(64) * log2(e)
 
@@ -114,16 +116,13 @@ __global__ __launch_bounds__(256, 4) void attention_bf16_kernel(AttnArgs p)
     int dst = lrow * 128 + ((lc ^ ((lrow >> 1) & 7)) << 4);
     auto fetch_keys = [&](int kt0, bf16x8 (&r)[2]) {
 #pragma unroll
-        for (int i = 0; i < 2; ++i) {
-            int key = kt0 + lrow + 32 * i;
-            key = key < 0 ? 0 : (key < L ? key : L - 1);
-            r[i] = *(const bf16x8*)(base + ((unsigned)key * (unsigned)ld + (unsigned)(H + lc * 8)));
-        }
+        for (int i = 0; i < 2; ++i)
+            r[i] = *(const bf16x8*)(base + key_tile_offset(kt0, 3 * H) + (key_row_offset(kt0, lrow + 32 * i, L, 3 * H) + (unsigned)(H + lc * 8)));
     };
     auto fetch_values = [&](int kt0, bf16x8 (&r)[2]) {
         const int c = kt0 + lead + lc * 8;
 #pragma unroll
-        for (int i = 0; i < 2; ++i) r[i] = *(const bf16x8*)(vbase + ((unsigned)(lrow + 32 * i) * (unsigned)rows + (unsigned)(c < vlast ? c : vlast)));
+        for (int i = 0; i < 2; ++i) r[i] = *(const bf16x8*)(vrows + value_row_offset(32 * i, rows) + (c < vlast ? c : vlast));
     };
     // (values: the two halves of a lane's share of a reduction step, four keys each, side by side: half p of chunk c goes to half
     // c % 2 of slot (c - c % 2 + p) ^ ...)
