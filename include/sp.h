@@ -80,11 +80,12 @@ typedef struct {
                          calls of a few hundred rows of students of hidden 128, which compute everything after
                          the last attention for the first tokens only). */
     int32_t single_stream;
-                      /* 0 (default): a call with k_active >= 2 and work enough (tokens x k_active x hidden >=
-                         20 Mi) runs the active students as two groups side by side, the second on a stream the
-                         model owns, forked from and joined to the caller's stream with events (the call stays
-                         asynchronous and can be captured in a graph; the logits are bit-identical to the
-                         single-stream result).
+                      /* 0 (default): calls of >= 8192 tokens and k_active >= 2 run the active students as two
+                         groups side by side where that measured faster (by tokens x k_active x hidden, layers
+                         and dtype), the second on a stream the model owns, forked from and joined to the caller's
+                         stream with events (the call stays asynchronous and can be captured in a graph; the
+                         logits are bit-identical to the single-stream result).  The model has one such stream:
+                         calls that fork, issued on several streams, queue their second groups behind one another.
                          In calls of >= 8192 tokens a student's term has the same bits for every k_active;
                          smaller calls choose their kernels by the rows of all active students, so there the
                          term of a student may differ between two k_active by roundings of its arithmetic.

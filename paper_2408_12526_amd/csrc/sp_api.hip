@@ -588,7 +588,7 @@ static int run_students(const sp_model* M0, const WsLayout& W, const int32_t* id
     return SP_OK;
 }
 
-// Whole call: argument checks, then either all active students on the caller's stream, or, where there is work enough, two
+// Whole call: argument checks, then either all active students on the caller's stream, or, where that pays (two_groups_pay), two
 // halves of them side by side: the first on the caller's stream, the second on the model's auxiliary stream (forked
 // and joined with events, so the call stays asynchronous and capturable).  The matrix-core phases run at the
 // package power limit while the bandwidth-bound phases leave most of it unused; two groups of students drift out
@@ -596,17 +596,32 @@ static int run_students(const sp_model* M0, const WsLayout& W, const int32_t* id
 // better).  The logits are summed over all students in ascending order after the join, so the result does not depend on the
 // grouping.
 //
-// Work: tokens x active students x hidden width.  Fork and join cost about 20 us, and half the students fill the chip less well.  One
-// stream / two, us: 7 M (256 x 14.3 k tokens x 2) 168 / 183; 11 M (256 x 14.3 k x 3) 221 / 238; 13 M (768 x 8.5 k x 2) 392 / 406, (768 x
-// 4.3 k x 4) 401 / 426; 18.6 M (768 x 6 k x 4) 519 / 530; 22 M (768 x 14.3 k x 2) 586 / 592 and, of other lengths, 628 / 617, (1024 x
-// 10.6 k x 2) 726 / 720; 26 M (768 x 8.5 k x 4) 727 / 695, (1024 x 4.3 k x 6) 881 / 859; 27 M (768 x 4.3 k x 8) 739 / 723, quantised
-// 545 / 527; 37 M (768 x 6 k x 8) 1000 / 995; 40 M (1024 x 19.5 k x 2) 1219 / 1221; 88 M (768 x 14.3 k x 8) 2129 / 2150, quantised
-// 1491 / 1460.
-constexpr int64_t kTwoGroupsWork = 20 << 20;
 // Calls of at least this many tokens choose their kernels by the model's students, not by how many are active, and split no
 // reduction, so that a student's term has the same bits whatever k.  (Smaller calls go by the active ones: a call pruned to one student
 // would otherwise run on kernels for eight.)
 constexpr int kLargeTokens = 8192;
+
+// Two groups only in calls of kLargeTokens and more: smaller ones share nothing with other streams' calls on the same model.  By work, in
+// Mi = 2^20 tokens x active students x hidden width; one stream / two, us a call, both on one card in turn:
+//   * From 20: fork and join cost about 20 us, and half the students fill the chip less well.  768 wide, 2 students: 12.1 399 / 417, 16.7
+//     507 / 505, 20.9 606 / 603, 29 801 / 789; 4: 24 723 / 682; quantised, 2: 12.1 307 / 321, 20.8 451 / 441; 512 wide, 2: 13.9 351 / 363, 4:
+//     27.9 637 / 607; 256 wide, 3: 10.4 226 / 253, 20.5 408 / 402, 6: 20.9 412 / 381.  The cost is paid once, the gain per
+//     layer: six layers 768 wide, 2 students: 12.1 1626 / 1612, 16.8 2156 / 2106; 256 wide, 2: 4.0 483 / 471, 7.0 668 / 609.  Not so for an odd number
+//     of students, of which one group is done before the other: six layers 256 wide, 3: 10.4 898 / 974.
+//   * bf16 of hidden 512 and more, whose projections reach the power limit by themselves: even numbers of students only (768 wide, 3:
+//     31 852 / 858, 61 1635 / 1675; 5: 52 1421 / 1432; 512 wide, 3: 20.9 492 / 506), and up to 64, beyond which a group alone fills the chip as
+//     well (768 wide, 8: 49 1302 / 1288, 58 1567 / 1555, 70 1850 / 1918, 84 2136-2200 / 2196-2220, 328 8196 / 8329; 4: 42 1141 / 1103, 58.5 1576 /
+//     1558, 82 2156 / 2220; six layers, 2: 41 5092 / 4897, 59 7306 / 7255, 82 9953 / 10314; 1024 wide, 6: 48 1501 / 1501, 107 3201 / 3226).
+//     Quantised and narrow students have no such limit (quantised, 8: 84 1498 / 1472, 164 2878 / 2853; 256 wide, 6: 161 2569 / 2539).
+constexpr int64_t kTwoGroupsWork = 20 << 20, kTwoGroupsMostWork = 64 << 20;
+static bool two_groups_pay(const sp_config& c, int T, int k)
+{
+    if (k < 2 || T < kLargeTokens) return false;
+    const int64_t work = (int64_t)T * k * c.hidden;
+    const bool even = k % 2 == 0;
+    if (work * (even && c.layers > 2 ? c.layers - 1 : 1) < kTwoGroupsWork) return false;
+    return c.dtype == SP_DTYPE_FP8 || c.hidden < 512 || (even && work <= kTwoGroupsMostWork);
+}
 
 static int run_forward(const sp_model* M, const int32_t* ids, const int32_t* cu, int B, int T, int max_seqlen, int k,
                        int stop_layers, bool with_head, void* ws, size_t ws_bytes, float* logits, hipStream_t s,
@@ -624,9 +639,7 @@ static int run_forward(const sp_model* M, const int32_t* ids, const int32_t* cu,
 
     const bool large = T >= kLargeTokens;
     const int ka = (k + 1) / 2, k_rule = large ? (c.K + 1) / 2 : k;
-    // (a call of that much work has more tiles than any that splits a reduction)
-    const bool two_groups = with_head && !pt && k >= 2 && (int64_t)T * k * c.hidden >= kTwoGroupsWork && !c.single_stream && M->aux;
-    if (!two_groups)
+    if (!with_head || pt || c.single_stream || !M->aux || !two_groups_pay(c, T, k))
         return run_students(M, W, ids, cu, B, T, max_seqlen, 0, k, k_rule, !large, stop_layers, with_head, w, logits, s, pt);
 
     float* lpart = (float*)(w + W.lpart);

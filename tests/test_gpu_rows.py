@@ -107,30 +107,40 @@ def test_nothing_in_the_workspace_has_to_be_finite(oracle64, hidden, ffn, layers
     st.close()
 
 
-# (hidden, students, sequences of 60 tokens): the first-token rows of all students and of a group, of the two groups of an odd
+def _forks(hidden, layers, dtype, tokens, k):
+    """Whether a call is expected to run as two groups: the rule beside which both sides are measured, stated once more."""
+    work = tokens * k * hidden
+    return (k >= 2 and tokens >= 8192 and work * (layers - 1 if k % 2 == 0 and layers > 2 else 1) >= 20 << 20 and
+            (dtype == "fp8" or hidden < 512 or (k % 2 == 0 and work <= 64 << 20)))
+
+
+# (hidden, students, sequences, tokens of each, layers): the first-token rows of all students and of a group, of the two groups of an odd
 # number, or of few and of all students, lie on different sides of a limit between kernels; few tiles for one student
-@pytest.mark.parametrize("hidden,K,nseq", [(768, 3, 140), (768, 2, 200), (1024, 4, 138), (768, 5, 140), (1024, 6, 900),
-                                            (256, 3, 150)])
-@pytest.mark.parametrize("dtype", ["bf16", "fp8"])
-def test_one_group_of_students_or_two_give_the_same_bits(hidden, K, nseq, dtype):
+GROUP_SHAPES = [(768, 3, 153, 60, 2), (768, 4, 140, 60, 2), (768, 2, 230, 60, 2), (1024, 4, 138, 60, 2), (768, 5, 140, 60, 2),
+                (1024, 6, 900, 16, 2), (256, 3, 460, 60, 2), (256, 5, 280, 60, 2), (256, 2, 150, 60, 6)]
+
+
+@pytest.mark.parametrize("hidden,K,nseq,length,layers,dtype",
+                         [s + (d,) for s in GROUP_SHAPES for d in ("bf16", "fp8") if (s[:2], d) != ((768, 3), "bf16")])
+def test_one_group_of_students_or_two_give_the_same_bits(hidden, K, nseq, length, layers, dtype):
     """Which kernels a large call takes goes by its tokens and sequences and the model, not by the group of students at hand nor by
     how many are active: its logits are the same bits on one stream and on two, and the sum of the same terms for every k."""
     from paper_2408_12526_amd import sp
-    shape = synth.StudentShape(K=K, layers=2, hidden=hidden, heads=hidden // 64, ffn=1024, vocab=500, max_pos=64, classes=4, dtype=dtype)
+    shape = synth.StudentShape(K=K, layers=layers, hidden=hidden, heads=hidden // 64, ffn=1024, vocab=500, max_pos=64, classes=4, dtype=dtype)
     rng = np.random.default_rng(hidden + K)
-    lengths = np.full(nseq, 60, dtype=np.int32)
+    lengths = np.full(nseq, length, dtype=np.int32)
     ids = torch.from_numpy(synth.make_ids(rng, int(lengths.sum()), shape.vocab)).cuda()
-    assert ids.numel() >= 8192
+    assert any(_forks(hidden, layers, dtype, ids.numel(), k) for k in range(1, K + 1))
     cu = torch.from_numpy(sp.sp_pack(lengths)).cuda()
     blob = synth.make_weights(rng, shape, std=0.04, ln_random=True)
     two = sp.Students(sp.config_from_shape(shape), blob)
     one = sp.Students(sp.config_from_shape(shape, single_stream=True), blob)
-    two.sp_forward(ids, cu, 60, K)
+    two.sp_forward(ids, cu, length, K)
     z = torch.from_numpy(two.read_activation(two.workspace(ids.numel(), nseq), "z", ids.numel(), nseq, K)).float()
     total = torch.zeros(nseq, 4)
     for k in range(1, K + 1):
         total = total + z[k - 1]
-        a, b = two.sp_forward(ids, cu, 60, k).cpu(), one.sp_forward(ids, cu, 60, k).cpu()
+        a, b = two.sp_forward(ids, cu, length, k).cpu(), one.sp_forward(ids, cu, length, k).cpu()
         assert torch.equal(a, b), f"k_active {k}: {(a - b).abs().max().item():.3e}"
         assert torch.equal(a, total), f"k_active {k}, terms: {(a - total).abs().max().item():.3e}"
     two.close()
@@ -207,23 +217,46 @@ def test_tiles_of_every_height_at_their_edges(oracle64, hidden, ffn, K, tokens):
     st.close()
 
 
-@pytest.mark.parametrize("hidden,K,nseq", [(768, 8, 68), (1024, 6, 68), (512, 13, 64)])
+@pytest.mark.parametrize("hidden,K,nseq", [(768, 8, 68), (1024, 6, 68), (512, 13, 64), (1024, 24, 14)])
 @pytest.mark.parametrize("dtype", ["bf16", "fp8"])
-def test_two_groups_below_8192_tokens_give_the_same_bits(hidden, K, nseq, dtype):
-    """Calls whose work is enough for two groups of students although their tokens are fewer: the same logits on one stream."""
+def test_calls_below_8192_tokens_stay_on_their_own_stream(hidden, K, nseq, dtype):
+    """However much work they are.  Seen from outside: the model's second stream belongs to a capture (of a large call on another
+    stream), and the call runs eagerly beside it, with the single-stream bits; the graph then gives what the large call gives."""
     from paper_2408_12526_amd import sp
     shape = synth.StudentShape(K=K, layers=2, hidden=hidden, heads=hidden // 64, ffn=512, vocab=500, max_pos=64, classes=3, dtype=dtype)
     rng = np.random.default_rng(hidden + K)
-    lengths = np.full(nseq, 63, dtype=np.int32)
-    ids = torch.from_numpy(synth.make_ids(rng, int(lengths.sum()), shape.vocab)).cuda()
+
+    def call(n):
+        ids = torch.from_numpy(synth.make_ids(rng, 63 * n, shape.vocab)).cuda()
+        return ids, torch.from_numpy(sp.sp_pack(np.full(n, 63, dtype=np.int32))).cuda(), torch.empty(n, 3, device="cuda")
+    ids, cu, out = call(nseq)
     assert ids.numel() < 8192 and ids.numel() * K * hidden >= 20 << 20
-    cu = torch.from_numpy(sp.sp_pack(lengths)).cuda()
+    large, large_cu, large_out = call((20 << 20) // (2 * hidden) // 63 + 1)
+    assert _forks(hidden, 2, dtype, large.numel(), 2)
     blob = synth.make_weights(rng, shape, std=0.04, ln_random=True)
     two = sp.Students(sp.config_from_shape(shape), blob)
     one = sp.Students(sp.config_from_shape(shape, single_stream=True), blob)
+    ws, large_ws = (torch.empty(sp.sp_workspace_bytes(two.cfg, i.numel(), c.numel() - 1), dtype=torch.uint8, device="cuda")
+                    for i, c in ((ids, cu), (large, large_cu)))
+    want = {k: one.sp_forward(ids, cu, 63, k).clone() for k in (K, K - 1)}
+    want_large = one.sp_forward(large, large_cu, 63, 2).clone()
+    two.sp_forward(large, large_cu, 63, 2, large_out, large_ws)
+    torch.cuda.synchronize()
+    side, other, graph = torch.cuda.Stream(), torch.cuda.Stream(), torch.cuda.CUDAGraph()
+    got = {k: torch.zeros_like(out) for k in (K, K - 1)}
+    torch.cuda.synchronize()
+    with torch.cuda.graph(graph, stream=side, capture_error_mode="thread_local"):
+        two.sp_forward(large, large_cu, 63, 2, large_out, large_ws, stream=side)
+        for k in (K, K - 1):
+            two.sp_forward(ids, cu, 63, k, got[k], ws, stream=other)
+    torch.cuda.synchronize()
     for k in (K, K - 1):
-        a, b = two.sp_forward(ids, cu, 63, k).cpu(), one.sp_forward(ids, cu, 63, k).cpu()
-        assert torch.equal(a, b), f"k_active {k}: {(a - b).abs().max().item():.3e}"
+        assert torch.equal(got[k], want[k]), f"k_active {k}: {(got[k] - want[k]).abs().max().item():.3e}"
+    for _ in range(3):
+        large_out.zero_()
+        graph.replay()
+        torch.cuda.synchronize()
+        assert torch.equal(large_out, want_large)
     two.close()
     one.close()
 
