@@ -85,7 +85,8 @@ typedef struct {
                          and dtype), the second on a stream the model owns, forked from and joined to the caller's
                          stream with events (the call stays asynchronous and can be captured in a graph; the
                          logits are bit-identical to the single-stream result).  The model has one such stream:
-                         calls that fork, issued on several streams, queue their second groups behind one another.
+                         calls that fork, issued on several streams, queue their second groups behind one another,
+                         and while a capture has forked to it, calls outside that capture run on their own stream alone.
                          In calls of >= 8192 tokens a student's term has the same bits for every k_active;
                          smaller calls choose their kernels by the rows of all active students, so there the
                          term of a student may differ between two k_active by roundings of its arithmetic.

@@ -623,6 +623,20 @@ static bool two_groups_pay(const sp_config& c, int T, int k)
     return c.dtype == SP_DTYPE_FP8 || c.hidden < 512 || (even && work <= kTwoGroupsMostWork);
 }
 
+// Whether work on s can be continued on the model's stream.  A capture that forked to it keeps it until the capture ends, and other
+// streams' calls can neither join that capture nor wait for it: they stay on their own stream meanwhile (the same bits).
+static bool aux_may_follow(const sp_model* M, hipStream_t s)
+{
+    hipStreamCaptureStatus aux = hipStreamCaptureStatusNone, own = hipStreamCaptureStatusNone;
+    unsigned long long aux_id = 0, own_id = 0;
+    const bool known = hipStreamGetCaptureInfo(M->aux, &aux, &aux_id) == hipSuccess;
+    if (known && aux == hipStreamCaptureStatusNone) return true;
+    const bool same = known && aux == hipStreamCaptureStatusActive && hipStreamGetCaptureInfo(s, &own, &own_id) == hipSuccess &&
+                      own == hipStreamCaptureStatusActive && own_id == aux_id;
+    if (!same) (void)hipGetLastError();             // (a query that was refused is not an error of the call)
+    return same;
+}
+
 static int run_forward(const sp_model* M, const int32_t* ids, const int32_t* cu, int B, int T, int max_seqlen, int k,
                        int stop_layers, bool with_head, void* ws, size_t ws_bytes, float* logits, hipStream_t s,
                        PhaseTimer* pt = nullptr)
@@ -639,12 +653,18 @@ static int run_forward(const sp_model* M, const int32_t* ids, const int32_t* cu,
 
     const bool large = T >= kLargeTokens;
     const int ka = (k + 1) / 2, k_rule = large ? (c.K + 1) / 2 : k;
-    if (!with_head || pt || c.single_stream || !M->aux || !two_groups_pay(c, T, k))
+    std::unique_lock<std::mutex> hold;              // one fork/join at a time on the model's stream and events
+    bool two_groups = with_head && !pt && !c.single_stream && M->aux && two_groups_pay(c, T, k);
+    if (two_groups) {
+        hold = std::unique_lock<std::mutex>(*M->mu);
+        two_groups = aux_may_follow(M, s);
+        if (!two_groups) hold.unlock();
+    }
+    if (!two_groups)
         return run_students(M, W, ids, cu, B, T, max_seqlen, 0, k, k_rule, !large, stop_layers, with_head, w, logits, s, pt);
 
     float* lpart = (float*)(w + W.lpart);
     const size_t n = (size_t)B * c.classes;
-    std::lock_guard<std::mutex> hold(*M->mu);       // one fork/join at a time on the model's stream and events
     if (hipEventRecord(M->ev_fork, s) != hipSuccess || hipStreamWaitEvent(M->aux, M->ev_fork, 0) != hipSuccess)
         return SP_EHIP;
     int rc = run_students(M, W, ids, cu, B, T, max_seqlen, 0, ka, k_rule, false, stop_layers, true, w, lpart, s, nullptr);

@@ -219,9 +219,10 @@ def test_tiles_of_every_height_at_their_edges(oracle64, hidden, ffn, K, tokens):
 
 @pytest.mark.parametrize("hidden,K,nseq", [(768, 8, 68), (1024, 6, 68), (512, 13, 64), (1024, 24, 14)])
 @pytest.mark.parametrize("dtype", ["bf16", "fp8"])
-def test_calls_below_8192_tokens_stay_on_their_own_stream(hidden, K, nseq, dtype):
-    """However much work they are.  Seen from outside: the model's second stream belongs to a capture (of a large call on another
-    stream), and the call runs eagerly beside it, with the single-stream bits; the graph then gives what the large call gives."""
+def test_calls_beside_a_capture_of_the_same_model(hidden, K, nseq, dtype):
+    """While the model's second stream belongs to the capture of a large call, calls on another stream run eagerly with the single-stream
+    bits: below 8192 tokens, which never fork however much work they are, and of a size that would fork.  A second forking call joins the
+    capture.  The graph gives what the large calls give."""
     from paper_2408_12526_amd import sp
     shape = synth.StudentShape(K=K, layers=2, hidden=hidden, heads=hidden // 64, ffn=512, vocab=500, max_pos=64, classes=3, dtype=dtype)
     rng = np.random.default_rng(hidden + K)
@@ -243,20 +244,28 @@ def test_calls_below_8192_tokens_stay_on_their_own_stream(hidden, K, nseq, dtype
     two.sp_forward(large, large_cu, 63, 2, large_out, large_ws)
     torch.cuda.synchronize()
     side, other, graph = torch.cuda.Stream(), torch.cuda.Stream(), torch.cuda.CUDAGraph()
-    got = {k: torch.zeros_like(out) for k in (K, K - 1)}
+    got, beside, again_out, beside_ws = ({k: torch.zeros_like(out) for k in (K, K - 1)}, torch.zeros_like(large_out),
+                                         torch.zeros_like(large_out), torch.empty_like(large_ws))
     torch.cuda.synchronize()
     with torch.cuda.graph(graph, stream=side, capture_error_mode="thread_local"):
         two.sp_forward(large, large_cu, 63, 2, large_out, large_ws, stream=side)
         for k in (K, K - 1):
             two.sp_forward(ids, cu, 63, k, got[k], ws, stream=other)
+        two.sp_forward(large, large_cu, 63, 2, beside, beside_ws, stream=other)
+        two.sp_forward(large, large_cu, 63, 2, again_out, large_ws, stream=side)
     torch.cuda.synchronize()
+    assert torch.equal(beside, want_large)
     for k in (K, K - 1):
         assert torch.equal(got[k], want[k]), f"k_active {k}: {(got[k] - want[k]).abs().max().item():.3e}"
     for _ in range(3):
         large_out.zero_()
+        again_out.zero_()
         graph.replay()
         torch.cuda.synchronize()
-        assert torch.equal(large_out, want_large)
+        assert torch.equal(large_out, want_large) and torch.equal(again_out, want_large)
+        two.sp_forward(large, large_cu, 63, 2, beside, large_ws)             # eager work between the replays, two groups again
+        torch.cuda.synchronize()
+        assert torch.equal(beside, want_large)
     two.close()
     one.close()
 
