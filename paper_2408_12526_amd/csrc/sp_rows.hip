@@ -574,8 +574,8 @@ __global__ __launch_bounds__(256) void fold_query_kernel(FoldQArgs p)
 // Attention of the first token of each sequence on formed queries, keys and values (calls whose q|k|v projection covers
 // every token): WPH waves share one (student, sequence, head), 64 keys per step and wave, a lane per key for the scores
 // and a lane per dimension for the values (feature-major rows, eight tokens per 16 bytes).  Probabilities are rounded to
-// bf16 for the product and summed in fp32 as in the all-token kernels, and each tile of 32 keys against the maximum of
-// the keys up to its end as there, so that the two round alike.
+// bf16 for the product and summed in fp32 as in the all-token kernel, and each tile of 32 keys against the maximum of
+// the keys up to its end, as there in sequences of up to 128 tokens (64 keys in longer ones): up to that length the two round alike.
 // -------------------------------------------------------------------------------------
 template <int WPH>
 __global__ __launch_bounds__(256) void attention_first_kernel(const bf16* __restrict__ qkv, const bf16* __restrict__ vt,

@@ -76,6 +76,53 @@ def test_fp32_layer_in_one_launch(oracle64, ffn, layers, lengths, k):
     st.close()
 
 
+# one, two, three and eight rounds of 64 boundaries in the embedding of a whole call in few launches; 512 rows of all students and one more
+@pytest.mark.parametrize("lengths,k", [((3,) * 64, 2), ((3,) * 65, 2), ((1, 2) * 64 + (5,), 2), ((1,) * 200, 2), ((1,) * 255 + (257,), 1), ((1,) * 512, 1),
+                                       ((1,) * 513, 1)])
+@pytest.mark.parametrize("classes", [1, 2])
+def test_fp32_calls_of_many_sequences(oracle64, lengths, k, classes):
+    from paper_2408_12526_amd import sp
+    shape = synth.StudentShape(K=2, layers=2, hidden=128, heads=2, ffn=256, vocab=60, max_pos=304, classes=classes, dtype="fp32")
+    rng = np.random.default_rng(len(lengths))
+    ids = synth.make_ids(rng, sum(lengths), shape.vocab)
+    blob = synth.make_weights(rng, shape, std=0.04, ln_random=True)
+    cu = sp.sp_pack(np.array(lengths, dtype=np.int32))
+    st = sp.Students(sp.config_from_shape(shape), blob)
+    got = st.sp_forward(torch.from_numpy(ids).cuda(), torch.from_numpy(cu).cuda(), max(lengths), k).double().cpu().numpy()
+    st.close()
+    cfg = OracleConfig(shape.K, shape.layers, shape.hidden, shape.heads, shape.ffn, shape.vocab, shape.max_pos, shape.classes,
+                       shape.ln_eps)
+    want = oracle64.forward(cfg, blob, ids, cu, k)
+    assert np.abs(got - want).max() / np.abs(want).max() <= 1e-5         # (as in the test above)
+
+
+# the pooler's share of the classifier (with one class its last lanes' weights are the matrix's end), the classifier behind the tile kernels, the
+# one of the all-token last layer, the fp32 chain's
+@pytest.mark.parametrize("hidden,lengths,dtype", [(128, (64,), "bf16"), (256, (17, 3), "bf16"), (768, (64, 1, 63), "bf16"), (1024, (250, 6), "bf16"),
+                                                  (640, (90, 200, 13), "bf16"), (768, (30,) * 40, "bf16"), (256, (5,) * 3000, "bf16"),
+                                                  (128, (9, 30), "fp32"), (256, (9, 30), "fp32")])
+def test_one_class_is_the_first_of_two(hidden, lengths, dtype):
+    """The same sums in the same order, so the same bits."""
+    from paper_2408_12526_amd import sp
+    one, two = (synth.StudentShape(K=3, layers=2, hidden=hidden, heads=hidden // 64, ffn=2 * hidden, vocab=60, max_pos=256, classes=c, dtype=dtype)
+                for c in (1, 2))
+    rng = np.random.default_rng(hidden + len(lengths))
+    blob2 = synth.make_weights(rng, two, std=0.04, ln_random=True)
+    blob1 = np.empty(synth.blob_floats(one), np.float32)
+    for m in range(3):
+        for (name, a), (_, b) in zip(synth.student_views(blob1, one, m).items(), synth.student_views(blob2, two, m).items()):
+            a[...] = b if a.shape == b.shape else b[..., :1]
+    ids = torch.from_numpy(synth.make_ids(rng, sum(lengths), one.vocab)).cuda()
+    cu = torch.from_numpy(sp.sp_pack(np.array(lengths, np.int32))).cuda()
+    got = []
+    for shape, blob in ((one, blob1), (two, blob2)):
+        st = sp.Students(sp.config_from_shape(shape), blob)
+        got.append([st.sp_forward(ids, cu, max(lengths), k).cpu() for k in (1, 3)])
+        st.close()
+    for a, b in zip(*got):
+        assert a.shape[1] == 1 and torch.isfinite(a).all() and a.abs().max() > 0 and torch.equal(a, b[:, :1])
+
+
 # (hidden, ffn, layers, students, active, every token in the last layer): the attention-output projection splits its reduction and the
 # FFN down-projection does not; the other way round with slices over the attention output; both; a call of few tokens
 @pytest.mark.parametrize("hidden,ffn,layers,K,k,all_tokens,lengths",
