@@ -52,7 +52,8 @@ __device__ inline uint2 chunk_to_fp8(uint4 c, float qscale)
 // What bounds it: vector instructions (about seven issue slots per score, four of them the exponential) and the read of
 // queries, keys and values, neither saturated: a wave's chain of products, maximum, exponentials and products is issued in
 // order, so waves in flight are what counts.  Hence 32 queries a wave and 128 registers, four waves per SIMD (with 64 queries a
-// wave a key fragment served two products, but two waves per SIMD was all the registers held).  us per launch, a wave per
+// wave a key fragment served two products, but two waves per SIMD was all the registers held).  Sequences of up to 32 tokens would leave
+// three of the four waves idle: batches of them have a part of their own (attention_short).  us per launch, a wave per
 // sequence and head up to 128 tokens and 64 queries per wave above / this: 64 sequences of 64-512 tokens, 16 heads, one student
 // 84 / 66, six 466 / 335; 256 sequences of 8-256, 12 heads, eight students 238 / 214, two 65 / 54; 32 of 16-128, four students
 // 31 / 21; one of 64, one student 9.9 / 6.9.  Tried: keys and values in flight together (141 registers, three waves) 65, 357, 237,
@@ -68,6 +69,11 @@ constexpr int kOutPitch = kD * 2 + 16;              // bytes per staged output r
 constexpr int kAttnLdsBytes = 4 * kTileBytes;       // two buffers of a key and a value tile
 static_assert(4 * 32 * kOutPitch <= kAttnLdsBytes && (2 * kTileBytes & (2 * kTileBytes - 1)) == 0, "the output tiles reuse the key/value buffers; offsets change buffers by an exclusive or");
 
+constexpr int kShortLen = 32;   // longest sequence that one wave takes with all its queries
+constexpr int kShortBytes = kAttnLdsBytes / 4;      // LDS of such a wave: a key and a value tile of 32 keys
+constexpr int kShortKeys = kShortLen * kD * 2;      // bytes of the key tile
+static_assert(2 * kShortKeys == kShortBytes && kShortLen * kOutPitch <= kShortBytes, "the output tile reuses the wave's key/value tiles");
+
 struct AttnArgs {
     const bf16 *qkv, *vt;
     bf16* att;                        // null: the fp8 copy alone
@@ -76,11 +82,180 @@ struct AttnArgs {
     float qscale;
     int B, Tn, rows, H, heads, max_seqlen;
     int items, run;                   // work items per head; neighbouring items that stay on one XCD
+    int general;                      // workgroups of the general part; those behind it take sequences of up to kShortLen tokens
 };
 
+// Scores of a block of 32 keys (a query is a lane column): accumulator register v of a lane of half g is key 8 (v / 4) + 4 g + v % 4.  Only
+// the first and the last block of a sequence of L keys have keys to mask (k0: the block's first key, at least -7).
+__device__ __forceinline__ void mask_block(f32x16& sc, int k0, int L, int g)
+{
+    if (k0 >= 0 && k0 + 32 <= L) return;
+    const int g4 = 4 * g;
+#pragma unroll
+    for (int v = 0; v < 16; ++v) {
+        const int c = 8 * (v >> 2) + (v & 3);
+        bool ok = g4 < L - k0 - c;
+        if (v < 4) ok = ok && g4 >= -k0 - c;
+        if (!ok) sc[v] = -INFINITY;
+    }
+}
+__device__ __forceinline__ float block_maximum(const f32x16& sc)
+{
+    float mx = sc[0];
+#pragma unroll
+    for (int v = 1; v < 16; ++v) mx = fmaxf(mx, sc[v]);
+    return mx;
+}
+// New maximum of the queries; what the sums so far have to be multiplied by (no rescaling where no maximum moves).
+__device__ __forceinline__ float rescale_sums(float mx, float& mrun, f32x16 (&o)[2], float sl2)
+{
+    mx = max_across_halves(mx);
+    float alpha = 1.f;
+    if (__any(mx > mrun)) {
+        mx = fmaxf(mx, mrun);
+        alpha = exp2_raw((mrun - mx) * sl2);    // first block: exp2(-inf) = 0
+        mrun = mx;
+#pragma unroll
+        for (int db = 0; db < 2; ++db)
+#pragma unroll
+            for (int e = 0; e < 16; ++e) o[db][e] *= alpha;
+    }
+    return alpha;
+}
+// probabilities of a block as the second operand of the values' product: reduction slot e of step s2 is the key of register 8 s2 + e
+__device__ __forceinline__ void probabilities(const f32x16& sc, float mrun, float sl2, float& psum, bf16x8 (&pf)[2])
+{
+    const float nm = -mrun * sl2;
+#pragma unroll
+    for (int v = 0; v < 16; ++v) {
+        const float e = exp2_raw(fmaf(sc[v], sl2, nm));
+        psum += e;
+        pf[v >> 3][v & 7] = (bf16)e;
+    }
+}
+// A wave's 32 x 64 output block leaves through its own LDS tile (the key/value buffers are idle) as whole 128-byte rows, the first n of
+// them; at: element of the first row's first dimension.
+__device__ __forceinline__ void store_outputs(char* stg, const f32x16 (&o)[2], float lrun, int ln, int n, bf16* att, unsigned char* attq, size_t at,
+                                              int H, float qscale)
+{
+    const int oq = ln & 31, og = ln >> 5 & 1, orow = ln >> 3 & 7, oc = ln & 7;
+    const float inv = 1.0f / sum_across_halves(lrun);
+#pragma unroll
+    for (int db = 0; db < 2; ++db)
+#pragma unroll
+        for (int v4 = 0; v4 < 4; ++v4) {
+            bf16x4 w;
+#pragma unroll
+            for (int e = 0; e < 4; ++e) w[e] = (bf16)(o[db][4 * v4 + e] * inv);
+            *(bf16x4*)(stg + oq * kOutPitch + (db * 32 + 8 * v4 + 4 * og) * 2) = w;
+        }
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+    at += oc * 8;
+#pragma unroll
+    for (int r0 = 0; r0 < 32; r0 += 8)
+        if (r0 + orow < n) {
+            const uint4 c = *(const uint4*)(stg + (r0 + orow) * kOutPitch + oc * 16);
+            if (att) *(uint4*)(att + at + (size_t)(r0 + orow) * H) = c;   // (null: the fp8 copy alone)
+            if (attq) *(uint2*)(attq + at + (size_t)(r0 + orow) * H) = chunk_to_fp8(c, qscale);
+        }
+}
+
+// A sequence of up to kShortLen tokens: a wave takes it for one head, the four waves of a workgroup four heads, with nothing to wait for one
+// another for.  The keys' blocks and their order are the general part's, so the bits are too: the block in front may begin up to seven
+// tokens before the sequence, so there are one or two.  Bound by a chain of one memory round trip, products and exponentials per wave, of
+// which sixteen to a compute unit are in flight (128 registers).  us per launch, general part / this: eight students of 768, 256
+// sequences of 16 tokens 103 / 44, of 32 131 / 73, 1024 of 4 348 / 90; two students, 256 of 16 28.6 / 13.9.
+__device__ __forceinline__ void attention_short(const AttnArgs& p, char* lds, int bid)
+{
+    // Contiguous runs of (sequence, head group) per XCD (workgroup id mod 8): the lines of the token-contiguous value rows that
+    // neighbouring sequences share come into one L2.
+    const int groups = (p.heads + 3) >> 2, total = p.B * groups, chunk = (total + 7) >> 3, lin = (bid & 7) * chunk + (bid >> 3);
+    if ((bid >> 3) >= chunk || lin >= total) return;
+    const int b = lin / groups, m = blockIdx.y;
+    const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6), h = (lin % groups) * 4 + wave;
+    int t0 = p.cu[b], t1 = p.cu[b + 1];
+    t0 = t0 < 0 ? 0 : (t0 > p.Tn - 1 ? p.Tn - 1 : t0);
+    int L = t1 - t0;
+    L = L < 1 ? 1 : L;
+    L = L > p.max_seqlen ? p.max_seqlen : L;
+    L = L > p.Tn - t0 ? p.Tn - t0 : L;
+    if (L > kShortLen || h >= p.heads) return;              // (whole waves, and no barrier below)
+    lds += wave * kShortBytes;
+    const int j = lane & 31, g = lane >> 5, H = p.H, rows = p.rows;
+    const int lead = t0 & 7, vlast = (L + lead - 1) & ~7;
+    const bf16* base = p.qkv + ((size_t)m * rows + t0) * (3 * H) + h * kD;
+    const bf16* vrows = p.vt + ((size_t)m * H + h * kD) * rows + (t0 - lead);
+    const float sl2 = 0.125f * 1.44269504088896341f;        // 1/sqrt(64) * log2(e)
+    // 16-byte pieces per lane: keys lane / 8 + 8 i, chunk lane % 8; dimensions lane / 4 + 16 i, chunk lane % 4.  Slots as in the general part
+    // (values: four of them per row, slot ^ ((row / 2) % 4)); what lies outside the sequence repeats its first or last row (chunk).
+    const bf16* keys = base + H + (lane & 7) * 8;
+    const int vc = (lane & 3) * 8;
+    bf16x8 kr[4], vr[4], qf[4], k2, v2;
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+        kr[i] = *(const bf16x8*)(keys + key_tile_offset(-lead, 3 * H) + key_row_offset(-lead, (lane >> 3) + 8 * i, L, 3 * H));
+        vr[i] = *(const bf16x8*)(vrows + value_row_offset((lane >> 2) + 16 * i, rows) + (vc < vlast ? vc : vlast));
+    }
+#pragma unroll
+    for (int s4 = 0; s4 < 4; ++s4) qf[s4] = *(const bf16x8*)(base + (size_t)(j < L ? j : L - 1) * (3 * H) + 16 * s4 + 8 * g);
+    const bool two = 32 - lead < L;                         // (at most seven keys in the second block: eight rows, a chunk per dimension)
+    if (two) {
+        k2 = *(const bf16x8*)(keys + key_tile_offset(32 - lead, 3 * H) + key_row_offset(32 - lead, lane >> 3, L, 3 * H));
+        v2 = *(const bf16x8*)(vrows + value_row_offset(lane, rows) + 32);
+    }
+    f32x16 o[2];
+    float mrun = -INFINITY, lrun = 0.f;
+#pragma unroll
+    for (int db = 0; db < 2; ++db)
+#pragma unroll
+        for (int e = 0; e < 16; ++e) o[db][e] = 0.f;
+    const int kdst = (lane >> 3) * 128 + (((lane & 7) ^ (lane >> 4)) << 4);
+    auto stage_values = [&](int to, const bf16x8& r) {
+        *(bf16x4*)(lds + to) = bf16x4{r[0], r[1], r[2], r[3]};
+        *(bf16x4*)(lds + (to ^ 16)) = bf16x4{r[4], r[5], r[6], r[7]};
+    };
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+        *(bf16x8*)(lds + (kdst ^ (i & 1) * 64) + i * 8 * 128) = kr[i];
+        stage_values(kShortKeys + ((lane >> 2) + 16 * i) * 64 + (((lane & 2) ^ (lane >> 3 & 3)) << 4) + 8 * (lane & 1), vr[i]);
+    }
+    const int krow = j * 128 + ((g ^ ((j >> 1) & 7)) << 4), vrow = kShortKeys + j * 64 + ((g ^ ((j >> 1) & 3)) << 4);
+    for (int kt0 = -lead; kt0 < L; kt0 += 32) {
+        if (kt0 + lead) {                                   // second block: over the first keys of the first (the others are masked, and finite)
+            *(bf16x8*)(lds + kdst) = k2;
+            stage_values(kShortKeys + lane * 64 + ((lane >> 1 & 3) << 4), v2);
+        }
+        __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+        __builtin_amdgcn_wave_barrier();
+        f32x16 sc;
+#pragma unroll
+        for (int e = 0; e < 16; ++e) sc[e] = 0.f;
+#pragma unroll
+        for (int s4 = 0; s4 < 4; ++s4) sc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(*(const bf16x8*)(lds + (krow ^ (32 * s4))), qf[s4], sc, 0, 0, 0);
+        mask_block(sc, kt0, L, g);
+        const float alpha = rescale_sums(block_maximum(sc), mrun, o, sl2);
+        float psum = 0.f;
+        bf16x8 pf[2];
+        probabilities(sc, mrun, sl2, psum, pf);
+#pragma unroll
+        for (int s2 = 0; s2 < 2; ++s2)
+#pragma unroll
+            for (int db = 0; db < 2; ++db)
+                o[db] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(*(const bf16x8*)(lds + (vrow ^ (32 * s2)) + db * 32 * 64), pf[s2], o[db], 0, 0, 0);
+        lrun = lrun * alpha + psum;
+        __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+        __builtin_amdgcn_wave_barrier();                    // (the tiles are written again)
+    }
+    store_outputs(lds, o, lrun, lane, L, p.att, p.attq, ((size_t)m * rows + t0) * H + h * kD, H, p.qscale);
+}
+
+// SHORT: sequences of up to kShortLen tokens are taken by the workgroups behind the general part.
+template <bool SHORT>
 __global__ __launch_bounds__(256, 4) void attention_bf16_kernel(AttnArgs p)
 {
     __shared__ __attribute__((aligned(16))) char lds[kAttnLdsBytes];
+    if (SHORT && (int)blockIdx.x >= p.general) return attention_short(p, lds, (int)blockIdx.x - p.general);
     const int m = blockIdx.y;
     // workgroup id mod 8 selects the XCD: runs of neighbouring items (they share lines of the token-contiguous value rows)
     // stay on one XCD, the runs go round the XCDs, another way for every student
@@ -96,7 +271,7 @@ __global__ __launch_bounds__(256, 4) void attention_bf16_kernel(AttnArgs p)
     L = L < 1 ? 1 : L;
     L = L > p.max_seqlen ? p.max_seqlen : L;
     L = L > p.Tn - t0 ? p.Tn - t0 : L;
-    if (q0 < 0 || q0 >= L) return;                  // (the whole workgroup)
+    if (q0 < 0 || q0 >= L || (SHORT && L <= kShortLen)) return;   // (the whole workgroup)
 
     const int j = lane & 31, g = lane >> 5;
     const int H = p.H, rows = p.rows;
@@ -155,44 +330,10 @@ __global__ __launch_bounds__(256, 4) void attention_bf16_kernel(AttnArgs p)
         }
         return sc;
     };
-    // Accumulator register v of this lane is key 8 (v / 4) + 4 g + v % 4 of its block.  Only the first and the last block of a
-    // sequence have keys to mask (k0: the block's first key, at least -7).
-    auto mask = [&](f32x16& sc, int k0) {
-        if (k0 >= 0 && k0 + 32 <= L) return;
-        const int g4 = 4 * g;
-#pragma unroll
-        for (int v = 0; v < 16; ++v) {
-            const int c = 8 * (v >> 2) + (v & 3);
-            bool ok = g4 < L - k0 - c;
-            if (v < 4) ok = ok && g4 >= -k0 - c;
-            if (!ok) sc[v] = -INFINITY;
-        }
-    };
-    // New maximum of the queries; what the sums so far have to be multiplied by (no rescaling where no maximum moves).
-    auto rescale = [&](float mx) {
-        mx = max_across_halves(mx);
-        float alpha = 1.f;
-        if (__any(mx > mrun)) {
-            mx = fmaxf(mx, mrun);
-            alpha = exp2_raw((mrun - mx) * sl2);    // first block: exp2(-inf) = 0
-            mrun = mx;
-#pragma unroll
-            for (int db = 0; db < 2; ++db)
-#pragma unroll
-                for (int e = 0; e < 16; ++e) o[db][e] *= alpha;
-        }
-        return alpha;
-    };
-    // probabilities of a block, and its values weighted with them: reduction slot e of step s2 is the key of register 8 s2 + e
+    // a block's values weighted with its probabilities
     auto weigh = [&](const f32x16& sc, int kb, float& psum) {
-        const float nm = -mrun * sl2;
         bf16x8 pf[2];
-#pragma unroll
-        for (int v = 0; v < 16; ++v) {
-            const float e = exp2_raw(fmaf(sc[v], sl2, nm));
-            psum += e;
-            pf[v >> 3][v & 7] = (bf16)e;
-        }
+        probabilities(sc, mrun, sl2, psum, pf);
 #pragma unroll
         for (int s2 = 0; s2 < 2; ++s2)
 #pragma unroll
@@ -200,12 +341,6 @@ __global__ __launch_bounds__(256, 4) void attention_bf16_kernel(AttnArgs p)
                 const bf16x8 vf = *(const bf16x8*)(lds + (vrow ^ (64 * kb + 32 * s2)) + db * 32 * 128);
                 o[db] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(vf, pf[s2], o[db], 0, 0, 0);
             }
-    };
-    auto maximum = [](const f32x16& sc) {
-        float mx = sc[0];
-#pragma unroll
-        for (int v = 1; v < 16; ++v) mx = fmaxf(mx, sc[v]);
-        return mx;
     };
     const bool wide = L > kNarrowLen;
     auto tile = [&](int kt0) {
@@ -220,20 +355,20 @@ __global__ __launch_bounds__(256, 4) void attention_bf16_kernel(AttnArgs p)
             f32x16 s0 = scores(0), s1;
             if (two) s1 = scores(1);
             next_keys();
-            mask(s0, kt0);
-            float mx = maximum(s0), mx1 = -INFINITY;
+            mask_block(s0, kt0, L, g);
+            float mx = block_maximum(s0), mx1 = -INFINITY;
             if (two) {
-                mask(s1, kt0 + 32);
-                mx1 = maximum(s1);
+                mask_block(s1, kt0 + 32, L, g);
+                mx1 = block_maximum(s1);
             }
             if (wide) mx = fmaxf(mx, mx1);
-            float alpha = rescale(mx), psum = 0.f;
+            float alpha = rescale_sums(mx, mrun, o, sl2), psum = 0.f;
             weigh(s0, 0, psum);
             if (two) {
                 if (!wide) {
                     lrun = lrun * alpha + psum;
                     psum = 0.f;
-                    alpha = rescale(mx1);
+                    alpha = rescale_sums(mx1, mrun, o, sl2);
                 }
                 weigh(s1, 1, psum);
             }
@@ -270,30 +405,9 @@ __global__ __launch_bounds__(256, 4) void attention_bf16_kernel(AttnArgs p)
     for (int kt0 = -lead; kt0 < L; kt0 += kKeyTile) tile(kt0);
     if (q >= L) return;
 
-    // The 32 x 64 output block leaves through a wave-private LDS tile (the key/value buffers are idle) as whole 128-byte rows.
     int ln = tid;
     asm volatile("" : "+v"(ln));                    // (what follows from it is not kept through the loop)
-    const int stg = wave * (32 * kOutPitch), oq = ln & 31, og = ln >> 5 & 1, orow = ln >> 3 & 7, oc = ln & 7;
-    const float inv = 1.0f / sum_across_halves(lrun);
-#pragma unroll
-    for (int db = 0; db < 2; ++db)
-#pragma unroll
-        for (int v4 = 0; v4 < 4; ++v4) {
-            bf16x4 w;
-#pragma unroll
-            for (int e = 0; e < 4; ++e) w[e] = (bf16)(o[db][4 * v4 + e] * inv);
-            *(bf16x4*)(lds + stg + oq * kOutPitch + (db * 32 + 8 * v4 + 4 * og) * 2) = w;
-        }
-    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-    __builtin_amdgcn_wave_barrier();
-    const size_t at = ((size_t)m * rows + t0 + q) * H + h * kD + oc * 8;
-#pragma unroll
-    for (int r0 = 0; r0 < 32; r0 += 8)
-        if (q + r0 + orow < L) {
-            const uint4 c = *(const uint4*)(lds + stg + (r0 + orow) * kOutPitch + oc * 16);
-            if (p.att) *(uint4*)(p.att + at + (size_t)(r0 + orow) * H) = c;   // (null: the fp8 copy alone)
-            if (p.attq) *(uint2*)(p.attq + at + (size_t)(r0 + orow) * H) = chunk_to_fp8(c, p.qscale);
-        }
+    store_outputs(lds + wave * (32 * kOutPitch), o, lrun, ln, L - q, p.att, p.attq, ((size_t)m * rows + t0 + q) * H + h * kD, H, p.qscale);
 }
 
 // -------------------------------------------------------------------------------------
@@ -738,10 +852,19 @@ hipError_t launch_attention(const sp_model* M, const void* qkv, const void* vt, 
         // Runs of neighbouring items that stay on one XCD: 1, 2, 4, 8 and 16 measured 208 / 208 / 207 / 210 / 211 us on 371 items of
         // short sequences (eight students), 325 / 322 / 326 / 328 / 347 on 208 of long ones (six); few items go round one by one.
         AttnArgs a{(const bf16*)qkv, (const bf16*)vt, (bf16*)att, (unsigned char*)attq, cu, qscale, B, T, rows, c.hidden, c.heads,
-                   max_seqlen, T / kQItem + B, 1};
+                   max_seqlen, T / kQItem + B, 1, 0};
         a.run = a.items < 128 ? 1 : (a.items < 256 ? 2 : 4);
-        const int nitems = (a.items + 8 * a.run - 1) / (8 * a.run) * (8 * a.run);
-        hipLaunchKernelGGL(attention_bf16_kernel, dim3((unsigned)(nitems * c.heads), k), dim3(256), 0, s, a);
+        const int nitems = (a.items + 8 * a.run - 1) / (8 * a.run) * (8 * a.run), nshort = (B * ((c.heads + 3) / 4) + 7) / 8 * 8;
+        // Sequences of up to 32 tokens by single waves: alone where there are no others; beside the general part, whose workgroups then leave for
+        // those, where most are short (by the mean, all the host knows) and half a workgroup per compute unit comes together.  us a call,
+        // general part alone / this.  768 wide, eight students: 300 sequences of 4 tokens 496 / 426, 256 of 16 793 / 736, of 32 1290 / 1244; 256
+        // lognormal ones of mean 15 782 / 755, 24 1095 / 1075, 39 1588 / 1577, 58 2213 / 2207; two students, 24 of mean 25 102 / 102, 42 124 / 125.
+        // 256 wide, three students: 256 of 16 122 / 114, mean 24 144 / 142; 24 of mean 25 67.6 / 68.2, 36 71.3 / 71.9.
+        const bool few = (long)B * ((c.heads + 3) / 4) * k < 128, only = max_seqlen <= kShortLen, mixed = !only && !few && T <= (int64_t)32 * B;
+        a.general = only ? 0 : nitems * c.heads;
+        const dim3 grid((unsigned)(a.general + (only || mixed ? nshort : 0)), k);
+        if (only || mixed) hipLaunchKernelGGL(attention_bf16_kernel<true>, grid, dim3(256), 0, s, a);
+        else hipLaunchKernelGGL(attention_bf16_kernel<false>, grid, dim3(256), 0, s, a);
     } else {
         // (sixteen lanes per query: four times the workgroups; up to about two of them per compute unit)
         const int nq16 = (max_seqlen + 15) / 16, nq4 = (max_seqlen + 63) / 64;

@@ -42,6 +42,37 @@ def test_attention_at_tile_and_item_edges(oracle64, name, qk_std):
     st.close()
 
 
+# every length of the short part at every offset of the first key block, alone, beside longer sequences, and (few of them) in the general part
+@pytest.mark.parametrize("hidden", [128, 384, 768])      # two, six and twelve heads: waves of a head group without a head
+def test_short_sequences_alone_and_beside_longer_ones(oracle64, hidden):
+    """Against the definition as above, and the same bits in each of the three: blocks of keys and their order are the same."""
+    from paper_2408_12526_amd import sp
+    shape = synth.StudentShape(K=2, layers=1, hidden=hidden, heads=hidden // 64, ffn=128, vocab=100, max_pos=320, classes=2, dtype="bf16")
+    rng = np.random.default_rng(hidden)
+    few = np.array((9, 17, 25, 32, 31, 30, 29, 28, 27, 26, 24, 1), np.int32)             # 279 tokens, offsets 0 to 7
+    short = np.r_[few, 1, rng.permutation(np.tile(np.arange(1, 33), 8))].astype(np.int32)
+    calls = {"few, general": np.r_[few, 33], "alone": short, "mixed": np.r_[short, 33, 1, 200, 64, 3].astype(np.int32)}
+    assert set((np.r_[0, np.cumsum(few)] & 7).tolist()) == set(range(8)) and calls["mixed"].sum() <= 32 * len(calls["mixed"])
+    blob, ids = synth.make_weights(rng, shape, std=0.08, qk_std=1.36 / hidden ** 0.5), synth.make_ids(rng, int(calls["mixed"].sum()), shape.vocab)
+    st = sp.Students(sp.config_from_shape(shape), blob)
+    first, H, k = {}, hidden, shape.K
+    for name, lengths in calls.items():
+        lengths = lengths.astype(np.int32)
+        cu, T, B = sp.sp_pack(lengths), int(lengths.sum()), len(lengths)
+        ws = st.sp_forward_partial(torch.from_numpy(ids[:T]).cuda(), torch.from_numpy(cu).cuda(), int(lengths.max()), k, 1)
+        qkv, att = st.read_activation(ws, "qkv", T, B, k), st.read_activation(ws, "att", T, B, k)
+        first[name] = qkv[:, :279], att[:, :279]
+        for m in range(k):
+            for b in range(B):
+                a = qkv[m][cu[b]:cu[b + 1]]
+                want = oracle64.attention(a[:, :H], a[:, H:2 * H], a[:, 2 * H:], shape.heads)
+                err = np.abs(att[m][cu[b]:cu[b + 1]] - want).max() / np.abs(want).max()
+                assert err < 1.2e-2, f"{name}, student {m}, sequence {b} of {lengths[b]} tokens at {cu[b]}: {err:.3e}"
+    for name in ("alone", "mixed"):
+        assert all(np.array_equal(a, b) for a, b in zip(first[name], first["few, general"])), name
+    st.close()
+
+
 @pytest.mark.parametrize("copies", [1, 3])               # sixteen lanes per query; four
 def test_fp32_attention_at_block_and_chunk_edges(oracle64, copies):
     """Blocks of eight keys, chunks of 64 and blocks of 16 or 64 queries just missed, met and passed; sharp scores.  fp32 sums of up
