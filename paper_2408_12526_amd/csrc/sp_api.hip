@@ -279,6 +279,11 @@ struct PhaseTimer {
     void release() { for (int i = 0; i < n; ++i) (void)hipEventDestroy(ev[i]); ev.clear(); phase.clear(); n = 0; }
 };
 
+// Calls of at least this many tokens choose their kernels by the model's students, not by how many are active, and split no
+// reduction, so that a student's term has the same bits whatever k.  (Smaller calls go by the active ones: a call pruned to one student
+// would otherwise run on kernels for eight.)
+constexpr int kLargeTokens = 8192;
+
 // The forward of students [m0, m0 + k) of the model (k >= 1), all of it enqueued on stream s.  Every buffer of the
 // workspace is sliced per student, so groups of students can run side by side on different streams.  With
 // with_head the group's z rows are written; logits (the group's own sum, in student order) only if non-null.
@@ -482,13 +487,20 @@ static int run_students(const sp_model* M0, const WsLayout& W, const int32_t* id
     else SP_TRY(launch_embed_ln(M, ids, cu, B, T, rows, mrows, k, x, att, s, xq, kActQuantScale, attq));
     SP_MARK(SP_PHASE_EMBED);
     // Where the folded last layer follows, the rows stay as they are before the LayerNorm (see attention_first_fold_kernel) and only
-    // the first tokens' are normalised, into the first B rows of x: a read and a write of every row less, for a longer fold.  us a
-    // call, with the LayerNorm of all rows / this: hidden 768, 5.2 k tokens, eight students 876 / 858, quantised 666 / 633; 14.3 k
-    // tokens, eight 2152 / 2111, one 344 / 340; hidden 256, 4.3 k, three 122.4 / 122.7; hidden 1024, 19.5 k, six 3530 / 3474.
+    // the first tokens' are normalised, into the first B rows of x: a read and a write of every row less, for a longer fold and one more
+    // launch.  By tokens x students x hidden width (Mi), and not for sequences so short that the fold's tiles of 32 tokens are mostly
+    // empty.  us a call, with the LayerNorm of all rows / this.  768 wide: 5 236 / 240; 9 330 / 331; 11 383 / 381; 14 435 / 441; 18 569 / 566; 21
+    // 637 / 628; 22 629 / 620; 88 2290 / 2251, quantised 1588 / 1524; eight sequences of 512 tokens: 6 242 / 253, 12 414 / 421, 24 696 / 690.
+    // 1024 wide: 7 305 / 308, 12 463 / 465, 21 743 / 739, 29 978 / 966.  512 wide: 15 361 / 363, 16 396 / 402, 18 463 / 457.  256 wide: 3.6 120 /
+    // 120, 8.5 176 / 178 and 221 / 220, 11 248 / 246, 18 388 / 382.  Sequences of 4 tokens: 24 1021 / 1031 (768 wide), 1212 / 1263 (1024); of 16: 24 742 / 731, 875 / 872.
+    // (In calls of kLargeTokens and more by the model's students, not by those that are active: the two round differently.  One of three
+    // or of eight pays for that: 256 wide, 11 128 / 129 and, of long sequences, 138 / 141; 768 wide, 88 365 / 367.)
+    const int64_t fold_work = (int64_t)T * (T >= kLargeTokens ? c.K : k_rule) * H;
+    const bool raw_pays = fold_work > (int64_t)(H == 256 ? 10 : 16) << 20 && T >= (int64_t)16 * B;
     bool raw = false;
     for (int l = 0; l < stop_layers; ++l) {
         const size_t lo = L.layer0 + (size_t)l * L.layer_stride, pl = lo - L.layer_stride;
-        const bool fold_next = first_only && l == c.layers - 2;
+        const bool fold_next = first_only && raw_pays && l == c.layers - 2;
         if (first_only && l == c.layers - 1) {
             const bool own = T >= kFirstOnlyMinTokens;
             const size_t sT = (size_t)rows * H, sC = (size_t)crows * H;
@@ -596,10 +608,6 @@ static int run_students(const sp_model* M0, const WsLayout& W, const int32_t* id
 // better).  The logits are summed over all students in ascending order after the join, so the result does not depend on the
 // grouping.
 //
-// Calls of at least this many tokens choose their kernels by the model's students, not by how many are active, and split no
-// reduction, so that a student's term has the same bits whatever k.  (Smaller calls go by the active ones: a call pruned to one student
-// would otherwise run on kernels for eight.)
-constexpr int kLargeTokens = 8192;
 
 // Two groups only in calls of kLargeTokens and more: smaller ones share nothing with other streams' calls on the same model.  By work, in
 // Mi = 2^20 tokens x active students x hidden width; one stream / two, us a call, both on one card in turn:

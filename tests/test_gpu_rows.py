@@ -317,14 +317,15 @@ def test_calls_beside_a_capture_of_the_same_model(hidden, K, nseq, dtype):
     one.close()
 
 
-# 8192 tokens or more: no split reductions, so the folded last layer takes the rows before their LayerNorm
+# 8192 tokens or more and enough work over the model's students: the folded last layer takes the rows before their LayerNorm
 @pytest.mark.parametrize("hidden,dtype", [(256, "bf16"), (512, "bf16"), (768, "bf16"), (1024, "bf16"), (768, "fp8")])
 @pytest.mark.parametrize("offset", [0.0, 6.0])
 def test_folded_last_layer_on_rows_before_their_layernorm(oracle64, hidden, dtype, offset):
     """Against the oracle and the last layer on every token; a bias common to all features of the rows (their mean several times
     their deviation) must cancel but for the rounding of the rows themselves, which grows by that factor on either way."""
     from paper_2408_12526_amd import sp
-    shape = synth.StudentShape(K=2, layers=2, hidden=hidden, heads=hidden // 64, ffn=256, vocab=60, max_pos=256, classes=3, dtype=dtype)
+    shape = synth.StudentShape(K=5 if hidden == 256 else 4, layers=2, hidden=hidden, heads=hidden // 64, ffn=256, vocab=60, max_pos=256, classes=3,
+                               dtype=dtype)
     rng = np.random.default_rng(hidden)
     lengths = np.array((1, 2, 31, 32, 33, 64, 65, 256) + (60,) * 140, np.int32)
     T = int(lengths.sum())
@@ -361,7 +362,7 @@ def test_folded_attention_on_rows_before_their_layernorm_against_the_definition(
     """Its attention output against keys and values formed in fp64 from the rows before their LayerNorm (what the FFN's stages left,
     rounded to bf16 as the fold reads them), and softmax attention of the HIP path's own queries over them."""
     from paper_2408_12526_amd import sp
-    shape = synth.StudentShape(K=1, layers=2, hidden=hidden, heads=hidden // 64, ffn=256, vocab=300, max_pos=256, classes=2, dtype="bf16")
+    shape = synth.StudentShape(K=5, layers=2, hidden=hidden, heads=hidden // 64, ffn=256, vocab=300, max_pos=256, classes=2, dtype="bf16")
     rng = np.random.default_rng(hidden)
     lengths = np.array((1,) * 200 + (2, 31, 32, 33, 64, 65, 256, 129) + (60,) * 130, np.int32)
     T, B = int(lengths.sum()), len(lengths)
@@ -374,10 +375,11 @@ def test_folded_attention_on_rows_before_their_layernorm_against_the_definition(
     args = torch.from_numpy(ids).cuda(), torch.from_numpy(cu).cuda(), 256, 1
     st = sp.Students(sp.config_from_shape(shape), blob)
     st.sp_forward(*args)
-    q, got = (st.read_activation(st.workspace(T, B), n, T, B, 1)[0] for n in ("first_q", "first_att"))
+    q, got, x_first = (st.read_activation(st.workspace(T, B), n, T, B, 1)[0][:B] for n in ("first_q", "first_att", "x"))
     ws = st.sp_forward_partial(*args, 1)
-    x1, g = (st.read_activation(ws, n, T, B, 1)[0] for n in ("x1", "g"))
+    x1, g, x_all = (st.read_activation(ws, n, T, B, 1)[0] for n in ("x1", "g", "x"))
     st.close()
+    assert np.array_equal(x_first, x_all[cu[:-1]])           # (what such a call leaves in x)
     w = {n: (torch.from_numpy(a).bfloat16() if a.ndim == 2 else torch.from_numpy(a)).double().numpy() for n, a in v.items()}
     u64 = torch.from_numpy(x1 + g @ w["l0.W2"] + w["l0.b2"])
     u = u64.bfloat16().double().numpy()
