@@ -692,7 +692,7 @@ def main():
                    "total_tokens": T4, "batch": B4, "k_active": main_k,
                    "variant": "last layer on first-token rows only (exact work saving); "
                               + ("every call on one stream" if args.single_stream else
-                                 "active students run as two groups on two streams inside the call")
+                                 "active students in one group, or, where that is faster (k_active 4 and 2), in two on two streams inside the call")
                               + "; phases_k8 and roofline: one single-stream forward with an event after every launch "
                                 "(all active students in each launch), projection and attention phases = the all-token "
                                 "layer's launches alone"},

@@ -478,7 +478,8 @@ __device__ inline float sum_across_rows(float v)
 // 228.6 / 230.9.)
 template <int HEADS, bool RAW>
 struct FoldLds {
-    // (four heads: a wave's 32 features would be mostly the exchange between the waves)
+    // (Four heads: a wave's 32 features would be mostly the exchange between the waves.  Eight heads, 64 features: four waves and eight measured
+    // the same, 1061 / 1056 us for eight students on 256 sequences, 574 / 571 for four, 2155 / 2169 on 1024.)
     static constexpr int NW = HEADS == 4 ? 4 : 8;               // waves
     static constexpr int H = HEADS * kD, FW = H / NW;           // features per wave
     static constexpr int SCP = 36;                          // pitch of a head's 32 scores (floats)
@@ -866,7 +867,9 @@ hipError_t launch_attention(const sp_model* M, const void* qkv, const void* vt, 
         if (only || mixed) hipLaunchKernelGGL(attention_bf16_kernel<true>, grid, dim3(256), 0, s, a);
         else hipLaunchKernelGGL(attention_bf16_kernel<false>, grid, dim3(256), 0, s, a);
     } else {
-        // (sixteen lanes per query: four times the workgroups; up to about two of them per compute unit)
+        // Sixteen lanes per query: four times the workgroups; up to about two of them per compute unit.  us a call, four lanes / sixteen, two
+        // students, by workgroups of the latter: hidden 128: 16 44.5 / 38.5, 128 113 / 107, 256 (sequences of 128-256) 211 / 173, 512 182 / 179 and,
+        // of long sequences, 276 / 255, 960 344 / 356; hidden 768: 96 310 / 304, 384 776 / 773, 768 1252 / 1251, 1536 1661 / 1664 and 1799 / 1847.
         const int nq16 = (max_seqlen + 15) / 16, nq4 = (max_seqlen + 63) / 64;
         if ((long)B * c.heads * nq16 * k <= 512)
             hipLaunchKernelGGL(attention_f32_kernel<16>, dim3((unsigned)(B * c.heads * nq16), k), dim3(256), 0, s, (const float*)qkv,

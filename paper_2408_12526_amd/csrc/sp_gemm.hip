@@ -343,6 +343,9 @@ hipError_t launch_bf16(const sp_model* M, const GemmArgs& a, int N, int k, hipSt
     // tokens x 4 students, hidden 896: q|k|v 322 / 289, attention output 144 / 127, FFN down 507 / 471; calls of few tiles are
     // chains of k-tiles that a lower tile shortens: 1851 tokens, hidden 384: attention output 7.5 / 5.9, FFN down from 640 10 / 8.
     if (N % 256 || a.n_split % 256) {
+        // (Two k-tiles in flight while there is a workgroup per compute unit at most, as below, were measured here as well: no rule for all
+        // widths.  us a call, one in flight / two: one student, twelve sequences: hidden 128 70 / 73, 384 100 / 95, 640 124 / 117, 896 153 / 145;
+        // four students 79 / 81, 128 / 130, 177 / 177, 259 / 259; 64 tokens at hidden 128 47 / 50.)
         const long wide = (long)(N / 128) * k * a.splits;
         switch (tile_height(a.mrows, wide, 512, (a.mrows + 95) / 96 * wide >= 1024 ? 3 : 2)) {
             case 1: return launch_wreg_tile<1, 2, 1, EPI>(M, a, N, k, s);

@@ -167,9 +167,10 @@ constexpr int kRowsMaxTokens = 256;   // largest call whose all-token layers run
 // 35.4 us for a layer's embedding, q|k|v and FFN up against 38, 352 rows 40 against 38; hidden 256: 528 rows 17.5 against 26).
 constexpr long kRowsLnMaxElems = 262144;
 // First-token rows (elements as above) beyond which all their projections take the tile kernel, whose bare sums the LayerNorm
-// launches finish.  Measured, us for the two residual projections, the FFN up-projection, pooler and classifier, few-row kernels
-// against this: hidden 768: 2048 rows 108 / 113, 4096 rows 183 / 141, 8192 rows 349 / 221; hidden 1024, 1536 rows: 124 / 126;
-// hidden 256: 3072 rows 51 / 60, 12288 rows 115 / 110.
+// launches finish: where no width loses by it.  us a call, few-row kernels / this, by 2^20 elements: hidden 256, three students: 1.0 511 /
+// 515, 2.0 955 / 958, 2.9 1419 / 1418, 5.9 2728 / 2719; the wider ones break even earlier: 512, four: 1.0 547 / 533, 2.4 1223 / 1202; 768, two: 0.4
+// 447 / 455, 0.75 801 / 798, 1.5 1455 / 1435, 2.2 2106 / 2056; eight: 0.75 504 / 508, 1.5 898 / 889, 3.0 3329 / 3249; 1024, two: 0.8 925 / 915, 1.6
+// 1817 / 1793.
 constexpr long kRowsTilesElems = 1L << 21;
 constexpr int kRowsU = 1024;          // fp32 rows per student of the few-row projections' scratch
 constexpr int kFirstOnlyMinTokens = 1024;   // smallest call whose first-token rows have buffers of their own
