@@ -429,20 +429,19 @@ struct FoldQArgs {
     size_t q_ss;
     bf16* qt;                         // [student][qt_ss], row stride heads * H
     size_t qt_ss;
-    size_t g;                         // scaled: what feature f of a folded query is multiplied with (fp32, byte offset into a student slab)
-    bool scaled;
+    size_t g;                         // SCALED: what feature f of a folded query is multiplied with (fp32, byte offset into a student slab)
     int Tn, M, H, heads, heads8, nrb, rpw;                  // nrb: groups of rpw blocks of 16 sequences
 };
 
 constexpr int kFoldQPitch = 64 * 2 + 16;                    // bytes per staged query row
 constexpr int fold_x_pitch(int ns) { return ns * 64 + 16; } // bytes per staged token row
 constexpr int fold_o_pitch(int ns) { return ns * 16 + 16; } // bytes per row of a wave's staged output
-constexpr size_t fold_query_smem(int ns)
+constexpr size_t fold_query_smem(int ns, bool scaled)
 {
-    return 2 * 16 * (size_t)(fold_x_pitch(ns) + kFoldQPitch) + 4 * 16 * (size_t)fold_o_pitch(ns) + 32 * (size_t)ns * 4;
+    return 2 * 16 * (size_t)(fold_x_pitch(ns) + kFoldQPitch) + 4 * 16 * (size_t)fold_o_pitch(ns) + (scaled ? 32 * (size_t)ns * 4 : 0);
 }
 
-template <int NS>
+template <int NS, bool SCALED>
 __global__ __launch_bounds__(256) void fold_query_kernel(FoldQArgs p)
 {
     constexpr int H = 32 * NS, XP = fold_x_pitch(NS), QP = kFoldQPitch;
@@ -504,11 +503,11 @@ __global__ __launch_bounds__(256) void fold_query_kernel(FoldQArgs p)
     for (int j = 0; j < NS / 2; ++j)
 #pragma unroll
         for (int s = 0; s < 2; ++s) fk[j][s] = *(const bf16x8*)(kp + (size_t)(j >> 1) * 32 * H + 32 * (j & 1) + 512 * s);
-    f32x4 gv = {1.f, 1.f, 1.f, 1.f};
-    if (p.scaled && 4 * threadIdx.x < H) gv = *(const f32x4*)((const float*)(sb + p.g) + 4 * threadIdx.x);
+    f32x4 gv = {};
+    if (SCALED && 4 * threadIdx.x < H) gv = *(const f32x4*)((const float*)(sb + p.g) + 4 * threadIdx.x);
     __builtin_amdgcn_sched_barrier(0);
     write_x(S0);
-    if (4 * threadIdx.x < H) *(f32x4*)(gbuf + 4 * threadIdx.x) = gv;
+    if (SCALED && 4 * threadIdx.x < H) *(f32x4*)(gbuf + 4 * threadIdx.x) = gv;
     if (rb + 16 < re) load_x(rb + 16, S1);
     if (rb + 32 < re) load_x(rb + 32, S0);
     barrier_lds();
@@ -543,7 +542,7 @@ __global__ __launch_bounds__(256) void fold_query_kernel(FoldQArgs p)
             f32x4 a = {0.f, 0.f, 0.f, 0.f}, b = a;
 #pragma unroll
             for (int s = 0; s < 2; ++s) { a = mfma16(fk[j][s], fq[s], a); b = mfma16(fk[j + 1][s], fq[s], b); }
-            if (p.scaled) {
+            if (SCALED) {
                 a *= *(const f32x4*)(gbuf + f0 + 16 * j + 8 * kg);
                 b *= *(const f32x4*)(gbuf + f0 + 16 * j + 8 * kg + 4);
             }
@@ -829,11 +828,11 @@ hipError_t launch_rows_k(RowsKArgs a, int k, hipStream_t s)
     return launch_rows_k_tile<F32OUT, 4, 2>(a, grid, s);
 }
 
-template <int NS>
+template <int NS, bool SCALED>
 hipError_t launch_fold(const FoldQArgs& a, int k, hipStream_t s)
 {
-    constexpr size_t smem = fold_query_smem(NS);
-    auto kern = fold_query_kernel<NS>;
+    constexpr size_t smem = fold_query_smem(NS, SCALED);
+    auto kern = fold_query_kernel<NS, SCALED>;
     if (smem > 48 * 1024) {
         static std::atomic<bool> raised{false};             // per instantiation; the attribute is sticky for the process
         if (!raised.load(std::memory_order_acquire)) {
@@ -933,7 +932,7 @@ hipError_t launch_fold_query(const sp_model* M, size_t lo, const void* x, int ro
     const sp_config& c = M->cfg;
     if (!bf16_path(c) || c.heads * 64 != c.hidden || B < 1) return hipErrorInvalidValue;
     FoldQArgs a{};
-    a.scaled = scaled; a.g = g_off;
+    a.g = g_off;
     a.arena = M->arena; a.ss = M->L.student_stride; a.wq = lo + M->L.wqkv; a.bq = lo + M->L.bqkv; a.wk = lo + M->L.wk_io;
     a.x = (const bf16*)x; a.x_ss = (size_t)rows * c.hidden; a.cu = cu;
     a.q = (bf16*)q; a.q_ss = q_ss; a.qt = (bf16*)qt; a.qt_ss = qt_ss;
@@ -943,10 +942,10 @@ hipError_t launch_fold_query(const sp_model* M, size_t lo, const void* x, int ro
     a.rpw = (blocks + groups - 1) / groups;
     a.nrb = (blocks + a.rpw - 1) / a.rpw;
     switch (a.H) {                                          // (the folded attention's widths)
-        case 256: return launch_fold<8>(a, k, s);
-        case 512: return launch_fold<16>(a, k, s);
-        case 768: return launch_fold<24>(a, k, s);
-        case 1024: return launch_fold<32>(a, k, s);
+        case 256: return scaled ? launch_fold<8, true>(a, k, s) : launch_fold<8, false>(a, k, s);
+        case 512: return scaled ? launch_fold<16, true>(a, k, s) : launch_fold<16, false>(a, k, s);
+        case 768: return scaled ? launch_fold<24, true>(a, k, s) : launch_fold<24, false>(a, k, s);
+        case 1024: return scaled ? launch_fold<32, true>(a, k, s) : launch_fold<32, false>(a, k, s);
         default: return hipErrorInvalidValue;
     }
 }
