@@ -418,6 +418,8 @@ __global__ __launch_bounds__(256) void rows_ksplit_kernel(RowsKArgs p)
 // sequences 41 / 29; four, 1024 sequences 118 / 71; two, 4096 sequences 259 / 148.
 // A-operand row i of block j of a pair of blocks stands for feature 8 (i / 4) + 4 (j % 2) + i % 4 of the pair's 32, so
 // that a lane ends with eight neighbouring features and writes 16 bytes.
+// SCALED: the results times a LayerNorm's scale, feature by feature from LDS, before they are rounded (the attention behind it then
+// rounds nothing again): 26.3 -> 28.6 us for eight students of 768 on 256 sequences.
 // -------------------------------------------------------------------------------------
 struct FoldQArgs {
     const char* arena;

@@ -129,7 +129,10 @@ def test_one_class_is_the_first_of_two(hidden, lengths, dtype):
                          [(512, 640, 3, 2, 2, False, (100, 37, 150, 62)), (768, 640, 2, 2, 2, True, (200, 90, 5)),
                           (1024, 128, 3, 1, 1, False, (64, 64, 64, 65, 64)), (256, 1024, 3, 4, 1, True, (90, 200, 13)),
                           (768, 3072, 3, 2, 1, True, (301, 12, 90)), (768, 384, 2, 5, 5, False, (100, 53)),
-                          (384, 1536, 3, 2, 1, False, (301, 12, 90)), (640, 2560, 3, 1, 1, True, (77, 200, 13))])
+                          (384, 1536, 3, 2, 1, False, (301, 12, 90)), (640, 2560, 3, 1, 1, True, (77, 200, 13)),
+                          # (short sequences alone, in a call of few tokens, and beside a longer one)
+                          (768, 384, 2, 2, 2, False, (9,) * 33 + (5,)), (256, 512, 2, 3, 3, True, (31, 30, 3)),
+                          (512, 640, 2, 4, 4, True, (5,) * 80 + (45,))])
 def test_nothing_in_the_workspace_has_to_be_finite(oracle64, hidden, ffn, layers, K, k, all_tokens, lengths):
     """Padding rows reach attention with probability zero, which is no help against what is not a number: a workspace full of
     NaN gives what the oracle gives, for the last sequence too (token counts that are no multiple of eight)."""
