@@ -22,26 +22,29 @@ __device__ inline float gelu_erf(float u) { return 0.5f * u * (1.0f + erff(u * 0
 //   * weights: a feature's weights are used by one wave only, so they go from memory straight to its registers, in operand
 //     blocks (see ArenaLayout: a load is 256-byte runs).  A step's registers are requested again, for the next k-tile of 64
 //     reduction elements (D = 2: the one after), as soon as its matrix instructions are issued: four steps (1024 matrix-core
-//     cycles at 128 tokens) to arrive, twice that while the other workgroup has the matrix cores.
-//   * activations: through registers into one of two LDS stages (rows of eight 16-byte slots; slot s of row r holds chunk
-//     s ^ ((r >> 1) & 7): no bank conflicts), one barrier per k-tile that waits for LDS traffic only, requested two k-tiles
-//     ahead.  Ordinary loads throughout: with direct-to-LDS loads in flight the compiler waits for everything before the
-//     first use of any load, so the two kinds cannot be mixed.
+//     cycles at 128 tokens) to arrive, twice that while the other workgroup has the matrix cores.  Buffer loads as well: one register of
+//     address.
+//   * activations: by direct-to-LDS loads into one of D + 2 stages (rows of eight 16-byte slots; slot s of row r holds chunk
+//     s ^ ((r >> 1) & 7): no bank conflicts), requested D + 1 k-tiles ahead, one barrier per k-tile, in front of which a wave waits for
+//     its own share of the next one.  In their buffer form (load_lds16) they can be mixed with loads to registers.  A k-tile's are
+//     requested together: spread over its steps, the workgroups that share a row fetch it from beyond the L2 more often (FFN down of
+//     eight students of 768, 14653 tokens: 1070 MB and 510 us, together 482).  Through registers they held sixteen more and cost
+//     the LDS writes: us at hidden 1024, 18387 tokens, six students, before / this: q|k|v 634 / 611, attention output 240 / 236, FFN up 835 / 810,
+//     FFN down 770 / 744; eight of 768 on 14653 tokens 391 / 380, 161 / 158, 546 / 532, 481 / 482.  (Two k-tiles of weights in flight at 128
+//     tokens, requested step by step or together: no gain; another 32 registers.  256 x 256 tiles of eight waves whose halves share the weights through
+//     the L1: 652 / 266 / 958 / 780 on the first; 128 x 512: 624 / 249 / 903 / 736, and worse for fewer tokens.)
 //   * per matrix-core cycle at the full rate and 128 tokens a compute unit needs 48 bytes from the L2 (52-60 is what the load
 //     path delivers) and 80 from and to the LDS (of 128).  With both operands through LDS a 128 x 128 tile needs 192: that kernel
 //     stopped at half of this one's rate.
-//   * two workgroups per compute unit: one's first loads, epilogue arithmetic and stores run while the other multiplies.  (One
+//   * two workgroups per compute unit (three of 96 tokens): one's first loads, epilogue arithmetic and stores run while the other multiplies.  (One
 //     workgroup with a 256 x 256 tile and a five-slot LDS ring moves a third less through the load path but leaves the
 //     matrix cores idle for 44 % of a tile at depth 768.)
 //   * epilogue through LDS: each wave stages its tile in its own slice and stores whole 16-byte-per-lane row segments; the
 //     residual rows arrive there by direct-to-LDS loads.
-// Measured, us per launch, the 256 x 256 / 128 x 128 / 64 x 64 kernels before and this one: 7936 tokens x 4 students, hidden 768:
-// q|k|v 127 -> 117, attention output 59 -> 55, FFN up 188 -> 166, FFN down 159 -> 146; 1824 tokens x 4: 57 -> 36, 24 -> 18, 76 -> 46,
-// 67 -> 44; 18432 tokens, hidden 1024, one student: 124 -> 113, 62 -> 52, 185 -> 152, 193 -> 155.  Large launches are bound by the package
-// power limit (2.06 GHz of 2.4 here) and what the operands' way to the registers costs of it.
+// What bounds large launches: the package power limit (1.9 GHz of 2.4), of which the operands' way to the compute units takes more than
+// a third (the same loop without its loads runs at 1.8 PFLOP/s), and the wait for them (matrix cores 55-60 % busy; on operands that are all
+// zero a launch takes 8-20 % less).
 // -------------------------------------------------------------------------------------
-typedef unsigned u32x4 __attribute__((ext_vector_type(4)));
-
 struct GemmArgs {
     const bf16* A;
     size_t a_ss;
@@ -59,13 +62,12 @@ struct GemmArgs {
 };
 
 template <int TM, int NW, int D, int EPI>
-__global__ __launch_bounds__(64 * NW, D > 1 ? 1 : 2) void gemm_wreg_kernel(GemmArgs p)
+__global__ __launch_bounds__(64 * NW, 2) void gemm_wreg_kernel(GemmArgs p)
 {
-    static_assert(D == 1 || D == 2, "the k-tiles are an even number");
-    constexpr int BM = 32 * TM, BN = 64 * NW, NA = TM * 4 / NW;   // NA: 16-byte pieces of an activation k-tile per thread
+    constexpr int BM = 32 * TM, BN = 64 * NW, NA = TM * 4 / NW;   // NA: wave-loads (eight rows) of an activation k-tile per wave
     constexpr int STAGE = BM * 8;                           // 16-byte units
     constexpr int TKEY = TM == 3 ? 3 : TM * 4 - 1;          // swizzle of the transposed staging: bits of the chunk
-    static_assert(NA >= 1, "every thread moves activations");
+    static_assert(NA >= 1, "every wave moves activations");
     extern __shared__ uint4 smem[];
     const int chunk = (p.total + 7) >> 3;
     const int lin = (int)(blockIdx.x & 7) * chunk + (int)(blockIdx.x >> 3);
@@ -81,128 +83,129 @@ __global__ __launch_bounds__(64 * NW, D > 1 ? 1 : 2) void gemm_wreg_kernel(GemmA
     const char* sb = p.arena + (size_t)m * p.ss;
     const int Kd = p.Kd, nk = (EPI == EPI_PARTIAL ? p.Kper : Kd) >> 6;
 
-    // activations: thread -> (row tid / 8 + 8 NW i, chunk tid % 8) of a k-tile; rows beyond mrows repeat the last one
-    // (64-bit base of the tile, 32-bit offsets inside it: a buffer may hold more than 2^32 elements)
+    // activations: wave-load i of a k-tile is rows 8 (wave + NW i) .. + 7, lane -> (row lane / 8, slot lane % 8), which holds chunk
+    // slot ^ ((row >> 1) & 7); rows beyond mrows repeat the last one (64-bit base of the tile, 32-bit offsets inside it: a buffer may hold
+    // more than 2^32 elements)
     const bf16* Ag = p.A + (size_t)m * p.a_ss + (size_t)m0 * p.lda + (EPI == EPI_PARTIAL ? sp * p.Kper : 0);
-    unsigned aoff[NA], adst[NA];
+    int aoff[NA];
 #pragma unroll
     for (int i = 0; i < NA; ++i) {
-        const int r = (tid >> 3) + 8 * NW * i;
+        const int r = 8 * (wave + NW * i) + (lane >> 3);
         const int rr = m0 + r < p.mrows ? r : p.mrows - 1 - m0;
-        aoff[i] = (unsigned)rr * (unsigned)p.lda + (tid & 7) * 8;
-        adst[i] = r * 8 + ((tid & 7) ^ ((r >> 1) & 7));
+        aoff[i] = 2 * (rr * p.lda + ((lane & 7) ^ ((r >> 1) & 7)) * 8);
     }
     // weights: lane -> row j31 of a 32-feature block, chunk g of a 16-element step
     const bf16* Wg = (const bf16*)(sb + p.w_off) + (size_t)(nf >> 4) * 16 * Kd + (EPI == EPI_PARTIAL ? (size_t)sp * p.Kper * 16 : 0);
-    const unsigned wlane = (unsigned)((j31 >> 4) * 16 * Kd + g * 128 + (j31 & 15) * 8);
+    const int wlane = 2 * ((j31 >> 4) * 16 * Kd + g * 128 + (j31 & 15) * 8);
 
     bf16x8 w[D][4][2];
-    u32x4 ar[D][NA];
-    auto load_a = [&](int kt, int slot) {
+    auto dma_a = [&](int kt, int stage) {
 #pragma unroll
-        for (int i = 0; i < NA; ++i) ar[slot][i] = *(const u32x4*)(Ag + kt * 64 + aoff[i]);
+        for (int i = 0; i < NA; ++i) load_lds16(Ag, (lds_void*)(smem + stage * STAGE + (wave + NW * i) * 64), aoff[i], kt * 128);
     };
     auto load_w = [&](int kt, int slot, int s) {
 #pragma unroll
-        for (int i = 0; i < 2; ++i) w[slot][s][i] = *(const bf16x8*)(Wg + (size_t)i * 32 * Kd + kt * 1024 + s * 256 + wlane);
+        for (int i = 0; i < 2; ++i) w[slot][s][i] = __builtin_bit_cast(bf16x8, load16(Wg, wlane + s * 512, kt * 2048 + i * 64 * Kd));
     };
-    auto write_a = [&](int buf, int slot) {
-#pragma unroll
-        for (int i = 0; i < NA; ++i) *(u32x4*)(smem + buf * STAGE + adst[i]) = ar[slot][i];
-    };
-    int xoff[TM];
-#pragma unroll
-    for (int t = 0; t < TM; ++t) xoff[t] = (t * 32 + j31) * 8;
-    const int xkey = (j31 >> 1) & 7;
+    const int xlane = j31 * 8 + (g ^ ((j31 >> 1) & 7));     // slot of step 0; that of step s is at xlane ^ 2 s
     bf16x8 fx[2][TM];
-    auto frag = [&](int buf, int s, int t) { return *(const bf16x8*)(smem + buf * STAGE + xoff[t] + ((2 * s + g) ^ xkey)); };
+    auto frag = [&](int stage, int s, int t) { return *(const bf16x8*)(smem + ((stage * STAGE + xlane) ^ (2 * s)) + t * 256); };
 
     f32x16 acc[2][TM];
-    load_a(0, 0);
+    dma_a(0, 0);
+    f32x4 b4[2][4];
     {
         const float* bias = (const float*)(sb + p.b_off) + nf + 4 * g;
 #pragma unroll
         for (int i = 0; i < 2; ++i)
 #pragma unroll
-            for (int v4 = 0; v4 < 4; ++v4) {
-                const f32x4 b = EPI == EPI_PARTIAL ? f32x4{0.f, 0.f, 0.f, 0.f} : *(const f32x4*)(bias + 32 * i + 8 * v4);
-#pragma unroll
-                for (int t = 0; t < TM; ++t)
-#pragma unroll
-                    for (int e = 0; e < 4; ++e) acc[i][t][4 * v4 + e] = b[e];
-            }
+            for (int v4 = 0; v4 < 4; ++v4) b4[i][v4] = EPI == EPI_PARTIAL ? f32x4{0.f, 0.f, 0.f, 0.f} : *(const f32x4*)(bias + 32 * i + 8 * v4);
     }
     __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
     for (int s = 0; s < 4; ++s) load_w(0, 0, s);
     __builtin_amdgcn_sched_barrier(0);
+    dma_a(1, 1);
+    __builtin_amdgcn_sched_barrier(0);
+    if constexpr (D > 1) {
 #pragma unroll
-    for (int d = 1; d < D; ++d) {
-        load_a(d, d);
-#pragma unroll
-        for (int s = 0; s < 4; ++s) load_w(d, d, s);
+        for (int s = 0; s < 4; ++s) load_w(1, 1, s);
         __builtin_amdgcn_sched_barrier(0);
     }
-    write_a(0, 0);
+#pragma unroll
+    for (int i = 0; i < 2; ++i)
+#pragma unroll
+        for (int t = 0; t < TM; ++t)
+#pragma unroll
+            for (int e = 0; e < 16; ++e) acc[i][t][e] = b4[i][e >> 2][e & 3];
     __builtin_amdgcn_sched_barrier(0);
-    load_a(D < nk ? D : nk - 1, 0);
+    wait_vmcnt<8 * D + NA>();                               // activations of k-tile 0
     barrier_lds();
+    if (D > 1 && nk > 2) dma_a(2, 2);
+    __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
     for (int t = 0; t < TM; ++t) fx[0][t] = frag(0, 0, t);
 
-    // One k-tile: j, slot = j % D.  W: k-tile j + D exists; AW, AL: so do j + 1 and j + 1 + D.
-    auto ktile = [&](int j, auto slot_c, auto w_c, auto aw_c, auto al_c) {
-        constexpr int slot = decltype(slot_c)::value, next = (slot + 1) % D;
-        constexpr bool W = decltype(w_c)::value, AW = decltype(aw_c)::value, AL = decltype(al_c)::value;
-        const int buf = D % 2 == 0 ? slot & 1 : j & 1;
+    // One k-tile, j, weights in slot j % D.  Requested during it: W: the weights of k-tile j + D, a step's when its registers are free; AL:
+    // the activations of k-tile j + 1 + D, all together.  NEXT: k-tile j + 1 exists; V: loads that may be in flight when its activations have
+    // to be there, those requested behind them.
+    int prev = D + 1, cur = 0, next = 1;                    // stages of k-tiles j - 1 (free: the one requested goes there), j and j + 1
+    auto ktile = [&](int j, auto slot_c, auto w_c, auto a_c, auto next_c, auto v_c) {
+        constexpr int slot = decltype(slot_c)::value % D;
+        constexpr bool W = decltype(w_c)::value, AL = decltype(a_c)::value, NEXT = decltype(next_c)::value;
 #pragma unroll
         for (int s = 0; s < 4; ++s) {
-            if (s == 3) barrier_lds();
+            if (s == 3 && NEXT) {
+                wait_vmcnt<decltype(v_c)::value>();
+                barrier_lds();
+            }
             __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
             for (int t = 0; t < TM; ++t) {
-                if (s < 3) fx[(s + 1) & 1][t] = frag(buf, s + 1, t);
-                else if (AW) fx[0][t] = frag(buf ^ 1, 0, t);
+                if (s < 3) fx[(s + 1) & 1][t] = frag(cur, s + 1, t);
+                else if (NEXT) fx[0][t] = frag(next, 0, t);
 #pragma unroll
                 for (int i = 0; i < 2; ++i) acc[i][t] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(w[slot][s][i], fx[s & 1][t], acc[i][t], 0, 0, 0);
                 __builtin_amdgcn_sched_barrier(0);
             }
+            if (AL && s == 1) dma_a(j + 1 + D, prev);
             if (W) load_w(j + D, slot, s);
-            if (s == 1 && AW) {
-                write_a(buf ^ 1, next);
-                if (AL) load_a(j + 1 + D, next);
-            }
             __builtin_amdgcn_sched_barrier(0);
         }
-    };
-    // D k-tiles from j on (nk is a multiple of D)
-    auto ktiles = [&](int j, auto w_c, auto al_c) {
-        constexpr bool W = decltype(w_c)::value, AL = decltype(al_c)::value;
-        auto one = [&](auto slot_c) {
-            constexpr int slot = decltype(slot_c)::value;
-            constexpr bool last = slot == D - 1;
-            ktile(j + slot, slot_c, w_c, std::bool_constant<W || !last>{}, std::bool_constant<W && (AL || !last)>{});
-        };
-        one(std::integral_constant<int, 0>{});
-        if constexpr (D > 1) one(std::integral_constant<int, 1>{});
+        prev = cur;
+        cur = next;
+        next = next == D + 1 ? 0 : next + 1;
     };
     constexpr std::true_type Y{};
     constexpr std::false_type N{};
-    int j = 0;
+    constexpr std::integral_constant<int, 0> S0{};
+    constexpr std::integral_constant<int, 1> S1{};
+    int j = 0;                                              // (nk is even)
     if constexpr (D == 1) {
-        for (; j + 2 < nk; j += 2) {                        // (nk is even)
-            ktiles(j, Y, Y);
-            ktiles(j + 1, Y, Y);
+        constexpr std::integral_constant<int, 12 + NA> V{};     // W of the last three steps before, A and W of three steps since
+        if (nk > 2) {
+            ktile(0, S0, Y, Y, Y, std::integral_constant<int, 6 + NA>{});
+            ktile(1, S0, Y, Y, Y, V);
+            for (j = 2; j + 2 < nk; j += 2) {
+                ktile(j, S0, Y, Y, Y, V);
+                ktile(j + 1, S0, Y, Y, Y, V);
+            }
         }
-        ktiles(j, Y, N);
-        ktiles(j + 1, N, N);
+        ktile(j, S0, Y, N, Y, std::integral_constant<int, 6>{});
+        ktile(j + 1, S0, N, N, N, S0);
     } else {
-        for (; j + 2 * D < nk; j += D) ktiles(j, Y, Y);
-        if (j + D < nk) {
-            ktiles(j, Y, N);
-            j += D;
+        constexpr std::integral_constant<int, 14 + 2 * NA> V{};
+        for (; j + 4 < nk; j += 2) {
+            ktile(j, S0, Y, Y, Y, V);
+            ktile(j + 1, S1, Y, Y, Y, V);
         }
-        ktiles(j, N, N);
+        if (nk > 2) {
+            ktile(j, S0, Y, Y, Y, V);
+            ktile(j + 1, S1, Y, N, Y, std::integral_constant<int, 14 + NA>{});
+            j += 2;
+        }
+        ktile(j, S0, N, N, Y, std::integral_constant<int, 8>{});
+        ktile(j + 1, S1, N, N, N, S0);
     }
 
     // ---- epilogue: accumulator element v of lane l in block (i, t): token 32 t + l % 32, feature 32 i + 8 (v / 4) +
@@ -293,7 +296,7 @@ __global__ __launch_bounds__(64 * NW, D > 1 ? 1 : 2) void gemm_wreg_kernel(GemmA
 template <int TM, int NW, int D, int EPI>
 hipError_t launch_wreg_tile(const sp_model* M, GemmArgs a, int N, int k, hipStream_t s)
 {
-    constexpr size_t smem = (size_t)32 * TM * 128 * (NW < 2 ? 2 : NW);
+    constexpr size_t smem = (size_t)32 * TM * 128 * (D + 2 > NW ? D + 2 : NW);
     auto kern = gemm_wreg_kernel<TM, NW, D, EPI>;
     if (smem > 48 * 1024) {
         static std::atomic<bool> raised{false};

@@ -126,6 +126,28 @@ __device__ inline float wave_max(float v)
 typedef __attribute__((address_space(3))) void lds_void;
 typedef __attribute__((address_space(1))) const void gbl_void;
 
+// Sixteen bytes per lane straight into LDS: from base + soff (uniform) + voff to dst (uniform) + 16 lane.  The buffer form of the
+// instruction, not the global one: the compiler counts it among the loads in flight, where behind a global one it
+// waits for all of them (vmcnt(0)) before it uses the result of any.
+__device__ __forceinline__ void load_lds16(const void* base, lds_void* dst, int voff, int soff)
+{
+#if defined(__HIP_DEVICE_COMPILE__)                         // (the host pass does not know the resource type)
+    const __amdgpu_buffer_rsrc_t r = __builtin_amdgcn_make_buffer_rsrc(const_cast<void*>(base), 0, -1, 0x00020000);   // (raw, no bound)
+    __builtin_amdgcn_raw_ptr_buffer_load_lds(r, dst, 16, voff, soff, 0, 0);
+#endif
+}
+
+// Sixteen bytes per lane from base + soff (uniform) + voff to registers: one register of address per lane.
+typedef unsigned u32x4 __attribute__((ext_vector_type(4)));
+__device__ __forceinline__ u32x4 load16(const void* base, int voff, int soff)
+{
+#if defined(__HIP_DEVICE_COMPILE__)
+    return __builtin_amdgcn_raw_buffer_load_b128(__builtin_amdgcn_make_buffer_rsrc(const_cast<void*>(base), 0, -1, 0x00020000), voff, soff, 0);
+#else
+    return u32x4{};
+#endif
+}
+
 template <int N>
 __device__ inline void wait_vmcnt() { asm volatile("s_waitcnt vmcnt(%0)" ::"n"(N) : "memory"); }
 
