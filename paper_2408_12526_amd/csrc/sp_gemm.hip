@@ -59,6 +59,7 @@ struct GemmArgs {
     RowsLayout ol;
     int lda, ldr, ld2, n_split, Kd, Kper, splits, mrows, mtiles, ntiles, total, mb;     // Kper: reduction elements per split
     size_t slice;                     // EPI_PARTIAL: elements between the slices of a split reduction
+    bool stream;                      // output not kept in the memory-side cache
 };
 
 template <int TM, int NW, int D, int EPI>
@@ -278,19 +279,34 @@ __global__ __launch_bounds__(64 * NW, 2) void gemm_wreg_kernel(GemmArgs p)
         constexpr int CPR = TM * 4, RPI = 64 / CPR;         // chunks per feature row, rows per instruction
         const int fr = lane / CPR, fc = lane % CPR;
         bf16* dst = p.out2 + (size_t)m * p.o2_ss + (size_t)(nf - p.n_split) * p.ld2 + m0 + fc * 8;
-        if (fr < RPI && m0 + fc * 8 < p.mrows)
+        auto store = [&](auto stream) {
+            if (fr < RPI && m0 + fc * 8 < p.mrows)
 #pragma unroll 4
-            for (int f = fr; f < 64; f += RPI)
-                *(uint4*)(dst + (size_t)f * p.ld2) = *(const uint4*)(stg + f * (BM * 2) + ((fc ^ (f >> 2 & TKEY)) << 4));
+                for (int f = fr; f < 64; f += RPI)
+                    store16_through<decltype(stream)::value>(dst + (size_t)f * p.ld2, *(const u32x4*)(stg + f * (BM * 2) + ((fc ^ (f >> 2 & TKEY)) << 4)));
+        };
+        if (p.stream) store(Y); else store(N);
         return;
     }
     bf16* dst = p.out + (size_t)m * p.o_ss + (size_t)(nf / 8 + cc) * p.ol.cs;
-#pragma unroll 4
-    for (int q = 0; q < BM / 8; ++q) {
-        const int r = q * 8 + rr, row = m0 + r;
-        if (row < p.mrows)
-            *(uint4*)(dst + (size_t)(row >> 4) * p.ol.rb + (size_t)(row & 15) * p.ol.rs) = *(const uint4*)(stg + r * 128 + ((cc ^ ((r >> 1) & 7)) << 4));
-    }
+    auto store = [&](auto stream) {
+#pragma unroll
+        for (int q0 = 0; q0 < BM / 8; q0 += 4) {
+            u32x4 v[4];
+#pragma unroll
+            for (int q = 0; q < 4; ++q) {
+                const int r = (q0 + q) * 8 + rr;
+                v[q] = *(const u32x4*)(stg + r * 128 + ((cc ^ ((r >> 1) & 7)) << 4));
+            }
+#pragma unroll
+            for (int q = 0; q < 4; ++q) {
+                const int row = m0 + (q0 + q) * 8 + rr;
+                if (row < p.mrows)
+                    store16_through<decltype(stream)::value>(dst + (size_t)(row >> 4) * p.ol.rb + (size_t)(row & 15) * p.ol.rs, v[q]);
+            }
+        }
+    };
+    if (p.stream) store(Y); else store(N);
 }
 
 template <int TM, int NW, int D, int EPI>
@@ -316,15 +332,19 @@ hipError_t launch_wreg_tile(const sp_model* M, GemmArgs a, int N, int k, hipStre
 
 // Tile height.  The chip has 256 compute units and two workgroups of one run side by side, sharing its matrix cores, so a
 // launch takes about as long as the compute unit with the most work: workgroups per unit (rounded up) x tokens per tile x
-// what a token costs at that height (a lower tile reads the weights more often: measured 1.1 at 96 tokens, 1.2 at 64, 1.7 at
-// 32, 1 at 128).  Measured against it, us at 128 / 96 / 64 / 32 tokens: 960 tokens x 4 students, 2304 features from 768:
-// 25.1 / 21.7 / 23.2 / 28.2; 18432 tokens, 1024 features from 4096: 175 / 155 / 185 / -; 640 tokens, 768 from 768: 15.3 / 13.0 / 11.2 / 8.8.
+// what a token costs at that height.  A lower tile reads the weights more often, which counts the more the deeper the reduction; at 256
+// the first loads and the epilogue take longer than the four k-tiles, and lower tiles, of which three fit a unit, hide them better.
+// Measured against it, us at 128 / 96 / 64 tokens: 14653 tokens x 2 students, 768 from 256: 27.5 / 26.8 / 23.1, 1024 from 256 36.6 / 31.6 / 32.5;
+// 2304 features from 768 98.7 / 96.4 / 109; 768 from 3072 131 / 141 / 171; 4608 tokens x 2, 3072 from 768: 55.1 / 50.3 / 52.5; x 8, 768 from 3072: 177 / 188 /
+// 219; 18432 tokens, 1024 from 4096: 147 / 132 / 163; 640 tokens, 768 from 768, at 64 and 32: 11.2 / 8.8.
 }  // namespace
 
-// wide: tiles side by side; round: how many the chip takes at once; tallest: the largest height there is
-static int tile_height(int mrows, long wide, long round, int tallest)
+constexpr double kHalfTokenCost[5] = {0, 1.7, 1.2, 1.1, 1.0};       // tiles of half the features
+constexpr double kTokenCost[3][5] = {{0, 1.7, 0.88, 0.95, 1.0}, {0, 1.7, 1.2, 1.05, 1.0}, {0, 1.7, 1.25, 1.15, 1.0}};
+
+// wide: tiles side by side; round: how many the chip takes at once; tallest: the largest height there is; cost: of a token by height
+static int tile_height(int mrows, long wide, long round, int tallest, const double* cost)
 {
-    static const double cost[5] = {0, 1.7, 1.2, 1.1, 1.0};
     int best = tallest;
     double least = 0;
     for (int tm = tallest; tm >= 1; --tm) {
@@ -334,7 +354,10 @@ static int tile_height(int mrows, long wide, long round, int tallest)
     return best;
 }
 
-int gemm_tile_height(int mrows, int N, int k) { return tile_height(mrows, (long)(N / 256) * k, 256, 4); }
+int gemm_tile_height(int mrows, int N, int Kd, int k)
+{
+    return tile_height(mrows, (long)(N / 256) * k, 256, 4, kTokenCost[Kd <= 256 ? 0 : Kd < 2048 ? 1 : 2]);
+}
 
 namespace {
 
@@ -350,7 +373,7 @@ hipError_t launch_bf16(const sp_model* M, const GemmArgs& a, int N, int k, hipSt
         // widths.  us a call, one in flight / two: one student, twelve sequences: hidden 128 70 / 73, 384 100 / 95, 640 124 / 117, 896 153 / 145;
         // four students 79 / 81, 128 / 130, 177 / 177, 259 / 259; 64 tokens at hidden 128 47 / 50.)
         const long wide = (long)(N / 128) * k * a.splits;
-        switch (tile_height(a.mrows, wide, 512, (a.mrows + 95) / 96 * wide >= 1024 ? 3 : 2)) {
+        switch (tile_height(a.mrows, wide, 512, (a.mrows + 95) / 96 * wide >= 1024 ? 3 : 2, kHalfTokenCost)) {
             case 1: return launch_wreg_tile<1, 2, 1, EPI>(M, a, N, k, s);
             case 2: return launch_wreg_tile<2, 2, 1, EPI>(M, a, N, k, s);
             default: return launch_wreg_tile<3, 2, 1, EPI>(M, a, N, k, s);
@@ -366,7 +389,7 @@ hipError_t launch_bf16(const sp_model* M, const GemmArgs& a, int N, int k, hipSt
     const long half = (long)(N / 128) * k * a.splits;
     if ((a.mrows + 31) / 32 * half <= 256) return launch_wreg_tile<1, 2, 2, EPI>(M, a, N, k, s);
     if ((a.mrows + 63) / 64 * half <= 256) return launch_wreg_tile<2, 2, 2, EPI>(M, a, N, k, s);
-    switch (gemm_tile_height(a.mrows, N, k * a.splits)) {
+    switch (gemm_tile_height(a.mrows, N, a.Kper, k * a.splits)) {
         case 1: return launch_wreg_tile<1, 4, 1, EPI>(M, a, N, k, s);
         case 2: return launch_wreg_tile<2, 4, 1, EPI>(M, a, N, k, s);
         case 3: return launch_wreg_tile<3, 4, 1, EPI>(M, a, N, k, s);
@@ -582,7 +605,7 @@ hipError_t launch_gemm_split(const sp_model* M, const void* A, int lda, size_t w
 {
     if (!bf16_path(M->cfg) || mrows % 64 || N % 128 || splits < 1 || Kd % (128 * splits)) return hipErrorInvalidValue;
     const GemmArgs a{(const bf16*)A, a_student_stride / 2, M->arena, M->L.student_stride, w_off, 0, (bf16*)part, p_student_stride,
-                     nullptr, 0, nullptr, 0, rows_layout(N), lda, 0, 0, 0, Kd, Kd / splits, splits, mrows, 0, 0, 0, 0, slice};
+                     nullptr, 0, nullptr, 0, rows_layout(N), lda, 0, 0, 0, Kd, Kd / splits, splits, mrows, 0, 0, 0, 0, slice, false};
     return launch_bf16<EPI_PARTIAL>(M, a, N, k, s);
 }
 
@@ -600,7 +623,8 @@ hipError_t launch_gemm(const sp_model* M, const void* A, int lda, size_t w_off, 
     if (bf16_path(M->cfg)) {
         const GemmArgs a{(const bf16*)A, a_student_stride / 2, M->arena, M->L.student_stride, w_off, b_off, (bf16*)out,
                          o_student_stride / 2, (const bf16*)residual, r_student_stride / 2, (bf16*)out2, o2_student_stride / 2,
-                         packed_out ? packed_layout(ldo) : rows_layout(ldo), lda, ldr, ld2, n_split, Kd, Kd, 1, mrows, 0, 0, 0, 0, 0};
+                         packed_out ? packed_layout(ldo) : rows_layout(ldo), lda, ldr, ld2, n_split, Kd, Kd, 1, mrows, 0, 0, 0, 0, 0,
+                         (size_t)k * mrows * N * 2 >= kStreamBytes};
         switch (epi) {
             case EPI_BIAS_GELU: return launch_bf16<EPI_BIAS_GELU>(M, a, N, k, s);
             case EPI_QKV: return launch_bf16<EPI_QKV>(M, a, N, k, s);

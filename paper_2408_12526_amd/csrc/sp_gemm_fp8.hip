@@ -316,7 +316,7 @@ hipError_t launch_fp8_tile(Fp8Args a, int N, int k, hipStream_t s)
 template <int EPI>
 hipError_t launch_fp8(const Fp8Args& a, int N, int k, hipStream_t s)
 {
-    switch (gemm_tile_height(a.mrows, N, k)) {
+    switch (gemm_tile_height(a.mrows, N, a.Kd / 2, k)) {
         case 1: return launch_fp8_tile<1, EPI>(a, N, k, s);
         case 2: return launch_fp8_tile<2, EPI>(a, N, k, s);
         case 3: return launch_fp8_tile<3, EPI>(a, N, k, s);

@@ -148,6 +148,18 @@ __device__ __forceinline__ u32x4 load16(const void* base, int voff, int soff)
 #endif
 }
 
+// Stores of a projection's output, which the next launch reads.  Written through the L2 (sc1): nothing is left there for the end of the
+// launch to write back.  STREAM (nt): neither is it kept behind the L2, for outputs that the memory-side cache does not hold until
+// they are read (kStreamBytes).  (The idle slots around the instruction are those that the hardware wants between it and writes of its data.)
+template <bool STREAM>
+__device__ __forceinline__ void store16_through(void* p, u32x4 v)
+{
+    if (STREAM) __builtin_nontemporal_store(v, (u32x4*)p);
+#if defined(__HIP_DEVICE_COMPILE__)
+    else asm volatile("s_nop 0\n\tglobal_store_dwordx4 %0, %1, off sc1\n\ts_nop 0" ::"v"(p), "v"(v));   // (nothing here reads it back)
+#endif
+}
+
 template <int N>
 __device__ inline void wait_vmcnt() { asm volatile("s_waitcnt vmcnt(%0)" ::"n"(N) : "memory"); }
 
@@ -201,6 +213,12 @@ constexpr int kFirstOnlyMinTokens = 1024;   // smallest call whose first-token r
 // subnormal range), and only calls that compute at least kFp8MinRows rows use them
 constexpr float kActQuantScale = 16.f;
 constexpr int kFp8MinRows = 2048;
+
+// Outputs of a projection (bytes, all students) from which they are streamed.  us a call, hidden 768, 14653 tokens, kept / streamed, by
+// MiB: q|k|v 129 613 / 612, 193 901 / 898, 257 1176 / 1166, 515 2135 / 2125; FFN up 172 613 / 618, 258 901 / 894, 343 1176 / 1162, 687 2135 / 2118; hidden 1024:
+// q|k|v 108 594 / 595, 215 1202 / 1197, 322 1659 / 1645; FFN up 144 594 / 602, 160 694 / 697, 287 1202 / 1199.  The hidden-wide outputs: no difference at
+// any size up to 215.
+constexpr size_t kStreamBytes = (size_t)192 << 20;
 
 // Byte offsets of every tensor inside one student's slab of the weight arena.
 // The encoder matrices are stored transposed with respect to the host blob, reduction index innermost: fp32 as
@@ -295,8 +313,8 @@ hipError_t launch_ln_slices(const sp_model* M, const float* part, size_t slice, 
                             const void* residual, void* out, int rows, int T, int mrows, int k, size_t g_off, size_t b_off,
                             hipStream_t s);
 
-// Tile height in blocks of 32 tokens (1 to 4) for a projection of mrows rows onto N features (a multiple of 256) of k students.
-int gemm_tile_height(int mrows, int N, int k);
+// Tile height in blocks of 32 tokens (1 to 4) for a projection of mrows rows onto N features (a multiple of 256) from Kd of k students.
+int gemm_tile_height(int mrows, int N, int Kd, int k);
 
 // The same projection on fp8 operands (SP_DTYPE_FP8: mrows a multiple of 64, N and Kd of 256).
 // A8: e4m3 codes of activation * a_qscale, [m][row][lda] bytes; weights at w_off (e4m3, operand blocks) with fp32
