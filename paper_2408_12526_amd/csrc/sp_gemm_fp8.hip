@@ -12,7 +12,7 @@
 //   * weights: from memory straight to the registers of the one wave that uses them, in operand blocks (see ArenaLayout: a
 //     load is 1 KB in a row); a step's registers are requested again, for the next k-tile of 128 reduction elements, as soon as
 //     its matrix instructions are issued;
-//   * activations: through registers into one of two LDS stages (rows of eight 16-byte slots; slot s of row r holds chunk
+//   * activations: by direct-to-LDS loads into one of three stages (rows of eight 16-byte slots; slot s of row r holds chunk
 //     s ^ ((r >> 1) & 7): no bank conflicts), requested two k-tiles ahead.  Fragments have one register set: a block of 32
 //     tokens is read for the next step as soon as its two matrix instructions are issued (2 (TM - 1) instructions of 64 cycles
 //     to arrive), so the barrier of a k-tile sits behind the first block of its second step.
@@ -45,14 +45,14 @@ struct Fp8Args {
 };
 
 constexpr int F8_NW = 4, F8_BN = 64 * F8_NW;                // waves; features of a tile
-// two activation stages or the staged output tile, then scales and biases of the tile's features
+// three activation stages or the staged output tile, then scales and biases of the tile's features
 constexpr size_t fp8_tile_bytes(int tm) { return (size_t)32 * tm * 128 * F8_NW; }
 constexpr size_t fp8_smem_bytes(int tm) { return fp8_tile_bytes(tm) + 2 * F8_BN * sizeof(float); }
 
 template <int TM, int EPI>
 __global__ __launch_bounds__(256, 2) void gemm_fp8_kernel(Fp8Args p)
 {
-    constexpr int BM = 32 * TM, NA = TM;                    // NA: 16-byte pieces of an activation k-tile per thread
+    constexpr int BM = 32 * TM, NA = TM;                    // NA: wave-loads (eight rows) of an activation k-tile per wave
     constexpr int STAGE = BM * 8;                           // 16-byte units
     constexpr int TKEY = TM == 3 ? 3 : TM * 4 - 1;          // swizzle of the transposed staging: bits of the chunk
     extern __shared__ uint4 smem[];
@@ -70,59 +70,54 @@ __global__ __launch_bounds__(256, 2) void gemm_fp8_kernel(Fp8Args p)
     const char* sb = p.arena + (size_t)m * p.ss;
     const int Kd = p.Kd, nk = Kd >> 7;
 
-    // activations: thread -> (row tid / 8 + 32 i, chunk tid % 8) of a k-tile; rows beyond mrows repeat the last one
-    // (64-bit base of the tile, 32-bit offsets inside it: a buffer may hold more than 2^32 elements)
+    // activations: wave-load i of a k-tile is rows 8 (wave + 4 i) .. + 7, lane -> (row lane / 8, slot lane % 8), which holds chunk
+    // slot ^ ((row >> 1) & 7); rows beyond mrows repeat the last one (64-bit base of the tile, 32-bit offsets inside it: a buffer may hold
+    // more than 2^32 elements)
     const unsigned char* Ag = p.A + (size_t)m * p.a_ss + (size_t)m0 * p.lda;
-    // (the swizzle key repeats every 16 rows, so one LDS address serves a thread's pieces)
-    unsigned aoff[NA];
-    const unsigned adst = (tid >> 3) * 8 + ((tid & 7) ^ ((tid >> 4) & 7));
+    int aoff[NA];
 #pragma unroll
     for (int i = 0; i < NA; ++i) {
-        const int r = (tid >> 3) + 32 * i;
+        const int r = 8 * (wave + F8_NW * i) + (lane >> 3);
         const int rr = m0 + r < p.mrows ? r : p.mrows - 1 - m0;
-        aoff[i] = (unsigned)rr * (unsigned)p.lda + (tid & 7) * 16;
+        aoff[i] = rr * p.lda + ((lane & 7) ^ ((r >> 1) & 7)) * 16;
     }
     // weights: operand blocks of 32 features x 64 reduction elements, 2 KB, lane after lane in both halves
     const char* Wg = sb + p.w_off + (size_t)nf * Kd;
-    const unsigned wlane = (unsigned)lane * 16;
+    const int wlane = lane * 16;
 
     v8i w[2][2], fx[TM];
-    v4i ar[NA];
-    auto load_a = [&](int kt) {
+    auto dma_a = [&](int kt, int stage) {
 #pragma unroll
-        for (int i = 0; i < NA; ++i) ar[i] = *(const v4i*)(Ag + kt * 128 + aoff[i]);
+        for (int i = 0; i < NA; ++i) load_lds16(Ag, (lds_void*)(smem + stage * STAGE + (wave + F8_NW * i) * 64), aoff[i], kt * 128);
     };
     auto load_w = [&](int kt, int s) {
 #pragma unroll
         for (int i = 0; i < 2; ++i) {
-            const char* at = Wg + (size_t)i * 32 * Kd + (size_t)(2 * kt + s) * 2048 + wlane;
-            w[s][i] = __builtin_shufflevector(*(const v4i*)at, *(const v4i*)(at + 1024), 0, 1, 2, 3, 4, 5, 6, 7);
+            const int at = i * 32 * Kd + (2 * kt + s) * 2048;
+            w[s][i] = __builtin_shufflevector(__builtin_bit_cast(v4i, load16(Wg, wlane, at)), __builtin_bit_cast(v4i, load16(Wg, wlane + 1024, at)), 0, 1, 2, 3, 4, 5, 6, 7);
         }
     };
-    auto write_a = [&](int buf) {
-#pragma unroll
-        for (int i = 0; i < NA; ++i) *(v4i*)(smem + buf * STAGE + adst + i * 256) = ar[i];
-    };
     const int xrow = j31 * 8, xkey = (j31 >> 1) & 7;
-    auto frag = [&](int buf, int s, int t) {
-        const v4i* base = (const v4i*)(smem + buf * STAGE + t * 256 + xrow);
+    auto frag = [&](int stage, int s, int t) {
+        const v4i* base = (const v4i*)(smem + stage * STAGE + t * 256 + xrow);
         return __builtin_shufflevector(base[(4 * s + 2 * g) ^ xkey], base[(4 * s + 2 * g + 1) ^ xkey], 0, 1, 2, 3, 4, 5, 6, 7);
     };
 
     f32x16 acc[2][TM];
-    load_a(0);
+    dma_a(0, 0);
     const float scale = ((const float*)(sb + p.s_off))[n0 + tid], bias = ((const float*)(sb + p.b_off))[n0 + tid];
+    __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+    for (int s = 0; s < 2; ++s) load_w(0, s);
+    __builtin_amdgcn_sched_barrier(0);
+    dma_a(1, 1);
+    __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
     for (int i = 0; i < 2; ++i)
 #pragma unroll
         for (int t = 0; t < TM; ++t)
 #pragma unroll
             for (int e = 0; e < 16; ++e) acc[i][t][e] = 0.f;
-    __builtin_amdgcn_sched_barrier(0);
-#pragma unroll
-    for (int s = 0; s < 2; ++s) load_w(0, s);
-    __builtin_amdgcn_sched_barrier(0);
-    write_a(0);
     {
         // (GELU: the output scale rides in the factors)
         const float q = EPI == EPI_BIAS_GELU ? p.q_out : 1.f;
@@ -130,15 +125,17 @@ __global__ __launch_bounds__(256, 2) void gemm_fp8_kernel(Fp8Args p)
         coef[F8_BN + tid] = bias * q;
     }
     __builtin_amdgcn_sched_barrier(0);
-    load_a(1);
+    wait_vmcnt<8 + NA>();                                   // activations of k-tile 0
     barrier_lds();
 #pragma unroll
     for (int t = 0; t < TM; ++t) fx[t] = frag(0, 0, t);
 
-    // One k-tile.  The stage of k-tile j + 1 is free in step 0: its last fragments were in registers at the barrier of
-    // k-tile j - 1.  NEXT / NEXT2: k-tile j + 1 / j + 2 exists.
-    auto ktile = [&](int j, int buf, auto next_c, auto next2_c) {
-        constexpr bool NEXT = decltype(next_c)::value, NEXT2 = decltype(next2_c)::value;
+    // One k-tile, j.  Requested during it: the weights of k-tile j + 1 (NEXT), a step's when its registers are free, and the activations of
+    // k-tile j + 2 (AL) in the stage that k-tile j - 1 has left: its last fragments were in registers at the barrier of that k-tile.  V: loads
+    // that may be in flight when the activations of k-tile j + 1 have to be there, those requested behind them.
+    int prev = 2, cur = 0, next = 1;                        // stages of k-tiles j - 1, j and j + 1
+    auto ktile = [&](int j, auto next_c, auto a_c, auto v_c) {
+        constexpr bool NEXT = decltype(next_c)::value, AL = decltype(a_c)::value;
 #pragma unroll
         for (int s = 0; s < 2; ++s) {
 #pragma unroll
@@ -147,28 +144,36 @@ __global__ __launch_bounds__(256, 2) void gemm_fp8_kernel(Fp8Args p)
                 for (int i = 0; i < 2; ++i)
                     acc[i][t] = __builtin_amdgcn_mfma_scale_f32_32x32x64_f8f6f4(w[s][i], fx[t], acc[i][t], 0, 0, 0, 0x7f7f7f7f, 0, 0x7f7f7f7f);
                 __builtin_amdgcn_sched_barrier(0);
-                if (s == 1 && t == 0 && NEXT) barrier_lds();
-                if (s == 0) fx[t] = frag(buf, 1, t);
-                else if (NEXT) fx[t] = frag(buf ^ 1, 0, t);
-                if (s == 0 && t == 0 && NEXT) {
-                    write_a(buf ^ 1);
-                    if (NEXT2) load_a(j + 2);
+                if (s == 1 && t == 0 && NEXT) {
+                    wait_vmcnt<decltype(v_c)::value>();
+                    barrier_lds();
                 }
+                if (s == 0) fx[t] = frag(cur, 1, t);
+                else if (NEXT) fx[t] = frag(next, 0, t);
+                if (s == 0 && t == 0 && AL) dma_a(j + 2, prev);
                 __builtin_amdgcn_sched_barrier(0);
             }
             if (NEXT) load_w(j + 1, s);
             __builtin_amdgcn_sched_barrier(0);
         }
+        prev = cur;
+        cur = next;
+        next = next == 2 ? 0 : next + 1;
     };
     constexpr std::true_type Y{};
     constexpr std::false_type N{};
+    constexpr std::integral_constant<int, 8 + NA + 4> V{};  // both steps' weights, activations and weights of a step since
     int j = 0;
-    for (; j + 2 < nk; j += 2) {                            // (nk is even)
-        ktile(j, 0, Y, Y);
-        ktile(j + 1, 1, Y, Y);
+    if (nk > 2) {                                           // (nk is even)
+        ktile(0, Y, Y, std::integral_constant<int, NA + 4>{});
+        ktile(1, Y, Y, V);
+        for (j = 2; j + 2 < nk; j += 2) {
+            ktile(j, Y, Y, V);
+            ktile(j + 1, Y, Y, V);
+        }
     }
-    ktile(j, 0, Y, N);
-    ktile(j + 1, 1, N, N);
+    ktile(j, Y, N, std::integral_constant<int, 4>{});
+    ktile(j + 1, N, N, V);
 
     // ---- epilogue: accumulator element v of lane l in block (i, t): token 32 t + l % 32, feature 32 i + 8 (v / 4) +
     // 4 (l / 32) + v % 4.
