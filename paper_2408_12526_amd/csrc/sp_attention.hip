@@ -82,6 +82,7 @@ struct AttnArgs {
     float qscale;
     int B, Tn, rows, H, heads, max_seqlen;
     int items, run;                   // work items per head; neighbouring items that stay on one XCD
+    int pairs, whole;                 // (student, head) pairs; how many of them an XCD has to itself (0: one row of the grid per student)
     int general;                      // workgroups of the general part; those behind it take sequences of up to kShortLen tokens
 };
 
@@ -256,12 +257,27 @@ __global__ __launch_bounds__(256, 4) void attention_bf16_kernel(AttnArgs p)
 {
     __shared__ __attribute__((aligned(16))) char lds[kAttnLdsBytes];
     if (SHORT && (int)blockIdx.x >= p.general) return attention_short(p, lds, (int)blockIdx.x - p.general);
-    const int m = blockIdx.y;
-    // workgroup id mod 8 selects the XCD: runs of neighbouring items (they share lines of the token-contiguous value rows)
-    // stay on one XCD, the runs go round the XCDs, another way for every student
-    const int xcd = ((int)blockIdx.x + m) & 7, y = (int)blockIdx.x >> 3;
-    const int h = y % p.heads, s = y / p.heads, item = ((s / p.run) * 8 + xcd) * p.run + s % p.run;
-    if (item >= p.items) return;
+    // Workgroup id mod 8 selects the XCD.  Runs of neighbouring items (they share lines of the token-contiguous value rows) stay on one XCD
+    // and go round the XCDs, another way for every student.  Long sequences: an XCD takes every eighth (student, head) with all its
+    // items, so that the XCDs have the same work whatever the lengths; only the items of the pairs left over go round.
+    const int xcd = (int)blockIdx.x & 7, y = (int)blockIdx.x >> 3, rest = y - p.whole * p.items;
+    int m = blockIdx.y, h, item;
+    if (rest < 0) {
+        const int pair = y / p.items * 8 + xcd;
+        m = pair / p.heads;
+        h = pair - m * p.heads;
+        item = y % p.items;
+    } else {
+        const int pairs = p.whole ? p.pairs - 8 * p.whole : p.heads, s = rest / pairs;
+        h = rest - s * pairs;
+        item = ((s / p.run) * 8 + ((xcd + m) & 7)) * p.run + s % p.run;
+        if (p.whole) {
+            h += 8 * p.whole;
+            m = h / p.heads;
+            h -= m * p.heads;
+        }
+        if (item >= p.items) return;
+    }
     const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     int t0, t1;
     const int b = last_sequence(p.cu, p.B, lane, [&](int i, int c) { return (c >> 7) + i <= item; }, t0, t1);
@@ -853,7 +869,10 @@ hipError_t launch_attention(const sp_model* M, const void* qkv, const void* vt, 
         // Runs of neighbouring items that stay on one XCD: 1, 2, 4, 8 and 16 measured 208 / 208 / 207 / 210 / 211 us on 371 items of
         // short sequences (eight students), 325 / 322 / 326 / 328 / 347 on 208 of long ones (six); few items go round one by one.
         AttnArgs a{(const bf16*)qkv, (const bf16*)vt, (bf16*)att, (unsigned char*)attq, cu, qscale, B, T, rows, c.hidden, c.heads,
-                   max_seqlen, T / kQItem + B, 1, 0};
+                   max_seqlen, T / kQItem + B, 1, c.heads * k, max_seqlen > kShortLen && T >= (int64_t)kQItem * B ? c.heads * k / 8 : 0, 0};
+        // A pair's items all on one XCD from a mean of 128 tokens on (all the host knows): going round the XCDs, what an XCD gets of long and
+        // short sequences evens out over the students only.  us per launch, round / this: 64 sequences of 64-512 tokens, 16 heads, one student
+        // 65.0 / 60.0, six 348 / 345; 256 of 8-256 (mean 57), 12 heads, eight students, whose heads then are read by different XCDs: 214 / 221.
         a.run = a.items < 128 ? 1 : (a.items < 256 ? 2 : 4);
         const int nitems = (a.items + 8 * a.run - 1) / (8 * a.run) * (8 * a.run), nshort = (B * ((c.heads + 3) / 4) + 7) / 8 * 8;
         // Sequences of up to 32 tokens by single waves: alone where there are no others; beside the general part, whose workgroups then leave for
@@ -862,8 +881,8 @@ hipError_t launch_attention(const sp_model* M, const void* qkv, const void* vt, 
         // lognormal ones of mean 15 782 / 755, 24 1095 / 1075, 39 1588 / 1577, 58 2213 / 2207; two students, 24 of mean 25 102 / 102, 42 124 / 125.
         // 256 wide, three students: 256 of 16 122 / 114, mean 24 144 / 142; 24 of mean 25 67.6 / 68.2, 36 71.3 / 71.9.
         const bool few = (long)B * ((c.heads + 3) / 4) * k < 128, only = max_seqlen <= kShortLen, mixed = !only && !few && T <= (int64_t)32 * B;
-        a.general = only ? 0 : nitems * c.heads;
-        const dim3 grid((unsigned)(a.general + (only || mixed ? nshort : 0)), k);
+        a.general = only ? 0 : 8 * a.whole * a.items + nitems * (a.whole ? a.pairs - 8 * a.whole : c.heads);
+        const dim3 grid((unsigned)(a.general + (only || mixed ? nshort : 0)), a.whole ? 1 : k);
         if (only || mixed) hipLaunchKernelGGL(attention_bf16_kernel<true>, grid, dim3(256), 0, s, a);
         else hipLaunchKernelGGL(attention_bf16_kernel<false>, grid, dim3(256), 0, s, a);
     } else {

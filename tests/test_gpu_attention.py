@@ -42,6 +42,30 @@ def test_attention_at_tile_and_item_edges(oracle64, name, qk_std):
     st.close()
 
 
+# pairs of student and head that an XCD has to itself and pairs left over: 2 and none, 2, 4 and none, 10, 18, 12 (four left), 24
+@pytest.mark.parametrize("hidden,K", [(128, 1), (128, 2), (128, 4), (128, 5), (384, 3), (768, 1), (768, 2)])
+@pytest.mark.parametrize("lengths", [(256,), (129, 127), (320, 1, 190, 2, 300, 128, 57, 250, 256, 31), (319,) * 27])
+def test_long_sequences_by_pairs_of_student_and_head(oracle64, hidden, K, lengths):
+    """Means of 128 tokens and more: every (student, head, item) is taken once, whichever way it reaches its XCD.  Bound as above."""
+    from paper_2408_12526_amd import sp
+    shape = synth.StudentShape(K=K, layers=1, hidden=hidden, heads=hidden // 64, ffn=128, vocab=100, max_pos=320, classes=2, dtype="bf16")
+    lengths = np.array(lengths, np.int32)
+    rng = np.random.default_rng(hidden + K)
+    ids, blob = synth.make_ids(rng, int(lengths.sum()), shape.vocab), synth.make_weights(rng, shape, std=0.08, qk_std=1.36 / hidden ** 0.5)
+    st = sp.Students(sp.config_from_shape(shape), blob)
+    cu, H = sp.sp_pack(lengths), hidden
+    T, B = int(cu[-1]), len(lengths)
+    ws = st.sp_forward_partial(torch.from_numpy(ids).cuda(), torch.from_numpy(cu).cuda(), int(lengths.max()), K, 1)
+    qkv, att = st.read_activation(ws, "qkv", T, B, K), st.read_activation(ws, "att", T, B, K)
+    for m in range(K):
+        for b in range(B) if B < 20 else (0, 13, B - 1):
+            a = qkv[m][cu[b]:cu[b + 1]]
+            want = oracle64.attention(a[:, :H], a[:, H:2 * H], a[:, 2 * H:], shape.heads)
+            err = np.abs(att[m][cu[b]:cu[b + 1]] - want).max() / np.abs(want).max()
+            assert err < 1.2e-2, f"student {m}, sequence {b} of {lengths[b]} tokens at {cu[b]}: {err:.3e}"
+    st.close()
+
+
 # every length of the short part at every offset of the first key block, alone, beside longer sequences, and (few of them) in the general part
 @pytest.mark.parametrize("hidden", [128, 384, 768])      # two, six and twelve heads: waves of a head group without a head
 def test_short_sequences_alone_and_beside_longer_ones(oracle64, hidden):
