@@ -21,6 +21,20 @@ __device__ inline void load8(const bf16* p, float (&v)[8])
 #pragma unroll
     for (int i = 0; i < 8; ++i) v[i] = (float)a[i];
 }
+// eight values as they lie in memory
+template <typename T> struct Raw8;
+template <> struct Raw8<bf16> { bf16x8 v; };
+template <> struct Raw8<float> { f32x4 v[2]; };
+__device__ inline void widen(const Raw8<bf16>& r, float (&v)[8])
+{
+#pragma unroll
+    for (int i = 0; i < 8; ++i) v[i] = (float)r.v[i];
+}
+__device__ inline void widen(const Raw8<float>& r, float (&v)[8])
+{
+#pragma unroll
+    for (int i = 0; i < 8; ++i) v[i] = r.v[i >> 2][i & 3];
+}
 __device__ inline void store8(float* p, const float (&v)[8])
 {
     *(f32x4*)p = f32x4{v[0], v[1], v[2], v[3]};
@@ -95,9 +109,11 @@ __device__ inline void load_gamma_beta(const float* g, const float* b, int nch, 
     }
 }
 
-// Consecutive rows normalised by one wave (gamma / beta are fetched once for them): 8 for calls that fill the chip
-// either way, 1 for small calls, where the row-parallelism is worth more than the saved fetches.
-inline int rows_per_wave(int mrows, int k) { return (long)mrows * k >= 32768 ? 8 : 1; }
+// Consecutive rows normalised by one wave (gamma and beta are fetched once for them, and a row's loads run while the one before is
+// normalised): few rows one each, where the row-parallelism is worth more.  us by rows a wave: 18432 rows of 1024: LayerNorm 1 14.1, 2 13.7, 4
+// 15.0, embedding 22.6 / 20.6 / 20.8; 9216 of 768: 7.6 / 7.1 / 7.8, 12.7 / 12.0 / 11.4; 117 k rows of 768: LayerNorm 4 56.4, 8 57.9, embedding
+// 83.4 / 76.8 (whose waves look for their sequence first); 110 k of 1024: LayerNorm 66.9 / 71.9, embedding 87.6 / 90.1.
+inline int rows_per_wave(int mrows, int k, int many) { return (long)mrows * k >= 32768 ? many : (long)mrows * k >= 8192 ? 2 : 1; }
 
 // One wave per rpw consecutive packed token rows, grid.y = student.
 template <typename T, int MAXC, bool Q8>
@@ -123,43 +139,59 @@ __global__ __launch_bounds__(256) void embed_ln_kernel(const char* arena, size_t
     my_id = my_id < 0 ? 0 : (my_id >= V ? V - 1 : my_id);
     const int b = last_sequence(cu, B, lane, [&](int, int c) { return c <= first; }, c0, c1);
     const int begin = lane == 0 ? c0 : lane == 1 ? c1 : rpw > 1 && b + lane < B ? cu[b + lane] : 0x7fffffff;
-#pragma unroll 2
-    for (int r = 0; r < rpw; ++r) {
-        const int row = row0 + r;
-        if (row >= mrows) break;
-        T* out = x + ((size_t)m * rows + row) * H;
-        if (row >= Tn) {
-            // Padding rows of the token tile.  They never reach a result, but the projections compute them and the
-            // attention kernels fetch values in chunks of eight tokens, so they must hold finite numbers: zero the
-            // hidden state here and, once per call, the attention output rows that no kernel writes.
-            const float zero8[8] = {0, 0, 0, 0, 0, 0, 0, 0};
-            T* arow = att + ((size_t)m * rows + row) * H;
-            for (int c = lane; c < nch; c += 64) { store8(out + c * 8, zero8); store8(arow + c * 8, zero8); }
-            if (Q8)
-                for (int c = lane; c < nch; c += 64) {
-                    *(int2*)(xq + ((size_t)m * rows + row) * H + c * 8) = int2{0, 0};
-                    if (attq) *(int2*)(attq + ((size_t)m * rows + row) * H + c * 8) = int2{0, 0};
-                }
-            continue;
-        }
-        const int id = __builtin_amdgcn_readlane(my_id, r), nb = __popcll(__ballot(begin <= row));
+    // Rows of tokens, the next one's fetched while one is normalised; then padding rows.
+    const int end = row0 + rpw < mrows ? row0 + rpw : mrows, live = end < Tn ? end : Tn;
+    Raw8<T> te[2][MAXC], pe[2][MAXC];
+    auto fetch = [&](int row, int set) {
+        const int id = __builtin_amdgcn_readlane(my_id, row - row0), nb = __popcll(__ballot(begin <= row));
         int pos = row - __builtin_amdgcn_readlane(begin, nb > 0 ? nb - 1 : 0);
         pos = pos < 0 ? 0 : (pos >= P ? P - 1 : pos);
-        const T* te = (const T*)(sb + tok_off) + (size_t)id * H;
-        const T* pe = (const T*)(sb + pos_off) + (size_t)pos * H;
-        float v[MAXC][8];
+        const T* t = (const T*)(sb + tok_off) + (size_t)id * H;
+        const T* q = (const T*)(sb + pos_off) + (size_t)pos * H;
 #pragma unroll
         for (int i = 0; i < MAXC; ++i) {
             const int c = lane + 64 * i;
             if (c < nch) {
-                float a[8], p8[8];
-                load8(te + c * 8, a);
-                load8(pe + c * 8, p8);
-#pragma unroll
-                for (int e = 0; e < 8; ++e) v[i][e] = a[e] + p8[e];
+                te[set][i] = *(const Raw8<T>*)(t + c * 8);
+                pe[set][i] = *(const Raw8<T>*)(q + c * 8);
             }
         }
-        ln_row_store<T, MAXC, Q8>(v, nch, lane, H, gg, bb, eps, out, Q8 ? xq + ((size_t)m * rows + row) * H : nullptr, qscale);
+    };
+    auto normalise = [&](int row, int set) {
+        float v[MAXC][8];
+#pragma unroll
+        for (int i = 0; i < MAXC; ++i) {
+            float p8[8];
+            widen(te[set][i], v[i]);
+            widen(pe[set][i], p8);
+#pragma unroll
+            for (int e = 0; e < 8; ++e) v[i][e] += p8[e];
+        }
+        const size_t at = ((size_t)m * rows + row) * H;
+        ln_row_store<T, MAXC, Q8>(v, nch, lane, H, gg, bb, eps, x + at, Q8 ? xq + at : nullptr, qscale);
+    };
+    if (row0 < live) fetch(row0, 0);
+    for (int row = row0; row < live; row += 2) {
+        if (row + 1 < live) fetch(row + 1, 1);
+        __builtin_amdgcn_sched_barrier(0);
+        normalise(row, 0);
+        if (row + 1 >= live) break;
+        if (row + 2 < live) fetch(row + 2, 0);
+        __builtin_amdgcn_sched_barrier(0);
+        normalise(row + 1, 1);
+    }
+    // Padding rows of the token tile.  They never reach a result, but the projections compute them and the attention kernels fetch values in
+    // chunks of eight tokens, so they must hold finite numbers: zero the hidden state here and, once per call, the attention output rows
+    // that no kernel writes.
+    for (int row = row0 > Tn ? row0 : Tn; row < end; ++row) {
+        const float zero8[8] = {0, 0, 0, 0, 0, 0, 0, 0};
+        const size_t at = ((size_t)m * rows + row) * H;
+        for (int c = lane; c < nch; c += 64) { store8(x + at + c * 8, zero8); store8(att + at + c * 8, zero8); }
+        if (Q8)
+            for (int c = lane; c < nch; c += 64) {
+                *(int2*)(xq + at + c * 8) = int2{0, 0};
+                if (attq) *(int2*)(attq + at + c * 8) = int2{0, 0};
+            }
     }
 }
 
@@ -176,19 +208,31 @@ __global__ __launch_bounds__(256) void layernorm_kernel(const char* arena, size_
     const char* sb = arena + (size_t)m * student_stride;
     float gg[MAXC][8], bb[MAXC][8];
     load_gamma_beta<MAXC>((const float*)(sb + g_off), (const float*)(sb + b_off), nch, lane, gg, bb);
-#pragma unroll 2
-    for (int r = 0; r < rpw; ++r) {
-        const int row = row0 + r;
-        if (row >= mrows) break;
-        const T* in = u + ((size_t)m * rows + row) * H;
+    // (the next row is fetched while one is normalised)
+    const int end = row0 + rpw < mrows ? row0 + rpw : mrows;
+    Raw8<T> in[2][MAXC];
+    auto fetch = [&](int row, int set) {
+        const T* r = u + ((size_t)m * rows + row) * H;
+#pragma unroll
+        for (int i = 0; i < MAXC; ++i)
+            if (lane + 64 * i < nch) in[set][i] = *(const Raw8<T>*)(r + (lane + 64 * i) * 8);
+    };
+    auto normalise = [&](int row, int set) {
         float v[MAXC][8];
 #pragma unroll
-        for (int i = 0; i < MAXC; ++i) {
-            const int c = lane + 64 * i;
-            if (c < nch) load8(in + c * 8, v[i]);
-        }
-        ln_row_store<T, MAXC, Q8>(v, nch, lane, H, gg, bb, eps, out + ((size_t)m * rows + row) * H,
-                                  Q8 ? outq + ((size_t)m * rows + row) * H : nullptr, qscale);
+        for (int i = 0; i < MAXC; ++i) widen(in[set][i], v[i]);
+        const size_t at = ((size_t)m * rows + row) * H;
+        ln_row_store<T, MAXC, Q8>(v, nch, lane, H, gg, bb, eps, out + at, Q8 ? outq + at : nullptr, qscale);
+    };
+    fetch(row0, 0);
+    for (int row = row0; row < end; row += 2) {
+        if (row + 1 < end) fetch(row + 1, 1);
+        __builtin_amdgcn_sched_barrier(0);
+        normalise(row, 0);
+        if (row + 1 >= end) break;
+        if (row + 2 < end) fetch(row + 2, 0);
+        __builtin_amdgcn_sched_barrier(0);
+        normalise(row + 1, 1);
     }
 }
 
@@ -541,7 +585,7 @@ hipError_t launch_embed_ln(const sp_model* M, const int32_t* ids, const int32_t*
 {
     const sp_config& c = M->cfg;
     const ArenaLayout& L = M->L;
-    const int rpw = rows_per_wave(mrows, k);
+    const int rpw = rows_per_wave(mrows, k, 8);
     dim3 grid((mrows + 4 * rpw - 1) / (4 * rpw), k);
     const int maxc = (c.hidden / 8 + 63) / 64;              // 8-element chunks per lane
 #define SP_EMBED(T, MAXC) do {                                                                                     \
@@ -568,7 +612,7 @@ hipError_t launch_layernorm(const sp_model* M, const void* u, void* out, int row
                             size_t b_off, hipStream_t s, void* outq, float qscale)
 {
     const sp_config& c = M->cfg;
-    const int rpw = rows_per_wave(mrows, k);
+    const int rpw = rows_per_wave(mrows, k, 4);
     dim3 grid((mrows + 4 * rpw - 1) / (4 * rpw), k);
     const int maxc = (c.hidden / 8 + 63) / 64;              // 8-element chunks per lane
     if (maxc > kMaxChunks) return hipErrorInvalidValue;
