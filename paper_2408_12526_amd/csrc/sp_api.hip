@@ -481,9 +481,17 @@ static int run_students(const sp_model* M0, const WsLayout& W, const int32_t* id
         }
         return SP_OK;
     }
-    // (the partial forwards of the tests read the buffers between the projections)
+    // (the partial forwards of the tests read the buffers between the projections: not these either)
     const bool f32_layer = with_head && f32_layer_supported(c, (long)T * k_rule);
-    if (f32_layer) SP_TRY(launch_f32_embed(M, L.layer0, ids, cu, B, T, x, qkv, rows, k, s));
+    // Students of hidden width 256: two launches a layer, the attention between them.  Embedding and the first q|k|v in one from 8192 rows on;
+    // below, the more workgroups of two launches are quicker to look up their rows.  us a call, eight launches a layer / embedding and q|k|v apart / in
+    // one, by tokens: one student 319 66.1 / 65.0 / 69.3, 1344 76.4 / 69.0 / 71.4, 2718 82.5 / 73.8 / 75.2, 5475 93.1 / 78.7 / 78.7, 9143 98.0 / 82.7 / 81.1,
+    // 14653 112.8 / 96.9 / 86.9; three 658 79.0 / 71.2 / 73.4, 2718 98.5 / 79.8 / 79.2, 5475 119.8 / 107.1 / 102.4, 9143 155.6 / 128.2 / 117.2, 14653 220.0 /
+    // 175.1 / 166.0.
+    const bool narrow = with_head && !fp8 && layer_supported(c);
+    const bool narrow_qkv = narrow && (int64_t)T * k_rule >= 8192 && !(first_only && c.layers == 1);
+    if (narrow_qkv) SP_TRY(launch_embed_qkv(M, L.layer0, ids, cu, B, T, x, att, qkv, vt, rows, mrows, k, s));
+    else if (f32_layer) SP_TRY(launch_f32_embed(M, L.layer0, ids, cu, B, T, x, qkv, rows, k, s));
     else SP_TRY(launch_embed_ln(M, ids, cu, B, T, rows, mrows, k, x, att, s, xq, kActQuantScale, attq));
     SP_MARK(SP_PHASE_EMBED);
     // Where the folded last layer follows, the rows stay as they are before the LayerNorm (see attention_first_fold_kernel) and only
@@ -500,7 +508,7 @@ static int run_students(const sp_model* M0, const WsLayout& W, const int32_t* id
     bool raw = false;
     for (int l = 0; l < stop_layers; ++l) {
         const size_t lo = L.layer0 + (size_t)l * L.layer_stride, pl = lo - L.layer_stride;
-        const bool fold_next = first_only && raw_pays && l == c.layers - 2;
+        const bool fold_next = first_only && raw_pays && !narrow && l == c.layers - 2;
         if (first_only && l == c.layers - 1) {
             const bool own = T >= kFirstOnlyMinTokens;
             const size_t sT = (size_t)rows * H, sC = (size_t)crows * H;
@@ -532,10 +540,10 @@ static int run_students(const sp_model* M0, const WsLayout& W, const int32_t* id
         if (fp8)
             SP_TRY(launch_gemm_fp8(M, xq, H, lo + L.wqkv8, lo + L.sqkv, lo + L.bqkv, kActQuantScale, qkv, 3 * H, nullptr, 0,
                                    mrows, 3 * H, H, k, EPI_QKV, qH, s3H, 0, s, vt, 2 * H, rows, sH, 1.f));
-        else if (bf16_path(c))
+        else if (bf16_path(c) && !(narrow_qkv && l == 0))
             SP_TRY(launch_gemm(M, x, H, lo + L.wqkv, lo + L.bqkv, qkv, 3 * H, nullptr, 0, mrows, 3 * H, H, k, EPI_QKV,
                                sH, s3H, 0, s, vt, 2 * H, rows, sH));
-        else if (!f32_layer)                                // (else the launch before has left q|k|v)
+        else if (!bf16_path(c) && !f32_layer)               // (else the launch before has left q|k|v)
             SP_TRY(launch_gemm(M, x, H, lo + L.wqkv, lo + L.bqkv, qkv, 3 * H, nullptr, 0, mrows, 3 * H, H, k, EPI_BIAS,
                                sH, s3H, 0, s));
         SP_MARK(SP_PHASE_QKV);
@@ -553,6 +561,11 @@ static int run_students(const sp_model* M0, const WsLayout& W, const int32_t* id
         }
         if (f32_layer) {
             SP_TRY(launch_f32_layer(M, lo, att, x, l + 1 < stop_layers ? qkv : nullptr, T, rows, k, s));
+            SP_MARK(SP_PHASE_FFN_DOWN);
+            continue;
+        }
+        if (narrow) {
+            SP_TRY(launch_layer(M, lo, att, x, x, rows, mrows, k, s));
             SP_MARK(SP_PHASE_FFN_DOWN);
             continue;
         }
@@ -620,7 +633,8 @@ static int run_students(const sp_model* M0, const WsLayout& W, const int32_t* id
 //     31 852 / 858, 61 1635 / 1675; 5: 52 1421 / 1432; 512 wide, 3: 20.9 492 / 506), and up to 64, beyond which a group alone fills the chip as
 //     well (768 wide, 8: 49 1302 / 1288, 58 1567 / 1555, 70 1850 / 1918, 84 2136-2200 / 2196-2220, 328 8196 / 8329; 4: 42 1141 / 1103, 58.5 1576 /
 //     1558, 82 2156 / 2220; six layers, 2: 41 5092 / 4897, 59 7306 / 7255, 82 9953 / 10314; 1024 wide, 6: 48 1501 / 1501, 107 3201 / 3226).
-//     Quantised and narrow students have no such limit (quantised, 8: 84 1498 / 1472, 164 2878 / 2853; 256 wide, 6: 161 2569 / 2539).
+//     Quantised and narrow students have no such limit (quantised, 8: 84 1498 / 1472, 164 2878 / 2853; 256 wide, 6: 161 2569 / 2539; with a layer
+//     in two launches: 6: 21 295 / 299, 52 653 / 639, 4: 35 444 / 440, 3: 26 339 / 341, 47 597 / 601).
 constexpr int64_t kTwoGroupsWork = 20 << 20, kTwoGroupsMostWork = 64 << 20;
 static bool two_groups_pay(const sp_config& c, int T, int k)
 {

@@ -330,6 +330,17 @@ hipError_t launch_gemm_fp8(const sp_model* M, const void* A8, int lda, size_t w_
 hipError_t launch_gelu_probe(const float* x, float* y, long n, hipStream_t s);
 hipError_t launch_gelu_q8_probe(const float* x, float* y, long n, hipStream_t s);
 
+// ---- students of hidden width 256 (sp_layer.hip; bf16 path): out = LN(x1 + FFN(x1)), x1 = LN(x + att Wo + bo), of mrows
+// rows per student (a multiple of 64; all three buffers [m][rows][256]; out may be x)
+bool layer_supported(const sp_config& c);
+hipError_t launch_layer(const sp_model* M, size_t lo, const void* att, const void* x, void* out, int rows, int mrows, int k,
+                        hipStream_t s);
+
+// x = LN(embedding) of T rows per student and q|k|v of the layer at lo from them (values transposed into vt); rows T..mrows: x and att
+// become zero
+hipError_t launch_embed_qkv(const sp_model* M, size_t lo, const int32_t* ids, const int32_t* cu, int B, int T, void* x, void* att, void* qkv,
+                            void* vt, int rows, int mrows, int k, hipStream_t s);
+
 // ---- projections of few rows (sp_rows.hip; bf16 path).  u: fp32 rows before a LayerNorm, [student][u_ss], row stride H.
 // Student strides (_ss) are in elements.
 // q|k|v of all T tokens (values transposed into vt) from the embedding rows (u null; g_off / b_off: the embedding
