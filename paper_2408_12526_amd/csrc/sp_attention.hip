@@ -56,7 +56,8 @@ __device__ inline uint2 chunk_to_fp8(uint4 c, float qscale)
 // three of the four waves idle: batches of them have a part of their own (attention_short).  us per launch, a wave per
 // sequence and head up to 128 tokens and 64 queries per wave above / this: 64 sequences of 64-512 tokens, 16 heads, one student
 // 84 / 66, six 466 / 335; 256 sequences of 8-256, 12 heads, eight students 238 / 214, two 65 / 54; 32 of 16-128, four students
-// 31 / 21; one of 64, one student 9.9 / 6.9.  Tried: keys and values in flight together (141 registers, three waves) 65, 357, 237,
+// 31 / 21; one of 64, one student 9.9 / 6.9.  With the next tile's keys in flight across the loop's end (they were waited for there, for
+// the sake of a copy) and a loop of their own for waves without queries 60.0 / 58.9, 345 / 339, two students of the third 32.3 / 31.6.  Tried: keys and values in flight together (141 registers, three waves) 65, 357, 237,
 // 60, 22 and 6.6; two heads per workgroup side by side where a sequence fits one tile: 382 for the second where one head took 340.
 // A reference that moves only when it is outgrown by 2^8 saves most rescaling (317 for the second), but then the largest
 // probability is no longer 1 and is rounded: up to 1.2 times the error against 64 bits on sharp distributions.
@@ -330,7 +331,7 @@ __global__ __launch_bounds__(256, 4) void attention_bf16_kernel(AttnArgs p)
         }
     };
     const int q = q0 + 32 * wave;                   // the wave's first query
-    bf16x8 qf[4], moving[2];
+    bf16x8 qf[4], kr[2], vr[2];
     f32x16 o[2];
     float mrun = -INFINITY, lrun = 0.f;             // running maximum (raw scores); sum over this lane's keys
     // LDS offsets of this lane's row in the current buffer, slot g; slot g + 2 n is at offset ^ 32 n
@@ -359,15 +360,19 @@ __global__ __launch_bounds__(256, 4) void attention_bf16_kernel(AttnArgs p)
             }
     };
     const bool wide = L > kNarrowLen;
-    auto tile = [&](int kt0) {
+    auto tile = [&](int kt0, auto busy) {            // busy: the wave has queries
         const bool more = kt0 + kKeyTile < L, two = kt0 + 32 < L;
         // (the other buffer is idle since the barrier of the previous tile)
         auto next_keys = [&] {                      // keys of the next tile down, its values requested
             if (!more) return;
-            stage_keys(dst ^ 2 * kTileBytes, moving);
-            fetch_values(kt0 + kKeyTile, moving);
+            stage_keys(dst ^ 2 * kTileBytes, kr);
+            __builtin_amdgcn_sched_barrier(0);
+            fetch_values(kt0 + kKeyTile, vr);
         };
-        if (q < L) {
+        // (Without a condition, in front of the last tile those of the last once more: behind a branch the compiler copies what is
+        // requested to the registers that the next tile expects it in, and waits for it before it can.)
+        auto keys_after = [&] { fetch_keys(kt0 + 2 * kKeyTile < L ? kt0 + 2 * kKeyTile : kt0 + kKeyTile, kr); };
+        if constexpr (decltype(busy)::value) {
             f32x16 s0 = scores(0), s1;
             if (two) s1 = scores(1);
             next_keys();
@@ -389,12 +394,16 @@ __global__ __launch_bounds__(256, 4) void attention_bf16_kernel(AttnArgs p)
                 weigh(s1, 1, psum);
             }
             lrun = lrun * alpha + psum;
-        } else {
+            if (more) {
+                stage_values(vdst ^ 2 * kTileBytes, vr);
+                __builtin_amdgcn_sched_barrier(0);
+                keys_after();
+            }
+        } else if (more) {
             next_keys();
-        }
-        if (more) {
-            stage_values(vdst ^ 2 * kTileBytes, moving);
-            if (kt0 + 2 * kKeyTile < L) fetch_keys(kt0 + 2 * kKeyTile, moving);
+            keys_after();
+            __builtin_amdgcn_sched_barrier(0);
+            stage_values(vdst ^ 2 * kTileBytes, vr);
         }
         barrier_lds();
         dst ^= 2 * kTileBytes;
@@ -409,7 +418,7 @@ __global__ __launch_bounds__(256, 4) void attention_bf16_kernel(AttnArgs p)
         const int r = q + j < L ? q + j : L - 1;
 #pragma unroll
         for (int s4 = 0; s4 < 4; ++s4) qf[s4] = *(const bf16x8*)(base + (size_t)r * ld + 16 * s4 + 8 * g);
-        if (kKeyTile - lead < L) fetch_keys(kKeyTile - lead, moving);
+        if (kKeyTile - lead < L) fetch_keys(kKeyTile - lead, kr);
 #pragma unroll
         for (int db = 0; db < 2; ++db)
 #pragma unroll
@@ -418,8 +427,12 @@ __global__ __launch_bounds__(256, 4) void attention_bf16_kernel(AttnArgs p)
         stage_values(vdst, v0);
     }
     barrier_lds();
-    for (int kt0 = -lead; kt0 < L; kt0 += kKeyTile) tile(kt0);
-    if (q >= L) return;
+    // (Two loops, a barrier per tile in either: where the two meet inside one, the compiler waits for the keys on their way.)
+    if (q >= L) {
+        for (int kt0 = -lead; kt0 < L; kt0 += kKeyTile) tile(kt0, std::false_type{});
+        return;
+    }
+    for (int kt0 = -lead; kt0 < L; kt0 += kKeyTile) tile(kt0, std::true_type{});
 
     int ln = tid;
     asm volatile("" : "+v"(ln));                    // (what follows from it is not kept through the loop)
