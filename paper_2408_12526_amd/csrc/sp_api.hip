@@ -528,8 +528,10 @@ static int run_students(const sp_model* M0, const WsLayout& W, const int32_t* id
             }
             SP_TRY(launch_fold_query(M, lo, x, rows, raw ? nullptr : cu, T, B, q1, s1, qt1, sq, k, s, raw, pl + L.ln2g));
             SP_MARK(SP_PHASE_LAST_FIRST);
+            // (scratch: the FFN's activations, which the last layer of such a call has elsewhere)
+            const bool split = own && fold_splits(c, B, T, (long)B * (T >= kLargeTokens ? c.K : k_rule), sF);
             SP_TRY(launch_attention_first_fold(M, raw ? u : x, qt1, sq, xb1, sx, cu, B, T, max_seqlen, rows, k, s, raw, pl + L.ln2g,
-                                               pl + L.ln2b));
+                                               pl + L.ln2b, split ? (float*)g : nullptr, sF / 4));
             SP_MARK(SP_PHASE_LAST_FIRST);
             SP_TRY(launch_rows_head_values(M, lo, xb1, sx, att1, s1, B, k, s));
             SP_MARK(SP_PHASE_LAST_FIRST);

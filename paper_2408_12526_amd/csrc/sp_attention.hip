@@ -527,9 +527,20 @@ struct FoldArgs {
     const char* arena;                // RAW: scale and shift (byte offsets into a student slab)
     size_t ss, g, b;
     float eps;
+    float* parts;                     // SPLIT: [student][p_ss], per item the unscaled rows of its heads (HEADS * H), then maximum and sum of each
+    size_t p_ss;
+    int B;
 };
 
-template <int HEADS, bool RAW>
+// SPLIT: sequences in parts of up to kFoldPart tokens, a workgroup each.  Item i belongs to the last sequence b with cu[b] / kFoldPart + b
+// <= i, as in the all-token kernel; a sequence's tiles of 32 tokens are dealt evenly over its parts, none of which is empty.  A sequence of
+// one part leaves its result, one of several its parts' unscaled sums for fold_join_kernel.
+constexpr int kFoldPartLog = 7, kFoldPart = 1 << kFoldPartLog;
+__device__ __forceinline__ int fold_parts(int L) { return (L + kFoldPart - 1) >> kFoldPartLog; }
+template <int HEADS>
+constexpr size_t fold_item_floats() { return (size_t)HEADS * HEADS * kD + 2 * HEADS; }
+
+template <int HEADS, bool RAW, bool SPLIT>
 __global__ __launch_bounds__((64 * FoldLds<HEADS, RAW>::NW), (HEADS == 16 ? 2 : 4)) void attention_first_fold_kernel(FoldArgs p)
 {
     using F = FoldLds<HEADS, RAW>;
@@ -546,16 +557,27 @@ __global__ __launch_bounds__((64 * FoldLds<HEADS, RAW>::NW), (HEADS == 16 ? 2 : 
     const int32_t* cu = p.cu;
     const int Tn = p.Tn, rows = p.rows, max_seqlen = p.max_seqlen;
     const size_t qt_ss = p.qt_ss;
-    const int m = blockIdx.y, b = blockIdx.x;
+    const int m = blockIdx.y, item = blockIdx.x;
     const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    int t0, t1, b = item;
+    if (SPLIT) b = last_sequence(cu, p.B, lane, [&](int i, int c) { return (c >> kFoldPartLog) + i <= item; }, t0, t1);
+    else { t0 = cu[b]; t1 = cu[b + 1]; }
+    const int part_of = SPLIT ? item - ((t0 >> kFoldPartLog) + b) : 0;
     char* slab = (char*)fold_smem + wave * F::slab_bytes;   // this wave's features of the tile: [token][FW / 8 chunks]
     bf16* xb = p.xbar + (size_t)m * p.xb_ss + (size_t)b * HEADS * H;
-    int t0 = cu[b], t1 = cu[b + 1];
     t0 = t0 < 0 ? 0 : (t0 > Tn - 1 ? Tn - 1 : t0);
     int L = t1 - t0;
     L = L < 1 ? 1 : L;
     L = L > max_seqlen ? max_seqlen : L;
     L = L > Tn - t0 ? Tn - t0 : L;
+    bool whole = true;
+    if (SPLIT) {
+        const int n = fold_parts(L), each = ((L + 31) / 32 + n - 1) / n * 32;
+        if (part_of < 0 || part_of >= n) return;            // (the whole workgroup: an item without tokens)
+        t0 += part_of * each;
+        L = L - part_of * each < each ? L - part_of * each : each;
+        whole = n == 1;
+    }
     const int l16 = lane & 15, kg = lane >> 4;
     const bf16* xw = x + ((size_t)m * rows + t0) * H + wave * FW + 8 * kg;   // this lane's features of the first token
     const int nt = (L + 31) >> 5;
@@ -734,7 +756,20 @@ __global__ __launch_bounds__((64 * FoldLds<HEADS, RAW>::NW), (HEADS == 16 ? 2 : 
     // (the lane is counted anew, so that nothing that follows from it is kept through the loop)
     const int ln = (int)__builtin_amdgcn_mbcnt_hi(~0u, __builtin_amdgcn_mbcnt_lo(~0u, 0u));
     const int fh = ln & 15, fk = ln >> 4;                   // head; group of four rows
-    const float inv = 1.0f / sum_across_rows(lrun);
+    const float sum = sum_across_rows(lrun), inv = 1.0f / sum;
+    if (SPLIT && !whole) {
+        float* const out = p.parts + (size_t)m * p.p_ss + (size_t)item * fold_item_floats<HEADS>();
+        if (fh < HEADS) {
+#pragma unroll
+            for (int gq = 0; gq < KS; ++gq)
+#pragma unroll
+                for (int i = 0; i < 8; i += 4)
+                    *(f32x4*)(out + (size_t)fh * H + wave * FW + 32 * gq + 8 * fk + i) =
+                        f32x4{acc[2 * gq][i >> 1], acc[2 * gq + 1][i >> 1], acc[2 * gq][(i >> 1) + 1], acc[2 * gq + 1][(i >> 1) + 1]};
+            if (wave == 0 && fk == 0) *(f32x2*)(out + HEADS * H + 2 * fh) = f32x2{mrun, sum};
+        }
+        return;
+    }
     const float *gam = (const float*)(p.arena + (size_t)m * p.ss + p.g) + wave * FW, *bet = (const float*)(p.arena + (size_t)m * p.ss + p.b) + wave * FW;
     float common = 0.f;                                     // mean of the head's weighted row over the features
     if (RAW) {
@@ -762,6 +797,67 @@ __global__ __launch_bounds__((64 * FoldLds<HEADS, RAW>::NW), (HEADS == 16 ? 2 : 
             }
             *(bf16x8*)(xb + (size_t)fh * H + wave * FW + 32 * gq + 8 * fk) = r;
         }
+    }
+}
+
+// Sequences of several parts: their sums at a common maximum, scaled (RAW: with the LayerNorm's scale and shift as above); a wave per head.
+template <int HEADS, bool RAW>
+__global__ __launch_bounds__(256) void fold_join_kernel(FoldArgs p)
+{
+    constexpr int H = HEADS * kD, NC = (H / 4 + 63) / 64;   // chunks of four features per lane
+    const int m = blockIdx.y, b = blockIdx.x / (HEADS / 4), lane = threadIdx.x & 63;
+    const int h = (int)(blockIdx.x % (HEADS / 4)) * 4 + __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    int t0 = p.cu[b], t1 = p.cu[b + 1];
+    int first = (t0 >> kFoldPartLog) + b;
+    t0 = t0 < 0 ? 0 : (t0 > p.Tn - 1 ? p.Tn - 1 : t0);
+    int L = t1 - t0;
+    L = L < 1 ? 1 : L;
+    L = L > p.max_seqlen ? p.max_seqlen : L;
+    L = L > p.Tn - t0 ? p.Tn - t0 : L;
+    const int n = fold_parts(L);
+    if (n == 1) return;
+    const int last = (p.Tn >> kFoldPartLog) + p.B - n;      // (boundaries out of order: some items, but no others than there are)
+    first = first < 0 ? 0 : (first > last ? last : first);
+    const float* from = p.parts + (size_t)m * p.p_ss + (size_t)first * fold_item_floats<HEADS>();
+    f32x4 acc[NC];
+#pragma unroll
+    for (int c = 0; c < NC; ++c) acc[c] = f32x4{0.f, 0.f, 0.f, 0.f};
+    float mrun = -INFINITY, lrun = 0.f;
+    for (int i = 0; i < n; ++i, from += fold_item_floats<HEADS>()) {
+        const f32x2 ml = *(const f32x2*)(from + HEADS * H + 2 * h);
+        f32x4 v[NC];
+#pragma unroll
+        for (int c = 0; c < NC; ++c) {
+            const int e = 4 * (lane + 64 * c);
+            v[c] = e < H ? *(const f32x4*)(from + (size_t)h * H + e) : f32x4{0.f, 0.f, 0.f, 0.f};
+        }
+        const float mx = fmaxf(mrun, ml[0]), down = exp2_raw(mrun - mx), w = exp2_raw(ml[0] - mx);      // (first part: exp2(-inf) = 0)
+        mrun = mx;
+        lrun = fmaf(lrun, down, ml[1] * w);
+#pragma unroll
+        for (int c = 0; c < NC; ++c) acc[c] = acc[c] * down + v[c] * w;
+    }
+    const float inv = 1.0f / lrun;
+    float common = 0.f;
+    if (RAW) {
+#pragma unroll
+        for (int c = 0; c < NC; ++c) common += acc[c][0] + acc[c][1] + (acc[c][2] + acc[c][3]);
+        common = wave_sum(common) * (1.0f / H);
+    }
+    const char* sb = p.arena + (size_t)m * p.ss;
+    bf16* out = p.xbar + (size_t)m * p.xb_ss + ((size_t)b * HEADS + h) * H;
+#pragma unroll
+    for (int c = 0; c < NC; ++c) {
+        const int e0 = 4 * (lane + 64 * c);
+        if (e0 >= H) continue;
+        bf16x4 o;
+#pragma unroll
+        for (int e = 0; e < 4; ++e) {
+            float v = (acc[c][e] - common) * inv;
+            if (RAW) v = ((const float*)(sb + p.g))[e0 + e] * v + ((const float*)(sb + p.b))[e0 + e];
+            o[e] = (bf16)v;
+        }
+        *(bf16x4*)(out + e0) = o;
     }
 }
 
@@ -919,18 +1015,29 @@ bool attention_first_fold_supported(const sp_config& c, int max_seqlen)
     return bf16_path(c) && c.hidden / c.heads == kD && c.heads % 4 == 0 && c.heads <= 16;
 }
 
+// Whether sequences are split, in calls that have the buffers for it.  work: sequences x students.  Few long sequences alone, by the mean
+// length, all the host knows: a part costs the way to its first rows (3-4 us; a tile of 32 tokens takes 1.4-3 us) and its sums a write, a
+// read and one more launch.  us a call, whole / split, by sequences x students, mean: 768 wide: 4 400 130 / 117, 16 512 228 / 215, 32 140 161 / 163,
+// 64 190 316 / 316, 256 140 697 / 710, 256 319 804 / 790; six layers: 32 382 1231 / 1220; 1024 wide: 4 377 148 / 136, 96 191 594 / 594, 252 287
+// 2093 / 2117; 256 wide: 48 317 98.6 / 95.7, 255 192 161.5 / 163.8.
+bool fold_splits(const sp_config& c, int B, int T, long work, size_t bytes)
+{
+    const size_t items = (size_t)(T >> kFoldPartLog) + B, floats = (size_t)c.heads * c.hidden + 2 * c.heads;
+    return T >= (int64_t)2 * kFoldPart * B && work <= 128 && items * floats * 4 <= bytes;
+}
+
 hipError_t launch_attention_first_fold(const sp_model* M, const void* x, const void* qt, size_t qt_ss, void* xbar,
                                        size_t xb_ss, const int32_t* cu, int B, int T, int max_seqlen, int rows, int k,
-                                       hipStream_t s, bool raw, size_t g_off, size_t b_off)
+                                       hipStream_t s, bool raw, size_t g_off, size_t b_off, float* parts, size_t p_ss)
 {
     const sp_config& c = M->cfg;
     if (!attention_first_fold_supported(c, max_seqlen)) return hipErrorInvalidValue;
     const FoldArgs a{(const bf16*)x, (const bf16*)qt, (bf16*)xbar, qt_ss, xb_ss, cu, T, rows, max_seqlen, M->arena, M->L.student_stride,
-                     g_off, b_off, c.ln_eps};
-    dim3 grid((unsigned)B, (unsigned)k);
-#define SP_FOLD(HEADS, RAW)                                                                                         \
+                     g_off, b_off, c.ln_eps, parts, p_ss, B};
+    const dim3 grid((unsigned)(parts ? (T >> kFoldPartLog) + B : B), (unsigned)k);
+#define SP_FOLD(HEADS, RAW, SPLIT)                                                                                  \
     do {                                                                                                            \
-        auto kern = attention_first_fold_kernel<HEADS, RAW>;                                                        \
+        auto kern = attention_first_fold_kernel<HEADS, RAW, SPLIT>;                                                 \
         constexpr size_t smem = FoldLds<HEADS, RAW>::bytes;                                                         \
         static std::atomic<bool> raised{false}; /* the attribute is sticky for the process */                      \
         if (smem > 48 * 1024 && !raised) {                                                                          \
@@ -939,9 +1046,15 @@ hipError_t launch_attention_first_fold(const sp_model* M, const void* x, const v
             if (e != hipSuccess) return e;                                                                          \
             raised = true;                                                                                          \
         }                                                                                                           \
-        hipLaunchKernelGGL(kern, grid, dim3((64 * FoldLds<HEADS, RAW>::NW)), smem, s, a);                                          \
+        hipLaunchKernelGGL(kern, grid, dim3((64 * FoldLds<HEADS, RAW>::NW)), smem, s, a);                           \
+        if (SPLIT) {                                                                                                \
+            const hipError_t e = hipGetLastError();                                                                 \
+            if (e != hipSuccess) return e;                                                                          \
+            hipLaunchKernelGGL((fold_join_kernel<HEADS, RAW>), dim3((unsigned)(B * (HEADS / 4)), (unsigned)k), dim3(256), 0, s, a); \
+        }                                                                                                           \
     } while (0)
-#define SP_FOLD_ANY(HEADS) do { if (raw) SP_FOLD(HEADS, true); else SP_FOLD(HEADS, false); } while (0)
+#define SP_FOLD_RAW(HEADS, RAW) do { if (parts) SP_FOLD(HEADS, RAW, true); else SP_FOLD(HEADS, RAW, false); } while (0)
+#define SP_FOLD_ANY(HEADS) do { if (raw) SP_FOLD_RAW(HEADS, true); else SP_FOLD_RAW(HEADS, false); } while (0)
     switch (c.heads) {
         case 4: SP_FOLD_ANY(4); break;
         case 8: SP_FOLD_ANY(8); break;
@@ -949,6 +1062,7 @@ hipError_t launch_attention_first_fold(const sp_model* M, const void* x, const v
         default: SP_FOLD_ANY(16); break;
     }
 #undef SP_FOLD_ANY
+#undef SP_FOLD_RAW
 #undef SP_FOLD
     return hipGetLastError();
 }

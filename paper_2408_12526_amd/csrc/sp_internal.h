@@ -400,10 +400,12 @@ hipError_t launch_attention(const sp_model* M, const void* qkv, const void* vt, 
 // p = softmax_t(qt[m][b][h] . x[m][t] / 8) over the tokens t of the sequence and xbar[m][b][h][:] = sum_t p_t x[m][t][:].
 // qt and xbar are [m][.._ss elements], rows of [heads][H].  raw: x holds rows before their LayerNorm (g_off, b_off), and qt carries
 // its scale.
+// parts (may be null): scratch for sequences split over workgroups, p_ss floats per student (fold_splits says whether it pays and suffices).
 bool attention_first_fold_supported(const sp_config& c, int max_seqlen);
+bool fold_splits(const sp_config& c, int B, int T, long work, size_t bytes);
 hipError_t launch_attention_first_fold(const sp_model* M, const void* x, const void* qt, size_t qt_ss, void* xbar,
                                        size_t xb_ss, const int32_t* cu, int B, int T, int max_seqlen, int rows, int k,
-                                       hipStream_t s, bool raw, size_t g_off, size_t b_off);
+                                       hipStream_t s, bool raw, size_t g_off, size_t b_off, float* parts, size_t p_ss);
 
 // Head on the pooler's sums without bias (fp32 rows, p_ss elements from student to student): z[m][b][c] = tanh(sums + bp) . Wc + bc;
 // logits[b][c] = sum_{m<k} z[m][b][c] (m ascending; not written if null).
