@@ -260,11 +260,11 @@ __global__ __launch_bounds__(256) void layernorm_first_kernel(const char* arena,
 // Sum of the slices of a split reduction + bias + residual, then LayerNorm: one wave per row.  Rows T..mrows become zero:
 // attention multiplies the values of up to seven of them by zero probabilities, so what the next layer forms there
 // must be finite, and the operands of this projection need not be (the slices lie over the attention output's padding rows).
-constexpr int kMaxSlices = 8;
-template <int MAXC>
+// All loads of a row are requested at once, without a branch between them (one per chunk made a second round trip to memory of it).
+template <int MAXC, int SLICES>
 __global__ __launch_bounds__(256) void ln_slices_kernel(const char* arena, size_t student_stride, size_t g_off, size_t b_off,
                                                         size_t bias_off, const float* __restrict__ part, size_t slice,
-                                                        size_t p_ss, int splits, const bf16* __restrict__ res,
+                                                        size_t p_ss, const bf16* __restrict__ res,
                                                         bf16* __restrict__ out, int rows, int T, int mrows, int H, float eps)
 {
     const int m = blockIdx.y, lane = threadIdx.x & 63;
@@ -278,30 +278,34 @@ __global__ __launch_bounds__(256) void ln_slices_kernel(const char* arena, size_
         return;
     }
     const char* sb = arena + (size_t)m * student_stride;
-    float gg[MAXC][8], bb[MAXC][8];
-    load_gamma_beta<MAXC>((const float*)(sb + g_off), (const float*)(sb + b_off), nch, lane, gg, bb);
     const float* bias = (const float*)(sb + bias_off);
     const bf16* rrow = res + ((size_t)m * rows + row) * H;
     const float* prow = part + (size_t)m * p_ss + (size_t)row * H;
-    float v[MAXC][8];
+    float v[MAXC][8], gg[MAXC][8], bb[MAXC][8];
+    Raw8<bf16> r8[MAXC];
+    Raw8<float> b8[MAXC], p8[SLICES][MAXC];
+#pragma unroll
+    for (int i = 0; i < MAXC; ++i) {                        // (lanes behind the row's end: its last chunk, and nothing comes of it)
+        const int c = (lane + 64 * i < nch ? lane + 64 * i : nch - 1) * 8;
+#pragma unroll
+        for (int sl = 0; sl < SLICES; ++sl) p8[sl][i] = *(const Raw8<float>*)(prow + (size_t)sl * slice + c);
+        r8[i] = *(const Raw8<bf16>*)(rrow + c);
+        b8[i] = *(const Raw8<float>*)(bias + c);
+    }
+    load_gamma_beta<MAXC>((const float*)(sb + g_off), (const float*)(sb + b_off), nch, lane, gg, bb);
+    __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
     for (int i = 0; i < MAXC; ++i) {
-        const int c = lane + 64 * i;
-        if (c < nch) {
-            float r8[8], b8[8], p8[kMaxSlices][8];            // all slices requested at once, added in ascending order
-            load8(rrow + c * 8, r8);
-            load8(bias + c * 8, b8);
+        float t[8];
+        widen(r8[i], v[i]);
+        widen(b8[i], t);
 #pragma unroll
-            for (int sidx = 0; sidx < kMaxSlices; ++sidx)
-                if (sidx < splits) load8(prow + (size_t)sidx * slice + c * 8, p8[sidx]);
+        for (int e = 0; e < 8; ++e) v[i][e] += t[e];
 #pragma unroll
-            for (int e = 0; e < 8; ++e) v[i][e] = r8[e] + b8[e];
+        for (int sl = 0; sl < SLICES; ++sl) {               // ascending
+            widen(p8[sl][i], t);
 #pragma unroll
-            for (int sidx = 0; sidx < kMaxSlices; ++sidx)
-                if (sidx < splits) {
-#pragma unroll
-                    for (int e = 0; e < 8; ++e) v[i][e] += p8[sidx][e];
-                }
+            for (int e = 0; e < 8; ++e) v[i][e] += t[e];
         }
     }
     ln_row_store<bf16, MAXC>(v, nch, lane, H, gg, bb, eps, orow);
@@ -687,12 +691,17 @@ hipError_t launch_ln_slices(const sp_model* M, const float* part, size_t slice, 
                             hipStream_t s)
 {
     const sp_config& c = M->cfg;
-    if (!bf16_path(c) || splits < 1 || splits > kMaxSlices || c.hidden > 1024) return hipErrorInvalidValue;
+    if (!bf16_path(c) || c.hidden > 1024) return hipErrorInvalidValue;
     dim3 grid((mrows + 3) / 4, k);
-#define SP_LNS(MAXC)                                                                                               \
-    hipLaunchKernelGGL((ln_slices_kernel<MAXC>), grid, dim3(256), 0, s, M->arena, M->L.student_stride, g_off, b_off, bias_off, \
-                       part, slice, p_ss, splits, (const bf16*)residual, (bf16*)out, rows, T, mrows, c.hidden, c.ln_eps)
-    if (c.hidden <= 512) SP_LNS(1); else SP_LNS(2);
+#define SP_LNS(MAXC, SLICES)                                                                                       \
+    hipLaunchKernelGGL((ln_slices_kernel<MAXC, SLICES>), grid, dim3(256), 0, s, M->arena, M->L.student_stride, g_off, b_off, bias_off, \
+                       part, slice, p_ss, (const bf16*)residual, (bf16*)out, rows, T, mrows, c.hidden, c.ln_eps)
+#define SP_GO(SLICES) case SLICES: if (c.hidden <= 512) SP_LNS(1, SLICES); else SP_LNS(2, SLICES); break
+    switch (splits) {                                       // (what callers choose from)
+        SP_GO(2); SP_GO(3); SP_GO(4); SP_GO(6); SP_GO(8);
+        default: return hipErrorInvalidValue;
+    }
+#undef SP_GO
 #undef SP_LNS
     return hipGetLastError();
 }
