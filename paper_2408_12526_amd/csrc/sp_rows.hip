@@ -694,7 +694,9 @@ struct RowsAdd {
     const int32_t* cu;                // null: residual row r
     int Tn;
 };
-template <int MAXC, bool ADD>
+// NC: chunks of 256 features, the last one perhaps half.  Everything that a row takes is requested at once, without a branch between the
+// loads: one per chunk, in front of the chunk's sums and again of its scale and shift, made six memory round trips of one.
+template <int NC, bool ADD>
 __global__ __launch_bounds__(256) void rows_ln_kernel(const char* arena, size_t ss, size_t g_off, size_t b_off,
                                                       const float* __restrict__ u, size_t u_ss, RowsAdd add,
                                                       bf16* __restrict__ out, size_t o_ss, int M, int H, float eps)
@@ -704,42 +706,44 @@ __global__ __launch_bounds__(256) void rows_ln_kernel(const char* arena, size_t 
     const char* sb = arena + (size_t)m * ss;
     const float* ur = u + (size_t)m * u_ss + (size_t)row * H;
     const bf16* rr = ADD ? add.res + (size_t)m * add.r_ss + (size_t)(add.cu ? first_row(add.cu, row, add.Tn) : row) * H : nullptr;
-    f32x4 v[MAXC];
+    // (lanes behind the row's end: its last four features, which do not count)
+    auto in_row = [&](int c) { return c + 1 < NC || 4 * (lane + 64 * c) < H; };
+    auto el = [&](int c) { return in_row(c) ? 4 * (lane + 64 * c) : H - 4; };
+    f32x4 v[NC], bias[NC], g[NC], b[NC];
+    bf16x4 r[NC];
+#pragma unroll
+    for (int c = 0; c < NC; ++c) {
+        v[c] = *(const f32x4*)(ur + el(c));
+        if (ADD) {
+            bias[c] = *(const f32x4*)((const float*)(sb + add.bias) + el(c));
+            r[c] = *(const bf16x4*)(rr + el(c));
+        }
+        g[c] = *(const f32x4*)((const float*)(sb + g_off) + el(c));
+        b[c] = *(const f32x4*)((const float*)(sb + b_off) + el(c));
+    }
+    __builtin_amdgcn_sched_barrier(0);
     float s = 0.f;
 #pragma unroll
-    for (int c = 0; c < MAXC; ++c) {
-        const int e0 = 4 * (lane + 64 * c);
-        v[c] = f32x4{0.f, 0.f, 0.f, 0.f};
-        if (e0 < H) {
-            v[c] = *(const f32x4*)(ur + e0);
-            if (ADD) {
-                const f32x4 b = *(const f32x4*)((const float*)(sb + add.bias) + e0);
-                const bf16x4 r = *(const bf16x4*)(rr + e0);
+    for (int c = 0; c < NC; ++c) {
 #pragma unroll
-                for (int e = 0; e < 4; ++e) v[c][e] = v[c][e] + b[e] + (float)r[e];
-            }
+        for (int e = 0; e < 4; ++e) {
+            if (ADD) v[c][e] = v[c][e] + bias[c][e] + (float)r[c][e];
+            s += in_row(c) ? v[c][e] : 0.f;
         }
-#pragma unroll
-        for (int e = 0; e < 4; ++e) s += v[c][e];
     }
     const float inv_h = __builtin_amdgcn_rcpf((float)H), mean = wave_sum(s) * inv_h;
     float q = 0.f;
 #pragma unroll
-    for (int c = 0; c < MAXC; ++c)
-        if (4 * (lane + 64 * c) < H)
+    for (int c = 0; c < NC; ++c)
 #pragma unroll
-            for (int e = 0; e < 4; ++e) { const float d = v[c][e] - mean; q += d * d; }
+        for (int e = 0; e < 4; ++e) { const float d = in_row(c) ? v[c][e] - mean : 0.f; q += d * d; }
     const float inv = __builtin_amdgcn_rsqf(wave_sum(q) * inv_h + eps);
 #pragma unroll
-    for (int c = 0; c < MAXC; ++c) {
-        const int e0 = 4 * (lane + 64 * c);
-        if (e0 < H) {
-            const f32x4 g = *(const f32x4*)((const float*)(sb + g_off) + e0), b = *(const f32x4*)((const float*)(sb + b_off) + e0);
-            bf16x4 o;
+    for (int c = 0; c < NC; ++c) {
+        bf16x4 o;
 #pragma unroll
-            for (int e = 0; e < 4; ++e) o[e] = (bf16)(g[e] * ((v[c][e] - mean) * inv) + b[e]);
-            *(bf16x4*)(out + (size_t)m * o_ss + (size_t)row * H + e0) = o;
-        }
+        for (int e = 0; e < 4; ++e) o[e] = (bf16)(g[c][e] * ((v[c][e] - mean) * inv) + b[c][e]);
+        if (in_row(c)) *(bf16x4*)(out + (size_t)m * o_ss + (size_t)row * H + el(c)) = o;
     }
 }
 
@@ -976,9 +980,12 @@ hipError_t launch_rows_ln_any(const sp_model* M, size_t g_off, size_t b_off, con
     const sp_config& c = M->cfg;
     if (!bf16_path(c) || nrows < 1) return hipErrorInvalidValue;
     const dim3 grid((unsigned)((nrows + 3) / 4), (unsigned)k);
-#define SP_GO(MAXC) hipLaunchKernelGGL((rows_ln_kernel<MAXC, ADD>), grid, dim3(256), 0, s, M->arena, M->L.student_stride, g_off, \
-                                       b_off, u, u_ss, add, (bf16*)out, o_ss, nrows, c.hidden, c.ln_eps)
-    if (c.hidden <= 256) SP_GO(1); else SP_GO(4);
+#define SP_GO(NC) case NC: hipLaunchKernelGGL((rows_ln_kernel<NC, ADD>), grid, dim3(256), 0, s, M->arena, M->L.student_stride, g_off, \
+                                       b_off, u, u_ss, add, (bf16*)out, o_ss, nrows, c.hidden, c.ln_eps); break
+    switch ((c.hidden + 255) / 256) {
+        SP_GO(1); SP_GO(2); SP_GO(3); SP_GO(4);
+        default: return hipErrorInvalidValue;
+    }
 #undef SP_GO
     return hipGetLastError();
 }
