@@ -483,6 +483,7 @@ static int run_students(const sp_model* M0, const WsLayout& W, const int32_t* id
     }
     // (the partial forwards of the tests read the buffers between the projections: not these either)
     const bool f32_layer = with_head && f32_layer_supported(c, (long)T * k_rule);
+    char* const f32_other = w + W.vt + m0 * s3H;            // values, attention output and pre-LayerNorm rows lie one behind another
     // Students of hidden width 256: two launches a layer, the attention between them.  Embedding and the first q|k|v in one from 8192 rows on;
     // below, the more workgroups of two launches are quicker to look up their rows.  us a call, eight launches a layer / embedding and q|k|v apart / in
     // one, by tokens: one student 319 66.1 / 65.0 / 69.3, 1344 76.4 / 69.0 / 71.4, 2718 82.5 / 73.8 / 75.2, 5475 93.1 / 78.7 / 78.7, 9143 98.0 / 82.7 / 81.1,
@@ -549,23 +550,26 @@ static int run_students(const sp_model* M0, const WsLayout& W, const int32_t* id
             SP_TRY(launch_gemm(M, x, H, lo + L.wqkv, lo + L.bqkv, qkv, 3 * H, nullptr, 0, mrows, 3 * H, H, k, EPI_BIAS,
                                sH, s3H, 0, s));
         SP_MARK(SP_PHASE_QKV);
+        if (f32_layer) {
+            // (the rows' q|k|v alternate between their buffer and the three behind it: other workgroups read those of a layer while the
+            // next one's are written)
+            char* const own = l & 1 ? f32_other : qkv;
+            if (l == c.layers - 1 && !c.last_layer_all_tokens) {
+                SP_TRY(launch_f32_last(M, lo, own, x, cu, B, T, max_seqlen, rows, k, z, s));
+                SP_MARK(SP_PHASE_LAST_FIRST);
+                if (logits) SP_TRY(launch_sum_students(z, B * c.classes, k, logits, s));
+                SP_MARK(SP_PHASE_HEAD);
+                return SP_OK;
+            }
+            SP_TRY(launch_f32_layer(M, lo, own, x, l + 1 < stop_layers ? (l & 1 ? qkv : f32_other) : nullptr, cu, B, T, max_seqlen, rows, k, s));
+            SP_MARK(SP_PHASE_FFN_DOWN);
+            continue;
+        }
         // (quantised students: the output projection reads the fp8 copy only, so a whole forward skips the bf16 one;
         // the partial forwards of the tests keep it)
         SP_TRY(launch_attention(M, qkv, vt, fp8 && with_head ? nullptr : att, cu, B, T, max_seqlen, rows, k, s, attq,
                                 kActQuantScale));
         SP_MARK(SP_PHASE_ATTENTION);
-        if (f32_layer && l == c.layers - 1 && !c.last_layer_all_tokens) {
-            SP_TRY(launch_f32_last(M, lo, att, x, cu, B, T, rows, k, z, s));
-            SP_MARK(SP_PHASE_LAST_FIRST);
-            if (logits) SP_TRY(launch_sum_students(z, B * c.classes, k, logits, s));
-            SP_MARK(SP_PHASE_HEAD);
-            return SP_OK;
-        }
-        if (f32_layer) {
-            SP_TRY(launch_f32_layer(M, lo, att, x, l + 1 < stop_layers ? qkv : nullptr, T, rows, k, s));
-            SP_MARK(SP_PHASE_FFN_DOWN);
-            continue;
-        }
         if (narrow) {
             SP_TRY(launch_layer(M, lo, att, x, x, rows, mrows, k, s));
             SP_MARK(SP_PHASE_FFN_DOWN);

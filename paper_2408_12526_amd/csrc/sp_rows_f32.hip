@@ -26,6 +26,8 @@ namespace {
 constexpr int kWaves = 8, kRows = 2, H = 128;             // (see f32_layer_supported)
 constexpr int kAhead = 4;                                   // blocks of weights in registers
 
+constexpr int kPart = 68;                                   // floats of LDS per wave: its sums of a row's and head's values, maximum, sum
+
 enum { FROM_EMBEDDING, FROM_ATTENTION };                   // what the rows come from
 enum { TO_QKV, TO_ROWS, TO_CLASSES };                       // and what is made of them: q|k|v, x alone, the students' classifier outputs
 
@@ -34,10 +36,11 @@ struct F32LayerArgs {
     size_t ss, wo, bo, g1, be1, w1, b1, w2, b2, g2, be2;    // byte offsets into a student slab (FROM_EMBEDDING: g2, be2 alone)
     size_t wn, bn;                    // what follows the last LayerNorm: q|k|v or the pooler, [out][in]
     size_t wc, bc, tok, pos;
-    const float* att;
-    float *x, *qkv, *z;               // student strides: rows x H, rows x H, rows x 3 H, M x C
+    const float* qkv;                 // FROM_ATTENTION: queries, keys and values of the rows
+    float *x, *qkv_out, *z;           // student strides: rows x H, rows x 3 H, M x C
     const int32_t *ids, *cu;
     int M, Tn, rows, B, C, V, P;      // M: rows to compute (tokens, or first tokens of sequences)
+    int max_seqlen;
     float eps;
 };
 
@@ -114,8 +117,102 @@ __device__ __forceinline__ void each(Fn f) { each_of(std::make_integer_sequence<
 template <int FROM, int TO, int FB>
 constexpr int f32_layer_floats()                            // of LDS; see the kernel's carve-up
 {
-    return kRows * H + 2 * H + (TO == TO_QKV ? 3 : 1) * H + (FROM == FROM_EMBEDDING ? 0 : kRows * (H + 128 * FB) + 4 * H + 128 * FB);
+    return kRows * H + 2 * H + (TO == TO_QKV ? 3 : 1) * H + (FROM == FROM_EMBEDDING ? 0 : kRows * (H + 128 * FB) + 4 * H + 128 * FB + kWaves * kPart);
 }
+
+// Attention of one row and head by two waves, every other 32 keys each: sixteen lanes share a key (four dimensions each), four keys side
+// by side, 64 keys of both waves per step; the first step's keys and values are requested together by begin().  Running softmax with
+// exact exponentials; the wave's sums (unscaled), maximum and sum of the weights go to LDS, and a wave without keys leaves none.
+struct RowAttention {
+    const float* keys;                                      // of the sequence's first token, this lane's dimensions; values: H behind
+    int L, first;                                           // first: the wave's first key
+    f32x4 q, k[8], v[8];
+
+    __device__ __forceinline__ int key(int s0, int i, int lane) const { return s0 + first + 4 * i + (lane >> 4); }
+    __device__ __forceinline__ void request(int s0, int lane)
+    {
+#pragma unroll
+        for (int i = 0; i < 8; ++i) {
+            const int t = key(s0, i, lane) < L ? key(s0, i, lane) : L - 1;
+            k[i] = *(const f32x4*)(keys + (size_t)t * 3 * H);
+            v[i] = *(const f32x4*)(keys + (size_t)t * 3 * H + H);
+        }
+    }
+    // row: index of the sequence (of_first), else of the token
+    __device__ __forceinline__ void begin(const F32LayerArgs& p, const float* qkv, bool of_first, int row, int token, int head, int half, int lane)
+    {
+        int t0, t1;
+        if (of_first) { t0 = p.cu[row]; t1 = p.cu[row + 1]; }
+        else last_sequence(p.cu, p.B, lane, [&](int, int c) { return c <= row; }, t0, t1);
+        t0 = t0 < 0 ? 0 : (t0 > p.Tn - 1 ? p.Tn - 1 : t0);
+        L = t1 - t0;
+        L = L < 1 ? 1 : L;
+        L = L > p.max_seqlen ? p.max_seqlen : L;
+        L = L > p.Tn - t0 ? p.Tn - t0 : L;
+        first = 32 * half;
+        const int d = head * 64 + (lane & 15) * 4;
+        q = *(const f32x4*)(qkv + (size_t)token * 3 * H + d);
+        keys = qkv + (size_t)t0 * 3 * H + H + d;
+        request(0, lane);
+    }
+    __device__ __forceinline__ void run(float* out, int lane)
+    {
+        float mrun = -INFINITY, lrun = 0.f;
+        f32x4 o = {0.f, 0.f, 0.f, 0.f};
+        for (int s0 = 0;;) {
+            float s[8], mx = mrun;
+#pragma unroll
+            for (int i = 0; i < 8; ++i) {
+                float a = q[0] * k[i][0];
+#pragma unroll
+                for (int e = 1; e < 4; ++e) a = fmaf(q[e], k[i][e], a);
+                a += dpp_moved<kDppPair>(a);
+                a += dpp_moved<kDppQuad>(a);
+                a += dpp_moved<kDppHalfRowMirror>(a);
+                a += dpp_moved<kDppRowMirror>(a);
+                s[i] = key(s0, i, lane) < L ? a * 0.125f : -INFINITY;
+                mx = fmaxf(mx, s[i]);
+            }
+            float a = mx, b = mx;
+            swap_rows(a, b);
+            mx = fmaxf(a, b);
+            a = mx;
+            b = mx;
+            swap_halves(a, b);
+            mx = fmaxf(a, b);
+            const float ref = mx == -INFINITY ? 0.f : mx, alpha = expf(mrun - ref);     // (no key of the wave's yet: weights of zero)
+            mrun = mx;
+            lrun *= alpha;
+            o *= alpha;
+#pragma unroll
+            for (int i = 0; i < 8; ++i) {
+                const float w = expf(s[i] - ref);
+                lrun += w;
+                o += w * v[i];
+            }
+            s0 += 64;
+            if (s0 >= L) break;
+            request(s0, lane);
+        }
+        auto over_keys = [](float x) {                      // over the four keys side by side
+            float a = x, b = x;
+            swap_rows(a, b);
+            x = a + b;
+            a = x;
+            b = x;
+            swap_halves(a, b);
+            return a + b;
+        };
+#pragma unroll
+        for (int e = 0; e < 4; ++e) o[e] = over_keys(o[e]);
+        lrun = over_keys(lrun);
+        if (lane < 16) *(f32x4*)(out + 4 * lane) = o;
+        if (lane == 0) {
+            out[64] = mrun;
+            out[65] = lrun;
+        }
+    }
+};
 
 // FB: FFN width / 128
 template <int FROM, int TO, int FB>
@@ -127,7 +224,7 @@ __global__ __launch_bounds__(64 * kWaves) void f32_layer_kernel(F32LayerArgs p)
     const int m = blockIdx.y, r0 = blockIdx.x * kRows;
     const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     float *xa = lds, *g2 = xa + kRows * H, *be2 = g2 + H, *bn = be2 + H, *xr = bn + NB, *bo = xr + kRows * H, *g1 = bo + H;
-    float *be1 = g1 + H, *b2 = be1 + H, *b1 = b2 + H, *xg = b1 + F;
+    float *be1 = g1 + H, *b2 = be1 + H, *b1 = b2 + H, *xg = b1 + F, *part = xg + kRows * F;
     const char* sb = p.arena + (size_t)m * p.ss;
 
     auto fill = [&](float* dst, size_t off, int n) {
@@ -157,6 +254,11 @@ __global__ __launch_bounds__(64 * kWaves) void f32_layer_kernel(F32LayerArgs p)
         request(std::integral_constant<int, i + kAhead>{});
     };
 
+    RowAttention at;
+    if constexpr (FROM == FROM_ATTENTION) {                 // (its loads in front of the weights': they are waited for first)
+        const int row = r0 + (wave >> 2) < p.M ? r0 + (wave >> 2) : p.M - 1;
+        at.begin(p, p.qkv + (size_t)m * p.rows * 3 * H, TO == TO_CLASSES, row, token(row), wave >> 1 & 1, wave & 1, lane);
+    }
     if constexpr (FROM == FROM_EMBEDDING) {
         if (wave < kRows) {                                 // a wave per row: its sequence starts at the last boundary up to it
             const int row = token(r0 + wave), id = p.ids[row];
@@ -175,9 +277,7 @@ __global__ __launch_bounds__(64 * kWaves) void f32_layer_kernel(F32LayerArgs p)
     } else {
         for (int i = tid; i < kRows * H; i += 64 * kWaves) {
             const int r = i / H;
-            const size_t at = ((size_t)m * p.rows + token(r0 + r)) * H + (i - r * H);
-            xa[i] = p.att[at];
-            xr[i] = p.x[at];
+            xr[i] = p.x[((size_t)m * p.rows + token(r0 + r)) * H + (i - r * H)];
         }
         fill(bo, p.bo, H);
         fill(g1, p.g1, H);
@@ -191,6 +291,15 @@ __global__ __launch_bounds__(64 * kWaves) void f32_layer_kernel(F32LayerArgs p)
     __builtin_amdgcn_sched_barrier(0);
     each<kAhead>(request);
     __builtin_amdgcn_sched_barrier(0);
+    if constexpr (FROM == FROM_ATTENTION) {
+        at.run(part + wave * kPart, lane);
+        barrier_lds();
+        if (tid < kRows * H) {                              // the halves of the keys, waves 2 n and 2 n + 1
+            const float *a = part + (tid >> 6) * 2 * kPart, *b = a + kPart;
+            const float mx = fmaxf(a[64], b[64]), wa = expf(a[64] - mx), wb = expf(b[64] - mx);
+            xa[tid] = (a[tid & 63] * wa + b[tid & 63] * wb) / (a[65] * wa + b[65] * wb);
+        }
+    }
     barrier_lds();
     if constexpr (FROM == FROM_ATTENTION) {
         multiply(std::integral_constant<int, 0>{}, xa, H);
@@ -219,7 +328,7 @@ __global__ __launch_bounds__(64 * kWaves) void f32_layer_kernel(F32LayerArgs p)
         each<3>([&](auto i) {
             multiply(std::integral_constant<int, BODY + decltype(i)::value>{}, xa, H);
             finish_block(acc, lane, wave, [&](int f, int r, float v) {
-                if (r0 + r < p.M) p.qkv[((size_t)m * p.rows + r0 + r) * 3 * H + i() * 128 + f] = v + bn[i() * 128 + f];
+                if (r0 + r < p.M) p.qkv_out[((size_t)m * p.rows + r0 + r) * 3 * H + i() * 128 + f] = v + bn[i() * 128 + f];
             });
         });
     }
@@ -253,7 +362,7 @@ hipError_t launch(const sp_model* M, const F32LayerArgs& a, int k, hipStream_t s
     return hipGetLastError();
 }
 
-F32LayerArgs layer_args(const sp_model* M, size_t lo, const void* att, void* x, const int32_t* cu, int B, int T, int rows)
+F32LayerArgs layer_args(const sp_model* M, size_t lo, const void* qkv, void* x, const int32_t* cu, int B, int T, int max_seqlen, int rows)
 {
     const sp_config& c = M->cfg;
     const ArenaLayout& L = M->L;
@@ -261,7 +370,7 @@ F32LayerArgs layer_args(const sp_model* M, size_t lo, const void* att, void* x, 
     a.arena = M->arena; a.ss = L.student_stride;
     a.wo = lo + L.wo; a.bo = lo + L.bo; a.g1 = lo + L.ln1g; a.be1 = lo + L.ln1b; a.w1 = lo + L.w1; a.b1 = lo + L.b1;
     a.w2 = lo + L.w2; a.b2 = lo + L.b2; a.g2 = lo + L.ln2g; a.be2 = lo + L.ln2b;
-    a.att = (const float*)att; a.x = (float*)x; a.cu = cu;
+    a.qkv = (const float*)qkv; a.x = (float*)x; a.cu = cu; a.max_seqlen = max_seqlen;
     a.M = T; a.Tn = T; a.rows = rows; a.B = B; a.C = c.classes; a.V = c.vocab; a.P = c.max_pos; a.eps = c.ln_eps;
     return a;
 }
@@ -280,25 +389,26 @@ hipError_t launch_f32_embed(const sp_model* M, size_t lo, const int32_t* ids, co
                             int rows, int k, hipStream_t s)
 {
     const ArenaLayout& L = M->L;
-    F32LayerArgs a = layer_args(M, lo, nullptr, x, cu, B, T, rows);
+    F32LayerArgs a = layer_args(M, lo, nullptr, x, cu, B, T, 0, rows);
     a.g2 = L.emb_g; a.be2 = L.emb_b; a.wn = lo + L.wqkv; a.bn = lo + L.bqkv; a.tok = L.tok; a.pos = L.pos; a.ids = ids;
-    a.qkv = (float*)qkv;
+    a.qkv_out = (float*)qkv;
     return launch<FROM_EMBEDDING, TO_QKV>(M, a, k, s);
 }
 
-hipError_t launch_f32_layer(const sp_model* M, size_t lo, const void* att, void* x, void* qkv_next, int T, int rows, int k,
-                            hipStream_t s)
+hipError_t launch_f32_layer(const sp_model* M, size_t lo, const void* qkv, void* x, void* qkv_next, const int32_t* cu, int B, int T, int max_seqlen,
+                            int rows, int k, hipStream_t s)
 {
-    F32LayerArgs a = layer_args(M, lo, att, x, nullptr, 0, T, rows);
+    F32LayerArgs a = layer_args(M, lo, qkv, x, cu, B, T, max_seqlen, rows);
     if (!qkv_next) return launch<FROM_ATTENTION, TO_ROWS>(M, a, k, s);
-    a.wn = lo + M->L.layer_stride + M->L.wqkv; a.bn = lo + M->L.layer_stride + M->L.bqkv; a.qkv = (float*)qkv_next;
+    if (qkv_next == qkv) return hipErrorInvalidValue;       // (other workgroups read it)
+    a.wn = lo + M->L.layer_stride + M->L.wqkv; a.bn = lo + M->L.layer_stride + M->L.bqkv; a.qkv_out = (float*)qkv_next;
     return launch<FROM_ATTENTION, TO_QKV>(M, a, k, s);
 }
 
-hipError_t launch_f32_last(const sp_model* M, size_t lo, const void* att, void* x, const int32_t* cu, int B, int T, int rows, int k,
+hipError_t launch_f32_last(const sp_model* M, size_t lo, const void* qkv, void* x, const int32_t* cu, int B, int T, int max_seqlen, int rows, int k,
                            float* z, hipStream_t s)
 {
-    F32LayerArgs a = layer_args(M, lo, att, x, cu, B, T, rows);
+    F32LayerArgs a = layer_args(M, lo, qkv, x, cu, B, T, max_seqlen, rows);
     a.M = B; a.wn = M->L.wp_t; a.bn = M->L.bp; a.wc = M->L.wc; a.bc = M->L.bc; a.z = z;
     return launch<FROM_ATTENTION, TO_CLASSES>(M, a, k, s);
 }

@@ -76,6 +76,29 @@ def test_fp32_layer_in_one_launch(oracle64, ffn, layers, lengths, k):
     st.close()
 
 
+# the attention inside that launch: 32 keys of either wave and 64 of both just missed, met and passed, a second wave without keys, steps of
+# which the last has few; rows' q|k|v in either of their two buffers; the narrowest FFN, whose own activations are smaller than those
+@pytest.mark.parametrize("lengths,k", [((1, 31, 32, 33, 63, 64, 1), 2), ((65, 96, 97, 2), 1), ((127, 128, 129), 1), ((1, 320, 5), 1)])
+@pytest.mark.parametrize("layers,ffn,all_tokens", [(1, 128, True), (2, 512, False), (3, 128, True), (4, 256, False)])
+def test_fp32_layer_with_its_attention(oracle64, lengths, k, layers, ffn, all_tokens):
+    """Sharp scores, a workspace full of NaN beforehand, and twice the same bits; bound as above."""
+    from paper_2408_12526_amd import sp
+    shape = synth.StudentShape(K=2, layers=layers, hidden=128, heads=2, ffn=ffn, vocab=60, max_pos=320, classes=2, dtype="fp32")
+    rng = np.random.default_rng(layers + sum(lengths))
+    ids, cu = synth.make_ids(rng, sum(lengths), shape.vocab), sp.sp_pack(np.array(lengths, dtype=np.int32))
+    assert len(ids) * k <= 512
+    blob = synth.make_weights(rng, shape, std=0.04, ln_random=True, qk_std=0.3)
+    st = sp.Students(sp.config_from_shape(shape, last_layer_all_tokens=all_tokens), blob)
+    st.workspace(len(ids), len(lengths)).fill_(255)
+    args = torch.from_numpy(ids).cuda(), torch.from_numpy(cu).cuda(), max(lengths), k
+    first = st.sp_forward(*args).clone()
+    assert torch.equal(first, st.sp_forward(*args))
+    st.close()
+    cfg = OracleConfig(shape.K, shape.layers, shape.hidden, shape.heads, shape.ffn, shape.vocab, shape.max_pos, shape.classes, shape.ln_eps)
+    want = oracle64.forward(cfg, blob, ids, cu, k)
+    assert np.abs(first.double().cpu().numpy() - want).max() / max(np.abs(want).max(), 1e-3) <= 1e-5
+
+
 # one, two, three and eight rounds of 64 boundaries in the embedding of a whole call in few launches; 512 rows of all students and one more
 @pytest.mark.parametrize("lengths,k", [((3,) * 64, 2), ((3,) * 65, 2), ((1, 2) * 64 + (5,), 2), ((1,) * 200, 2), ((1,) * 255 + (257,), 1), ((1,) * 512, 1),
                                        ((1,) * 513, 1)])
