@@ -227,9 +227,6 @@ __global__ __launch_bounds__(64 * kWaves) void f32_layer_kernel(F32LayerArgs p)
     float *be1 = g1 + H, *b2 = be1 + H, *b1 = b2 + H, *xg = b1 + F, *part = xg + kRows * F;
     const char* sb = p.arena + (size_t)m * p.ss;
 
-    auto fill = [&](float* dst, size_t off, int n) {
-        for (int i = tid; i < n; i += 64 * kWaves) dst[i] = ((const float*)(sb + off))[i];
-    };
     // token row of row r (rows beyond the last one repeat it)
     auto token = [&](int r) {
         r = r < p.M ? r : p.M - 1;
@@ -274,25 +271,44 @@ __global__ __launch_bounds__(64 * kWaves) void f32_layer_kernel(F32LayerArgs p)
 #pragma unroll
             for (int c = lane; c < H; c += 64) xa[wave * H + c] = te[c] + pe[c];
         }
-    } else {
-        for (int i = tid; i < kRows * H; i += 64 * kWaves) {
-            const int r = i / H;
-            xr[i] = p.x[((size_t)m * p.rows + token(r0 + r)) * H + (i - r * H)];
-        }
-        fill(bo, p.bo, H);
-        fill(g1, p.g1, H);
-        fill(be1, p.be1, H);
-        fill(b1, p.b1, F);
-        fill(b2, p.b2, H);
     }
-    fill(g2, p.g2, H);
-    fill(be2, p.be2, H);
-    if (TO != TO_ROWS) fill(bn, p.bn, NB);
+    // Biases, LayerNorm parameters and residual rows: requested here, put down behind the attention (a wait for them in between would keep the
+    // weights' requests back).
+    constexpr int NT = 64 * kWaves, NB1 = (F + NT - 1) / NT;
+    auto element = [&](size_t off, int n, int i) { return ((const float*)(sb + off))[i < n ? i : n - 1]; };
+    const float v_g2 = element(p.g2, H, tid), v_be2 = element(p.be2, H, tid), v_bn = TO == TO_ROWS ? 0.f : element(p.bn, NB, tid);
+    float v_bo, v_g1, v_be1, v_b2, v_x, v_b1[NB1];
+    if constexpr (FROM == FROM_ATTENTION) {
+        v_bo = element(p.bo, H, tid);
+        v_g1 = element(p.g1, H, tid);
+        v_be1 = element(p.be1, H, tid);
+        v_b2 = element(p.b2, H, tid);
+#pragma unroll
+        for (int i = 0; i < NB1; ++i) v_b1[i] = element(p.b1, F, tid + NT * i);
+        v_x = p.x[((size_t)m * p.rows + token(r0 + (tid / H) % kRows)) * H + tid % H];
+    }
     __builtin_amdgcn_sched_barrier(0);
     each<kAhead>(request);
     __builtin_amdgcn_sched_barrier(0);
     if constexpr (FROM == FROM_ATTENTION) {
         at.run(part + wave * kPart, lane);
+        if (tid < kRows * H) xr[tid] = v_x;
+        if (tid < H) {
+            bo[tid] = v_bo;
+            g1[tid] = v_g1;
+            be1[tid] = v_be1;
+            b2[tid] = v_b2;
+        }
+#pragma unroll
+        for (int i = 0; i < NB1; ++i)
+            if (tid + NT * i < F) b1[tid + NT * i] = v_b1[i];
+    }
+    if (tid < H) {
+        g2[tid] = v_g2;
+        be2[tid] = v_be2;
+    }
+    if (TO != TO_ROWS && tid < NB) bn[tid] = v_bn;
+    if constexpr (FROM == FROM_ATTENTION) {
         barrier_lds();
         if (tid < kRows * H) {                              // the halves of the keys, waves 2 n and 2 n + 1
             const float *a = part + (tid >> 6) * 2 * kPart, *b = a + kPart;
