@@ -555,10 +555,8 @@ static int run_students(const sp_model* M0, const WsLayout& W, const int32_t* id
             // next one's are written)
             char* const own = l & 1 ? f32_other : qkv;
             if (l == c.layers - 1 && !c.last_layer_all_tokens) {
-                SP_TRY(launch_f32_last(M, lo, own, x, cu, B, T, max_seqlen, rows, k, z, s));
+                SP_TRY(launch_f32_last(M, lo, own, x, cu, B, T, max_seqlen, rows, k, z, logits, s));
                 SP_MARK(SP_PHASE_LAST_FIRST);
-                if (logits) SP_TRY(launch_sum_students(z, B * c.classes, k, logits, s));
-                SP_MARK(SP_PHASE_HEAD);
                 return SP_OK;
             }
             SP_TRY(launch_f32_layer(M, lo, own, x, l + 1 < stop_layers ? (l & 1 ? qkv : f32_other) : nullptr, cu, B, T, max_seqlen, rows, k, s));

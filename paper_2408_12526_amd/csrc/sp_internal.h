@@ -385,9 +385,9 @@ hipError_t launch_f32_embed(const sp_model* M, size_t lo, const int32_t* ids, co
 // new x (qkv_next, not qkv; null: there is none)
 hipError_t launch_f32_layer(const sp_model* M, size_t lo, const void* qkv, void* x, void* qkv_next, const int32_t* cu, int B, int T, int max_seqlen,
                             int rows, int k, hipStream_t s);
-// the same of the first token of every sequence, then z[m][b][c] = tanh(x Wp + bp) Wc + bc
+// the same of the first token of every sequence, then z[m][b][c] = tanh(x Wp + bp) Wc + bc and (not null) logits, their sum over the students
 hipError_t launch_f32_last(const sp_model* M, size_t lo, const void* qkv, void* x, const int32_t* cu, int B, int T, int max_seqlen, int rows, int k,
-                           float* z, hipStream_t s);
+                           float* z, float* logits, hipStream_t s);
 
 // att[m][t][h*64..] = softmax(q k^T / 8) v inside each sequence; qkv rows are [q | k | v] of width 3H.
 // bf16 path: the values are read from vt[m][H][rows] (transposed) instead of the third slice of qkv.

@@ -1,19 +1,21 @@
-// fp32 path, calls of few rows: a launch from one attention to the next.  What it starts with is the embedding or everything of an
-// encoder layer that follows the attention; what it ends with is the q|k|v projection of the next layer, or, in the last layer, which
-// then has the first token of every sequence as its rows, pooler and classifier.
+// fp32 path, calls of few rows: a launch per layer.  What it starts with is the embedding, or the attention over the queries, keys and values
+// that the launch before left; what it ends with is the q|k|v projection of the next layer, or, in the last layer, which then has the first
+// token of every sequence as its rows, pooler and classifier.
 //
-// Such a call is a chain of dependent launches of 4-6 us that leave the chip idle: five per layer after the attention and one
-// for q|k|v.  All of it is row-wise, so a workgroup takes two rows through the whole chain with the rows in LDS and reads
+// Such a call is a chain of dependent launches of 4-6 us that leave the chip idle: six per layer and one for the attention.  All but the
+// keys and values of the other rows is row-wise, so a workgroup takes two rows through the whole chain with the rows in LDS and reads
 // the layer's weights (768 KB at 128 x 512) from the L2, which is what bounds it: about 64 bytes per cycle and compute unit.
+//   * attention (RowAttention): two waves per row and head; its loads are requested first, then the first four blocks of weights, then it
+//     is computed.  The rows' q|k|v alternate between two buffers: other workgroups read a layer's while the next one's are written.
 //   * sixteen lanes share an output feature and read 256 bytes in a row of its weights ([out][in]); eight waves x four
 //     features x four make a block of 128 features x 128 reduction elements, eight wave-loads per wave; the next three blocks are
 //     in flight, also across the barriers between the projections (one in flight: twice the time, a block waits for its
 //     memory round trip).  The order of the blocks is fixed at compile time, an instance per FFN width.
 //   * a lane's partial sums are added over the sixteen lanes by four data-parallel-primitive adds; then one lane per output
 //     applies bias, GELU or residual.  Biases and LayerNorm parameters come through LDS, so nothing waits behind the weights.
-// Measured, two students of 2 layers x 128 wide on 86 tokens: separate launches, 19 of them, 83.6 us a call; one launch per layer after
-// the attention, a block of weights in flight, and embedding, first q|k|v, pooler and classifier apart, 8 launches, 51 us; this, 6
-// launches, 38.8 us (a layer 14.4 -> 11.8 us, the last one 13.0 -> 10.2).
+// us a call, two students of 2 layers x 128 wide on 86 tokens: separate launches, 19 of them, 83.6; one launch per layer after
+// the attention, a block of weights in flight, and embedding, first q|k|v, pooler and classifier apart, 8 launches, 51; these as now, the
+// attention apart, 6 launches, 38.8; this, 4 launches, 30.7.  One of 256 tokens 90.9 / 40.8, one student on one of 512 147 / 49.6.
 #include <type_traits>
 #include <utility>
 
@@ -38,6 +40,7 @@ struct F32LayerArgs {
     size_t wc, bc, tok, pos;
     const float* qkv;                 // FROM_ATTENTION: queries, keys and values of the rows
     float *x, *qkv_out, *z;           // student strides: rows x H, rows x 3 H, M x C
+    float* logits;                    // one student: its classifier outputs once more (null: somebody adds the students' up)
     const int32_t *ids, *cu;
     int M, Tn, rows, B, C, V, P;      // M: rows to compute (tokens, or first tokens of sequences)
     int max_seqlen;
@@ -357,7 +360,10 @@ __global__ __launch_bounds__(64 * kWaves) void f32_layer_kernel(F32LayerArgs p)
                 const float* wc = (const float*)(sb + p.wc) + c;
                 const float v = wave_sum(xr[wave * H + lane] * wc[(size_t)lane * p.C] + xr[wave * H + lane + 64] * wc[(size_t)(lane + 64) * p.C]) +
                                 ((const float*)(sb + p.bc))[c];
-                if (lane == 0) p.z[((size_t)m * p.M + r0 + wave) * p.C + c] = v;
+                if (lane == 0) {
+                    p.z[((size_t)m * p.M + r0 + wave) * p.C + c] = v;
+                    if (p.logits) p.logits[(size_t)(r0 + wave) * p.C + c] = v;
+                }
             }
     }
 }
@@ -422,11 +428,12 @@ hipError_t launch_f32_layer(const sp_model* M, size_t lo, const void* qkv, void*
 }
 
 hipError_t launch_f32_last(const sp_model* M, size_t lo, const void* qkv, void* x, const int32_t* cu, int B, int T, int max_seqlen, int rows, int k,
-                           float* z, hipStream_t s)
+                           float* z, float* logits, hipStream_t s)
 {
     F32LayerArgs a = layer_args(M, lo, qkv, x, cu, B, T, max_seqlen, rows);
-    a.M = B; a.wn = M->L.wp_t; a.bn = M->L.bp; a.wc = M->L.wc; a.bc = M->L.bc; a.z = z;
-    return launch<FROM_ATTENTION, TO_CLASSES>(M, a, k, s);
+    a.M = B; a.wn = M->L.wp_t; a.bn = M->L.bp; a.wc = M->L.wc; a.bc = M->L.bc; a.z = z; a.logits = k == 1 ? logits : nullptr;
+    const hipError_t e = launch<FROM_ATTENTION, TO_CLASSES>(M, a, k, s);
+    return e != hipSuccess || k == 1 || !logits ? e : launch_sum_students(z, B * M->cfg.classes, k, logits, s);
 }
 
 }  // namespace sp
