@@ -219,7 +219,8 @@ int sp_check_inputs(const sp_model* model, const int32_t* token_ids, const int32
  *   z    float32 [K][batch][C] per-student classifier outputs before the sum
  * (After a whole fp32 forward in few launches, students of hidden 128 and up to 512 rows of
  * all of them, x holds the last layer's output in the first tokens' rows and its input in the
- * others, or its output in all with last_layer_all_tokens; x1 and g are not written.)
+ * others, or its output in all with last_layer_all_tokens; att holds the attention output in the
+ * first tokens' rows, or in all; x1 and g are not written.)
  * and, written only when the last layer ran on the first-token rows (see
  * sp_config.last_layer_all_tokens; `x` then holds the last layer's input, or, where that
  * layer reads the other rows before their LayerNorm, row b = its input for the first token

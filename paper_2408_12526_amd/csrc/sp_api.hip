@@ -483,7 +483,9 @@ static int run_students(const sp_model* M0, const WsLayout& W, const int32_t* id
     }
     // (the partial forwards of the tests read the buffers between the projections: not these either)
     const bool f32_layer = with_head && f32_layer_supported(c, (long)T * k_rule);
-    char* const f32_other = w + W.vt + m0 * s3H;            // values, attention output and pre-LayerNorm rows lie one behind another
+    // Their rows' q|k|v alternate between qkv and the three buffers behind it (values, attention output and pre-LayerNorm rows lie one behind
+    // another): other workgroups read those of a layer while the next one's are written.  The last layer's are in qkv.
+    auto f32_qkv = [&](int l) { return (c.layers - 1 - l) & 1 ? w + W.vt + m0 * s3H : qkv; };
     // Students of hidden width 256: two launches a layer, the attention between them.  Embedding and the first q|k|v in one from 8192 rows on;
     // below, the more workgroups of two launches are quicker to look up their rows.  us a call, eight launches a layer / embedding and q|k|v apart / in
     // one, by tokens: one student 319 66.1 / 65.0 / 69.3, 1344 76.4 / 69.0 / 71.4, 2718 82.5 / 73.8 / 75.2, 5475 93.1 / 78.7 / 78.7, 9143 98.0 / 82.7 / 81.1,
@@ -492,7 +494,7 @@ static int run_students(const sp_model* M0, const WsLayout& W, const int32_t* id
     const bool narrow = with_head && !fp8 && layer_supported(c);
     const bool narrow_qkv = narrow && (int64_t)T * k_rule >= 8192 && !(first_only && c.layers == 1);
     if (narrow_qkv) SP_TRY(launch_embed_qkv(M, L.layer0, ids, cu, B, T, x, att, qkv, vt, rows, mrows, k, s));
-    else if (f32_layer) SP_TRY(launch_f32_embed(M, L.layer0, ids, cu, B, T, x, qkv, rows, k, s));
+    else if (f32_layer) SP_TRY(launch_f32_embed(M, L.layer0, ids, cu, B, T, x, f32_qkv(0), rows, k, s));
     else SP_TRY(launch_embed_ln(M, ids, cu, B, T, rows, mrows, k, x, att, s, xq, kActQuantScale, attq));
     SP_MARK(SP_PHASE_EMBED);
     // Where the folded last layer follows, the rows stay as they are before the LayerNorm (see attention_first_fold_kernel) and only
@@ -551,15 +553,12 @@ static int run_students(const sp_model* M0, const WsLayout& W, const int32_t* id
                                sH, s3H, 0, s));
         SP_MARK(SP_PHASE_QKV);
         if (f32_layer) {
-            // (the rows' q|k|v alternate between their buffer and the three behind it: other workgroups read those of a layer while the
-            // next one's are written)
-            char* const own = l & 1 ? f32_other : qkv;
             if (l == c.layers - 1 && !c.last_layer_all_tokens) {
-                SP_TRY(launch_f32_last(M, lo, own, x, cu, B, T, max_seqlen, rows, k, z, logits, s));
+                SP_TRY(launch_f32_last(M, lo, f32_qkv(l), x, att, cu, B, T, max_seqlen, rows, k, z, logits, s));
                 SP_MARK(SP_PHASE_LAST_FIRST);
                 return SP_OK;
             }
-            SP_TRY(launch_f32_layer(M, lo, own, x, l + 1 < stop_layers ? (l & 1 ? qkv : f32_other) : nullptr, cu, B, T, max_seqlen, rows, k, s));
+            SP_TRY(launch_f32_layer(M, lo, f32_qkv(l), x, l + 1 < stop_layers ? f32_qkv(l + 1) : nullptr, att, cu, B, T, max_seqlen, rows, k, s));
             SP_MARK(SP_PHASE_FFN_DOWN);
             continue;
         }

@@ -382,12 +382,12 @@ bool f32_layer_supported(const sp_config& c, long rows_of_all_students);
 hipError_t launch_f32_embed(const sp_model* M, size_t lo, const int32_t* ids, const int32_t* cu, int B, int T, void* x, void* qkv,
                             int rows, int k, hipStream_t s);
 // x = LN(x1 + FFN(x1)), x1 = LN(x + att Wo + bo), att the attention over qkv, of T rows per student, and q|k|v of the next layer from the
-// new x (qkv_next, not qkv; null: there is none)
-hipError_t launch_f32_layer(const sp_model* M, size_t lo, const void* qkv, void* x, void* qkv_next, const int32_t* cu, int B, int T, int max_seqlen,
-                            int rows, int k, hipStream_t s);
-// the same of the first token of every sequence, then z[m][b][c] = tanh(x Wp + bp) Wc + bc and (not null) logits, their sum over the students
-hipError_t launch_f32_last(const sp_model* M, size_t lo, const void* qkv, void* x, const int32_t* cu, int B, int T, int max_seqlen, int rows, int k,
-                           float* z, float* logits, hipStream_t s);
+// new x (qkv_next, not qkv; null: there is none, and the attention output is kept in att)
+hipError_t launch_f32_layer(const sp_model* M, size_t lo, const void* qkv, void* x, void* qkv_next, void* att, const int32_t* cu, int B, int T,
+                            int max_seqlen, int rows, int k, hipStream_t s);
+// the same of the first token of every sequence (att: their rows alone), then z[m][b][c] = tanh(x Wp + bp) Wc + bc and (not null) logits, their sum over the students
+hipError_t launch_f32_last(const sp_model* M, size_t lo, const void* qkv, void* x, void* att, const int32_t* cu, int B, int T, int max_seqlen, int rows,
+                           int k, float* z, float* logits, hipStream_t s);
 
 // att[m][t][h*64..] = softmax(q k^T / 8) v inside each sequence; qkv rows are [q | k | v] of width 3H.
 // bf16 path: the values are read from vt[m][H][rows] (transposed) instead of the third slice of qkv.

@@ -15,7 +15,7 @@
 //     applies bias, GELU or residual.  Biases and LayerNorm parameters come through LDS, so nothing waits behind the weights.
 // us a call, two students of 2 layers x 128 wide on 86 tokens: separate launches, 19 of them, 83.6; one launch per layer after
 // the attention, a block of weights in flight, and embedding, first q|k|v, pooler and classifier apart, 8 launches, 51; these as now, the
-// attention apart, 6 launches, 38.8; this, 4 launches, 30.7.  One of 256 tokens 90.9 / 40.8, one student on one of 512 147 / 49.6.
+// attention apart, 6 launches, 38.8; this, 4 launches, 30.7, and 30.9 with the last layer's attention output left in the workspace.  One of 256 tokens 90.9 / 40.8, one student on one of 512 147 / 49.6.
 #include <type_traits>
 #include <utility>
 
@@ -39,7 +39,7 @@ struct F32LayerArgs {
     size_t wn, bn;                    // what follows the last LayerNorm: q|k|v or the pooler, [out][in]
     size_t wc, bc, tok, pos;
     const float* qkv;                 // FROM_ATTENTION: queries, keys and values of the rows
-    float *x, *qkv_out, *z;           // student strides: rows x H, rows x 3 H, M x C
+    float *x, *qkv_out, *z, *att;     // student strides: rows x H, rows x 3 H, M x C, rows x H (att: last layer only)
     float* logits;                    // one student: its classifier outputs once more (null: somebody adds the students' up)
     const int32_t *ids, *cu;
     int M, Tn, rows, B, C, V, P;      // M: rows to compute (tokens, or first tokens of sequences)
@@ -281,6 +281,7 @@ __global__ __launch_bounds__(64 * kWaves) void f32_layer_kernel(F32LayerArgs p)
     auto element = [&](size_t off, int n, int i) { return ((const float*)(sb + off))[i < n ? i : n - 1]; };
     const float v_g2 = element(p.g2, H, tid), v_be2 = element(p.be2, H, tid), v_bn = TO == TO_ROWS ? 0.f : element(p.bn, NB, tid);
     float v_bo, v_g1, v_be1, v_b2, v_x, v_b1[NB1];
+    size_t own = 0;                                         // this thread's element of the rows (of the first kRows * H threads)
     if constexpr (FROM == FROM_ATTENTION) {
         v_bo = element(p.bo, H, tid);
         v_g1 = element(p.g1, H, tid);
@@ -288,7 +289,8 @@ __global__ __launch_bounds__(64 * kWaves) void f32_layer_kernel(F32LayerArgs p)
         v_b2 = element(p.b2, H, tid);
 #pragma unroll
         for (int i = 0; i < NB1; ++i) v_b1[i] = element(p.b1, F, tid + NT * i);
-        v_x = p.x[((size_t)m * p.rows + token(r0 + (tid / H) % kRows)) * H + tid % H];
+        own = ((size_t)m * p.rows + token(r0 + (tid / H) % kRows)) * H + tid % H;
+        v_x = p.x[own];
     }
     __builtin_amdgcn_sched_barrier(0);
     each<kAhead>(request);
@@ -316,7 +318,9 @@ __global__ __launch_bounds__(64 * kWaves) void f32_layer_kernel(F32LayerArgs p)
         if (tid < kRows * H) {                              // the halves of the keys, waves 2 n and 2 n + 1
             const float *a = part + (tid >> 6) * 2 * kPart, *b = a + kPart;
             const float mx = fmaxf(a[64], b[64]), wa = expf(a[64] - mx), wb = expf(b[64] - mx);
-            xa[tid] = (a[tid & 63] * wa + b[tid & 63] * wb) / (a[65] * wa + b[65] * wb);
+            const float v = (a[tid & 63] * wa + b[tid & 63] * wb) / (a[65] * wa + b[65] * wb);
+            xa[tid] = v;
+            if (TO != TO_QKV) p.att[own] = v;
         }
     }
     barrier_lds();
@@ -417,21 +421,23 @@ hipError_t launch_f32_embed(const sp_model* M, size_t lo, const int32_t* ids, co
     return launch<FROM_EMBEDDING, TO_QKV>(M, a, k, s);
 }
 
-hipError_t launch_f32_layer(const sp_model* M, size_t lo, const void* qkv, void* x, void* qkv_next, const int32_t* cu, int B, int T, int max_seqlen,
+hipError_t launch_f32_layer(const sp_model* M, size_t lo, const void* qkv, void* x, void* qkv_next, void* att, const int32_t* cu, int B, int T, int max_seqlen,
                             int rows, int k, hipStream_t s)
 {
     F32LayerArgs a = layer_args(M, lo, qkv, x, cu, B, T, max_seqlen, rows);
+    a.att = (float*)att;
     if (!qkv_next) return launch<FROM_ATTENTION, TO_ROWS>(M, a, k, s);
     if (qkv_next == qkv) return hipErrorInvalidValue;       // (other workgroups read it)
     a.wn = lo + M->L.layer_stride + M->L.wqkv; a.bn = lo + M->L.layer_stride + M->L.bqkv; a.qkv_out = (float*)qkv_next;
     return launch<FROM_ATTENTION, TO_QKV>(M, a, k, s);
 }
 
-hipError_t launch_f32_last(const sp_model* M, size_t lo, const void* qkv, void* x, const int32_t* cu, int B, int T, int max_seqlen, int rows, int k,
+hipError_t launch_f32_last(const sp_model* M, size_t lo, const void* qkv, void* x, void* att, const int32_t* cu, int B, int T, int max_seqlen, int rows, int k,
                            float* z, float* logits, hipStream_t s)
 {
     F32LayerArgs a = layer_args(M, lo, qkv, x, cu, B, T, max_seqlen, rows);
-    a.M = B; a.wn = M->L.wp_t; a.bn = M->L.bp; a.wc = M->L.wc; a.bc = M->L.bc; a.z = z; a.logits = k == 1 ? logits : nullptr;
+    a.M = B; a.wn = M->L.wp_t; a.bn = M->L.bp; a.wc = M->L.wc; a.bc = M->L.bc; a.z = z; a.att = (float*)att;
+    a.logits = k == 1 ? logits : nullptr;
     const hipError_t e = launch<FROM_ATTENTION, TO_CLASSES>(M, a, k, s);
     return e != hipSuccess || k == 1 || !logits ? e : launch_sum_students(z, B * M->cfg.classes, k, logits, s);
 }

@@ -99,6 +99,30 @@ def test_fp32_layer_with_its_attention(oracle64, lengths, k, layers, ffn, all_to
     assert np.abs(first.double().cpu().numpy() - want).max() / max(np.abs(want).max(), 1e-3) <= 1e-5
 
 
+# both buffers of the rows' q|k|v, in either order
+@pytest.mark.parametrize("layers", [1, 2, 3, 4])
+@pytest.mark.parametrize("all_tokens", [False, True])
+def test_what_an_fp32_call_in_few_launches_leaves(layers, all_tokens):
+    """The last layer's q|k|v, and its attention output and state in the rows that it computes, beside what the separate launches of a
+    forward that stops behind it leave: sums of at most 256 fp32 terms in another order, over up to four layers."""
+    from paper_2408_12526_amd import sp
+    shape = synth.StudentShape(K=3, layers=layers, hidden=128, heads=2, ffn=256, vocab=60, max_pos=70, classes=2, dtype="fp32")
+    rng, lengths = np.random.default_rng(layers), np.array((1, 70, 33, 2, 7), np.int32)
+    cu, T, B = sp.sp_pack(lengths), int(lengths.sum()), len(lengths)
+    st = sp.Students(sp.config_from_shape(shape, last_layer_all_tokens=all_tokens), synth.make_weights(rng, shape, std=0.04, ln_random=True, qk_std=0.2))
+    for k in (1, 3):
+        args = torch.from_numpy(synth.make_ids(rng, T, shape.vocab)).cuda(), torch.from_numpy(cu).cuda(), 70, k
+        ws = st.workspace(T, B).fill_(255)
+        st.sp_forward(*args, workspace=ws)
+        got = {n: st.read_activation(ws, n, T, B, k) for n in ("qkv", "att", "x")}
+        ws = st.sp_forward_partial(*args, layers)
+        rows = np.arange(T) if all_tokens else cu[:-1]
+        for n, r in (("qkv", np.arange(T)), ("att", rows), ("x", rows)):
+            want = st.read_activation(ws, n, T, B, k)[:, r]
+            assert np.abs(got[n][:, r] - want).max() / np.abs(want).max() < 1e-5, (n, k)
+    st.close()
+
+
 # one, two, three and eight rounds of 64 boundaries in the embedding of a whole call in few launches; 512 rows of all students and one more
 @pytest.mark.parametrize("lengths,k", [((3,) * 64, 2), ((3,) * 65, 2), ((1, 2) * 64 + (5,), 2), ((1,) * 200, 2), ((1,) * 255 + (257,), 1), ((1,) * 512, 1),
                                        ((1,) * 513, 1)])
