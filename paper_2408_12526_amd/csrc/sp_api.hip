@@ -98,6 +98,7 @@ WsLayout make_ws_layout(const sp_config& c, int total_tokens, int batch)
     W.vt = take(K * rows * H * ab);
     W.att = take(K * rows * H * ab);
     W.u = take(K * rows * H * ab);
+    W.qkv2 = W.vt;                       // (the three above: taken one behind another, with x1 behind them)
     W.x1 = take(K * rows * H * ab);
     W.g = take(K * rows * F * ab);
     W.z = take(K * (size_t)batch * c.classes * 4);
@@ -483,9 +484,10 @@ static int run_students(const sp_model* M0, const WsLayout& W, const int32_t* id
     }
     // (the partial forwards of the tests read the buffers between the projections: not these either)
     const bool f32_layer = with_head && f32_layer_supported(c, (long)T * k_rule);
-    // Their rows' q|k|v alternate between qkv and the three buffers behind it (values, attention output and pre-LayerNorm rows lie one behind
-    // another): other workgroups read those of a layer while the next one's are written.  The last layer's are in qkv.
-    auto f32_qkv = [&](int l) { return (c.layers - 1 - l) & 1 ? w + W.vt + m0 * s3H : qkv; };
+    // Their rows' q|k|v alternate between two buffers: other workgroups read those of a layer while the next one's are written.  The last
+    // layer's are in qkv.
+    if (f32_layer && W.x1 - W.qkv2 < c.K * s3H) return SP_EINVAL;
+    auto f32_qkv = [&](int l) { return (c.layers - 1 - l) & 1 ? w + W.qkv2 + m0 * s3H : qkv; };
     // Students of hidden width 256: two launches a layer, the attention between them.  Embedding and the first q|k|v in one from 8192 rows on;
     // below, the more workgroups of two launches are quicker to look up their rows.  us a call, eight launches a layer / embedding and q|k|v apart / in
     // one, by tokens: one student 319 66.1 / 65.0 / 69.3, 1344 76.4 / 69.0 / 71.4, 2718 82.5 / 73.8 / 75.2, 5475 93.1 / 78.7 / 78.7, 9143 98.0 / 82.7 / 81.1,

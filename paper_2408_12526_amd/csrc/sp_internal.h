@@ -244,6 +244,7 @@ ArenaLayout make_arena_layout(const sp_config& c);
 // Workspace carve-up for one call.
 struct WsLayout {
     size_t x, qkv, vt, att, u, x1, g, z, zpart, end;
+    size_t qkv2;                         // second q|k|v of fp32 calls in few launches, [K][rows][3H]: all of vt, att and u
     size_t cu0, cq, catt, cx1, cg;       // first-token rows only: [K][crows][H] (cu0: fp32; cg: [F]), last layer
     size_t cqt, cxb;                     // folded queries / weighted mean rows: [K][crows][heads][H]
     size_t part;                         // fp32 rows between the few-row projections: [K][kRowsU][H]

@@ -72,6 +72,17 @@ def test_size_queries(sp):
     assert sp.sp_blob_floats(bad) == 0 and sp.sp_arena_bytes(bad) == 0
 
 
+@pytest.mark.parametrize("K,tokens", [(1, 1), (2, 86), (3, 300), (24, 20)])
+def test_second_buffer_of_fp32_projections_has_room(sp, K, tokens):
+    """fp32 calls in few launches keep every other layer's q|k|v in the buffers of the values, the attention output and the rows before a
+    LayerNorm: those must lie between qkv and x1 with nothing else among them."""
+    cfg = sp.config_from_shape(synth.StudentShape(K=K, layers=2, hidden=128, heads=2, ffn=512, vocab=100, max_pos=512, classes=2, dtype="fp32"))
+    lay = sp.sp_workspace_layout(cfg, tokens, 1)
+    need = K * lay.rows * 3 * 128 * 4
+    assert lay.vt >= lay.qkv + need and lay.x1 >= lay.vt + need
+    assert not any(lay.vt <= at < lay.vt + need for at in (lay.x, lay.qkv, lay.x1, lay.g, lay.z))
+
+
 def test_argument_errors_without_touching_a_gpu(sp):
     lib = sp.raw_lib()
     assert lib.sp_forward(None, None, None, 1, 1, 1, 1, None, 0, None, None) == -1
