@@ -263,9 +263,16 @@ enum {
                            * phases above then cover the other layers alone */
     SP_PHASE_COUNT
 };
+/* A launch that covers several steps counts as one of them, and the others are 0 where it is the only one:
+ *   - fp32 calls in few launches (students of hidden 128, up to 512 rows of all of them): EMBED has the first layer's
+ *     q|k|v as well; FFN_DOWN is a layer from its attention to the next one's q|k|v; LAST_FIRST is the last layer, pooler and
+ *     classifiers (and the logits of one student); HEAD is the sum over several;
+ *   - bf16 students of hidden 256 and FFN 512, 768 or 1024, calls of more than 256 tokens: FFN_DOWN is all of a layer behind
+ *     its attention; in calls of 8192 tokens x students and more EMBED has the first layer's q|k|v as well;
+ *   - bf16 calls of up to 256 tokens: embedding and LayerNorms are part of the projection that takes their rows, while those are few. */
 
-/* sp_forward with HIP events recorded on hip_stream after every kernel launch; waits for
- * the stream and adds each phase's device time, in milliseconds and summed over layers,
+/* sp_forward with HIP events recorded on hip_stream after every step (one launch, now and then
+ * two); waits for the stream and adds each phase's device time, in milliseconds and summed over layers,
  * into phase_ms_host[SP_PHASE_COUNT] (host).  A measurement aid: it creates and destroys
  * events and synchronises, so it is not for latency-critical callers. */
 int sp_forward_profiled(const sp_model* model, const int32_t* token_ids, const int32_t* cu_seqlens,

@@ -544,20 +544,24 @@ static int run_students(const sp_model* M0, const WsLayout& W, const int32_t* id
                 return first_rows_tail_tiles(lo, f, att1, s1, !raw, x11, s1, g1, sg, xb1, sx);
             return first_rows_tail(lo, f, att1, s1, false, !raw, x11, s1, g1, sg);
         }
+        const bool left = f32_layer || (narrow_qkv && l == 0);          // the launch before has left q|k|v
         if (fp8)
             SP_TRY(launch_gemm_fp8(M, xq, H, lo + L.wqkv8, lo + L.sqkv, lo + L.bqkv, kActQuantScale, qkv, 3 * H, nullptr, 0,
                                    mrows, 3 * H, H, k, EPI_QKV, qH, s3H, 0, s, vt, 2 * H, rows, sH, 1.f));
-        else if (bf16_path(c) && !(narrow_qkv && l == 0))
+        else if (bf16_path(c) && !left)
             SP_TRY(launch_gemm(M, x, H, lo + L.wqkv, lo + L.bqkv, qkv, 3 * H, nullptr, 0, mrows, 3 * H, H, k, EPI_QKV,
                                sH, s3H, 0, s, vt, 2 * H, rows, sH));
-        else if (!bf16_path(c) && !f32_layer)               // (else the launch before has left q|k|v)
+        else if (!left)
             SP_TRY(launch_gemm(M, x, H, lo + L.wqkv, lo + L.bqkv, qkv, 3 * H, nullptr, 0, mrows, 3 * H, H, k, EPI_BIAS,
                                sH, s3H, 0, s));
-        SP_MARK(SP_PHASE_QKV);
+        if (!left) SP_MARK(SP_PHASE_QKV);
         if (f32_layer) {
             if (l == c.layers - 1 && !c.last_layer_all_tokens) {
-                SP_TRY(launch_f32_last(M, lo, f32_qkv(l), x, att, cu, B, T, max_seqlen, rows, k, z, logits, s));
+                SP_TRY(launch_f32_last(M, lo, f32_qkv(l), x, att, cu, B, T, max_seqlen, rows, k, z, k == 1 ? logits : nullptr, s));
                 SP_MARK(SP_PHASE_LAST_FIRST);
+                if (k == 1 || !logits) return SP_OK;
+                SP_TRY(launch_sum_students(z, B * c.classes, k, logits, s));
+                SP_MARK(SP_PHASE_HEAD);
                 return SP_OK;
             }
             SP_TRY(launch_f32_layer(M, lo, f32_qkv(l), x, l + 1 < stop_layers ? f32_qkv(l + 1) : nullptr, att, cu, B, T, max_seqlen, rows, k, s));

@@ -386,7 +386,7 @@ hipError_t launch_f32_embed(const sp_model* M, size_t lo, const int32_t* ids, co
 // new x (qkv_next, not qkv; null: there is none, and the attention output is kept in att)
 hipError_t launch_f32_layer(const sp_model* M, size_t lo, const void* qkv, void* x, void* qkv_next, void* att, const int32_t* cu, int B, int T,
                             int max_seqlen, int rows, int k, hipStream_t s);
-// the same of the first token of every sequence (att: their rows alone), then z[m][b][c] = tanh(x Wp + bp) Wc + bc and (not null) logits, their sum over the students
+// the same of the first token of every sequence (att: their rows alone), then z[m][b][c] = tanh(x Wp + bp) Wc + bc and (not null, one student) the same as logits
 hipError_t launch_f32_last(const sp_model* M, size_t lo, const void* qkv, void* x, void* att, const int32_t* cu, int B, int T, int max_seqlen, int rows,
                            int k, float* z, float* logits, hipStream_t s);
 

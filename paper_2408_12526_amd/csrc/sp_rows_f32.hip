@@ -437,9 +437,9 @@ hipError_t launch_f32_last(const sp_model* M, size_t lo, const void* qkv, void* 
 {
     F32LayerArgs a = layer_args(M, lo, qkv, x, cu, B, T, max_seqlen, rows);
     a.M = B; a.wn = M->L.wp_t; a.bn = M->L.bp; a.wc = M->L.wc; a.bc = M->L.bc; a.z = z; a.att = (float*)att;
-    a.logits = k == 1 ? logits : nullptr;
-    const hipError_t e = launch<FROM_ATTENTION, TO_CLASSES>(M, a, k, s);
-    return e != hipSuccess || k == 1 || !logits ? e : launch_sum_students(z, B * M->cfg.classes, k, logits, s);
+    if (logits && k > 1) return hipErrorInvalidValue;       // (their sum takes all students' outputs)
+    a.logits = logits;
+    return launch<FROM_ATTENTION, TO_CLASSES>(M, a, k, s);
 }
 
 }  // namespace sp

@@ -123,6 +123,24 @@ def test_what_an_fp32_call_in_few_launches_leaves(layers, all_tokens):
     st.close()
 
 
+# (embedding and q|k|v of hidden 256 in two launches and in one)
+@pytest.mark.parametrize("hidden,ffn,layers,lengths,k,some", [
+    (128, 256, 3, (5, 60, 33), 2, {"embed", "ffn_down", "last_first", "head"}),
+    (128, 256, 3, (5, 60, 33), 1, {"embed", "ffn_down", "last_first"}),
+    (256, 768, 2, (60,) * 20, 2, {"embed", "qkv", "attention", "ffn_down", "last_first", "head"}),
+    (256, 768, 2, (60,) * 70, 2, {"embed", "attention", "ffn_down", "last_first", "head"})])
+def test_phases_of_calls_in_few_launches(hidden, ffn, layers, lengths, k, some):
+    """What sp_forward_profiled says of launches that cover several steps: the phases that it names have time, the others none."""
+    from paper_2408_12526_amd import sp
+    shape = synth.StudentShape(K=2, layers=layers, hidden=hidden, heads=hidden // 64, ffn=ffn, vocab=60, max_pos=64, classes=2,
+                               dtype="fp32" if hidden == 128 else "bf16")
+    rng, cu = np.random.default_rng(k), sp.sp_pack(np.array(lengths, np.int32))
+    st = sp.Students(sp.config_from_shape(shape), synth.make_weights(rng, shape))
+    ms = st.sp_forward_profiled(torch.from_numpy(synth.make_ids(rng, sum(lengths), 60)).cuda(), torch.from_numpy(cu).cuda(), max(lengths), k)
+    assert {n for n, t in ms.items() if t > 0} == some, ms
+    st.close()
+
+
 # one, two, three and eight rounds of 64 boundaries in the embedding of a whole call in few launches; 512 rows of all students and one more
 @pytest.mark.parametrize("lengths,k", [((3,) * 64, 2), ((3,) * 65, 2), ((1, 2) * 64 + (5,), 2), ((1,) * 200, 2), ((1,) * 255 + (257,), 1), ((1,) * 512, 1),
                                        ((1,) * 513, 1)])
