@@ -217,10 +217,19 @@ int sp_check_inputs(const sp_model* model, const int32_t* token_ids, const int32
  *   x1   [rows][H]  state after the attention block's LayerNorm
  *   g    [rows][F]  GELU(FFN up-projection)
  *   z    float32 [K][batch][C] per-student classifier outputs before the sum
- * (After a whole fp32 forward in few launches, students of hidden 128 and up to 512 rows of
- * all of them, x holds the last layer's output in the first tokens' rows and its input in the
- * others, or its output in all with last_layer_all_tokens; att holds the attention output in the
- * first tokens' rows, or in all; x1 and g are not written.)
+ * A partial forward leaves all of that.  A whole one leaves z, forms of the rest what the logits
+ * need, and uses as scratch what it is done with:
+ *   - fp32 in few launches, students of hidden 128 and up to 512 rows of all of them: x holds the
+ *     last layer's output in the first tokens' rows and its input in the others, or its output in
+ *     all with last_layer_all_tokens; att the attention output in the first tokens' rows, or in
+ *     all; x1 and g are not written;
+ *   - bf16 students of hidden 256 and FFN 512, 768 or 1024, calls of more than 256 tokens: x1 and g
+ *     are not written;
+ *   - quantised students, calls of >= 2048 token rows: att is not written (attq is);
+ *   - bf16 calls of fewer than 8192 tokens: qkv, vt and att may hold the fp32 slices of a split
+ *     reduction;
+ *   - a last layer on the first-token rows: in calls of fewer than 1024 tokens its rows lie in qkv,
+ *     vt, att, x1 and g; in calls of few long sequences their parts' sums lie in g
  * and, written only when the last layer ran on the first-token rows (see
  * sp_config.last_layer_all_tokens; `x` then holds the last layer's input, or, where that
  * layer reads the other rows before their LayerNorm, row b = its input for the first token
