@@ -666,7 +666,11 @@ __global__ __launch_bounds__((64 * FoldLds<HEADS, RAW>::NW), (HEADS == 16 ? 2 : 
         if (tile + 1 < nt) load_tile(tile + 1);
         barrier_lds();
         {
-            const int hh = tid >> 5, t = tid & 31;          // 2 NW heads x 32 sums, one per thread, waves in a fixed order
+            int id = tid;
+            // (What follows from it is not kept through the loop: with 12 heads three addresses did not fit the registers.  us for the last layer,
+            // kept / not, 768 wide, four students on 32 sequences of 340: 100 / 95.)
+            if (RAW && SPLIT) asm volatile("" : "+v"(id));
+            const int hh = id >> 5, t = id & 31;            // 2 NW heads x 32 sums, one per thread, waves in a fixed order
             float sum = 0.f;
 #pragma unroll
             for (int w = 0; w < NW; ++w) sum += part[(w * 16 + hh) * 32 + t];

@@ -83,6 +83,16 @@ def test_second_buffer_of_fp32_projections_has_room(sp, K, tokens):
     assert not any(lay.vt <= at < lay.vt + need for at in (lay.x, lay.qkv, lay.x1, lay.g, lay.z))
 
 
+def test_no_kernel_spills_registers(sp):
+    """What the compiler notes of every kernel of the built library: no memory of its own, no spilled vector register."""
+    from paper_2408_12526_amd.build import LIB
+    with open(LIB, "rb") as f:
+        image = f.read()
+    for key in (b".private_segment_fixed_size", b".vgpr_spill_count"):
+        notes = [part[0] for part in image.split(key)[1:]]      # (a small number is one byte behind its name)
+        assert len(notes) > 100 and not any(notes), (key, [n for n in notes if n])
+
+
 def test_argument_errors_without_touching_a_gpu(sp):
     lib = sp.raw_lib()
     assert lib.sp_forward(None, None, None, 1, 1, 1, 1, None, 0, None, None) == -1
