@@ -336,7 +336,8 @@ hipError_t launch_wreg_tile(const sp_model* M, GemmArgs a, int N, int k, hipStre
 // the first loads and the epilogue take longer than the four k-tiles, and lower tiles, of which three fit a unit, hide them better.
 // Measured against it, us at 128 / 96 / 64 tokens: 14653 tokens x 2 students, 768 from 256: 27.5 / 26.8 / 23.1, 1024 from 256 36.6 / 31.6 / 32.5;
 // 2304 features from 768 98.7 / 96.4 / 109; 768 from 3072 131 / 141 / 171; 4608 tokens x 2, 3072 from 768: 55.1 / 50.3 / 52.5; x 8, 768 from 3072: 177 / 188 /
-// 219; 18432 tokens, 1024 from 4096: 147 / 132 / 163; 640 tokens, 768 from 768, at 64 and 32: 11.2 / 8.8.
+// 219; 18432 tokens, 1024 from 4096: 147 / 132 / 163; 640 tokens, 768 from 768, at 64 and 32: 11.2 / 8.8.  (A split reduction goes by the depth of a share,
+// 256 at least: one student of 768 or 1024, 1600-5300 tokens, the height that costs of 1.2 and 1.1 choose as well, and the quickest of the three.)
 }  // namespace
 
 constexpr double kHalfTokenCost[5] = {0, 1.7, 1.2, 1.1, 1.0};       // tiles of half the features
@@ -354,10 +355,8 @@ static int tile_height(int mrows, long wide, long round, int tallest, const doub
     return best;
 }
 
-int gemm_tile_height(int mrows, int N, int Kd, int k)
-{
-    return tile_height(mrows, (long)(N / 256) * k, 256, 4, kTokenCost[Kd <= 256 ? 0 : Kd < 2048 ? 1 : 2]);
-}
+int gemm_tile_height(int mrows, int N, int k, const double* cost) { return tile_height(mrows, (long)(N / 256) * k, 256, 4, cost); }
+const double* gemm_token_cost(int Kd) { return kTokenCost[Kd <= 256 ? 0 : Kd < 2048 ? 1 : 2]; }
 
 namespace {
 
@@ -389,7 +388,7 @@ hipError_t launch_bf16(const sp_model* M, const GemmArgs& a, int N, int k, hipSt
     const long half = (long)(N / 128) * k * a.splits;
     if ((a.mrows + 31) / 32 * half <= 256) return launch_wreg_tile<1, 2, 2, EPI>(M, a, N, k, s);
     if ((a.mrows + 63) / 64 * half <= 256) return launch_wreg_tile<2, 2, 2, EPI>(M, a, N, k, s);
-    switch (gemm_tile_height(a.mrows, N, a.Kper, k * a.splits)) {
+    switch (gemm_tile_height(a.mrows, N, k * a.splits, gemm_token_cost(a.Kper))) {
         case 1: return launch_wreg_tile<1, 4, 1, EPI>(M, a, N, k, s);
         case 2: return launch_wreg_tile<2, 4, 1, EPI>(M, a, N, k, s);
         case 3: return launch_wreg_tile<3, 4, 1, EPI>(M, a, N, k, s);

@@ -314,8 +314,10 @@ hipError_t launch_ln_slices(const sp_model* M, const float* part, size_t slice, 
                             const void* residual, void* out, int rows, int T, int mrows, int k, size_t g_off, size_t b_off,
                             hipStream_t s);
 
-// Tile height in blocks of 32 tokens (1 to 4) for a projection of mrows rows onto N features (a multiple of 256) from Kd of k students.
-int gemm_tile_height(int mrows, int N, int Kd, int k);
+// Tile height in blocks of 32 tokens (1 to 4) for a projection of mrows rows onto N features (a multiple of 256) of k students.  cost[h]:
+// what a token costs in a tile of height h, of one in the tallest; gemm_token_cost: of a bf16 projection from Kd.
+int gemm_tile_height(int mrows, int N, int k, const double* cost);
+const double* gemm_token_cost(int Kd);
 
 // The same projection on fp8 operands (SP_DTYPE_FP8: mrows a multiple of 64, N and Kd of 256).
 // A8: e4m3 codes of activation * a_qscale, [m][row][lda] bytes; weights at w_off (e4m3, operand blocks) with fp32

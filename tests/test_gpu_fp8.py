@@ -289,8 +289,9 @@ def test_fp8_large_width(sp, oracle64):
     st.close()
 
 
-# K picks the tile height (32 K tokens) of the projections of 768 features at these row counts: q|k|v and FFN up at the first
-# width, attention output, FFN up and down at the second; one row beyond a tile of any height, and one short of 64
+# K picks the tile height of the projections of 768 features at these row counts: 32 K tokens for attention output, FFN up and down at the
+# second width, 32, 64, 96 and 64 for q|k|v and FFN up at the first; 128 for q|k|v at the second with K of 3 and 4.  One row beyond a tile of
+# any height, and one short of 64
 @pytest.mark.parametrize("tokens", [2049, 2111])
 @pytest.mark.parametrize("K", [1, 2, 3, 4])
 @pytest.mark.parametrize("hidden", [256, 768])
