@@ -223,8 +223,8 @@ int sp_check_inputs(const sp_model* model, const int32_t* token_ids, const int32
  *     last layer's output in the first tokens' rows and its input in the others, or its output in
  *     all with last_layer_all_tokens; att the attention output in the first tokens' rows, or in
  *     all; x1 and g are not written;
- *   - bf16 students of hidden 256 and FFN 512, 768 or 1024, calls of more than 256 tokens: x1 and g
- *     are not written;
+ *   - bf16 students of hidden 256 and FFN 512 (768, 1024), calls of more than 256 tokens (and of
+ *     1280, 1664 tokens x students and more): x1 and g are not written;
  *   - quantised students, calls of >= 2048 token rows: att is not written (attq is);
  *   - bf16 calls of fewer than 8192 tokens: qkv, vt and att may hold the fp32 slices of a split
  *     reduction;
@@ -276,8 +276,8 @@ enum {
  *   - fp32 calls in few launches (students of hidden 128, up to 512 rows of all of them): EMBED has the first layer's
  *     q|k|v as well; FFN_DOWN is a layer from its attention to the next one's q|k|v; LAST_FIRST is the last layer, pooler and
  *     classifiers (and the logits of one student); HEAD is the sum over several;
- *   - bf16 students of hidden 256 and FFN 512, 768 or 1024, calls of more than 256 tokens: FFN_DOWN is all of a layer behind
- *     its attention; in calls of 8192 tokens x students and more EMBED has the first layer's q|k|v as well;
+ *   - bf16 students of hidden 256 and FFN 512 (768, 1024), calls of more than 256 tokens (and of 1280, 1664 tokens x students
+ *     and more): FFN_DOWN is all of a layer behind its attention; in calls of 8192 tokens x students and more EMBED has the first layer's q|k|v as well;
  *   - bf16 calls of up to 256 tokens: embedding and LayerNorms are part of the projection that takes their rows, while those are few. */
 
 /* sp_forward with HIP events recorded on hip_stream after every step (one launch, now and then

@@ -488,12 +488,12 @@ static int run_students(const sp_model* M0, const WsLayout& W, const int32_t* id
     // layer's are in qkv.
     if (f32_layer && W.x1 - W.qkv2 < c.K * s3H) return SP_EINVAL;
     auto f32_qkv = [&](int l) { return (c.layers - 1 - l) & 1 ? w + W.qkv2 + m0 * s3H : qkv; };
-    // Students of hidden width 256: two launches a layer, the attention between them.  Embedding and the first q|k|v in one from 8192 rows on;
-    // below, the more workgroups of two launches are quicker to look up their rows.  us a call, eight launches a layer / embedding and q|k|v apart / in
-    // one, by tokens: one student 319 66.1 / 65.0 / 69.3, 1344 76.4 / 69.0 / 71.4, 2718 82.5 / 73.8 / 75.2, 5475 93.1 / 78.7 / 78.7, 9143 98.0 / 82.7 / 81.1,
-    // 14653 112.8 / 96.9 / 86.9; three 658 79.0 / 71.2 / 73.4, 2718 98.5 / 79.8 / 79.2, 5475 119.8 / 107.1 / 102.4, 9143 155.6 / 128.2 / 117.2, 14653 220.0 /
+    // Students of hidden width 256: two launches a layer, the attention between them, where the rows are enough (see layer_pays).  Embedding and
+    // the first q|k|v in one from 8192 rows on; below, the more workgroups of two launches are quicker to look up their rows.  us a call, FFN 1024,
+    // eight launches a layer / embedding and q|k|v apart / in one, by tokens: one student 2718 82.5 / 73.8 / 75.2, 5475 93.1 / 78.7 / 78.7, 9143 98.0 / 82.7 /
+    // 81.1, 14653 112.8 / 96.9 / 86.9; three 658 79.0 / 71.2 / 73.4, 2718 98.5 / 79.8 / 79.2, 5475 119.8 / 107.1 / 102.4, 9143 155.6 / 128.2 / 117.2, 14653 220.0 /
     // 175.1 / 166.0.
-    const bool narrow = with_head && !fp8 && layer_supported(c);
+    const bool narrow = with_head && !fp8 && layer_pays(c, (int64_t)T * k_rule);
     const bool narrow_qkv = narrow && (int64_t)T * k_rule >= 8192 && !(first_only && c.layers == 1);
     if (narrow_qkv) SP_TRY(launch_embed_qkv(M, L.layer0, ids, cu, B, T, x, att, qkv, vt, rows, mrows, k, s));
     else if (f32_layer) SP_TRY(launch_f32_embed(M, L.layer0, ids, cu, B, T, x, f32_qkv(0), rows, k, s));

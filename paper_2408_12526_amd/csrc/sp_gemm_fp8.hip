@@ -320,9 +320,10 @@ hipError_t launch_fp8_tile(Fp8Args a, int N, int k, hipStream_t s)
 
 // Tile height.  A depth of 256 is two k-tiles: low tiles hide the first loads and the epilogue better, as in the bf16 kernel, whose costs
 // are good here as well; deeper reductions have costs of their own.  us a call on 14653 tokens, the costs of a bf16 projection half as
-// deep / these: 512 wide, eight students 896 / 850, four 467 / 452, two 271 / 264, one 162 / 163; 768 wide, four 774 / 766; 1024 wide, two 605 / 590, the
-// others within 1 %.  At a depth of 256, bf16's / these: eight 402 / 409, two 151 / 155.  us per launch at 128 / 96 / 64 tokens, eight students: q|k|v from 256 56 / 58 / 59, from 512 133 / 143 / 147, from 768 238 / 247 / 262; FFN up from 256 68 / 67 /
-// 61, from 512 172 / 163 / 167, from 768 299 / 305 / 310; FFN down from 1024 58 / 61 / 62, from 2048 162 / 163 / 192, from 3072 270 / 298 / 346.
+// deep / these: 512 wide, eight students 896 / 850, four 467 / 452, two 271 / 264, one 162 / 163; 768 wide, four 774 / 766; 1024 wide, two 605 / 590,
+// the others within 1 %.  At a depth of 256, bf16's / these: eight 402 / 409, two 151 / 155.  us per launch at 128 / 96 / 64 tokens, eight
+// students: q|k|v from 256 56 / 58 / 59, from 512 133 / 143 / 147, from 768 238 / 247 / 262; FFN up from 256 68 / 67 / 61, from 512 172 / 163 / 167, from
+// 768 299 / 305 / 310; FFN down from 1024 58 / 61 / 62, from 2048 162 / 163 / 192, from 3072 270 / 298 / 346.
 constexpr double kFp8TokenCost[5] = {0, 1.7, 1.2, 1.1, 1.0};
 
 template <int EPI>

@@ -336,6 +336,7 @@ hipError_t launch_gelu_q8_probe(const float* x, float* y, long n, hipStream_t s)
 // ---- students of hidden width 256 (sp_layer.hip; bf16 path): out = LN(x1 + FFN(x1)), x1 = LN(x + att Wo + bo), of mrows
 // rows per student (a multiple of 64; all three buffers [m][rows][256]; out may be x)
 bool layer_supported(const sp_config& c);
+bool layer_pays(const sp_config& c, int64_t rows_of_all_students);
 hipError_t launch_layer(const sp_model* M, size_t lo, const void* att, const void* x, void* out, int rows, int mrows, int k,
                         hipStream_t s);
 

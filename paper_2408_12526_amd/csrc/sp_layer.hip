@@ -438,6 +438,16 @@ bool layer_supported(const sp_config& c)
     return bf16_path(c) && c.hidden == kH && c.ffn % 256 == 0 && c.ffn > kH && c.ffn <= kMaxF;
 }
 
+// A workgroup's chain is 1 + 2 F / 256 products behind one another, while separate launches spread their features over the chip: a call of few
+// rows takes them unless the FFN is narrow.  us a call, separate / this, by tokens x students, two and six layers: FFN 512: 260 54 / 51 162 / 149, 1000 65 / 62
+// 179 / 160, 3000 79 / 71 235 / 183; 768: 260 55 / 60 170 / 167, 600 60 / 62 176 / 177, 1020 60 / 63 186 / 180, 1250 63 / 64 and 63 / 58 196 / 181, 1400 67 / 65 209 / 186, 2000
+// 71 / 67 228 / 190; 1024: 260 55 / 63 168 / 185, 600 59 / 66 179 / 194, 1020 61 / 66 187 / 197, 1250 65 / 68 200 / 199, 1600 67 / 69 209 / 203 and, two students, 69 / 69 217 /
+// 203, 2000 70 / 69 224 / 207.  Twelve layers, 1024: 260 323 / 373, 1020 379 / 397, 1600 437 / 411.
+bool layer_pays(const sp_config& c, int64_t rows_of_all_students)
+{
+    return layer_supported(c) && rows_of_all_students >= (c.ffn <= 512 ? 0 : c.ffn <= 768 ? 1280 : 1664);
+}
+
 hipError_t launch_layer(const sp_model* M, size_t lo, const void* att, const void* x, void* out, int rows, int mrows, int k, hipStream_t s)
 {
     const sp_config& c = M->cfg;

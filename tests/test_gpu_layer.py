@@ -8,10 +8,10 @@ from paper_2408_12526_amd import synth
 pytestmark = pytest.mark.gpu
 
 
-# 257: the first call that takes them; tiles of 64 tokens with 1, 64 and 63 or fewer in the last; on both sides of 8192 rows of all students
-# (embedding and q|k|v in one launch); every number of blocks of 256 FFN activations, and one block, which keeps the separate launches
-@pytest.mark.parametrize("total,k", [(257, 1), (320, 2), (447, 3), (2730, 3), (2731, 3), (4096, 2), (8191, 1), (8193, 1)])
-@pytest.mark.parametrize("ffn", [256, 512, 768, 1024])
+# the first call that takes them and tiles of 64 tokens with 1, 64 and fewer in the last (one block of FFN activations keeps the separate
+# launches); on both sides of 8192 rows of all students (embedding and q|k|v in one launch)
+@pytest.mark.parametrize("ffn,total,k", [(ffn, total, k) for ffn, first in ((256, 257), (512, 257), (768, 1280), (1024, 1664)) for total, k in (
+    (first, 1), (first + 1, 1), (first + 63, 2), (first + 190, 3), (2730, 3), (2731, 3), (4096, 2), (8191, 1), (8193, 1))])
 def test_layer_of_narrow_students(ffn, total, k):
     """q|k|v from the embedding rows and the layer's output from the attention output, against torch in fp64 on the weights as stored:
     operands, x1 and FFN activations in bf16, sums in fp32, one rounding of the output (the bound of the stage tests)."""
@@ -44,6 +44,35 @@ def test_layer_of_narrow_students(ffn, total, k):
             err = float((got[n][m] - w).abs().max() / w.abs().max())
             assert err < 1.2e-2, f"student {m} {n}: {err:.3e}"
     st.close()
+
+
+# few rows for the FFN: the first and the last call that keep the separate launches, whose stages a whole forward leaves
+@pytest.mark.parametrize("ffn,total,k", [(768, 257, 1), (768, 1279, 1), (768, 426, 3), (1024, 257, 1), (1024, 1663, 1), (1024, 831, 2)])
+def test_layers_of_few_rows_keep_the_separate_launches(ffn, total, k):
+    """x1, g and x of one layer on every token, each from the stage before it; bounds as above (one rounding of each)."""
+    from paper_2408_12526_amd import sp
+    shape = synth.StudentShape(K=3, layers=1, hidden=256, heads=4, ffn=ffn, vocab=100, max_pos=128, classes=2, dtype="bf16")
+    rng = np.random.default_rng(total + ffn)
+    lengths = np.array([64] * (total // 64) + [total % 64], np.int32)
+    ids, blob, B, H = synth.make_ids(rng, total, shape.vocab), synth.make_weights(rng, shape, std=0.06, ln_random=True), len(lengths), shape.hidden
+    st = sp.Students(sp.config_from_shape(shape, last_layer_all_tokens=True), blob)
+    args = torch.from_numpy(ids).cuda(), torch.from_numpy(sp.sp_pack(lengths)).cuda(), 64, k
+    x = st.read_activation(st.sp_forward_partial(*args, 0), "x", total, B, k)
+    att = st.read_activation(st.sp_forward_partial(*args, 1), "att", total, B, k)
+    st.workspace(total, B).fill_(255)
+    st.sp_forward(*args)
+    got = {n: torch.from_numpy(st.read_activation(st.workspace(total, B), n, total, B, k)) for n in ("x1", "g", "x")}
+    st.close()
+    for m in range(k):
+        v = {n: torch.from_numpy(a).bfloat16().double() if a.ndim == 2 else torch.from_numpy(a).double()
+             for n, a in synth.student_views(blob, shape, m).items()}
+        ln = lambda u, w: torch.nn.functional.layer_norm(u, (H,), v[f"l0.ln{w}_g"], v[f"l0.ln{w}_b"], shape.ln_eps)
+        lin = lambda a, w, b: a @ v["l0." + w] + v["l0." + b]
+        want = {"x1": ln(torch.from_numpy(x[m]) + lin(torch.from_numpy(att[m]), "Wo", "bo"), 1), "g": torch.nn.functional.gelu(lin(got["x1"][m], "W1", "b1")),
+                "x": ln(got["x1"][m] + lin(got["g"][m], "W2", "b2"), 2)}
+        for n, w in want.items():
+            err = float((got[n][m] - w).abs().max() / w.abs().max())
+            assert err < 1.2e-2, f"student {m} {n}: {err:.3e}"
 
 
 def test_deeper_narrow_students(oracle64):
