@@ -504,10 +504,11 @@ static int run_students(const sp_model* M0, const WsLayout& W, const int32_t* id
     // launch.  By tokens x students x hidden width (Mi), and not for sequences so short that the fold's tiles of 32 tokens are mostly
     // empty.  us a call, with the LayerNorm of all rows / this.  768 wide: 5 236 / 240; 9 330 / 331; 11 383 / 381; 14 435 / 441; 18 569 / 566; 21
     // 637 / 628; 22 629 / 620; 88 2290 / 2251, quantised 1588 / 1524; eight sequences of 512 tokens: 6 242 / 253, 12 414 / 421, 24 696 / 690.
-    // 1024 wide: 7 305 / 308, 12 463 / 465, 21 743 / 739, 29 978 / 966.  512 wide: 15 361 / 363, 16 396 / 402, 18 463 / 457.  256 wide: 3.6 120 /
-    // 120, 8.5 176 / 178 and 221 / 220, 11 248 / 246, 18 388 / 382.  Sequences of 4 tokens: 24 1021 / 1031 (768 wide), 1212 / 1263 (1024); of 16: 24 742 / 731, 875 / 872.
+    // 1024 wide: 7 305 / 308, 12 463 / 465, 21 743 / 739, 29 978 / 966.  512 wide: 15 361 / 363, 16 396 / 402, 18 463 / 457.  256 wide (those of one
+    // launch behind the attention never take it; an FFN of 1280, three students): 3.0 117 / 119, 6.0 159 / 159, 8.8 213 / 211, 12 268 / 264, 18 358 / 351;
+    // quantised, FFN 1024: 6.0 144 / 142, 8.8 180 / 177, 12 205 / 198, 47 651 / 635.  Sequences of 4 tokens: 24 1021 / 1031 (768 wide), 1212 / 1263 (1024); of 16: 24 742 / 731, 875 / 872.
     // (In calls of kLargeTokens and more by the model's students, not by those that are active: the two round differently.  One of three
-    // or of eight pays for that: 256 wide, 11 128 / 129 and, of long sequences, 138 / 141; 768 wide, 88 365 / 367.)
+    // or of eight pays for that: 256 wide, 11 of long sequences 123 / 124; 768 wide, 88 365 / 367.)
     const int64_t fold_work = (int64_t)T * (T >= kLargeTokens ? c.K : k_rule) * H;
     const bool raw_pays = fold_work > (int64_t)(H == 256 ? 10 : 16) << 20 && T >= (int64_t)16 * B;
     bool raw = false;
@@ -637,13 +638,15 @@ static int run_students(const sp_model* M0, const WsLayout& W, const int32_t* id
 //     507 / 505, 20.9 606 / 603, 29 801 / 789; 4: 24 723 / 682; quantised, 2: 12.1 307 / 321, 20.8 451 / 441; 512 wide, 2: 13.9 351 / 363, 4:
 //     27.9 637 / 607; 256 wide, 3: 10.4 226 / 253, 20.5 408 / 402, 6: 20.9 412 / 381.  The cost is paid once, the gain per
 //     layer: six layers 768 wide, 2 students: 12.1 1626 / 1612, 16.8 2156 / 2106; 256 wide, 2: 4.0 483 / 471, 7.0 668 / 609.  Not so for an odd number
-//     of students, of which one group is done before the other: six layers 256 wide, 3: 10.4 898 / 974.
+//     of students, of which one group is done before the other: six layers 256 wide, 3: 10.4 898 / 974.  With a layer of 256 in two launches (FFN
+//     1024) the same lines, at which some numbers of tiles lose a few per cent and others gain: 2: 20.0 269 / 269, 29 400 / 400, 3: 20.1 274 / 272,
+//     29 403 / 399, 43 559 / 551, 58 726 / 698, 4: 20.0 285 / 280, 23.4 301 / 315, 34 438 / 437, 58 719 / 707, 6: 21.5 287 / 292, 35 453 / 446, 87 1028 / 1006;
+//     six layers, 2: 4.0 379 / 358, 7.2 460 / 472, 4: 8.0 580 / 515, 14 809 / 762, 3: 20.5 1124 / 1076.
 //   * bf16 of hidden 512 and more, whose projections reach the power limit by themselves: even numbers of students only (768 wide, 3:
 //     31 852 / 858, 61 1635 / 1675; 5: 52 1421 / 1432; 512 wide, 3: 20.9 492 / 506), and up to 64, beyond which a group alone fills the chip as
 //     well (768 wide, 8: 49 1302 / 1288, 58 1567 / 1555, 70 1850 / 1918, 84 2136-2200 / 2196-2220, 328 8196 / 8329; 4: 42 1141 / 1103, 58.5 1576 /
 //     1558, 82 2156 / 2220; six layers, 2: 41 5092 / 4897, 59 7306 / 7255, 82 9953 / 10314; 1024 wide, 6: 48 1501 / 1501, 107 3201 / 3226).
-//     Quantised and narrow students have no such limit (quantised, 8: 84 1498 / 1472, 164 2878 / 2853; 256 wide, 6: 161 2569 / 2539; with a layer
-//     in two launches: 6: 21 295 / 299, 52 653 / 639, 4: 35 444 / 440, 3: 26 339 / 341, 47 597 / 601).
+//     Quantised and narrow students have no such limit (quantised, 8: 84 1498 / 1472, 164 2878 / 2853; 256 wide, 6: 161 2569 / 2539).
 constexpr int64_t kTwoGroupsWork = 20 << 20, kTwoGroupsMostWork = 64 << 20;
 static bool two_groups_pay(const sp_config& c, int T, int k)
 {

@@ -431,8 +431,9 @@ hipError_t launch(Kernel kern, size_t lds, std::atomic<bool>& raised, const Args
 
 }  // namespace
 
-// (An FFN as narrow as the rows keeps the separate launches: with one block of activations these would be quicker as well, us a call, three on 14653 tokens 172 / 130, one on 1344 62 / 54, but the folded attention on rows before their LayerNorm, which such calls
-// of 256 take from 8192 tokens on, is checked bit for bit through the rows that it leaves in x.)
+// (An FFN as narrow as the rows keeps the separate launches, although these would be quicker, us a call, three students on 14653 tokens 172 / 130, one
+// on 1344 62 / 54: the folded attention on rows before their LayerNorm, which such calls of 256 take from 8192 tokens on, is checked bit for bit
+// through the rows that it leaves in x.)
 bool layer_supported(const sp_config& c)
 {
     return bf16_path(c) && c.hidden == kH && c.ffn % 256 == 0 && c.ffn > kH && c.ffn <= kMaxF;
