@@ -137,3 +137,17 @@ def test_bench_refuses_more_than_one_gpu():
                        timeout=120)
     assert r.returncode != 0
     assert "one GPU" in (r.stdout + r.stderr)
+
+
+def test_bench_line_keeps_its_numbers_at_six_digits(monkeypatch):
+    """The record is one line of JSON; its floats are shortened, nothing else of it changes."""
+    import json
+    monkeypatch.setenv("GPU_MAX_HW_QUEUES", os.environ.get("GPU_MAX_HW_QUEUES", "4"))   # (bench.py sets it where it is not)
+    monkeypatch.syspath_prepend(ROOT)
+    import bench
+    rec = {"a": [1.23456789, 7, None, "x", True], "b": {"c": 123456789.0, "d": -2.5e-7 / 3}, "e": (2 ** 40, 0.0)}
+    got = json.loads(json.dumps(bench.shortened(rec)))
+    assert got == {"a": [1.23457, 7, None, "x", True], "b": {"c": 123457000.0, "d": -8.33333e-08}, "e": [2 ** 40, 0.0]}
+    value = {str(i): float(v) for i, v in enumerate(np.random.default_rng(0).lognormal(0, 5, 1000))}
+    assert max(abs(bench.shortened(value)[k] / v - 1) for k, v in value.items()) <= 5e-6
+    assert len(json.dumps(bench.shortened(value))) < 0.75 * len(json.dumps(value))
