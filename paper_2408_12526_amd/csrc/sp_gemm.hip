@@ -41,9 +41,9 @@ __device__ inline float gelu_erf(float u) { return 0.5f * u * (1.0f + erff(u * 0
 //     matrix cores idle for 44 % of a tile at depth 768.)
 //   * epilogue through LDS: each wave stages its tile in its own slice and stores whole 16-byte-per-lane row segments; the
 //     residual rows arrive there by direct-to-LDS loads.
-// What bounds large launches: the package power limit (1.9 GHz of 2.4), of which the operands' way to the compute units takes more than
-// a third (the same loop without its loads runs at 1.8 PFLOP/s), and the wait for them (matrix cores 55-60 % busy; on operands that are all
-// zero a launch takes 8-20 % less).
+// What bounds large launches (eight students of 768, 14.7 k tokens): the wait for operands first (matrix cores 52-57 % busy, waves waiting 47-59 %
+// of their time, address units 69-83 % busy), then the package power limit (1.85-2.1 GHz of 2.4; on operands that are all zero a launch takes
+// 8-20 % less, and the same loop without its loads runs at 1.8 PFLOP/s).
 // -------------------------------------------------------------------------------------
 struct GemmArgs {
     const bf16* A;

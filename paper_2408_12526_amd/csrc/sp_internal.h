@@ -217,7 +217,8 @@ constexpr int kFp8MinRows = 2048;
 // Outputs of a projection (bytes, all students) from which they are streamed.  us a call, hidden 768, 14653 tokens, kept / streamed, by
 // MiB: q|k|v 129 613 / 612, 193 901 / 898, 257 1176 / 1166, 515 2135 / 2125; FFN up 172 613 / 618, 258 901 / 894, 343 1176 / 1162, 687 2135 / 2118; hidden 1024:
 // q|k|v 108 594 / 595, 215 1202 / 1197, 322 1659 / 1645; FFN up 144 594 / 602, 160 694 / 697, 287 1202 / 1199.  The hidden-wide outputs: no difference at
-// any size up to 215.
+// any size up to 215.  Both kinds together, both sides three times in turn on another card: hidden 768, students 3 869 / 859, 6 1643 / 1592, 8 2119 / 2071;
+// hidden 1024, 18.4 k tokens, 3 1577 / 1536, 6 3096 / 3038; runs of one side within 0.3 %.
 constexpr size_t kStreamBytes = (size_t)192 << 20;
 
 // Byte offsets of every tensor inside one student's slab of the weight arena.

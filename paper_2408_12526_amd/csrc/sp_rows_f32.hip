@@ -15,7 +15,8 @@
 //     applies bias, GELU or residual.  Biases and LayerNorm parameters come through LDS, so nothing waits behind the weights.
 // us a call, two students of 2 layers x 128 wide on 86 tokens: separate launches, 19 of them, 83.6; one launch per layer after
 // the attention, a block of weights in flight, and embedding, first q|k|v, pooler and classifier apart, 8 launches, 51; these as now, the
-// attention apart, 6 launches, 38.8; this, 4 launches, 30.7, and 30.9 with the last layer's attention output left in the workspace.  One of 256 tokens 90.9 / 40.8, one student on one of 512 147 / 49.6.
+// attention apart, 6 launches, 38.8; this, 4 launches, 30.9 (30.8 with the last layer's q|k|v in the other buffer where layers are even).  One
+// of 256 tokens 90.9 / 40.8, one student on one of 512 147 / 49.6.
 #include <type_traits>
 #include <utility>
 
